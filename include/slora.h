@@ -329,10 +329,8 @@ int32_t slora_lora_shrink_expand(slora_pool *pool, int32_t slot, const void *x,
  *   "upload_groups"    workgroups of slora_adapter_upload when the source is host memory (default
  *                      32: enough requests in flight to fill the host link; many more delay the
  *                      HBM traffic of kernels running on other streams)
- *   "xcd_group"        how MFMA expand items are handed to the 8 accelerator dies (one L2 each).
- *                      0 (default): round-robin.  Bit 1 (value 2): the expand list is cut into 8
- *                      contiguous, equally heavy runs, one per die, so the tiles of an adapter
- *                      share an L2 (measured 13 % slower).  Bit 0 is accepted and has no effect.
+ *   "xcd_group"        0..3, accepted without effect (grouping the MFMA items by accelerator die was
+ *                      never faster, and an MFMA expand workgroup walks the tiles of an adapter itself)
  * Results never depend on these beyond floating-point summation order.  Unknown key: EINVAL.
  */
 int32_t slora_set_option(slora_pool *pool, const char *key, int64_t value);

@@ -524,21 +524,6 @@ __device__ __forceinline__ f32x16 mfma32(const u32x4 &a, const u32x4 &b, const f
                                                        0, 0, 0);
 }
 
-// Workgroup -> (item, slot) for the MFMA work lists.  The scheduler lays these lists out in rows
-// of kXcds items, column k holding work of the k-th share of the batch; workgroups are handed
-// to the 8 XCDs round-robin by their linear id, so making the item's column the fastest-varying
-// part of the id keeps every share on one XCD (all tiles of an adapter then find its pages in
-// that XCD's L2).  Within a row the slots follow one another.
-__device__ __forceinline__ int mfma_item_of(unsigned bid, int n)
-{
-    const unsigned per_row = kXcds * (unsigned)n;
-    return (int)((bid / per_row) * kXcds + (bid % kXcds));
-}
-__device__ __forceinline__ int mfma_slot_of(unsigned bid, int n)
-{
-    return (int)((bid % (kXcds * (unsigned)n)) / kXcds);
-}
-
 // accumulator register v of lane `lane` holds this row of the 32 x 32 block
 __device__ __forceinline__ int mfma_row(int v, int lane) { return 8 * (v >> 2) + 4 * (lane >> 5) + (v & 3); }
 
@@ -629,6 +614,48 @@ constexpr int kExpMin = -24, kExpMax = 40;           // range of the row exponen
 static_assert(kMsRowsPerPass == 32 && kMsTok == 128 && kMsRanks == 128, "copy duty and tile shape are tied");
 
 __device__ __forceinline__ float pow2f(int e) { return __uint_as_float((uint32_t)(e + 127) << 23); }
+
+// 64 lanes x 16 bytes from per-lane addresses to 1 KiB of LDS at a wave-uniform address
+template <int AUX>
+__device__ __forceinline__ void load_to_lds(const unsigned char *src, unsigned char *dst)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                     (__attribute__((address_space(3))) void *)dst, 16, 0, AUX);
+}
+// N 16-byte LDS reads, waited for together.  Reads and wait are one asm block because the compiler
+// cannot tell which stage of a ring filled by global_load_lds a read touches: before an ordinary
+// LDS read it waits for every load in flight.
+template <int N>
+__device__ __forceinline__ void lds_read(const uint32_t (&a)[N], u32x4 (&o)[N])
+{
+    static_assert(N == 4 || N == 6, "write the block for this number of reads");
+    if constexpr (N == 4)
+        asm volatile(
+            "ds_read_b128 %0, %4\n\t"
+            "ds_read_b128 %1, %5\n\t"
+            "ds_read_b128 %2, %6\n\t"
+            "ds_read_b128 %3, %7\n\t"
+            "s_waitcnt lgkmcnt(0)"
+            : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3])
+            : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3])
+            : "memory");
+    else if constexpr (N == 6)
+        asm volatile(
+            "ds_read_b128 %0, %6\n\t"
+            "ds_read_b128 %1, %7\n\t"
+            "ds_read_b128 %2, %8\n\t"
+            "ds_read_b128 %3, %9\n\t"
+            "ds_read_b128 %4, %10\n\t"
+            "ds_read_b128 %5, %11\n\t"
+            "s_waitcnt lgkmcnt(0)"
+            : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]), "=&v"(o[4]), "=&v"(o[5])
+            : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5])
+            : "memory");
+}
+__device__ __forceinline__ uint32_t lds_address(const unsigned char *p)
+{
+    return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char *)p;
+}
 
 // Partial sums of a split tile: [share][token block][rank block][octet pair i][lane][8 floats];
 // lane l holds token l % 32 of its wavefront's block and the rank octets l / 32 + 2 i.
@@ -1036,233 +1063,395 @@ __global__ __launch_bounds__(kMfmaThreads) void join_shares_kernel(const MsItem 
 }
 
 // ---------------------------------------------------------------------------------------
-// prefill expand: y[tok, d] += sum_j V[pos, j] * Bpage_j[d] for a tile of up to 32 tokens and
-// up to 256 columns.  The four wavefronts of a workgroup are independent: wavefront w owns
-// columns 64w .. 64w+63 (two 32-column MFMA blocks) and keeps a 32 x 64 fp32 tile of y in its
-// accumulators - y is loaded INTO the accumulators, the MFMAs add onto it, and it is stored
-// once, 128 contiguous bytes per token row and instruction.  Many small independent tiles
-// (up to 20 wavefronts per CU) rather than deep software pipelines hide the memory latency.
+// prefill expand: y[tok, d] += sum_j V[pos, j] * Bpage_j[d] for a run of 32-token tiles of one
+// adapter and up to 256 columns.  Wavefront w owns columns 64w .. 64w+63 (two 32-column MFMA blocks)
+// of every tile of the run.
 //
-// The first operand is V (tokens x ranks, fp32 in memory).  So that no precision is lost to
-// the 16-bit operand format it is split into 16-bit pieces whose sum is V: hi + lo for
-// binary16 (22+ bits), hi + mid + lo by truncation for bfloat16 (exactly 24 bits); each piece
-// costs one more MFMA on a path that is bound by memory, not by the matrix cores.
-// The second operand needs, per lane, 8 consecutive ranks of ONE column, but a page is
+// Adapters of up to 128 ranks (RegStages 32-rank stages): the B operands of a wavefront's columns do
+// not depend on the tile; it reads them once, keeps them in registers (16 per stage) and walks the
+// tiles with one read-modify-write of y each.  V of a tile is the same for all four wavefronts: it is
+// copied straight into LDS (global_load_lds), a quarter by each, into one of two buffers - read by
+// every wavefront for itself it was a larger part of the kernel's requests than y.  V and y of the
+// next tile are requested before the current one is computed; one barrier per tile hands the
+// buffers over, and the stores of a tile are only waited for a tile later.
+// Adapters of more ranks (expand_mfma_stream) read V and B again for every tile, without barriers.
+//
+// The first operand is V (tokens x ranks, fp32 precision), split by the shrink into 16-bit pieces
+// (see VPieces); each piece costs one more MFMA on a path that is bound by memory, not by the
+// matrix cores.  The second operand needs, per lane, 8 consecutive ranks of ONE column, but a page is
 // contiguous along columns; the wavefront therefore copies a 32-rank x 64-column slab of B
 // through LDS, transposing on the way in (two ranks packed per dword), and reads its operand
-// back with one 16-byte LDS load.  Each wavefront uses only its own LDS slab, so the
-// workgroup needs no barrier.  All global loads are unconditional: token rows beyond the
-// tile, columns beyond the item and ranks beyond the adapter's are redirected to a valid
-// row / column / page; what they produce is multiplied by the zero padding of V or is never
-// stored.
+// back with one 16-byte LDS load.  The 32 x 64 tile of y passes through the same LDS (fp32, 16 rows at
+// a time) INTO the MFMA accumulators; the products are added on top, and it returns the same way, to be
+// rounded once if y is 16-bit: 16-byte accesses of whole row pieces towards memory.  All global loads are unconditional: token rows beyond the tile, columns beyond the item
+// and ranks beyond the adapter's are redirected to a valid row / column / page; what they produce is
+// multiplied by the zero padding of V or is never stored.
+//
+// Bound by HBM (y read and written once).  What each part measured, per step, on batches of 4524 tokens
+// (4 slots, H = 4096, fp32 y, 16 prompts of ranks 8-128) / 3781 tokens (4 slots, H = 5120, bfloat16 y) /
+// 24675 tokens (4 slots, H = 4096, binary16 y): a workgroup per tile, everything read per tile
+// 132 / 110 / 395 us; runs of tiles with B in registers 130 / 116 / 345; V shared through LDS
+// 131 / 97 / 340; y moved with streaming (non-temporal) loads AND stores 111 / 83 / 311 us = 5.6 / 4.2 /
+// 5.3 TB/s of y, B and V (streaming on one side only changes nothing: y otherwise displaces, line by line,
+// what the other side still needs in L2).  Workgroups per launch 1024-4096 measure alike, fewer than
+// 1024 and runs of 32 tiles gain nothing; three wavefronts per SIMD need registers that spill (+25 %).
 // ---------------------------------------------------------------------------------------
 constexpr int kSlabStride = 20; // dwords per column in LDS: 16 (32 ranks) + 4 pad, keeps 16-byte alignment
 constexpr int kSlabGroupPad = 8; // extra dwords before every 8 columns: the 8 column groups a transposing store
                                  // touches then fall into different banks (8 x 20 dwords alone is a multiple of 32:
                                  // rocprofv3 counted bank conflicts on 58 % of this kernel's LDS cycles)
 __device__ __forceinline__ int slab_col(int c) { return c * kSlabStride + (c >> 3) * kSlabGroupPad; }
-// The y tile of a wavefront (32 rows x 64 columns) is staged in the same slab; padded rows keep the
-// 16-byte alignment and spread the accumulator-layout accesses over the banks.
-template <bool Y16>
-struct YTile;
-template <>
-struct YTile<true> {
-    using type = uint16_t;
-    static constexpr int stride = 72;                  // 144-byte rows
-    static constexpr int bytes = 32 * stride * 2;
-};
-template <>
-struct YTile<false> {
-    using type = float;
-    static constexpr int stride = 68;                  // 272-byte rows
-    static constexpr int bytes = 32 * stride * 4;
-};
-constexpr int kSlabBytes = (64 * kSlabStride + 8 * kSlabGroupPad) * 4;
+constexpr int kTileStride = 68;  // floats per row of the y tile: 16-byte aligned, rows spread over the banks
+constexpr int kWaveLds = (64 * kSlabStride + 8 * kSlabGroupPad) * 4; // a wavefront's own LDS
+static_assert(16 * kTileStride * 4 <= kWaveLds && kWaveLds % 16 == 0, "half a y tile shares the B slab's LDS");
 
-template <int DT, bool Y16>
-__global__ __launch_bounds__(kMfmaThreads, 4) void expand_mfma_kernel(const Item *__restrict__ items,
-                                                                    const int32_t *__restrict__ arena,
-                                                                    const uint16_t *__restrict__ pool,
-                                                                    const int32_t *__restrict__ tok_idx, int H,
-                                                                    int v_stride, MultiArgs args)
+__device__ __forceinline__ void wave_lds_fence() // LDS written by one lane is read by another of the same wavefront
 {
-    constexpr int kWaveLds = YTile<Y16>::bytes > kSlabBytes ? YTile<Y16>::bytes : kSlabBytes;
-    __shared__ u32x4 slab_mem[4][kWaveLds / 16];
-    const int cs = mfma_slot_of(blockIdx.x, args.n);
-    const Item it = items[mfma_item_of(blockIdx.x, args.n)];
-    if (it.ntok == 0) return; // padding of a short per-XCD list
-    void *args_y = args.y[cs];
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = threadIdx.x / kWave;
-    const int n = lane & 31;
-    const int q = lane >> 5;
-    const int col_end = it.a + it.b;        // <= H, multiple of 8
-    const int colw = it.a + wave * 64;      // this wavefront's first column
-    if (colw >= col_end) return;            // whole wavefront; no barrier is used below
-    uint32_t *slab = reinterpret_cast<uint32_t *>(slab_mem[wave]);
-    const int32_t *pbl = arena + it.arena_off + (int64_t)args.slot[cs] * 2 * it.rank + it.rank;
-    constexpr int NP = VPieces<DT>::N;
-    const int n_kk = v_stride >> 4;
-    const u32x4 *vfrag = reinterpret_cast<const u32x4 *>(args.v[cs] + args.vfrag_off) + lane;
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
-    const int cg = lane & 7;   // column group (8 columns) this lane copies
-    const int kp = lane >> 3;  // rank pair this lane copies
-    const int col8 = min(colw + 8 * cg, col_end - 8);
-    // page numbers of the four B rows this lane copies per stage, fetched one stage ahead
-    int pg[4];
-    auto load_pg = [&](int k0) {
-#pragma unroll
-        for (int rd = 0; rd < 2; ++rd) {
-            const int ka = k0 + 16 * rd + 2 * kp;
-            pg[2 * rd] = pbl[min(ka, it.rank - 1)];
-            pg[2 * rd + 1] = pbl[min(ka + 1, it.rank - 1)];
-        }
-    };
-    load_pg(0);
-    // row exponents of the tile's first rank block (binary16 pools), see below
-    typedef int32_t e_i32x4 __attribute__((ext_vector_type(4)));
-    [[maybe_unused]] const e_i32x4 *vexp_t = nullptr;
-    [[maybe_unused]] e_i32x4 e_cur = e_i32x4{0, 0, 0, 0};
-    if constexpr (DT == SLORA_F16) {
-        const int n_rb = (v_stride + kMsRanks - 1) / kMsRanks;
-        vexp_t = reinterpret_cast<const e_i32x4 *>(reinterpret_cast<const int8_t *>(args.v[cs] + args.vexp_off) +
-                                                   (int64_t)it.tile * n_rb * 32 + q * 16);
-        e_cur = vexp_t[0];
-    }
-
-    // accumulators start as the y tile (rows / columns outside the tile read a valid element)
-    f32x16 acc[2];
-    // The 32 x 64 tile of y passes through the wavefront's LDS slab, which is idle before the
-    // first and after the last stage: 16-byte accesses of whole row pieces (128 or 256 bytes)
-    // towards memory, single-element LDS accesses in accumulator layout on the other side.
-    // A lane moves the kYVec columns of group lane % kYLanes of rows lane / kYLanes + kYRows * i.
-    using YT = typename YTile<Y16>::type;
-    constexpr int kYVec = 16 / (int)sizeof(YT);   // elements per 16-byte access
-    constexpr int kYLanes = 64 / kYVec;           // lanes per tile row
-    constexpr int kYRows = kWave / kYLanes;       // rows per access of the wavefront
-    constexpr int kYStride = YTile<Y16>::stride;  // padded row, elements
-    YT *ytile = reinterpret_cast<YT *>(slab);
-    YT *yg = static_cast<YT *>(args_y);
-    const int ygrp = lane % kYLanes;
-    {
-        const int ycol = min(colw + kYVec * ygrp, col_end - kYVec);
-#pragma unroll
-        for (int i = 0; i < 32 / kYRows; ++i) {
-            const int r = lane / kYLanes + kYRows * i;
-            const int64_t row = (int64_t)tok_idx[it.pos0 + min(r, it.ntok - 1)] * H;
-            const u32x4 w8 = *reinterpret_cast<const u32x4 *>(yg + row + ycol);
-            *reinterpret_cast<u32x4 *>(ytile + r * kYStride + kYVec * ygrp) = w8;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-#pragma unroll
-        for (int vv = 0; vv < 16; ++vv)
-#pragma unroll
-            for (int nb = 0; nb < 2; ++nb) {
-                const YT e = ytile[mfma_row(vv, lane) * kYStride + nb * 32 + n];
-                if constexpr (Y16)
-                    acc[nb][vv] = widen1<DT>(e);
-                else
-                    acc[nb][vv] = e;
-            }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront"); // the stages overwrite the slab
-    }
-    // binary16 pools: the shrink scaled token row i of rank block rb (kMsRanks ranks) by 2^e[rb][i].
-    // The accumulators follow: they hold (y + products so far) * 2^e of the CURRENT rank block -
-    // scaled up before the first block, re-scaled where the block changes, scaled back at the end.
-    // Powers of two: every step is exact.  A lane's 16 exponents of a block are one 16-byte load,
-    // requested with the first page numbers (e_cur) so that it has arrived when y has.
+// One wavefront's view of a run: its columns, the rows of y it moves, and the ways of B and of the
+// finished deltas through its LDS.
+template <int DT, bool Y16>
+struct ExpandWave {
     typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-    [[maybe_unused]] auto scale_rows = [&](const i32x4 &from, const i32x4 &to) { // acc *= 2^(to - from), row by row
-#pragma unroll
-        for (int g = 0; g < 4; ++g)
-#pragma unroll
-            for (int k = 0; k < 4; ++k) {
-                const int d = (int)(int8_t)(to[g] >> (8 * k)) - (int)(int8_t)(from[g] >> (8 * k));
-                const float f = pow2f(d);
-                acc[0][4 * g + k] *= f;
-                acc[1][4 * g + k] *= f;
-            }
-    };
-    [[maybe_unused]] const i32x4 e_zero = i32x4{0, 0, 0, 0};
-    if constexpr (DT == SLORA_F16) scale_rows(e_zero, e_cur);
+    static constexpr int NP = VPieces<DT>::N;
+    static constexpr int kElem = Y16 ? 2 : 4;
+    static constexpr int kYVec = 16 / kElem;             // elements per 16-byte access
+    static constexpr int kYLanes = 64 / kYVec;           // lanes per tile row
+    static constexpr int kYRows = kWave / kYLanes;       // rows per access of the wavefront
+    static constexpr int kYLoads = 32 / kYRows;          // accesses per tile
+    const Item &it;
+    const int32_t *pbl;
+    const int32_t *tok_idx;
+    uint32_t *slab;
+    int H, lane, n, q, cg, kp, ygrp, yrow, tiles, last;
+    bool store_ok;
+    unsigned char *yg;
+    const uint16_t *bcol;
+    f32x16 acc[2];
 
-    for (int k0 = 0; k0 < it.rank; k0 += 32) {
-        if constexpr (DT == SLORA_F16) {
-            if (k0 > 0 && (k0 & (kMsRanks - 1)) == 0) {
-                const i32x4 e_next = vexp_t[(k0 / kMsRanks) * 2];
-                scale_rows(e_cur, e_next);
-                e_cur = e_next;
-            }
-        }
-        // ---- operands of this stage: two B rows per lane and round, V for both k-steps
-        u32x4 wa[2], wb[2];
+    __device__ __forceinline__ ExpandWave(const Item &item, int colw, const int32_t *pages, const uint16_t *pool,
+                                          const int32_t *tokens, int H_, void *y, uint32_t *lds)
+        : it(item), pbl(pages), tok_idx(tokens), slab(lds), H(H_)
+    {
+        lane = threadIdx.x & (kWave - 1);
+        n = lane & 31;
+        q = lane >> 5;
+        cg = lane & 7;  // column group (8 columns) this lane copies of B
+        kp = lane >> 3; // rank pair this lane copies of B
+        ygrp = lane % kYLanes;
+        yrow = lane / kYLanes;
+        tiles = it.run & 0xff; // tiles of the run
+        last = it.run >> 8;    // tokens of the last one
+        const int col_end = it.a + it.b;      // <= H, a multiple of 8
+        const int ycol = colw + kYVec * ygrp; // a group of columns is inside or outside: both ends are multiples of 8
+        store_ok = ycol < col_end;
+        yg = static_cast<unsigned char *>(y) + (int64_t)min(ycol, col_end - kYVec) * kElem;
+        bcol = pool + min(colw + 8 * cg, col_end - 8);
+    }
+    __device__ __forceinline__ int tokens_of(int t) const { return t == tiles - 1 ? last : kMfmaTok; }
+    __device__ __forceinline__ void load_rows(int t, int (&row)[kYLoads]) const
+    {
+        const int nt = tokens_of(t);
 #pragma unroll
-        for (int rd = 0; rd < 2; ++rd) {
-            wa[rd] = *reinterpret_cast<const u32x4 *>(pool + (int64_t)pg[2 * rd] * H + col8);
-            wb[rd] = *reinterpret_cast<const u32x4 *>(pool + (int64_t)pg[2 * rd + 1] * H + col8);
-        }
-        load_pg(k0 + 32); // clamped to the last rank past the end
-        u32x4 piece[2][NP];
+        for (int i = 0; i < kYLoads; ++i) row[i] = tok_idx[it.pos0 + t * kMfmaTok + min(yrow + kYRows * i, nt - 1)];
+    }
+    __device__ __forceinline__ void load_y(const int (&row)[kYLoads], u32x4 (&w)[kYLoads]) const
+    {
 #pragma unroll
-        for (int s = 0; s < 2; ++s)
+        for (int i = 0; i < kYLoads; ++i) w[i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(yg + (int64_t)row[i] * H * kElem));
+    }
+    // the page numbers of the four B rows this lane copies per 32-rank stage; beyond the last rank: the last one's
+    __device__ __forceinline__ void load_pg(int k0, int (&pg)[4]) const
+    {
 #pragma unroll
-            for (int p = 0; p < NP; ++p)
-                piece[s][p] = vfrag[vfrag_index(it.tile, (k0 >> 4) + s, p, n_kk, NP) / 8];
-        // ---- B slab: ranks k0..k0+31 x this wavefront's 64 columns, transposed into LDS
-        __builtin_amdgcn_wave_barrier();
+        for (int i = 0; i < 4; ++i) pg[i] = pbl[min(k0 + 16 * (i >> 1) + 2 * kp + (i & 1), it.rank - 1)];
+    }
+    __device__ __forceinline__ void load_b(const int (&pg)[4], u32x4 (&w)[4]) const
+    {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) w[i] = *reinterpret_cast<const u32x4 *>(bcol + (int64_t)pg[i] * H);
+    }
+    // 32 ranks x 64 columns, transposed through LDS into the operands of two k-steps x two column blocks
+    __device__ __forceinline__ void transpose_b(const u32x4 (&w)[4], u32x4 (&op)[2][2]) const
+    {
+        wave_lds_fence(); // the previous contents have been read
 #pragma unroll
         for (int rd = 0; rd < 2; ++rd) {
             uint32_t *dst = slab + slab_col(8 * cg) + 8 * rd + kp; // columns 8 cg .. 8 cg + 7: one group, same pad
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
-                dst[(2 * e) * kSlabStride] = (wa[rd][e] & 0xffffu) | (wb[rd][e] << 16);
-                dst[(2 * e + 1) * kSlabStride] = (wa[rd][e] >> 16) | (wb[rd][e] & 0xffff0000u);
+                dst[(2 * e) * kSlabStride] = (w[2 * rd][e] & 0xffffu) | (w[2 * rd + 1][e] << 16);
+                dst[(2 * e + 1) * kSlabStride] = (w[2 * rd][e] >> 16) | (w[2 * rd + 1][e] & 0xffff0000u);
             }
         }
-        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-        __builtin_amdgcn_wave_barrier();
-        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-
+        wave_lds_fence();
 #pragma unroll
-        for (int s = 0; s < 2; ++s) {
-            u32x4 bop[2];
+        for (int s = 0; s < 2; ++s)
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb)
-                bop[nb] = *reinterpret_cast<const u32x4 *>(slab + slab_col(nb * 32 + n) + 8 * s + 4 * q);
+                op[s][nb] = *reinterpret_cast<const u32x4 *>(slab + slab_col(nb * 32 + n) + 8 * s + 4 * q);
+    }
+    __device__ __forceinline__ void multiply(const u32x4 &piece, const u32x4 (&op)[2])
+    {
 #pragma unroll
-            for (int p = 0; p < NP; ++p)
+        for (int nb = 0; nb < 2; ++nb) acc[nb] = mfma32<DT>(piece, op[nb], acc[nb]);
+    }
+    // Binary16 pools: the shrink scaled token row i of a block of kMsRanks ranks by 2^e[i].  The accumulators
+    // follow: they hold (y + products so far) * 2^e of the CURRENT block - scaled up before the first
+    // block, re-scaled where the block changes, scaled back at the end.  Powers of two: every step is exact.
+    __device__ __forceinline__ void scale_rows(const i32x4 &from, const i32x4 &to)
+    {
 #pragma unroll
-                for (int nb = 0; nb < 2; ++nb) acc[nb] = mfma32<DT>(piece[s][p], bop[nb], acc[nb]);
+        for (int g = 0; g < 4; ++g)
+#pragma unroll
+            for (int k = 0; k < 4; ++k) {
+                const float f = pow2f((int)(int8_t)(to[g] >> (8 * k)) - (int)(int8_t)(from[g] >> (8 * k)));
+                acc[0][4 * g + k] *= f;
+                acc[1][4 * g + k] *= f;
+            }
+    }
+    // row pieces of the y tile -> accumulators (fp32), through LDS
+    __device__ __forceinline__ void start_from(const u32x4 (&w)[kYLoads])
+    {
+        float *half = reinterpret_cast<float *>(slab);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) { // accumulator registers 8 h .. 8 h + 7 hold rows 16 h .. 16 h + 15
+            wave_lds_fence();
+#pragma unroll
+            for (int i = 0; i < kYLoads / 2; ++i) {
+                const u32x4 &v = w[h * (kYLoads / 2) + i];
+                float *dst = half + (yrow + kYRows * i) * kTileStride + kYVec * ygrp;
+                if constexpr (Y16) {
+                    float f[8];
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) widen2<DT>(v[e], f[2 * e], f[2 * e + 1]);
+                    *reinterpret_cast<f32x4 *>(dst) = f32x4{f[0], f[1], f[2], f[3]};
+                    *reinterpret_cast<f32x4 *>(dst + 4) = f32x4{f[4], f[5], f[6], f[7]};
+                } else {
+                    *reinterpret_cast<u32x4 *>(dst) = v;
+                }
+            }
+            wave_lds_fence();
+#pragma unroll
+            for (int v = 0; v < 8; ++v)
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb) acc[nb][8 * h + v] = half[mfma_row(v, lane) * kTileStride + nb * 32 + n];
         }
     }
+    // accumulators -> row pieces of the y tile, rounded once if y is 16-bit
+    __device__ __forceinline__ void finish(u32x4 (&w)[kYLoads]) const
+    {
+        float *half = reinterpret_cast<float *>(slab);
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            wave_lds_fence();
+#pragma unroll
+            for (int v = 0; v < 8; ++v)
+#pragma unroll
+                for (int nb = 0; nb < 2; ++nb) half[mfma_row(v, lane) * kTileStride + nb * 32 + n] = acc[nb][8 * h + v];
+            wave_lds_fence();
+#pragma unroll
+            for (int i = 0; i < kYLoads / 2; ++i) {
+                const float *src = half + (yrow + kYRows * i) * kTileStride + kYVec * ygrp;
+                u32x4 &o = w[h * (kYLoads / 2) + i];
+                if constexpr (Y16) {
+                    const f32x4 a = *reinterpret_cast<const f32x4 *>(src), b = *reinterpret_cast<const f32x4 *>(src + 4);
+                    o = u32x4{narrow2<DT>(a.x, a.y), narrow2<DT>(a.z, a.w), narrow2<DT>(b.x, b.y), narrow2<DT>(b.z, b.w)};
+                } else {
+                    o = *reinterpret_cast<const u32x4 *>(src);
+                }
+            }
+        }
+    }
+    __device__ __forceinline__ void store_y(int t, const int (&row)[kYLoads], const u32x4 (&w)[kYLoads]) const
+    {
+        const int nt = tokens_of(t);
+#pragma unroll
+        for (int i = 0; i < kYLoads; ++i) {
+            int r = row[i];
+            asm("" : "+v"(r)); // the address is computed anew: kept since the load, it would cost registers the tile needs
+            if (yrow + kYRows * i < nt && store_ok)
+                __builtin_nontemporal_store(w[i], reinterpret_cast<u32x4 *>(yg + (int64_t)r * H * kElem));
+        }
+    }
+};
 
-    if constexpr (DT == SLORA_F16) scale_rows(e_cur, e_zero);
-    __builtin_amdgcn_wave_barrier();
-#pragma unroll
-    for (int vv = 0; vv < 16; ++vv)
-#pragma unroll
-        for (int nb = 0; nb < 2; ++nb) {
-            YT &e = ytile[mfma_row(vv, lane) * kYStride + nb * 32 + n];
-            if constexpr (Y16)
-                e = narrow1<DT>(acc[nb][vv]);
-            else
-                e = acc[nb][vv];
+template <int DT, bool Y16, int RegStages>
+__device__ __forceinline__ void expand_mfma_run(const Item &it, int wave, const int32_t *__restrict__ pbl,
+                                                const uint16_t *__restrict__ pool,
+                                                const int32_t *__restrict__ tok_idx, int H, int v_stride,
+                                                const uint16_t *__restrict__ vfrag, const int8_t *__restrict__ vexp,
+                                                void *__restrict__ y, unsigned char *lds)
+{
+    typedef ExpandWave<DT, Y16> W;
+    typedef typename W::i32x4 i32x4;
+    constexpr int NP = W::NP, kYLoads = W::kYLoads;
+    constexpr int kFrags = 2 * RegStages * NP;    // operand fragments (1 KiB) of V per tile
+    const int n_kk = v_stride >> 4, n_rb = (v_stride + kMsRanks - 1) / kMsRanks;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int tiles = it.run & 0xff;
+    auto load_v = [&](int t) { // this wavefront's part of the fragments of tile t
+        const unsigned char *src = reinterpret_cast<const unsigned char *>(vfrag + vfrag_index(it.tile + t, 0, 0, n_kk, NP)) + lane * 16;
+        unsigned char *dst = lds + (t & 1) * (kFrags * 1024);
+        for (int f = wave; f < kFrags; f += 4) load_to_lds<0>(src + f * 1024, dst + f * 1024);
+    };
+    const int colw = it.a + wave * 64;            // this wavefront's first column
+    load_v(0);
+    if (colw >= it.a + it.b) {                    // no columns: it only does its part of the copying
+        for (int t = 0; t < tiles; ++t) {
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+            if (t + 1 < tiles) load_v(t + 1);
         }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    const int ycol = colw + kYVec * ygrp; // a multiple of kYVec, and col_end one of 8: a group is inside or outside
+        return;
+    }
+    W w(it, colw, pbl, pool, tok_idx, H, y, reinterpret_cast<uint32_t *>(lds + 2 * kFrags * 1024 + wave * kWaveLds));
+    int row_cur[kYLoads], row_next[kYLoads];
+    u32x4 yt[kYLoads], out[kYLoads];
+    u32x4 bop[RegStages][2][2];
+    // a lane's 16 row exponents of a tile are one load
+    auto exponents = [&](int t) { return *reinterpret_cast<const i32x4 *>(vexp + (int64_t)(it.tile + t) * n_rb * 32 + w.q * 16); };
+    [[maybe_unused]] i32x4 e_cur = i32x4{0, 0, 0, 0}, e_next = i32x4{0, 0, 0, 0};
+    if constexpr (DT == SLORA_F16) e_cur = exponents(0);
+    w.load_rows(0, row_cur);
+    constexpr int kAhead = RegStages < 2 ? RegStages : 2; // stages of B in flight
 #pragma unroll
-    for (int i = 0; i < 32 / kYRows; ++i) {
-        const int r = lane / kYLanes + kYRows * i;
-        if (r < it.ntok && ycol < col_end) {
-            const int64_t row = (int64_t)tok_idx[it.pos0 + r] * H;
-            *reinterpret_cast<u32x4 *>(yg + row + ycol) =
-                *reinterpret_cast<const u32x4 *>(ytile + r * kYStride + kYVec * ygrp);
+    for (int s0 = 0; s0 < RegStages; s0 += kAhead) {
+        int pg[kAhead][4];
+        u32x4 b[kAhead][4];
+#pragma unroll
+        for (int s = 0; s < kAhead; ++s) w.load_pg(32 * (s0 + s), pg[s]);
+#pragma unroll
+        for (int s = 0; s < kAhead; ++s) w.load_b(pg[s], b[s]);
+        if (s0 == 0) w.load_y(row_cur, yt);
+#pragma unroll
+        for (int s = 0; s < kAhead; ++s)
+            if (s0 + s < RegStages) w.transpose_b(b[s], bop[s0 + s]);
+        if constexpr (RegStages > kAhead) __builtin_amdgcn_sched_barrier(0);
+    }
+    w.load_rows(min(1, tiles - 1), row_next);
+    const uint32_t frag_at = lds_address(lds) + lane * 16;
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __builtin_amdgcn_s_barrier();                 // V of the first tile is complete
+    asm volatile("" ::: "memory");
+    for (int t = 0; t < tiles; ++t) {
+        w.start_from(yt);
+        if constexpr (DT == SLORA_F16) w.scale_rows(i32x4{0, 0, 0, 0}, e_cur);
+        if (t + 1 < tiles) {
+            load_v(t + 1);
+            if constexpr (DT == SLORA_F16) e_next = exponents(t + 1);
+            w.load_y(row_next, yt);
+        }
+        const uint32_t buf_at = frag_at + (uint32_t)((t & 1) * (kFrags * 1024));
+#pragma unroll
+        for (int s = 0; s < RegStages; ++s) {
+            uint32_t at[2 * NP];
+            u32x4 piece[2 * NP];
+#pragma unroll
+            for (int f = 0; f < 2 * NP; ++f) at[f] = buf_at + (s * 2 * NP + f) * 1024;
+            lds_read(at, piece);
+#pragma unroll
+            for (int f = 0; f < 2 * NP; ++f) w.multiply(piece[f], bop[s][f / NP]);
+        }
+        if constexpr (DT == SLORA_F16) w.scale_rows(e_cur, i32x4{0, 0, 0, 0});
+        w.finish(out);
+        // what was requested for the next tile has arrived, and so have the stores of the previous one
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        w.store_y(t, row_cur, out);
+        if (t + 1 < tiles) {
+            // every wavefront's part of V(t + 1) is in LDS, and every one has read V(t)
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int i = 0; i < kYLoads; ++i) row_cur[i] = row_next[i];
+            e_cur = e_next;
+            w.load_rows(min(t + 2, tiles - 1), row_next);
         }
     }
+}
+
+// adapters of more than 128 ranks: V and B come from memory for every tile
+template <int DT, bool Y16>
+__device__ __forceinline__ void expand_mfma_stream(const Item &it, int wave, const int32_t *__restrict__ pbl,
+                                                   const uint16_t *__restrict__ pool,
+                                                   const int32_t *__restrict__ tok_idx, int H, int v_stride,
+                                                   const uint16_t *__restrict__ vfrag, const int8_t *__restrict__ vexp,
+                                                   void *__restrict__ y, unsigned char *lds)
+{
+    typedef ExpandWave<DT, Y16> W;
+    typedef typename W::i32x4 i32x4;
+    constexpr int NP = W::NP, kYLoads = W::kYLoads;
+    const int n_kk = v_stride >> 4, n_rb = (v_stride + kMsRanks - 1) / kMsRanks;
+    const int colw = it.a + wave * 64;            // this wavefront's first column
+    if (colw >= it.a + it.b) return;              // whole wavefront; no barrier is used below
+    W w(it, colw, pbl, pool, tok_idx, H, y, reinterpret_cast<uint32_t *>(lds + wave * kWaveLds));
+    const u32x4 *frags = reinterpret_cast<const u32x4 *>(vfrag) + w.lane;
+    for (int t = 0; t < w.tiles; ++t) {
+        const int tile = it.tile + t;
+        int row[kYLoads], pg[4];
+        u32x4 yt[kYLoads];
+        w.load_rows(t, row);
+        w.load_pg(0, pg);
+        const i32x4 *et = reinterpret_cast<const i32x4 *>(vexp + (int64_t)tile * n_rb * 32 + w.q * 16);
+        [[maybe_unused]] i32x4 e_cur = i32x4{0, 0, 0, 0};
+        if constexpr (DT == SLORA_F16) e_cur = et[0];
+        w.load_y(row, yt);
+        w.start_from(yt);
+        if constexpr (DT == SLORA_F16) w.scale_rows(i32x4{0, 0, 0, 0}, e_cur);
+        for (int k0 = 0; k0 < it.rank; k0 += 32) {
+            if constexpr (DT == SLORA_F16) {
+                if (k0 > 0 && (k0 & (kMsRanks - 1)) == 0) { // the sums so far follow the next block's scale
+                    const i32x4 e_next = et[(k0 / kMsRanks) * 2];
+                    w.scale_rows(e_cur, e_next);
+                    e_cur = e_next;
+                }
+            }
+            u32x4 b[4], piece[2][NP], op[2][2];
+            w.load_b(pg, b);
+            w.load_pg(k0 + 32, pg); // clamped to the last rank past the end
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int p = 0; p < NP; ++p) piece[s][p] = frags[vfrag_index(tile, (k0 >> 4) + s, p, n_kk, NP) / 8];
+            w.transpose_b(b, op);
+#pragma unroll
+            for (int s = 0; s < 2; ++s)
+#pragma unroll
+                for (int p = 0; p < NP; ++p) w.multiply(piece[s][p], op[s]);
+        }
+        if constexpr (DT == SLORA_F16) w.scale_rows(e_cur, i32x4{0, 0, 0, 0});
+        w.finish(yt);
+        w.store_y(t, row, yt);
+    }
+}
+
+template <int DT, bool Y16>
+__global__ __launch_bounds__(kMfmaThreads, 2) void expand_mfma_kernel(const Item *__restrict__ items,
+                                                                    const int32_t *__restrict__ arena,
+                                                                    const uint16_t *__restrict__ pool,
+                                                                    const int32_t *__restrict__ tok_idx, int H,
+                                                                    int v_stride, int run, MultiArgs args)
+{
+    // two buffers of V for the plan's widest adapter of up to 128 ranks, then each wavefront's own part
+    extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
+    const int cs = blockIdx.x % args.n;
+    const Item it = items[(int64_t)(blockIdx.x / args.n) * run]; // the first tile of the run stands for all of them
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int32_t *pbl = arena + it.arena_off + (int64_t)args.slot[cs] * 2 * it.rank + it.rank;
+    const uint16_t *vfrag = reinterpret_cast<const uint16_t *>(args.v[cs] + args.vfrag_off);
+    const int8_t *vexp = reinterpret_cast<const int8_t *>(args.v[cs] + args.vexp_off);
+#define SLORA_ME(S) expand_mfma_run<DT, Y16, S>(it, wave, pbl, pool, tok_idx, H, v_stride, vfrag, vexp, args.y[cs], lds)
+    if (it.rank <= 32) SLORA_ME(1);
+    else if (it.rank <= 64) SLORA_ME(2);
+    else if (it.rank <= 96) SLORA_ME(3);
+    else if (it.rank <= 128) SLORA_ME(4);
+    else expand_mfma_stream<DT, Y16>(it, wave, pbl, pool, tok_idx, H, v_stride, vfrag, vexp, args.y[cs], lds);
+#undef SLORA_ME
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1462,9 +1651,27 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *
         if (rc != SLORA_OK) return rc;
     }
     if (!plan->me_items.empty()) {
-        const dim3 grid((unsigned)(plan->me_items.size() * (size_t)n));
-        hipLaunchKernelGGL(SLORA_PICK(expand_mfma_kernel), grid, dim3(kMfmaThreads), 0, st, plan->d_me, pool->d_arena,
-                           base, plan->d_tok_idx, pool->H, plan->v_stride, args);
+        const dim3 grid((unsigned)(plan->me_items.size() / (size_t)plan->me_run * (size_t)n));
+        // LDS: two buffers of V fragments (the plan's most 32-rank stages) and the wavefronts' own parts
+        const size_t lds = (size_t)2 * plan->me_stages * 2 * (pool->dtype == SLORA_F16 ? 2 : 3) * 1024 + 4 * kWaveLds;
+#define SLORA_MEK(DT, Y)                                                                                             \
+    {                                                                                                                \
+        static bool allowed = false;                                                                                 \
+        if (!allowed && lds > 65536) {                                                                               \
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&expand_mfma_kernel<DT, Y>),          \
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);              \
+            if (e != hipSuccess) return fail(SLORA_EHIP, "hipFuncSetAttribute(LDS size): %s", hipGetErrorString(e)); \
+            allowed = true;                                                                                          \
+        }                                                                                                            \
+        hipLaunchKernelGGL((expand_mfma_kernel<DT, Y>), grid, dim3(kMfmaThreads), lds, st, plan->d_me,               \
+                           pool->d_arena, base, plan->d_tok_idx, pool->H, plan->v_stride, plan->me_run, args);       \
+    }
+        if (pool->dtype == SLORA_F16) {
+            if (y16) SLORA_MEK(SLORA_F16, true) else SLORA_MEK(SLORA_F16, false)
+        } else {
+            if (y16) SLORA_MEK(SLORA_BF16, true) else SLORA_MEK(SLORA_BF16, false)
+        }
+#undef SLORA_MEK
         int32_t rc = check_launch("expand_mfma");
         if (rc != SLORA_OK) return rc;
     }

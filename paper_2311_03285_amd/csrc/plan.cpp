@@ -30,40 +30,6 @@ struct Group {
 
 int32_t hip_fail(hipError_t e, const char *what) { return fail(SLORA_EHIP, "%s: %s", what, hipGetErrorString(e)); }
 
-// Lay an MFMA work list out for the 8 XCDs.  The list arrives in group order (all items of an
-// adapter adjacent, adapters by descending rank).  It is cut into kXcds runs of about equal
-// cost (bytes moved), run k becomes column k of a row-major table with kXcds columns, short
-// columns are padded with empty items (ntok == 0).  The kernels map workgroup ids so that
-// column k runs on XCD k: the tiles of one adapter share an L2 and its pages are fetched
-// from HBM once per XCD instead of once per tile.  A big adapter may straddle two columns.
-template <class Cost>
-void xcd_layout(std::vector<Item> &items, Cost cost, bool group)
-{
-    if (items.empty()) return;
-    if (!group) { // plain order: consecutive items go to consecutive XCDs; pad the last row
-        items.resize((items.size() + kXcds - 1) / kXcds * kXcds, Item{0, 0, 0, 0, 0, 0, 0, 0});
-        return;
-    }
-    int64_t total = 0;
-    for (const Item &i : items) total += cost(i);
-    std::vector<std::vector<Item>> col((size_t)kXcds);
-    int64_t seen = 0;
-    for (const Item &i : items) {
-        // column of the item's midpoint in the running cost
-        const int64_t c = cost(i);
-        int k = (int)(((seen + c / 2) * kXcds) / std::max<int64_t>(total, 1));
-        k = std::min(std::max(k, 0), kXcds - 1);
-        col[(size_t)k].push_back(i);
-        seen += c;
-    }
-    size_t rows = 0;
-    for (const auto &c : col) rows = std::max(rows, c.size());
-    std::vector<Item> out(rows * (size_t)kXcds, Item{0, 0, 0, 0, 0, 0, 0, 0});
-    for (int k = 0; k < kXcds; ++k)
-        for (size_t r = 0; r < col[(size_t)k].size(); ++r) out[r * (size_t)kXcds + (size_t)k] = col[(size_t)k][r];
-    items.swap(out);
-}
-
 } // namespace
 
 int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids, int32_t T,
@@ -156,6 +122,17 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         }
         const int64_t launch_slots = std::min<int64_t>(pool->n_slots, SLORA_MAX_MULTI);
         const int64_t share_bytes = std::max<int64_t>(pool->mfma_split_bytes, ms_bytes * launch_slots / (3 * 256));
+        // MFMA expand: a workgroup keeps the B operands of its columns and walks a run of tiles.  Long runs
+        // pay for them once, but the launch still needs several workgroups per compute unit.
+        int64_t me_tiles = 0;
+        for (int32_t gi : order) {
+            const int64_t n = (int64_t)groups[(size_t)gi].toks.size();
+            if (n >= min_tokens) me_tiles += (n + kMfmaTok - 1) / kMfmaTok;
+        }
+        const int64_t me_wgs = me_tiles * ((H + kMfmaExpandCols - 1) / kMfmaExpandCols) * launch_slots;
+        const int32_t me_run = (int32_t)std::min<int64_t>(kMfmaRunMax, std::max<int64_t>(1, me_wgs / 1024));
+        plan->me_run = me_run;
+        plan->me_stages = 0;
         int32_t n_vec_groups = 0;
         for (int32_t gi : order)
             if ((int64_t)groups[(size_t)gi].toks.size() < min_tokens) n_vec_groups++;
@@ -205,6 +182,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                 // v tiles of 32 tokens, numbered in order; an expand item covers one tile, a shrink
                 // item up to four consecutive ones (its pages are then read once for them all)
                 const int32_t tile0 = plan->n_mfma_tiles;
+
                 const int32_t n_tiles = (n + kMfmaTok - 1) / kMfmaTok;
                 plan->n_mfma_tiles += n_tiles;
                 for (int32_t p = 0; p < n; p += kMsTok) {
@@ -249,12 +227,19 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                         }
                     }
                 }
-                for (int32_t t = 0; t < n_tiles; ++t) {
-                    const int32_t p = t * kMfmaTok;
-                    const int32_t nt = std::min(kMfmaTok, n - p);
-                    for (int32_t c = 0; c < H; c += kMfmaExpandCols)
-                        plan->me_items.push_back(
-                            Item{off, g.rank, c, std::min(kMfmaExpandCols, H - c), pos_base + p, nt, tile0 + t, 0});
+                // expand: the tiles in runs of equal length; a run of one column range is one workgroup
+                if (g.rank <= kMsRanks) plan->me_stages = std::max(plan->me_stages, (g.rank + 31) / 32);
+                const int32_t n_runs = (n_tiles + me_run - 1) / me_run;
+                for (int32_t k = 0; k < n_runs; ++k) {
+                    const int32_t t0 = n_tiles * k / n_runs, t1 = n_tiles * (k + 1) / n_runs;
+                    const int32_t last = std::min(kMfmaTok, n - (t1 - 1) * kMfmaTok);
+                    for (int32_t c = 0; c < H; c += kMfmaExpandCols) {
+                        for (int32_t t = t0; t < t1; ++t)
+                            plan->me_items.push_back(Item{off, g.rank, c, std::min(kMfmaExpandCols, H - c), pos_base + t * kMfmaTok,
+                                                          std::min(kMfmaTok, n - t * kMfmaTok), tile0 + t,
+                                                          t == t0 ? (t1 - t0) + 256 * last : 0});
+                        plan->me_items.resize(plan->me_items.size() + (size_t)(me_run - (t1 - t0)), Item{0, 0, 0, 0, 0, 0, 0, 0});
+                    }
                 }
             } else {
                 plan->n_groups_vec++;
@@ -287,7 +272,6 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         std::stable_sort(plan->ms_items.begin(), plan->ms_items.end(), [](const MsItem &a, const MsItem &b) {
             return (int64_t)(a.ntok + a.nj) * (a.c1 - a.c0) > (int64_t)(b.ntok + b.nj) * (b.c1 - b.c0);
         });
-        xcd_layout(plan->me_items, [](const Item &i) { return (int64_t)i.b * (i.ntok * 8 + i.rank * 2); }, (pool->xcd_group & 2) != 0);
         plan->T_act = (int32_t)plan->tok_idx.size();
         plan->v_stride = std::max(kRankPad, (max_rank + kRankPad - 1) / kRankPad * kRankPad);
         plan->n_rank_blocks = (plan->v_stride + kMsRanks - 1) / kMsRanks;

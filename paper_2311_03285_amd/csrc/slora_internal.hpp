@@ -33,7 +33,7 @@ struct Item {
     int32_t pos0;      // first position in the sorted token list (also the row of v)
     int32_t ntok;      // tokens handled by this item
     int32_t tile;      // MFMA lists: number of the (adapter, 32-token) tile, shared by shrink and expand
-    int32_t pad1;
+    int32_t run;       // MFMA expand: first item of a run: tiles of the run + 256 * tokens of its last tile
 };
 static_assert(sizeof(Item) == 32, "Item must stay 32 bytes");
 
@@ -76,7 +76,7 @@ constexpr int kMsTok = 128;       // tokens per MFMA-shrink item (one 32-row blo
 constexpr int kMsRanks = 128;     // ranks per MFMA-shrink item (up to four 32-column blocks per wavefront)
 constexpr int kMsGranule = 128;   // elements of H the MFMA shrink fetches per row at a time; shares of H are whole granules
 constexpr int kMfmaExpandCols = 256; // columns per MFMA-expand item (4 wavefronts x 64)
-constexpr int kXcds = 8;         // accelerator dies (each with its own L2); MFMA lists are padded to this
+constexpr int kMfmaRunMax = 16;  // most 32-token tiles an MFMA-expand workgroup walks
 constexpr int kRankPad = 32;      // v rows are zero-padded to a multiple of this many ranks
 
 // ---------------------------------------------------------------------------------------
@@ -145,7 +145,7 @@ struct slora_pool {
     int64_t live_plans = 0;
     int64_t mfma_min_tokens = 16;
     int64_t mfma_min_tiles = 32;
-    int64_t xcd_group = 0;                            // bit 1: MFMA expand list grouped per XCD (bit 0, once the same for the shrink list, is ignored)
+    int64_t xcd_group = 0;                            // accepted, no effect
     int64_t upload_groups = 32;                       // workgroups of an adapter upload from host memory
     int64_t fuse_decode = 1;                          // 0: never, 1: when the batch has enough small groups, 2: always
     int64_t shrink_pages = 4;                         // pages of A per vector-shrink item (its x rows are staged once for all of them)
@@ -193,6 +193,8 @@ struct slora_plan {
     std::vector<slora::MsItem> ms_items;
     std::vector<slora::MsItem> mj_items; // one record per split tile, for the kernel that joins the shares
     int32_t ms_max_nj = 0;     // most ranks in one MFMA shrink item (sizes the kernel's LDS)
+    int32_t me_run = 1;        // list entries per MFMA expand workgroup (a run of tiles, padded with empty entries)
+    int32_t me_stages = 0;     // most 32-rank stages an MFMA expand workgroup keeps in registers (sizes its LDS)
     int32_t n_sync = 0;        // split tiles
     int64_t part_floats = 0;   // partial sums of the split tiles, per slot
     int32_t n_rank_blocks = 1; // kMsRanks-blocks per row of v (exponent sets per tile)
