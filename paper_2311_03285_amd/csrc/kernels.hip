@@ -572,46 +572,56 @@ __device__ __forceinline__ void split_pieces(const float (&f)[8], u32x4 (&piece)
 }
 
 // ---------------------------------------------------------------------------------------
-// prefill shrink: V[pos, j] = sum_h x[tok, h] * Apage_j[h] for up to 128 tokens of one adapter
-// (MB = 2 or 4 blocks of 32 rows, one per wavefront), up to 128 of its ranks (NB = 1, 2 or 4
-// blocks of 32) and a range of H.
+// prefill shrink: V[pos, j] = sum_h x[tok, h] * Apage_j[h] for up to 128 tokens of one adapter,
+// up to 128 of its ranks and a range of H (one work item).
 //
-// An LDS-tiled product with the second operand gathered through the page list.  The range of H
-// is walked in chunks of 64 elements.  Per chunk the workgroup copies the x rows and the page
-// rows (128 bytes of each) into LDS; the rows are fetched 256 bytes at a time with coalesced
-// 16-byte loads through a register ring that keeps two such granules in flight.  LDS rows are
-// padded by 16 bytes; wavefront w owns token block w, reads its operands in MFMA layout with
-// 16-byte LDS loads and accumulates 32 x 32 tiles for all rank blocks, so no sum across
-// wavefronts is needed.  Large tiles (128 tokens share every page row) keep the pages from
-// being fetched once per 32 or 64 tokens.
+// A workgroup takes the item's tokens, or sub_tok of them when the items alone are too few (the plan
+// decides): a tile of MB (1, 2, 4) blocks of 32 token rows x NL (1..4) blocks of 32 page rows.  Its range of H is
+// walked in pieces of 64 elements (128 bytes of every row).  Pieces travel from memory straight
+// into LDS (global_load_lds, 16 bytes per lane: 8 rows of 128 bytes per instruction) through a ring
+// of S stages, so the loads in flight cost no registers and the wavefronts never copy anything;
+// one barrier per piece hands a stage over: after it every wavefront's part of the piece has
+// arrived, and the stage read a piece ago may be overwritten.  The 16-byte groups of a row are
+// permuted in LDS (group p of row r sits at p ^ (r / 2 % 8)), on the address side of the load, so
+// that the 16 rows an operand read touches at a time fall into different banks.
 //
-// A workgroup streams its rows at a rate set by the loads it keeps in flight, so the scheduler
-// cuts the H range of a tile into n_parts shares, one workgroup each.  A share leaves its
+// The four wavefronts share the tile's 32 x 32 blocks out between them; the two accumulators of a
+// single rank block (even and odd k-steps) meet at the end, in a fixed order.  The finished sums pass through LDS once so that a lane holds 8 consecutive ranks of one
+// token - the 16 bytes it owns in an operand fragment.
+//
+// Bound by what a compute unit can have outstanding towards L2 (about 90 lines of 128 bytes on every
+// streaming kernel here, whatever is queued behind them), so lines that hit in L2 cost a good part of
+// what lines from HBM cost: large tiles (128 tokens share every page row) keep the page re-reads down.
+// Stage time with the join, 4 slots: 4524 tokens of H = 4096 (16 prompts, ranks 8-128) 60 us with a
+// register ring copied to LDS (48 beside the streaming expand below), 46 now; 3781 tokens of H = 5120
+// 57 -> 55; 24675 tokens of H = 4096 (ranks 16-64) 167 -> 164 = 5.3 TB/s of x and pages; 2615 tokens of
+// H = 2568 (ranks 5-200, sub-tiles of 32 tokens) 62 -> 35 us.  The sums
+// are formed in the same order as before and are bit-identical.  Tried: rings private to a wavefront
+// (no barriers, k split over the wavefronts) 50 us on the first of these, separate deep x and shallow
+// page rings with a loader role per wavefront 52-57, three workgroups per compute unit with shorter
+// rings 55, other cache policies than streaming x + plain pages 52-60.
+//
+// The scheduler may cut the range of H into n_parts shares, one workgroup each.  A share leaves its
 // partial sums (fp32) in the slot's scratch; a second, small kernel (join_shares_kernel, one
 // workgroup per split tile) adds them up in the order of their numbers.  The kernel boundary
-// is the only synchronisation: arrival counters with device-wide fences inside the shrink were
-// tried and cost more than the extra launch (a fence per workgroup writes back and invalidates
-// the die's whole L2: cfg3's shrink went from 77 us unsplit to 93 us with 168 shares).
+// is the only synchronisation.
 //
 // The finished tile goes to the expand as MFMA operand fragments (see VPieces).  For binary16
 // pools every token row is first scaled by a power of two, 2^e, that puts its largest |v| into
 // [2^10, 2^11): the hi piece then holds 11 bits and the lo piece 11 more whatever the magnitude
 // of v (row maxima in [2^-42, 2^35); the pieces overflow from 2^40 on).  e (clamped to [-24, 40]) is left
-// beside the fragments; the expand scales its accumulators by 2^e and back.
+// beside the fragments; the expand scales its accumulators back.
 // Token rows beyond the item and ranks beyond the adapter's are read from a valid row instead;
 // their results are not stored, or stored as zero (ranks up to the next multiple of 32, so the
 // expand can read whole blocks).
 // ---------------------------------------------------------------------------------------
 constexpr int kMfmaThreads = 256;
-constexpr int kMsChunk = kMsGranule / 2;             // elements of H per LDS chunk
-constexpr int kMsRowBytes = kMsChunk * 2;            // bytes of one row per chunk
-constexpr int kMsGranuleBytes = kMsGranule * 2;      // bytes of one row fetched at a time
-constexpr int kMsLdsRow = kMsRowBytes + 16;          // padded LDS row
-constexpr int kRing = 2;                             // granules in flight
-constexpr int kMsRowsPerPass = kMfmaThreads / 8;     // rows covered by one load per thread
-constexpr int kEpiStride = 36;                       // floats per row of a wavefront's 32 x 32 staging tile
+constexpr int kPiece = 64;                           // elements of H per piece
+constexpr int kPieceBytes = kPiece * 2;              // bytes of a row per piece
+constexpr int kPieceBlock = kMsBlockBytes;           // bytes of 32 rows of a piece in LDS
+static_assert(kMsBlockBytes == 32 * kPieceBytes, "the ring is laid out in pieces");
 constexpr int kExpMin = -24, kExpMax = 40;           // range of the row exponents of binary16 pools
-static_assert(kMsRowsPerPass == 32 && kMsTok == 128 && kMsRanks == 128, "copy duty and tile shape are tied");
+static_assert(kMsGranule % kPiece == 0 && kMsTok == 128 && kMsRanks == 128, "pieces and tiles are tied");
 
 __device__ __forceinline__ float pow2f(int e) { return __uint_as_float((uint32_t)(e + 127) << 23); }
 
@@ -622,14 +632,24 @@ __device__ __forceinline__ void load_to_lds(const unsigned char *src, unsigned c
     __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
                                      (__attribute__((address_space(3))) void *)dst, 16, 0, AUX);
 }
+constexpr int kLoadStreaming = 2; // cache policy "nt"
+
 // N 16-byte LDS reads, waited for together.  Reads and wait are one asm block because the compiler
 // cannot tell which stage of a ring filled by global_load_lds a read touches: before an ordinary
 // LDS read it waits for every load in flight.
 template <int N>
 __device__ __forceinline__ void lds_read(const uint32_t (&a)[N], u32x4 (&o)[N])
 {
-    static_assert(N == 4 || N == 6, "write the block for this number of reads");
-    if constexpr (N == 4)
+    static_assert(N == 2 || N == 4 || N == 6 || N == 8 || N == 10 || N == 12, "write the block for this number of reads");
+    if constexpr (N == 2)
+        asm volatile(
+            "ds_read_b128 %0, %2\n\t"
+            "ds_read_b128 %1, %3\n\t"
+            "s_waitcnt lgkmcnt(0)"
+            : "=&v"(o[0]), "=&v"(o[1])
+            : "v"(a[0]), "v"(a[1])
+            : "memory");
+    else if constexpr (N == 4)
         asm volatile(
             "ds_read_b128 %0, %4\n\t"
             "ds_read_b128 %1, %5\n\t"
@@ -651,32 +671,58 @@ __device__ __forceinline__ void lds_read(const uint32_t (&a)[N], u32x4 (&o)[N])
             : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]), "=&v"(o[4]), "=&v"(o[5])
             : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5])
             : "memory");
+    else if constexpr (N == 8)
+        asm volatile(
+            "ds_read_b128 %0, %8\n\t"
+            "ds_read_b128 %1, %9\n\t"
+            "ds_read_b128 %2, %10\n\t"
+            "ds_read_b128 %3, %11\n\t"
+            "ds_read_b128 %4, %12\n\t"
+            "ds_read_b128 %5, %13\n\t"
+            "ds_read_b128 %6, %14\n\t"
+            "ds_read_b128 %7, %15\n\t"
+            "s_waitcnt lgkmcnt(0)"
+            : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]), "=&v"(o[4]), "=&v"(o[5]), "=&v"(o[6]), "=&v"(o[7])
+            : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7])
+            : "memory");
+    else if constexpr (N == 10)
+        asm volatile(
+            "ds_read_b128 %0, %10\n\t"
+            "ds_read_b128 %1, %11\n\t"
+            "ds_read_b128 %2, %12\n\t"
+            "ds_read_b128 %3, %13\n\t"
+            "ds_read_b128 %4, %14\n\t"
+            "ds_read_b128 %5, %15\n\t"
+            "ds_read_b128 %6, %16\n\t"
+            "ds_read_b128 %7, %17\n\t"
+            "ds_read_b128 %8, %18\n\t"
+            "ds_read_b128 %9, %19\n\t"
+            "s_waitcnt lgkmcnt(0)"
+            : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]), "=&v"(o[4]), "=&v"(o[5]), "=&v"(o[6]), "=&v"(o[7]), "=&v"(o[8]), "=&v"(o[9])
+            : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]), "v"(a[8]), "v"(a[9])
+            : "memory");
+    else if constexpr (N == 12)
+        asm volatile(
+            "ds_read_b128 %0, %12\n\t"
+            "ds_read_b128 %1, %13\n\t"
+            "ds_read_b128 %2, %14\n\t"
+            "ds_read_b128 %3, %15\n\t"
+            "ds_read_b128 %4, %16\n\t"
+            "ds_read_b128 %5, %17\n\t"
+            "ds_read_b128 %6, %18\n\t"
+            "ds_read_b128 %7, %19\n\t"
+            "ds_read_b128 %8, %20\n\t"
+            "ds_read_b128 %9, %21\n\t"
+            "ds_read_b128 %10, %22\n\t"
+            "ds_read_b128 %11, %23\n\t"
+            "s_waitcnt lgkmcnt(0)"
+            : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2]), "=&v"(o[3]), "=&v"(o[4]), "=&v"(o[5]), "=&v"(o[6]), "=&v"(o[7]), "=&v"(o[8]), "=&v"(o[9]), "=&v"(o[10]), "=&v"(o[11])
+            : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]), "v"(a[8]), "v"(a[9]), "v"(a[10]), "v"(a[11])
+            : "memory");
 }
 __device__ __forceinline__ uint32_t lds_address(const unsigned char *p)
 {
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char *)p;
-}
-
-// Partial sums of a split tile: [share][token block][rank block][octet pair i][lane][8 floats];
-// lane l holds token l % 32 of its wavefront's block and the rank octets l / 32 + 2 i.
-template <int NB>
-__device__ __forceinline__ void store_share(const MsItem &it, int wave, int lane, const float (&val)[NB][2][8],
-                                            float *__restrict__ partial)
-{
-    const int mb_act = (it.ntok + 31) >> 5, nb_act = (it.nj + 31) >> 5;
-    const int64_t blk = (int64_t)mb_act * nb_act * 1024;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        if (nb < nb_act) {
-            float *dst = partial + it.part * blk + (int64_t)(wave * nb_act + nb) * 1024 + lane * 8;
-#pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                *reinterpret_cast<f32x4 *>(dst + i * 512) = f32x4{val[nb][i][0], val[nb][i][1], val[nb][i][2], val[nb][i][3]};
-                *reinterpret_cast<f32x4 *>(dst + i * 512 + 4) =
-                    f32x4{val[nb][i][4], val[nb][i][5], val[nb][i][6], val[nb][i][7]};
-            }
-        }
-    }
 }
 
 // Exponent e of the power of two that scales a token row of a binary16 pool: the row's largest
@@ -688,44 +734,37 @@ __device__ __forceinline__ int row_exponent(float vmax)
     return min(max(10 - (be - 127), kExpMin), kExpMax);
 }
 
-// Ranks beyond the adapter's become zero; returns the largest |value| this lane holds in the block.
-__device__ __forceinline__ float mask_block(const MsItem &it, int nb, int q, float (&val)[2][8])
+// Ranks beyond the adapter's become zero; returns the largest |value| of the eight.
+__device__ __forceinline__ float mask_octet(const MsItem &it, int oct, float (&val)[8])
 {
     float vmax = 0.f;
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            const int jn = nb * 32 + (q + 2 * i) * 8 + e;
-            const float f = jn < it.nj ? val[i][e] : 0.f;
-            val[i][e] = f;
-            vmax = fmaxf(vmax, fabsf(f));
-        }
+    for (int e = 0; e < 8; ++e) {
+        const float f = oct * 8 + e < it.nj ? val[e] : 0.f;
+        val[e] = f;
+        vmax = fmaxf(vmax, fabsf(f));
+    }
     return vmax;
 }
 
-// One 32-token x 32-rank block of finished sums -> the two operand fragments it fills (lane l:
-// token l % 32, rank octets l / 32 and l / 32 + 2), scaled by `sc` first.
+// Ranks 8 * oct .. + 7 of the item, finished, of token row `row` of v tile `tile` -> the 16 bytes
+// they fill in each piece's operand fragment, scaled by `sc` first.
 template <int DT>
-__device__ __forceinline__ void store_block(const MsItem &it, int tile, int nb, int lane, const float (&val)[2][8],
+__device__ __forceinline__ void store_octet(const MsItem &it, int tile, int row, int oct, const float (&val)[8],
                                             float sc, int v_stride, uint16_t *__restrict__ vfrag)
 {
     constexpr int NP = VPieces<DT>::N;
     const int n_kk = v_stride >> 4;
+    const int kk = (it.j0 >> 4) + (oct >> 1);
+    if (kk >= n_kk) return;
+    float f[8];
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-        const int kk = (it.j0 >> 4) + 2 * nb + i;
-        if (kk < n_kk) {
-            float f[8];
+    for (int k = 0; k < 8; ++k) f[k] = DT == SLORA_F16 ? val[k] * sc : val[k];
+    uint16_t *dst = vfrag + vfrag_index(tile, kk, 0, n_kk, NP) + (row + 32 * (oct & 1)) * 8;
+    u32x4 piece[NP];
+    split_pieces<DT>(f, piece);
 #pragma unroll
-            for (int k = 0; k < 8; ++k) f[k] = DT == SLORA_F16 ? val[i][k] * sc : val[i][k];
-            uint16_t *dst = vfrag + vfrag_index(tile, kk, 0, n_kk, NP) + lane * 8;
-            u32x4 piece[NP];
-            split_pieces<DT>(f, piece);
-#pragma unroll
-            for (int p = 0; p < NP; ++p) *reinterpret_cast<u32x4 *>(dst + p * (kWave * 8)) = piece[p];
-        }
-    }
+    for (int p = 0; p < NP; ++p) *reinterpret_cast<u32x4 *>(dst + p * (kWave * 8)) = piece[p];
 }
 
 // Row exponents are kept as signed bytes, 32 per (v tile, rank block), ordered so that the 16
@@ -738,225 +777,212 @@ __device__ __forceinline__ int8_t *vexp_row(int8_t *vexp, const MsItem &it, int 
     return vexp + ((int64_t)tile * n_rb + it.j0 / kMsRanks) * 32 + qq * 16 + g * 4 + k;
 }
 
-// The finished sums of one token block (this wavefront's), all rank blocks -> operand fragments.
-template <int DT, int NB>
-__device__ __forceinline__ void finish_tile(const MsItem &it, int wave, int lane, float (&val)[NB][2][8], int v_stride,
-                                            uint16_t *__restrict__ vfrag, int8_t *__restrict__ vexp)
+// Partial sums of a split tile: [share][token block][rank block][octet pair i][lane][8 floats];
+// lane l holds token l % 32 of the block and the rank octets l / 32 and l / 32 + 2 i.
+__device__ __forceinline__ int64_t share_block(const MsItem &it) // floats of one share
 {
-    const int row = lane & 31, q = lane >> 5;
-    const int nb_act = (it.nj + 31) >> 5;
-    const bool token_ok = wave * 32 + row < it.ntok;
-    float vmax = 0.f;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-        if (nb < nb_act) vmax = fmaxf(vmax, mask_block(it, nb, q, val[nb]));
-    float sc = 1.f;
-    if constexpr (DT == SLORA_F16) {
-        vmax = fmaxf(vmax, __shfl_xor(vmax, 32, kWave)); // the other half of the token's ranks
-        const int e = row_exponent(vmax);
-        sc = pow2f(e);
-        if (q == 0) *vexp_row(vexp, it, it.tile + wave, v_stride, row) = (int8_t)(token_ok ? e : 0);
-    }
-    if (!token_ok) return;
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
-        if (nb < nb_act) store_block<DT>(it, it.tile + wave, nb, lane, val[nb], sc, v_stride, vfrag);
+    return (int64_t)((it.ntok + 31) >> 5) * ((it.nj + 31) >> 5) * 1024;
 }
 
-template <int DT, int NB, int MB>
-__device__ __forceinline__ void shrink_mfma_tile(const MsItem &it, const int32_t *__restrict__ pa,
+template <int DT, int MB, int NL>
+__device__ __forceinline__ void shrink_mfma_tile(const MsItem &it, unsigned item_no, int sub0, const int32_t *__restrict__ pa,
                                                  const unsigned char *__restrict__ x,
                                                  const uint16_t *__restrict__ pool,
                                                  const int32_t *__restrict__ tok_idx, int H, int v_stride,
                                                  uint16_t *__restrict__ vfrag, int8_t *__restrict__ vexp,
-                                                 float *__restrict__ partial, unsigned char *lds, int args_n)
+                                                 float *__restrict__ partial, unsigned char *lds)
 {
-    constexpr int kLoads = MB + NB;                 // 16-byte loads per thread and chunk
-    constexpr int kRows = 32 * (MB + NB);           // LDS rows of one buffer
+    constexpr int kBlocks = MB + NL;                // 32-row blocks = loads per wavefront and piece
+    constexpr int S = ms_stages(kBlocks);
+    constexpr int kStage = kBlocks * kPieceBlock;
+    constexpr int NB = NL == 3 && MB < 4 ? 4 : NL;  // rank blocks computed (the fourth of three is dropped)
+    constexpr int WN = NB >= 4 / MB ? 4 / MB : NB;  // wavefronts along the ranks
+    constexpr int NBW = NB / WN;                    // rank blocks per wavefront
+    // A single rank block has two accumulators, for the even and the odd k-steps: one would make every
+    // MFMA wait for the one before it.  They sit in two wavefronts if there are that many (KG = 2).
+    constexpr int KG = NL == 1 && MB * WN <= 2 ? 2 : 1;
+    constexpr int KA = NL == 1 && KG == 1 ? 2 : 1;  // accumulators of a wavefront and rank block
+    constexpr int KS = 4 / KG;                      // k-steps per wavefront and piece
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
-    const int wave = tid / kWave;
-    const int row = lane & 31;
-    const int q = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
     const int64_t row_bytes = (int64_t)H * 2;
 
-    // ---- copy duty of this thread: byte column cb of LDS rows r8 + 32*i (x rows, then pages)
-    const int r8 = tid >> 3;
-    const int cb = (tid & 7) * 16;
-    const unsigned char *src[kLoads];
+    // ---- copy duty: rows 8 * wave .. + 7 of every block, lane -> row lane / 8, LDS group lane % 8
+    const int r8 = wave * 8 + (lane >> 3);
+    const int group = ((lane & 7) ^ ((r8 >> 1) & 7)) * 16; // byte offset, in the piece, of what this lane fetches
+    const unsigned char *src[kBlocks];
 #pragma unroll
     for (int i = 0; i < MB; ++i) {
-        const int r = r8 + kMsRowsPerPass * i;
+        const int r = sub0 + i * 32 + r8;
         src[i] = x + (int64_t)tok_idx[it.pos0 + (r < it.ntok ? r : 0)] * row_bytes;
     }
 #pragma unroll
-    for (int i = 0; i < NB; ++i) {
-        const int j = r8 + kMsRowsPerPass * i;
+    for (int i = 0; i < NL; ++i) {
+        const int j = i * 32 + r8;
         src[MB + i] = reinterpret_cast<const unsigned char *>(pool) + (int64_t)pa[j < it.nj ? j : 0] * row_bytes;
     }
-    const int n_gran = it.c1 - it.c0;
+    // Every item starts its sweep over its share at another granule (two pieces) and wraps around: tiles
+    // launched together would otherwise ask the same few memory channels for the same column offset
+    // of their rows at the same time.  By item: every slot of a launch, every sub-tile, and a launch
+    // of any number of slots add in the same order.
+    constexpr int kPerGranule = kMsGranule / kPiece;
+    const int n_gran = it.c1 - it.c0, n = n_gran * kPerGranule; // granules, pieces
+    const int g_first = (int)((item_no * 5u) % (unsigned)n_gran);
+    auto piece_of = [&](int s) { // position in H of the s-th piece of the sweep
+        const int g = s / kPerGranule + g_first;
+        return (it.c0 + (g < n_gran ? g : g - n_gran)) * kPerGranule + s % kPerGranule;
+    };
+    auto load = [&](int s) {
+        // bytes past the row's end (last granule of a ragged H) are clamped into the row; they are
+        // dropped when the operands are read
+        const int64_t off = min((int64_t)piece_of(s) * kPieceBytes + group, row_bytes - 16);
+        unsigned char *dst = lds + (s % S) * kStage + wave * 1024;
+#pragma unroll
+        for (int i = 0; i < kBlocks; ++i) {
+            // x rows are read once: streaming; page rows come back for the adapter's other tiles
+            if (i < MB)
+                load_to_lds<kLoadStreaming>(src[i] + off, dst + i * kPieceBlock);
+            else
+                load_to_lds<0>(src[i] + off, dst + i * kPieceBlock);
+        }
+    };
 
-    // Memory is read in granules of 256 bytes per row (two LDS chunks): a thread fetches the two
-    // 16-byte pieces cb and cb + 128 of a granule back to back, so the two 128-byte lines of a
-    // granule are requested together (128-byte pieces fetched a chunk apart ran at two thirds of
-    // the rate).
-    struct Regs {
-        u32x4 w[2][kLoads];
-    };
-    // Every workgroup starts its sweep over the share at another granule and wraps around: tiles
-    // launched together would otherwise walk H in lockstep, all of them asking the same few memory
-    // channels for the same column offset of their rows at the same time (a load-only probe of
-    // this access pattern: 4.5 TB/s in lockstep, 5.5 TB/s with staggered starts).  The order of a
-    // sum over H changes with it, its value only in the rounding.
-    const int g_first = (int)(((blockIdx.x / (unsigned)args_n) * 5u) % (unsigned)n_gran); // by item: every slot of a launch, and a launch of any number of slots, adds in the same order
-    auto granule = [&](int g) { // position in H of the share's g-th granule in this workgroup's order
-        const int k = min(g, n_gran - 1) + g_first;
-        return it.c0 + (k < n_gran ? k : k - n_gran);
-    };
-    auto load = [&](int g, Regs &r) { // g-th granule of the share, bytes clamped into the row
-        const int gg = granule(g);
+    const int row = lane & 31, q = lane >> 5;
+    const int mb = wave % MB, wn = (wave / MB) % WN, kg = wave / (MB * WN);
+    const bool computes = wave < MB * WN * KG;       // a tile of one token block leaves wavefronts without work
+    f32x16 acc[NBW][KA];
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const int64_t off = min((int64_t)gg * kMsGranuleBytes + h * kMsRowBytes + cb, row_bytes - 16);
-#pragma unroll
-            for (int i = 0; i < kLoads; ++i) {
-                // x rows are read once: streaming loads; page rows come back for the adapter's other
-                // token tiles and stay cacheable (measured on 8192-token batches of rank 8 / 128:
-                // all plain 77 / 115 us, all streaming 68 / 121 us)
-                if (i < MB)
-                    r.w[h][i] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(src[i] + off));
-                else
-                    r.w[h][i] = *reinterpret_cast<const u32x4 *>(src[i] + off);
-            }
-        }
-    };
-    const int last_gran = (int)((row_bytes - 1) / kMsGranuleBytes);
-    const bool ragged = row_bytes % kMsGranuleBytes != 0; // only then can a granule reach past the row
-    auto stash = [&](int g, int h, const Regs &r) { // half h of granule g -> LDS buffer h; bytes past the row become zero
-        unsigned char *buf = lds + h * (kRows * kMsLdsRow);
-        const int gg = granule(g);
-        if (ragged && gg == last_gran) { // uniform over the workgroup
-            const bool ok = (int64_t)gg * kMsGranuleBytes + h * kMsRowBytes + cb < row_bytes;
-            const u32x4 zero = u32x4{0u, 0u, 0u, 0u};
-#pragma unroll
-            for (int i = 0; i < kLoads; ++i)
-                *reinterpret_cast<u32x4 *>(buf + (r8 + kMsRowsPerPass * i) * kMsLdsRow + cb) = ok ? r.w[h][i] : zero;
-        } else {
-#pragma unroll
-            for (int i = 0; i < kLoads; ++i)
-                *reinterpret_cast<u32x4 *>(buf + (r8 + kMsRowsPerPass * i) * kMsLdsRow + cb) = r.w[h][i];
-        }
-    };
-    // A single rank block would make every MFMA wait for the one before it (they share the
-    // accumulator): such tiles keep two accumulators, for alternate k-steps, added at the end.
-    constexpr int KA = NB == 1 ? 2 : 1;
-    f32x16 acc[NB][KA];
-#pragma unroll
-    for (int nb = 0; nb < NB; ++nb)
+    for (int b = 0; b < NBW; ++b)
 #pragma unroll
         for (int a = 0; a < KA; ++a)
 #pragma unroll
-            for (int e = 0; e < 16; ++e) acc[nb][a][e] = 0.f;
-    auto compute = [&](int h) { // the four k-steps of the chunk in LDS buffer h, for this wavefront's token block
-        if (wave >= MB) return;
-        const unsigned char *buf = lds + h * (kRows * kMsLdsRow);
+            for (int e = 0; e < 16; ++e) acc[b][a][e] = 0.f;
+    // LDS addresses, in stage 0, of this lane's operands: KS of x, then KS of each rank block
+    uint32_t lds_at[KS * (1 + NBW)];
 #pragma unroll
-        for (int k = 0; k < kMsChunk / 16; ++k) {
-            const int kb = k * 32 + q * 16; // byte offset of this lane's 8 k-values in the row
-            const u32x4 xa = *reinterpret_cast<const u32x4 *>(buf + (wave * 32 + row) * kMsLdsRow + kb);
-            u32x4 pb[NB];
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb)
-                pb[nb] = *reinterpret_cast<const u32x4 *>(buf + (32 * MB + nb * 32 + row) * kMsLdsRow + kb);
-#pragma unroll
-            for (int nb = 0; nb < NB; ++nb) acc[nb][k % KA] = mfma32<DT>(xa, pb[nb], acc[nb][k % KA]);
-        }
-    };
-
-    // register ring: granule g is copied to LDS, half by half, while granule g+1 is still in
-    // flight and granule g+2 is requested.  The two halves use the two LDS buffers, one barrier
-    // each.  The last granules, which have nothing left to request, are peeled off the loop: its
-    // body then has no condition in it, and nothing is fetched that is not used.
-    static_assert(kRing == 2, "the peeled loop below is written for a ring of two");
-    auto step = [&](int g, Regs &r, bool more) { // `more`: granule g + 2 exists and is requested into r
-        stash(g, 0, r);
-        __syncthreads();
-        compute(0);
-        stash(g, 1, r);
-        if (more) load(g + 2, r);
-        __syncthreads();
-        compute(1);
-    };
-    Regs ring[kRing];
-    load(0, ring[0]);
-    // keep the granules' loads in issue order: the wait before a granule is copied to LDS then
-    // counts only the loads of the younger one as outstanding
-    __builtin_amdgcn_sched_barrier(0);
-    load(n_gran > 1 ? 1 : 0, ring[1]); // a share of one granule fetches it twice
-    __builtin_amdgcn_sched_barrier(0);
-    if constexpr (kLoads <= 6) {
-        int g = 0;
-        for (; g + 3 < n_gran; g += 2) {
-            step(g, ring[0], true);
-            step(g + 1, ring[1], true);
-        }
-        // one to three granules are left; only the first of three still has one to request
-        step(g, ring[0], g + 2 < n_gran);
-        if (g + 1 < n_gran) step(g + 1, ring[1], false);
-        if (g + 2 < n_gran) step(g + 2, ring[0], false);
-    } else {
-        // the widest tiles have no register to spare for the peeled copies: their loop keeps
-        // requesting (the last granule again, dropped) to its end
-        for (int g = 0; g < n_gran; g += 2) {
-            step(g, ring[0], true);
-            if (g + 1 < n_gran) step(g + 1, ring[1], true);
-        }
+    for (int i = 0; i < KS * (1 + NBW); ++i) {
+        const int p = 2 * ((i % KS) * KG + kg % KG) + q; // 16-byte group of the lane's 8 k-values
+        const int blk = i < KS ? mb : MB + min(wn * NBW + i / KS - 1, NL - 1);
+        lds_at[i] = lds_address(lds) + blk * kPieceBlock + row * kPieceBytes + ((p ^ ((row >> 1) & 7)) * 16);
     }
-    __syncthreads(); // the chunk buffers are free: each wavefront now stages its tiles in its own part
+    const bool ragged = row_bytes % (kMsGranule * 2) != 0;
+    const int full = (int)(row_bytes / kPieceBytes); // pieces that lie inside the row
 
-    // ---- accumulator layout -> 8 consecutive ranks of one token per lane -------------------
-    // lane l ends up with token l % 32 of its wavefront's v tile and, per 32-rank block, the rank
-    // octets l / 32 and l / 32 + 2: exactly the 16 bytes it owns in two operand fragments.
-    const int mb_act = (it.ntok + 31) >> 5;          // token blocks / rank blocks that exist
-    const int nb_act = (it.nj + 31) >> 5;
-    const bool live = wave < mb_act;
-    float *stage = reinterpret_cast<float *>(lds) + wave * 32 * kEpiStride;
-    float val[NB][2][8];
 #pragma unroll
-    for (int nb = 0; nb < NB; ++nb) {
-        if (live && nb < nb_act) {
+    for (int s = 0; s < S - 1; ++s)
+        if (s < n) load(s);
+    for (int s = 0; s < n; ++s) {
+        // piece s has arrived when at most the S - 2 younger ones are outstanding
+        if (s + S - 2 < n)
+            asm volatile("s_waitcnt vmcnt(%0)" ::"n"((S - 2) * kBlocks) : "memory");
+        else
+            asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+        if (s + S - 1 < n) load(s + S - 1);
+        if (!computes) continue;
+        const uint32_t stage_at = (uint32_t)((s % S) * kStage);
+        // operands of KC k-steps at a time: a lane's KC groups of x, then of each rank block
+        constexpr int KC = KS * (1 + NBW) > 12 ? KS / 2 : KS;
 #pragma unroll
-            for (int vv = 0; vv < 16; ++vv) {
-                float sum = acc[nb][0][vv];
-                if constexpr (KA == 2) sum += acc[nb][1][vv];
-                stage[mfma_row(vv, lane) * kEpiStride + row] = sum;
-            }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+        for (int k0 = 0; k0 < KS; k0 += KC) {
+            uint32_t at[KC * (1 + NBW)];
+            u32x4 op[KC * (1 + NBW)];
 #pragma unroll
-            for (int i = 0; i < 2; ++i) {
-                const int oct = q + 2 * i;
-                const f32x4 lo = *reinterpret_cast<const f32x4 *>(stage + row * kEpiStride + oct * 8);
-                const f32x4 hi = *reinterpret_cast<const f32x4 *>(stage + row * kEpiStride + oct * 8 + 4);
+            for (int i = 0; i < KC * (1 + NBW); ++i) at[i] = lds_at[(i / KC) * KS + k0 + i % KC] + stage_at;
+            lds_read(at, op);
+            if (ragged && piece_of(s) >= full) { // uniform: groups past the row's end
 #pragma unroll
-                for (int e = 0; e < 4; ++e) {
-                    val[nb][i][e] = lo[e];
-                    val[nb][i][4 + e] = hi[e];
+                for (int i = 0; i < KC * (1 + NBW); ++i) {
+                    const int p = 2 * ((k0 + i % KC) * KG + kg) + q;
+                    op[i] = (int64_t)piece_of(s) * kPieceBytes + p * 16 < row_bytes ? op[i] : u32x4{0u, 0u, 0u, 0u};
                 }
             }
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-            __builtin_amdgcn_wave_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+#pragma unroll
+            for (int k = 0; k < KC; ++k)
+#pragma unroll
+                for (int b = 0; b < NBW; ++b)
+                    acc[b][(k0 + k) % KA] = mfma32<DT>(op[k], op[KC * (1 + b) + k], acc[b][(k0 + k) % KA]);
         }
     }
+    __syncthreads(); // the ring is free: it now stages the finished blocks
 
-    // ---- a share of a split tile: leave the partial sums for join_shares_kernel ----------------
+    // ---- accumulator layout -> 8 consecutive ranks of one token per lane -------------------------
+    // Block (kg, mb, nb) is 32 x 32 floats; group g (four ranks) of row r sits at g ^ (r / 2 % 8).
+    float *stage = reinterpret_cast<float *>(lds);
+    if (computes) {
+#pragma unroll
+        for (int b = 0; b < NBW; ++b) {
+            float *blk = stage + ((kg * MB + mb) * NB + wn * NBW + b) * 1024;
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const int r = mfma_row(v, lane);
+                float sum = acc[b][0][v];
+                if constexpr (KA == 2) sum += acc[b][1][v];
+                blk[r * 32 + (((row >> 2) ^ ((r >> 1) & 7)) << 2) + (row & 3)] = sum;
+            }
+        }
+    }
+    __syncthreads();
+    // wavefront w finishes rows R w .. R w + R - 1; a lane has one row and every OL-th octet of ranks
+    constexpr int R = 8 * MB, OL = kWave / R, NI = (NB * 4 + OL - 1) / OL;
+    const int tb = (wave * R + lane % R) >> 5, r = (wave * R + lane % R) & 31; // token block and row of the tile
+    const int trow = sub0 + tb * 32 + r;             // token of the item
+    const int nb_act = (it.nj + 31) >> 5;
+    const int o0 = lane / R;
+    float val[NI][8];
+    float vmax = 0.f;
+#pragma unroll
+    for (int i = 0; i < NI; ++i) {
+        const int oct = o0 + OL * i;
+#pragma unroll
+        for (int e = 0; e < 8; ++e) val[i][e] = 0.f;
+        if (oct < nb_act * 4) {
+#pragma unroll
+            for (int k = 0; k < KG; ++k) {
+                const float *blk = stage + ((k * MB + tb) * NB + (oct >> 2)) * 1024 + r * 32;
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const f32x4 f = *reinterpret_cast<const f32x4 *>(blk + (((2 * (oct & 3) + h) ^ ((r >> 1) & 7)) << 2));
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) val[i][4 * h + e] += f[e];
+                }
+            }
+        }
+    }
+    // ---- a share of a split tile: leave the partial sums for join_shares_kernel -------------------
     if (it.n_parts > 1) {
-        if (live) store_share<NB>(it, wave, lane, val, partial);
+        if (trow < ((it.ntok + 31) & ~31)) {
+#pragma unroll
+            for (int i = 0; i < NI; ++i) {
+                const int oct = o0 + OL * i;
+                if (oct < nb_act * 4) {
+                    float *dst = partial + it.part * share_block(it) + ((int64_t)(trow >> 5) * nb_act + (oct >> 2)) * 1024 +
+                                 ((oct >> 1) & 1) * 512 + (r + 32 * (oct & 1)) * 8;
+                    *reinterpret_cast<f32x4 *>(dst) = f32x4{val[i][0], val[i][1], val[i][2], val[i][3]};
+                    *reinterpret_cast<f32x4 *>(dst + 4) = f32x4{val[i][4], val[i][5], val[i][6], val[i][7]};
+                }
+            }
+        }
         return;
     }
-    if (live) finish_tile<DT, NB>(it, wave, lane, val, v_stride, vfrag, vexp);
+#pragma unroll
+    for (int i = 0; i < NI; ++i) vmax = fmaxf(vmax, mask_octet(it, o0 + OL * i, val[i]));
+    const int tile = it.tile + (trow >> 5);
+    const bool token_ok = trow < it.ntok;
+    float sc = 1.f;
+    if constexpr (DT == SLORA_F16) {
+#pragma unroll
+        for (int m = R; m < kWave; m <<= 1) vmax = fmaxf(vmax, __shfl_xor(vmax, m, kWave)); // the token's other ranks
+        const int e = row_exponent(vmax);
+        sc = pow2f(e);
+        if (o0 == 0 && trow < ((it.ntok + 31) & ~31)) *vexp_row(vexp, it, tile, v_stride, r) = (int8_t)(token_ok ? e : 0);
+    }
+    if (!token_ok) return;
+#pragma unroll
+    for (int i = 0; i < NI; ++i)
+        if (o0 + OL * i < nb_act * 4) store_octet<DT>(it, tile, r, o0 + OL * i, val[i], sc, v_stride, vfrag);
 }
 
 template <int DT>
@@ -964,29 +990,34 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void shrink_mfma_kernel(const MsIt
                                                                        const int32_t *__restrict__ arena,
                                                                        const uint16_t *__restrict__ pool,
                                                                        const int32_t *__restrict__ tok_idx, int H,
-                                                                       int v_stride, MultiArgs args)
+                                                                       int v_stride, int sub_tok, MultiArgs args)
 {
-    // two chunk buffers of (128 token rows + the plan's widest rank block) padded rows, sized at
-    // launch: a batch of low-rank adapters leaves room for more workgroups per compute unit
+    // the rings of the plan's largest tile, sized at launch
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     // slots vary fastest: the shares of a tile, and the tiles of an adapter, follow one another
     const int cs = blockIdx.x % args.n;
-    const MsItem it = items[blockIdx.x / args.n];
+    const unsigned rest = blockIdx.x / args.n, per_item = (unsigned)(kMsTok / sub_tok);
+    const unsigned item_no = rest / per_item;
+    const int sub = (int)(rest % per_item) * sub_tok;
+    const MsItem it = items[item_no];
+    if (sub >= it.ntok) return;              // the whole workgroup
+    const int rows = min(it.ntok - sub, sub_tok);
     const unsigned char *x = static_cast<const unsigned char *>(args.x[cs]);
     const int32_t *pa = arena + it.arena_off + (int64_t)args.slot[cs] * 2 * it.rank + it.j0;
     uint16_t *vfrag = reinterpret_cast<uint16_t *>(args.v[cs] + args.vfrag_off);
     int8_t *vexp = reinterpret_cast<int8_t *>(args.v[cs] + args.vexp_off);
     float *partial = args.v[cs] + args.part_off + it.part_off;
-#define SLORA_MS(NBV, MBV) shrink_mfma_tile<DT, NBV, MBV>(it, pa, x, pool, tok_idx, H, v_stride, vfrag, vexp, partial, lds, args.n)
-    if (it.ntok <= 64) {
-        if (it.nj <= 32) SLORA_MS(1, 2);
-        else if (it.nj <= 64) SLORA_MS(2, 2);
-        else SLORA_MS(4, 2);
-    } else {
-        if (it.nj <= 32) SLORA_MS(1, 4);
-        else if (it.nj <= 64) SLORA_MS(2, 4);
-        else SLORA_MS(4, 4);
-    }
+#define SLORA_MS(MBV, NLV) \
+    shrink_mfma_tile<DT, MBV, NLV>(it, item_no, sub, pa, x, pool, tok_idx, H, v_stride, vfrag, vexp, partial, lds)
+#define SLORA_MS_RANKS(MBV)              \
+    if (it.nj <= 32) SLORA_MS(MBV, 1);      \
+    else if (it.nj <= 64) SLORA_MS(MBV, 2); \
+    else if (it.nj <= 96) SLORA_MS(MBV, 3); \
+    else SLORA_MS(MBV, 4);
+    if (rows <= 32) { SLORA_MS_RANKS(1) }
+    else if (rows <= 64) { SLORA_MS_RANKS(2) }
+    else { SLORA_MS_RANKS(4) }
+#undef SLORA_MS_RANKS
 #undef SLORA_MS
 }
 
@@ -1015,7 +1046,7 @@ __global__ __launch_bounds__(kMfmaThreads) void join_shares_kernel(const MsItem 
 #pragma unroll
         for (int e = 0; e < 8; ++e) val[i][e] = 0.f;
     if (live) {
-        const int64_t blk = (int64_t)mb_act * nb_act * 1024;
+        const int64_t blk = share_block(it);
         const float *base = args.v[cs] + args.part_off + it.part_off + (int64_t)(tb * nb_act + nb) * 1024 + lane * 8;
         constexpr int kBatch = 4;
         for (int p0 = 0; p0 < it.n_parts; p0 += kBatch) {
@@ -1045,7 +1076,7 @@ __global__ __launch_bounds__(kMfmaThreads) void join_shares_kernel(const MsItem 
     }
     float sc = 1.f;
     const bool token_ok = tb * 32 + row < it.ntok;
-    float vmax = live ? mask_block(it, nb, q, val) : 0.f;
+    float vmax = fmaxf(mask_octet(it, nb * 4 + q, val[0]), mask_octet(it, nb * 4 + q + 2, val[1]));
     if constexpr (DT == SLORA_F16) {
         vmax = fmaxf(vmax, __shfl_xor(vmax, 32, kWave));
         if (q == 0) smax[nb][row] = vmax;
@@ -1057,9 +1088,11 @@ __global__ __launch_bounds__(kMfmaThreads) void join_shares_kernel(const MsItem 
         if (nb == 0 && q == 0)
             *vexp_row(reinterpret_cast<int8_t *>(args.v[cs] + args.vexp_off), it, it.tile + tb, v_stride, row) = (int8_t)(token_ok ? e : 0);
     }
-    if (live && token_ok)
-        store_block<DT>(it, it.tile + tb, nb, lane, val, sc, v_stride,
-                        reinterpret_cast<uint16_t *>(args.v[cs] + args.vfrag_off));
+    if (live && token_ok) {
+        uint16_t *vfrag = reinterpret_cast<uint16_t *>(args.v[cs] + args.vfrag_off);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) store_octet<DT>(it, it.tile + tb, row, nb * 4 + q + 2 * i, val[i], sc, v_stride, vfrag);
+    }
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1601,17 +1634,23 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *
         if (rc != SLORA_OK) return rc;
     }
     if (!plan->ms_items.empty()) {
-        const dim3 grid((unsigned)(plan->ms_items.size() * (size_t)n));
-        // LDS: the kernel's two chunk buffers for the widest tile of this plan (never less than the
-        // four staging tiles of the epilogue)
-        const int nb_max = plan->ms_max_nj <= 32 ? 1 : plan->ms_max_nj <= 64 ? 2 : 4;
-        const size_t lds = std::max<size_t>((size_t)2 * (kMsTok + 32 * nb_max) * kMsLdsRow, (size_t)4 * 32 * kEpiStride * sizeof(float));
-        if (pool->dtype == SLORA_F16)
-            hipLaunchKernelGGL(shrink_mfma_kernel<SLORA_F16>, grid, dim3(kMfmaThreads), lds, st, plan->d_ms,
-                               pool->d_arena, base, plan->d_tok_idx, pool->H, plan->v_stride, args);
-        else
-            hipLaunchKernelGGL(shrink_mfma_kernel<SLORA_BF16>, grid, dim3(kMfmaThreads), lds, st, plan->d_ms,
-                               pool->d_arena, base, plan->d_tok_idx, pool->H, plan->v_stride, args);
+        const dim3 grid((unsigned)(plan->ms_items.size() * (size_t)(kMsTok / plan->ms_sub_tok) * (size_t)n));
+        const size_t lds = (size_t)plan->ms_lds_bytes;
+        // more than 64 KiB of dynamic LDS has to be allowed once per kernel instance
+#define SLORA_MSK(DT)                                                                                                \
+    {                                                                                                                \
+        static bool allowed = false;                                                                                 \
+        if (!allowed && lds > 65536) {                                                                               \
+            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&shrink_mfma_kernel<DT>),             \
+                                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);              \
+            if (e != hipSuccess) return fail(SLORA_EHIP, "hipFuncSetAttribute(LDS size): %s", hipGetErrorString(e)); \
+            allowed = true;                                                                                          \
+        }                                                                                                            \
+        hipLaunchKernelGGL(shrink_mfma_kernel<DT>, grid, dim3(kMfmaThreads), lds, st, plan->d_ms, pool->d_arena,     \
+                           base, plan->d_tok_idx, pool->H, plan->v_stride, plan->ms_sub_tok, args);                  \
+    }
+        if (pool->dtype == SLORA_F16) SLORA_MSK(SLORA_F16) else SLORA_MSK(SLORA_BF16)
+#undef SLORA_MSK
         int32_t rc = check_launch("shrink_mfma");
         if (rc != SLORA_OK) return rc;
         if (plan->n_sync > 0) {

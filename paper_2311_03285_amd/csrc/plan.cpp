@@ -93,7 +93,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         plan->n_groups_vec = plan->n_groups_mfma = 0;
         plan->n_mfma_tiles = 0;
         plan->n_sync = 0;
-        plan->ms_max_nj = 0;
+        plan->ms_lds_bytes = 0;
         plan->part_floats = 0;
         plan->max_shrink_tok = 0;
         const int32_t n_chunks = (pool->H + kMsGranule - 1) / kMsGranule;
@@ -202,7 +202,6 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                         const int64_t mb = (nt + 31) / 32, nb = (nj + 31) / 32;
                         if (parts < 2 || plan->part_floats + parts * mb * nb * 1024 > (int64_t(1) << 30))
                             parts = 1;
-                        plan->ms_max_nj = std::max(plan->ms_max_nj, nj);
                         MsItem it{};
                         it.arena_off = off;
                         it.rank = g.rank;
@@ -266,6 +265,22 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         plan->n_ve_head = (int32_t)plan->ve_items.size();
         plan->vs_items.insert(plan->vs_items.end(), vs_tail.begin(), vs_tail.end());
         plan->ve_items.insert(plan->ve_items.end(), ve_tail.begin(), ve_tail.end());
+        // Tokens of an item per workgroup of the MFMA shrink.  The items of a batch of modest size are too
+        // few for the GPU; halves or quarters of their tokens read the pages two or four times as often,
+        // which pays only while compute units stand idle: 111 items 62 us in as many workgroups, 48 in 153,
+        // 35 in 222, but 236 items 47 -> 52 and 252 items 55 -> 58 us (launches of three or four slots).
+        plan->ms_sub_tok = kMsTok;
+        auto ms_wgs = [&](int32_t sub) {
+            int64_t c = 0;
+            for (const MsItem &i : plan->ms_items) c += (i.ntok + sub - 1) / sub;
+            return c * launch_slots;
+        };
+        while (plan->ms_sub_tok > 32 && ms_wgs(plan->ms_sub_tok) < 192) plan->ms_sub_tok /= 2;
+        for (const MsItem &i : plan->ms_items)
+            for (int32_t p = 0; p < i.ntok; p += plan->ms_sub_tok) {
+                const int32_t rows = std::min(plan->ms_sub_tok, i.ntok - p);
+                plan->ms_lds_bytes = std::max(plan->ms_lds_bytes, ms_lds_bytes((rows <= 32 ? 1 : rows <= 64 ? 2 : 4) + (i.nj + 31) / 32));
+            }
         // longest first: the hardware hands a workgroup to a compute unit as one becomes free, so
         // with the big shares at the head of the list and the small ones at its end the launch
         // ends on every unit at about the same time

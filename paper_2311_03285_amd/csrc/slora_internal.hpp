@@ -72,9 +72,14 @@ constexpr int kShrinkTok = 4;     // tokens per vector-shrink item (x rows stage
 constexpr int kExpandTok = 4;     // tokens per vector-expand item (accumulators in registers)
 constexpr int kExpandColsMax = 1024; // most columns per vector-expand item (a multiple of 512, <= 4096; measured best on cfg4: 1024)
 constexpr int kMfmaTok = 32;      // tokens per v tile = per MFMA-expand item (one 32-row MFMA block)
-constexpr int kMsTok = 128;       // tokens per MFMA-shrink item (one 32-row block per wavefront)
-constexpr int kMsRanks = 128;     // ranks per MFMA-shrink item (up to four 32-column blocks per wavefront)
-constexpr int kMsGranule = 128;   // elements of H the MFMA shrink fetches per row at a time; shares of H are whole granules
+constexpr int kMsTok = 128;       // most tokens per MFMA-shrink item
+constexpr int kMsRanks = 128;     // ranks per MFMA-shrink item (up to four blocks of 32)
+constexpr int kMsGranule = 128;   // shares of H are whole runs of this many elements
+// LDS of the MFMA shrink for a tile of `blocks` 32-row blocks (token rows and page rows): a ring of
+// pieces of 32 rows x 128 bytes per block, at most 80 KiB - two workgroups per compute unit
+constexpr int kMsBlockBytes = 32 * 128;
+constexpr int ms_stages(int blocks) { return blocks <= 2 ? 8 : 80 * 1024 / kMsBlockBytes / blocks; }
+constexpr int ms_lds_bytes(int blocks) { return ms_stages(blocks) * blocks * kMsBlockBytes; }
 constexpr int kMfmaExpandCols = 256; // columns per MFMA-expand item (4 wavefronts x 64)
 constexpr int kMfmaRunMax = 16;  // most 32-token tiles an MFMA-expand workgroup walks
 constexpr int kRankPad = 32;      // v rows are zero-padded to a multiple of this many ranks
@@ -192,7 +197,8 @@ struct slora_plan {
     int32_t n_vs_head = 0, n_ve_head = 0; // items of vs / ve that belong to other groups
     std::vector<slora::MsItem> ms_items;
     std::vector<slora::MsItem> mj_items; // one record per split tile, for the kernel that joins the shares
-    int32_t ms_max_nj = 0;     // most ranks in one MFMA shrink item (sizes the kernel's LDS)
+    int32_t ms_sub_tok = slora::kMsTok;  // tokens of an MFMA shrink item that one workgroup takes
+    int32_t ms_lds_bytes = 0;  // LDS of the MFMA shrink's largest tile
     int32_t me_run = 1;        // list entries per MFMA expand workgroup (a run of tiles, padded with empty entries)
     int32_t me_stages = 0;     // most 32-rank stages an MFMA expand workgroup keeps in registers (sizes its LDS)
     int32_t n_sync = 0;        // split tiles
