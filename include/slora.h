@@ -313,7 +313,9 @@ int32_t slora_lora_shrink_expand(slora_pool *pool, int32_t slot, const void *x,
  *                      (default 16; 1 forces everything onto MFMA, a value > 2^30 disables it)
  *   "mfma_min_tiles"   the MFMA kernels are used only if such groups make up at least this many
  *                      32-token tiles in the batch (default 32: fewer tiles cannot fill the GPU
- *                      and run faster on the vector kernels)
+ *                      and run faster on the vector kernels - except where those would read 30 MB
+ *                      of pages again, 128 MB beside groups of few tokens: applies to fp32 y then
+ *                      take the MFMA kernels all the same, with shorter shares of H)
  *   "mfma_split_bytes" the MFMA shrink hands the H range of a tile (up to 128 tokens x up to 128 ranks)
  *                      to several workgroups, each taking about this many bytes of x and page rows
  *                      (default 1 MiB); their partial sums are added in a fixed order by a small

@@ -10,6 +10,7 @@
 
 #include <algorithm>
 #include <mutex>
+#include <type_traits>
 
 #include "slora_internal.hpp"
 
@@ -1114,9 +1115,9 @@ __global__ __launch_bounds__(kMfmaThreads) void join_shares_kernel(const MsItem 
 // matrix cores.  The second operand needs, per lane, 8 consecutive ranks of ONE column, but a page is
 // contiguous along columns; the wavefront therefore copies a 32-rank x 64-column slab of B
 // through LDS, transposing on the way in (two ranks packed per dword), and reads its operand
-// back with one 16-byte LDS load.  The 32 x 64 tile of y passes through the same LDS (fp32, 16 rows at
-// a time) INTO the MFMA accumulators; the products are added on top, and it returns the same way, to be
-// rounded once if y is 16-bit: 16-byte accesses of whole row pieces towards memory.  All global loads are unconditional: token rows beyond the tile, columns beyond the item
+// back with one 16-byte LDS load.  The finished 32 x 64 tile passes through the same LDS (fp32, 16 rows at a
+// time) into whole row pieces, and is rounded once if y is 16-bit, added to y if y is fp32: 16-byte accesses
+// towards memory.  All global loads are unconditional: token rows beyond the tile, columns beyond the item
 // and ranks beyond the adapter's are redirected to a valid row / column / page; what they produce is
 // multiplied by the zero padding of V or is never stored.
 //
@@ -1234,7 +1235,7 @@ struct ExpandWave {
         for (int nb = 0; nb < 2; ++nb) acc[nb] = mfma32<DT>(piece, op[nb], acc[nb]);
     }
     // Binary16 pools: the shrink scaled token row i of a block of kMsRanks ranks by 2^e[i].  The accumulators
-    // follow: they hold (y + products so far) * 2^e of the CURRENT block - scaled up before the first
+    // follow: they hold (16-bit y + products so far) * 2^e of the CURRENT block - scaled up before the first
     // block, re-scaled where the block changes, scaled back at the end.  Powers of two: every step is exact.
     __device__ __forceinline__ void scale_rows(const i32x4 &from, const i32x4 &to)
     {
@@ -1247,37 +1248,45 @@ struct ExpandWave {
                 acc[1][4 * g + k] *= f;
             }
     }
-    // row pieces of the y tile -> accumulators (fp32), through LDS
-    __device__ __forceinline__ void start_from(const u32x4 (&w)[kYLoads])
+    // Accumulators at the start of a tile: y itself if it is 16-bit (widened, through LDS), zero if fp32.
+    __device__ __forceinline__ void begin(const u32x4 (&w)[kYLoads], [[maybe_unused]] const i32x4 &scale)
     {
-        float *half = reinterpret_cast<float *>(slab);
+        if constexpr (!Y16) {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) { // accumulator registers 8 h .. 8 h + 7 hold rows 16 h .. 16 h + 15
-            wave_lds_fence();
+            for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
-            for (int i = 0; i < kYLoads / 2; ++i) {
-                const u32x4 &v = w[h * (kYLoads / 2) + i];
-                float *dst = half + (yrow + kYRows * i) * kTileStride + kYVec * ygrp;
-                if constexpr (Y16) {
+                for (int v = 0; v < 16; ++v) acc[nb][v] = 0.f;
+        } else {
+            float *half = reinterpret_cast<float *>(slab);
+#pragma unroll
+            for (int h = 0; h < 2; ++h) { // accumulator registers 8 h .. 8 h + 7 hold rows 16 h .. 16 h + 15
+                wave_lds_fence();
+#pragma unroll
+                for (int i = 0; i < kYLoads / 2; ++i) {
+                    const u32x4 &v = w[h * (kYLoads / 2) + i];
+                    float *dst = half + (yrow + kYRows * i) * kTileStride + kYVec * ygrp;
                     float f[8];
 #pragma unroll
                     for (int e = 0; e < 4; ++e) widen2<DT>(v[e], f[2 * e], f[2 * e + 1]);
                     *reinterpret_cast<f32x4 *>(dst) = f32x4{f[0], f[1], f[2], f[3]};
                     *reinterpret_cast<f32x4 *>(dst + 4) = f32x4{f[4], f[5], f[6], f[7]};
-                } else {
-                    *reinterpret_cast<u32x4 *>(dst) = v;
                 }
+                wave_lds_fence();
+#pragma unroll
+                for (int v = 0; v < 8; ++v)
+#pragma unroll
+                    for (int nb = 0; nb < 2; ++nb) acc[nb][8 * h + v] = half[mfma_row(v, lane) * kTileStride + nb * 32 + n];
             }
-            wave_lds_fence();
-#pragma unroll
-            for (int v = 0; v < 8; ++v)
-#pragma unroll
-                for (int nb = 0; nb < 2; ++nb) acc[nb][8 * h + v] = half[mfma_row(v, lane) * kTileStride + nb * 32 + n];
+            if constexpr (DT == SLORA_F16) scale_rows(i32x4{0, 0, 0, 0}, scale);
         }
     }
-    // accumulators -> row pieces of the y tile, rounded once if y is 16-bit
-    __device__ __forceinline__ void finish(u32x4 (&w)[kYLoads]) const
+    // Accumulators -> row pieces of the finished y tile: rounded once if y is 16-bit, added to y if fp32
+    // (the sum of products then rounds at its own size and not at y's: 1.4e-7 -> 1.24e-7 against 64 bits for
+    // 512 tokens of rank 64, and one way through LDS less).  16-bit results are rounded from the sums formed
+    // as they always were, so that they stay the same bit for bit.
+    __device__ __forceinline__ void end(u32x4 (&w)[kYLoads], [[maybe_unused]] const i32x4 &scale)
     {
+        if constexpr (DT == SLORA_F16) scale_rows(scale, i32x4{0, 0, 0, 0});
         float *half = reinterpret_cast<float *>(slab);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -1291,11 +1300,13 @@ struct ExpandWave {
             for (int i = 0; i < kYLoads / 2; ++i) {
                 const float *src = half + (yrow + kYRows * i) * kTileStride + kYVec * ygrp;
                 u32x4 &o = w[h * (kYLoads / 2) + i];
+                const f32x4 a = *reinterpret_cast<const f32x4 *>(src);
                 if constexpr (Y16) {
-                    const f32x4 a = *reinterpret_cast<const f32x4 *>(src), b = *reinterpret_cast<const f32x4 *>(src + 4);
+                    const f32x4 b = *reinterpret_cast<const f32x4 *>(src + 4);
                     o = u32x4{narrow2<DT>(a.x, a.y), narrow2<DT>(a.z, a.w), narrow2<DT>(b.x, b.y), narrow2<DT>(b.z, b.w)};
                 } else {
-                    o = *reinterpret_cast<const u32x4 *>(src);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) o[e] = __float_as_uint(__uint_as_float(o[e]) + a[e]);
                 }
             }
         }
@@ -1345,7 +1356,7 @@ __device__ __forceinline__ void expand_mfma_run(const Item &it, int wave, const 
     }
     W w(it, colw, pbl, pool, tok_idx, H, y, reinterpret_cast<uint32_t *>(lds + 2 * kFrags * 1024 + wave * kWaveLds));
     int row_cur[kYLoads], row_next[kYLoads];
-    u32x4 yt[kYLoads], out[kYLoads];
+    u32x4 yt[kYLoads], y_next[kYLoads];
     u32x4 bop[RegStages][2][2];
     // a lane's 16 row exponents of a tile are one load
     auto exponents = [&](int t) { return *reinterpret_cast<const i32x4 *>(vexp + (int64_t)(it.tile + t) * n_rb * 32 + w.q * 16); };
@@ -1373,35 +1384,49 @@ __device__ __forceinline__ void expand_mfma_run(const Item &it, int wave, const 
     __builtin_amdgcn_s_barrier();                 // V of the first tile is complete
     asm volatile("" ::: "memory");
     for (int t = 0; t < tiles; ++t) {
-        w.start_from(yt);
-        if constexpr (DT == SLORA_F16) w.scale_rows(i32x4{0, 0, 0, 0}, e_cur);
         if (t + 1 < tiles) {
             load_v(t + 1);
             if constexpr (DT == SLORA_F16) e_next = exponents(t + 1);
-            w.load_y(row_next, yt);
+            w.load_y(row_next, y_next);
         }
+        w.begin(yt, e_cur);
         const uint32_t buf_at = frag_at + (uint32_t)((t & 1) * (kFrags * 1024));
+        // pieces P0 .. P1 - 1 of every k-step, two k-steps at a time
+        auto products = [&](auto first, auto end) {
+            constexpr int P0 = decltype(first)::value, N = decltype(end)::value - P0;
 #pragma unroll
-        for (int s = 0; s < RegStages; ++s) {
-            uint32_t at[2 * NP];
-            u32x4 piece[2 * NP];
+            for (int s = 0; s < RegStages; ++s) {
+                uint32_t at[2 * N];
+                u32x4 piece[2 * N];
 #pragma unroll
-            for (int f = 0; f < 2 * NP; ++f) at[f] = buf_at + (s * 2 * NP + f) * 1024;
-            lds_read(at, piece);
+                for (int f = 0; f < 2 * N; ++f) at[f] = buf_at + ((2 * s + f / N) * NP + P0 + f % N) * 1024;
+                lds_read(at, piece);
 #pragma unroll
-            for (int f = 0; f < 2 * NP; ++f) w.multiply(piece[f], bop[s][f / NP]);
+                for (int f = 0; f < 2 * N; ++f) w.multiply(piece[f], bop[s][f / N]);
+            }
+        };
+        if constexpr (Y16) {
+            products(std::integral_constant<int, 0>{}, std::integral_constant<int, NP>{});
+        } else {
+            // from zero: first the small pieces of all ranks, then the leading ones, so that only the latter's
+            // additions round at the size of the sum (512 tokens of rank 64, H = 4096, error against 64 bits: 1.24e-7 -> 1.17e-7
+            // in binary16, 1.15e-7 -> 1.00e-7 in bfloat16)
+            products(std::integral_constant<int, 1>{}, std::integral_constant<int, NP>{});
+            products(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
         }
-        if constexpr (DT == SLORA_F16) w.scale_rows(e_cur, i32x4{0, 0, 0, 0});
-        w.finish(out);
+        w.end(yt, e_cur);
         // what was requested for the next tile has arrived, and so have the stores of the previous one
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-        w.store_y(t, row_cur, out);
+        w.store_y(t, row_cur, yt);
         if (t + 1 < tiles) {
             // every wavefront's part of V(t + 1) is in LDS, and every one has read V(t)
             __builtin_amdgcn_s_barrier();
             asm volatile("" ::: "memory");
 #pragma unroll
-            for (int i = 0; i < kYLoads; ++i) row_cur[i] = row_next[i];
+            for (int i = 0; i < kYLoads; ++i) {
+                row_cur[i] = row_next[i];
+                yt[i] = y_next[i];
+            }
             e_cur = e_next;
             w.load_rows(min(t + 2, tiles - 1), row_next);
         }
@@ -1434,8 +1459,7 @@ __device__ __forceinline__ void expand_mfma_stream(const Item &it, int wave, con
         [[maybe_unused]] i32x4 e_cur = i32x4{0, 0, 0, 0};
         if constexpr (DT == SLORA_F16) e_cur = et[0];
         w.load_y(row, yt);
-        w.start_from(yt);
-        if constexpr (DT == SLORA_F16) w.scale_rows(i32x4{0, 0, 0, 0}, e_cur);
+        w.begin(yt, e_cur);
         for (int k0 = 0; k0 < it.rank; k0 += 32) {
             if constexpr (DT == SLORA_F16) {
                 if (k0 > 0 && (k0 & (kMsRanks - 1)) == 0) { // the sums so far follow the next block's scale
@@ -1457,8 +1481,7 @@ __device__ __forceinline__ void expand_mfma_stream(const Item &it, int wave, con
 #pragma unroll
                 for (int p = 0; p < NP; ++p) w.multiply(piece[s][p], op[s]);
         }
-        if constexpr (DT == SLORA_F16) w.scale_rows(e_cur, i32x4{0, 0, 0, 0});
-        w.finish(yt);
+        w.end(yt, e_cur);
         w.store_y(t, row, yt);
     }
 }
@@ -1607,7 +1630,7 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *
     slora_pool *pool = plan->pool;
     const uint16_t *base = static_cast<const uint16_t *>(pool->dev_base);
     hipStream_t st = (hipStream_t)stream;
-    const size_t n_vs = heads_only ? (size_t)plan->n_vs_head : plan->vs_items.size();
+    const size_t n_vs = plan->wide ? (size_t)plan->n_vs_plain : heads_only ? (size_t)plan->n_vs_head : plan->vs_items.size();
     if (n_vs > 0) {
         const dim3 grid((unsigned)(n_vs * (size_t)n));
         const size_t lds = (size_t)plan->max_shrink_tok * pool->H * 2;
@@ -1633,7 +1656,7 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *
         int32_t rc = check_launch("shrink_vec");
         if (rc != SLORA_OK) return rc;
     }
-    if (!plan->ms_items.empty()) {
+    if (!plan->ms_items.empty() && plan->mfma_on()) {
         const dim3 grid((unsigned)(plan->ms_items.size() * (size_t)(kMsTok / plan->ms_sub_tok) * (size_t)n));
         const size_t lds = (size_t)plan->ms_lds_bytes;
         // more than 64 KiB of dynamic LDS has to be allowed once per kernel instance
@@ -1677,7 +1700,7 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *
 #define SLORA_PICK(KERNEL)                                                                   \
     (pool->dtype == SLORA_F16 ? (y16 ? KERNEL<SLORA_F16, true> : KERNEL<SLORA_F16, false>)   \
                               : (y16 ? KERNEL<SLORA_BF16, true> : KERNEL<SLORA_BF16, false>))
-    const size_t n_ve = heads_only ? (size_t)plan->n_ve_head : plan->ve_items.size();
+    const size_t n_ve = plan->wide ? (size_t)plan->n_ve_plain : heads_only ? (size_t)plan->n_ve_head : plan->ve_items.size();
     if (n_ve > 0) {
         const dim3 grid((unsigned)(n_ve * (size_t)n));
         if (plan->expand_split)
@@ -1689,7 +1712,7 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *
         int32_t rc = check_launch("expand_vec");
         if (rc != SLORA_OK) return rc;
     }
-    if (!plan->me_items.empty()) {
+    if (!plan->me_items.empty() && plan->mfma_on()) {
         const dim3 grid((unsigned)(plan->me_items.size() / (size_t)plan->me_run * (size_t)n));
         // LDS: two buffers of V fragments (the plan's most 32-rank stages) and the wavefronts' own parts
         const size_t lds = (size_t)2 * plan->me_stages * 2 * (pool->dtype == SLORA_F16 ? 2 : 3) * 1024 + 4 * kWaveLds;

@@ -108,6 +108,26 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
             if (n >= pool->mfma_min_tokens) mfma_tiles += (n + kMfmaTok - 1) / kMfmaTok;
         }
         const int64_t min_tokens = mfma_tiles >= pool->mfma_min_tiles ? pool->mfma_min_tokens : INT64_MAX;
+        // Fewer tiles than that: applies to fp32 y take the MFMA kernels all the same where the vector kernels
+        // would read very much again - every four tokens of a group read all of its pages, while an MFMA
+        // tile of a small batch is spread over many workgroups (shares of H, quarters of its tokens).
+        // Measured, vector / MFMA, us per call, for pages read (all slots): 30 MB 18.0 / 16.2, 67 MB 43 / 27,
+        // 134 MB 35 / 18, 268 MB 60 / 22, 537 MB (512 tokens of rank 64, 4 slots) 110 / 32.  Groups that stay
+        // on the vector kernels put the three MFMA launches behind theirs: 59 MB 26 / 34, 214 MB 85 / 67,
+        // 236 MB 116 / 103.  A plan does not know the type of y: it holds both forms (dual), and 16-bit y and the
+        // two-stage calls keep the vector kernels, whose sums 16-bit results are rounded from.
+        int64_t reread = 0;
+        bool few_tokens = false;
+        const int64_t launch_slots = std::min<int64_t>(pool->n_slots, SLORA_MAX_MULTI);
+        for (int32_t gi : order) {
+            const int64_t n = (int64_t)groups[(size_t)gi].toks.size();
+            if (n >= pool->mfma_min_tokens)
+                reread += (n + kExpandTok - 1) / kExpandTok * groups[(size_t)gi].rank * (int64_t)H * 4 * launch_slots;
+            else
+                few_tokens = true;
+        }
+        plan->dual = min_tokens == INT64_MAX && reread >= (few_tokens ? 128000000 : 30000000);
+        const int64_t mfma_tokens = plan->dual ? pool->mfma_min_tokens : min_tokens; // groups with MFMA items
         // Size of a share of an MFMA shrink tile (see below): mfma_split_bytes, or more when the
         // batch is so large that shares of that size would be far more than the GPU can hold at a
         // time (every share of a split tile costs a set of partial sums) - about three workgroups
@@ -116,18 +136,23 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         for (int32_t gi : order) {
             const Group &g = groups[(size_t)gi];
             const int64_t n = (int64_t)g.toks.size();
-            if (n < min_tokens) continue;
+            if (n < mfma_tokens) continue;
             const int64_t n_tok_tiles = (n + kMsTok - 1) / kMsTok, n_rank_blocks = (g.rank + kMsRanks - 1) / kMsRanks;
             ms_bytes += (n * n_rank_blocks + (int64_t)g.rank * n_tok_tiles) * H * 2;
         }
-        const int64_t launch_slots = std::min<int64_t>(pool->n_slots, SLORA_MAX_MULTI);
-        const int64_t share_bytes = std::max<int64_t>(pool->mfma_split_bytes, ms_bytes * launch_slots / (3 * 256));
+        // A dual batch is small: there the shares are as short as pays, 256 elements of H (512 tokens of rank 64,
+        // H = 4096, 4 slots: 24 us for the stage with shares of 1 MiB, 18 at 512 KiB, 15 from 256 KiB on).  Short
+        // chains also keep the error where the vector kernels have it: 1.08e-7 against 1.09e-7 for these
+        // tokens in binary16 (2.9e-7 unsplit), 1.25e-7 against 1.41e-7 for rank 128 and H = 8192.
+        const int64_t split_bytes = plan->dual ? std::min<int64_t>(pool->mfma_split_bytes, 32 << 10) : pool->mfma_split_bytes;
+        const int64_t split_min_h = plan->dual ? std::min<int64_t>(pool->mfma_split_min_h, 256) : pool->mfma_split_min_h;
+        const int64_t share_bytes = std::max<int64_t>(split_bytes, ms_bytes * launch_slots / (3 * 256));
         // MFMA expand: a workgroup keeps the B operands of its columns and walks a run of tiles.  Long runs
         // pay for them once, but the launch still needs several workgroups per compute unit.
         int64_t me_tiles = 0;
         for (int32_t gi : order) {
             const int64_t n = (int64_t)groups[(size_t)gi].toks.size();
-            if (n >= min_tokens) me_tiles += (n + kMfmaTok - 1) / kMfmaTok;
+            if (n >= mfma_tokens) me_tiles += (n + kMfmaTok - 1) / kMfmaTok;
         }
         const int64_t me_wgs = me_tiles * ((H + kMfmaExpandCols - 1) / kMfmaExpandCols) * launch_slots;
         const int32_t me_run = (int32_t)std::min<int64_t>(kMfmaRunMax, std::max<int64_t>(1, me_wgs / 1024));
@@ -167,7 +192,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         const bool fuse = pool->fuse_decode != 0 && H <= 8192 &&
                           (pool->fuse_decode > 1 ||
                            (n_small * launch_slots >= 3 * 256 && small_bytes >= n_small * (int64_t(1) << 20)));
-        std::vector<Item> vs_tail, ve_tail;
+        std::vector<Item> vs_tail, ve_tail, vs_dual, ve_dual;
         plan->vf_items.clear();
         for (int32_t gi : order) {
             const Group &g = groups[(size_t)gi];
@@ -177,8 +202,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
             plan->sum_rank += g.rank;
             max_rank = std::max(max_rank, g.rank);
             const int32_t off = (int32_t)g.arena_off;
-            if ((int64_t)n >= min_tokens) {
-                plan->n_groups_mfma++;
+            if ((int64_t)n >= mfma_tokens) {
                 // v tiles of 32 tokens, numbered in order; an expand item covers one tile, a shrink
                 // item up to four consecutive ones (its pages are then read once for them all)
                 const int32_t tile0 = plan->n_mfma_tiles;
@@ -197,7 +221,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                         // leaves behind (and the last one reads back) must stay small beside its rows.
                         const int64_t cost = (int64_t)(nt + nj) * H * 2;
                         int64_t parts = (cost + share_bytes / 2) / share_bytes;
-                        parts = std::min<int64_t>(parts, H / std::max<int64_t>(pool->mfma_split_min_h, kMsGranule));
+                        parts = std::min<int64_t>(parts, H / std::max<int64_t>(split_min_h, kMsGranule));
                         parts = std::min<int64_t>(parts, std::min<int64_t>(n_chunks, 64));
                         const int64_t mb = (nt + 31) / 32, nb = (nj + 31) / 32;
                         if (parts < 2 || plan->part_floats + parts * mb * nb * 1024 > (int64_t(1) << 30))
@@ -240,13 +264,17 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                         plan->me_items.resize(plan->me_items.size() + (size_t)(me_run - (t1 - t0)), Item{0, 0, 0, 0, 0, 0, 0, 0});
                     }
                 }
+            }
+            if ((int64_t)n >= min_tokens) {
+                plan->n_groups_mfma++;
             } else {
                 plan->n_groups_vec++;
                 // a group the one-launch decode kernel can take goes to the end of the two lists
                 // (the two-stage calls run the whole lists, a fused apply only their heads)
                 const bool fused = fuse && n <= kExpandTok;
-                std::vector<Item> &vs = fused ? vs_tail : plan->vs_items;
-                std::vector<Item> &ve = fused ? ve_tail : plan->ve_items;
+                const bool both = (int64_t)n >= mfma_tokens; // has MFMA items as well
+                std::vector<Item> &vs = fused ? vs_tail : both ? vs_dual : plan->vs_items;
+                std::vector<Item> &ve = fused ? ve_tail : both ? ve_dual : plan->ve_items;
                 if (fused) plan->vf_items.push_back(Item{off, g.rank, 0, H, pos_base, n, 0, 0});
                 for (int32_t p = 0; p < n; p += shrink_tok) {
                     const int32_t nt = std::min(shrink_tok, n - p);
@@ -261,6 +289,10 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                 }
             }
         }
+        plan->n_vs_plain = (int32_t)plan->vs_items.size();
+        plan->n_ve_plain = (int32_t)plan->ve_items.size();
+        plan->vs_items.insert(plan->vs_items.end(), vs_dual.begin(), vs_dual.end());
+        plan->ve_items.insert(plan->ve_items.end(), ve_dual.begin(), ve_dual.end());
         plan->n_vs_head = (int32_t)plan->vs_items.size();
         plan->n_ve_head = (int32_t)plan->ve_items.size();
         plan->vs_items.insert(plan->vs_items.end(), vs_tail.begin(), vs_tail.end());
@@ -353,7 +385,7 @@ int32_t slora_plan::upload()
 
 void slora_plan::fill_args(MultiArgs &a, int32_t n, float *v) const
 {
-    const int64_t per_slot = v_slot_floats(pool->dtype);
+    const int64_t per_slot = v_slot_floats(pool->dtype, mfma_on());
     for (int32_t k = 0; k < n; ++k) a.v[k] = v + (int64_t)k * per_slot;
     a.vfrag_off = (int64_t)T_act * v_stride;
     a.vexp_off = a.vfrag_off + vfrag_floats(pool->dtype);
@@ -390,9 +422,10 @@ int32_t check_plan(slora_plan *plan, int32_t n, const int32_t *slots)
 
 // scratch: where v goes; NULL = the plan's own buffer (grown on demand)
 // y != NULL: part of an apply - decode groups the plan marked for it run both stages in one
-// launch here, and the two-stage launches (here and in do_expand) cover the other groups only
+// launch here, and the two-stage launches (here and in do_expand) cover the other groups only.
+// narrow: a dual plan stays on the vector kernels.
 int32_t do_shrink(slora_plan *plan, int32_t n, const int32_t *slots, const void *const *x, void *stream,
-                  float *scratch = nullptr, void *const *y = nullptr, bool y16 = false)
+                  float *scratch = nullptr, void *const *y = nullptr, bool y16 = false, bool narrow = false)
 {
     if (!x) return fail(SLORA_EINVAL, "x is NULL");
     if (plan->T_act == 0) return SLORA_OK;
@@ -406,11 +439,12 @@ int32_t do_shrink(slora_plan *plan, int32_t n, const int32_t *slots, const void 
     }
     DeviceScope dev(plan->pool->device);
     if (dev.status() != SLORA_OK) return dev.status();
+    plan->wide = plan->dual && y != nullptr && !y16 && !narrow;
     // the page lists of every adapter the plan names went to the device when it was built
     float *v = scratch;
     int32_t rc = SLORA_OK;
     if (!v) {
-        rc = plan->pool->grow_v(plan->set, (size_t)plan->v_total_floats(n, plan->pool->dtype));
+        rc = plan->pool->grow_v(plan->set, (size_t)plan->v_total_floats(n, plan->pool->dtype, plan->mfma_on()));
         v = plan->set->v;
     }
     if (rc == SLORA_OK) rc = plan->enter(stream);
@@ -532,7 +566,7 @@ int32_t slora_plan_info(const slora_plan *plan, int64_t *out, int32_t n)
                                           plan->v_stride,
                                           plan->sum_rank,
                                           plan->n_sync,
-                                          plan->v_slot_floats(plan->pool->dtype) * (int64_t)sizeof(float),
+                                          plan->v_slot_floats(plan->pool->dtype, true) * (int64_t)sizeof(float),
                                           (int64_t)plan->vf_items.size()};
     for (int32_t k = 0; k < n; ++k) out[k] = v[k];
     return SLORA_OK;
@@ -569,8 +603,11 @@ int32_t apply_multi(slora_plan *plan, int32_t n, const int32_t *slots, const voi
     rc = check_y(n, y); // validate the y side before the shrink is enqueued
     if (rc != SLORA_OK) return rc;
     float *scratch = nullptr;
+    bool narrow = false;
     if (static_scratch) {
-        const int64_t need = plan->v_total_floats(n, plan->pool->dtype) * (int64_t)sizeof(float);
+        auto bytes = [&](bool mfma) { return plan->v_total_floats(n, plan->pool->dtype, mfma) * (int64_t)sizeof(float); };
+        narrow = plan->dual && bytes(true) > (int64_t)SLORA_STATIC_SCRATCH_BYTES; // rows of v alone may still fit
+        const int64_t need = bytes(!narrow);
         if (need > (int64_t)SLORA_STATIC_SCRATCH_BYTES)
             return fail(SLORA_ERANGE,
                         "this batch needs %lld bytes of scratch for %d slot(s), the static scratch holds %lld: use "
@@ -579,7 +616,7 @@ int32_t apply_multi(slora_plan *plan, int32_t n, const int32_t *slots, const voi
         scratch = static_cast<float *>(plan->pool->static_scratch);
         if (!scratch) return fail(SLORA_EHIP, "the static scratch was not resolved for this pool's device");
     }
-    rc = do_shrink(plan, n, slots, x, stream, scratch, y, y16);
+    rc = do_shrink(plan, n, slots, x, stream, scratch, y, y16, narrow);
     if (rc != SLORA_OK) return rc;
     return do_expand(plan, n, slots, y, stream, y16, true);
 }

@@ -195,6 +195,12 @@ struct slora_plan {
     std::vector<slora::Item> vs_items, ve_items, me_items;
     std::vector<slora::Item> vf_items; // decode groups for the one-launch kernel (their two-stage items end vs / ve)
     int32_t n_vs_head = 0, n_ve_head = 0; // items of vs / ve that belong to other groups
+    // A dual plan's groups of many tokens are in both kernels' lists: in vs / ve between the plain groups'
+    // items and n_vs_head / n_ve_head, and in the MFMA lists.  fp32-y applies take the latter (wide).
+    bool dual = false;
+    bool wide = false;                    // the latest shrink did, and so does the expand that follows it
+    int32_t n_vs_plain = 0, n_ve_plain = 0;
+    bool mfma_on() const { return !dual || wide; }
     std::vector<slora::MsItem> ms_items;
     std::vector<slora::MsItem> mj_items; // one record per split tile, for the kernel that joins the shares
     int32_t ms_sub_tok = slora::kMsTok;  // tokens of an MFMA shrink item that one workgroup takes
@@ -219,11 +225,11 @@ struct slora_plan {
         return (int64_t)n_mfma_tiles * (v_stride / 16) * (dtype == SLORA_F16 ? 2 : 3) * 256;
     }
     int64_t vexp_floats() const { return (int64_t)n_mfma_tiles * n_rank_blocks * 8; } // one byte per row
-    int64_t v_slot_floats(int32_t dtype) const
+    int64_t v_slot_floats(int32_t dtype, bool mfma) const
     {
-        return (int64_t)T_act * v_stride + vfrag_floats(dtype) + vexp_floats() + part_floats;
+        return (int64_t)T_act * v_stride + (mfma ? vfrag_floats(dtype) + vexp_floats() + part_floats : 0);
     }
-    int64_t v_total_floats(int32_t n, int32_t dtype) const { return (int64_t)n * v_slot_floats(dtype); }
+    int64_t v_total_floats(int32_t n, int32_t dtype, bool mfma) const { return (int64_t)n * v_slot_floats(dtype, mfma); }
     float *v_used = nullptr; // where the latest shrink left v
     int32_t v_slots = 0;     // n of the latest shrink
     bool v_complete = false; // the latest shrink left v for every group (not so after an apply that fused decode groups)

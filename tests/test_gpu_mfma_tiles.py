@@ -10,7 +10,7 @@ import pytest
 
 from paper_2311_03285_amd import slora, synth
 from paper_2311_03285_amd.harness import DeviceWorkload
-from gpu_util import gpu_slot, oracle_slot
+from gpu_util import assert_close, gpu_slot, oracle_slot
 from test_gpu_mfma import MFMA_ALL, route
 from test_gpu_y16 import assert_y16_close, gpu_y16, oracle_y16
 
@@ -47,3 +47,41 @@ def test_runs_of_tiles_with_16_bit_y(dtype):
         got = gpu_y16(dw, [5])[0]
         ref, exact = oracle_y16(w, 5)
         assert_y16_close(got, ref, exact, w.y16_bits(5), w.dtype, "runs of tiles")
+
+
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+@pytest.mark.parametrize("few", [0, 3])
+def test_small_batch_with_both_kernels_lists(dtype, few):
+    """Fewer tiles than mfma_min_tiles, but many page re-reads: applies to fp32 y take the MFMA kernels (in
+    shares of H), 16-bit y and the two-stage calls the vector kernels; an expand after an apply still
+    works, and the static scratch serves both."""
+    lens = [190, 17, 40] + [1] * few
+    ranks = [128, 129, 65] + [5] * few
+    ids = np.repeat(np.arange(len(lens)), lens).astype(np.int32)
+    w = synth.make_workload("dual", 670 + few, 4096, dtype, 4 * 2 * sum(ranks) + 32, 4, ranks, ids)
+    with DeviceWorkload(w, real_adapters="all", max_rank=129) as dw:
+        plan = dw.plan()
+        info = slora.plan_info(plan)
+        assert info["groups_mfma"] == 0 and info["mfma_expand_items"] > 0 and info["split_tiles"] > 0
+        for slot in (0, 3):
+            rel, _ = assert_close(gpu_slot(dw, slot, plan), oracle_slot(w, slot), f"slot {slot}")
+            assert rel <= 5e-6, rel
+        want = gpu_slot(dw, 1, plan)
+        x, y = dw.x_dev(1), dw.y_dev(1)
+        slora.lora_apply_multi_static(plan, [1], [x.data_ptr()], [y.data_ptr()])
+        assert np.array_equal(y.cpu().numpy(), want)           # the same kernels, the other scratch
+        y2 = dw.y_dev(1)
+        slora.lora_expand(plan, [1], [y2.data_ptr()])          # v is still where the apply left it
+        assert np.array_equal(y2.cpu().numpy(), want)
+        y3 = dw.y_dev(1)
+        slora.lora_shrink(plan, [1], [x.data_ptr()])           # two-stage: the vector kernels
+        slora.lora_expand(plan, [1], [y3.data_ptr()])
+        two = y3.cpu().numpy()
+        assert_close(two, oracle_slot(w, 1), "two-stage")
+        got = gpu_y16(dw, [1], plan)[0]
+        ref, exact = oracle_y16(w, 1)
+        assert_y16_close(got, ref, exact, w.y16_bits(1), w.dtype, "dual, 16-bit y")
+    with DeviceWorkload(w, real_adapters="all", max_rank=129) as dw:
+        slora.set_option(dw.pool, "mfma_min_tokens", 1 << 40)  # vector kernels throughout
+        assert np.array_equal(gpu_slot(dw, 1, dw.plan()), two)
+        assert np.array_equal(gpu_y16(dw, [1])[0], got)
