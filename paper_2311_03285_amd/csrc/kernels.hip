@@ -142,6 +142,15 @@ __device__ __forceinline__ float wave_sum(float v)
     return v;
 }
 
+// 64 lanes x 16 bytes from per-lane addresses to 1 KiB of LDS at a wave-uniform address
+template <int AUX>
+__device__ __forceinline__ void load_to_lds(const unsigned char *src, unsigned char *dst)
+{
+    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
+                                     (__attribute__((address_space(3))) void *)dst, 16, 0, AUX);
+}
+constexpr int kLoadStreaming = 2; // cache policy "nt"
+
 // ---------------------------------------------------------------------------------------
 // page scatter / gather (exact copies)
 // ---------------------------------------------------------------------------------------
@@ -505,6 +514,135 @@ __global__ __launch_bounds__(1024) void lora_vec_fused_kernel(const Item *__rest
 }
 
 // ---------------------------------------------------------------------------------------
+// decode path, both stages in one launch, for SMALL batches: a workgroup = one item of the rank-split
+// expand (512 columns of a group of at most kExpandTok tokens), which computes the group's v = x*A for
+// itself.  Its eight wavefronts share out the A pages and leave v in LDS; the first four then do the
+// rank-split expand, whose B rows and y were requested before the first A page.  A is read once per 512
+// columns - from L2 but for the first.  What bounds such a batch is the chain of dependent round trips
+// and the two launches: one token of rank 16, H = 4096, 4 slots 9.8 -> 6.2 us per call, rank 8 10.4 -> 6.0.
+// Beyond a page or two per wavefront and token the repeated A reads cost more than the launch (rank 32
+// 9.9 / 9.7, ten groups of rank 16 and up to four tokens 11.3 / 12.6, H = 8192 9.1 / 10.1): see the plan's
+// rule.  Sixteen wavefronts (128 registers each, B rows through LDS) were slower: 7.1 us.
+// The first column range's workgroup also leaves v in memory, where a later expand expects it.
+// Results are bit-identical to the two kernels'.
+// ---------------------------------------------------------------------------------------
+constexpr int kSmallWaves = 8;
+static_assert(kSmallRanks <= kSplitWaves * 8, "a wavefront of the expand has at most one block of ranks");
+
+template <int DT, bool Y16, int TOK>
+__device__ __forceinline__ void small_body(const Item &it, const int32_t *__restrict__ pa,
+                                           const uint16_t *__restrict__ pool, const uint16_t *__restrict__ x,
+                                           const int32_t *__restrict__ tok_idx, int H, int v_stride,
+                                           void *__restrict__ y, float *__restrict__ v, u32x4 *xs)
+{
+    constexpr int UB = TOK <= 2 ? 16 : 8;             // ranks per block of the rank-split expand
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = threadIdx.x / kWave;
+    const int nch = H >> 3;
+    float *vl = reinterpret_cast<float *>(xs + (size_t)TOK * nch); // v [TOK][kSmallRanks]
+    float *red = vl + TOK * kSmallRanks;              // partial sums of wavefronts 1 .. 3
+    const int col = it.a + lane * 8;
+    const bool live = col < it.a + it.b;
+    const int col_ld = live ? col : it.a;             // lanes beyond the item's columns are dropped at the store
+
+    // wavefronts 0 .. 3: block `wave` of the B rows; rank indices beyond the last are clamped and meet v = 0
+    const bool expands = wave < kSplitWaves && wave * UB < it.rank;
+    u32x4 w[UB];
+    Y8<DT, Y16> yv[TOK];
+    int64_t yoff[TOK];
+    if (expands) {
+        int64_t page[UB];
+#pragma unroll
+        for (int u = 0; u < UB; ++u) page[u] = pa[it.rank + min(wave * UB + u, it.rank - 1)];
+#pragma unroll
+        for (int u = 0; u < UB; ++u)
+            w[u] = __builtin_nontemporal_load(reinterpret_cast<const u32x4 *>(pool + page[u] * H + col_ld));
+        if (wave == 0) {
+#pragma unroll
+            for (int t = 0; t < TOK; ++t) {
+                yoff[t] = (int64_t)tok_idx[it.pos0 + min(t, it.ntok - 1)] * H + col;
+                if (t < it.ntok && live) yv[t].load(y, yoff[t]);
+            }
+        }
+    }
+    // H <= 4096: a page is one block of eight loads per lane
+    shrink_vec_core<DT, 8>(
+        pa, it.rank, it.ntok, wave, kSmallWaves, lane, pool, H, xs,
+        [&]() {
+            for (int t = 0; t < it.ntok; ++t) {
+                const u32x4 *row = reinterpret_cast<const u32x4 *>(x + (int64_t)tok_idx[it.pos0 + t] * H);
+                for (int c = threadIdx.x; c < nch; c += kSmallWaves * kWave) xs[t * nch + c] = row[c];
+            }
+            __syncthreads();
+        },
+        [&](int t, int j, float s) {
+            vl[t * kSmallRanks + j] = s;
+            if (it.a == 0) v[(int64_t)(it.pos0 + t) * v_stride + j] = s;
+        });
+    __syncthreads();
+    float acc[TOK][8];
+#pragma unroll
+    for (int t = 0; t < TOK; ++t)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[t][e] = 0.f;
+    if (expands) {
+#pragma unroll
+        for (int u = 0; u < UB; ++u) {
+            const int j = wave * UB + u;
+            float f[8];
+            widen2<DT>(w[u].x, f[0], f[1]);
+            widen2<DT>(w[u].y, f[2], f[3]);
+            widen2<DT>(w[u].z, f[4], f[5]);
+            widen2<DT>(w[u].w, f[6], f[7]);
+#pragma unroll
+            for (int t = 0; t < TOK; ++t) {
+                const float vv = t < it.ntok && j < it.rank ? vl[t * kSmallRanks + j] : 0.f;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[t][e] = fmaf(vv, f[e], acc[t][e]);
+            }
+        }
+    }
+    if (wave > 0 && wave < kSplitWaves) {
+#pragma unroll
+        for (int t = 0; t < TOK; ++t)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) red[(((wave - 1) * TOK + t) * 8 + e) * kWave + lane] = acc[t][e];
+    }
+    __syncthreads();
+    if (wave > 0) return;
+#pragma unroll
+    for (int k = 0; k < kSplitWaves - 1; ++k)
+#pragma unroll
+        for (int t = 0; t < TOK; ++t)
+#pragma unroll
+            for (int e = 0; e < 8; ++e) acc[t][e] += red[((k * TOK + t) * 8 + e) * kWave + lane];
+    if (!live) return;
+#pragma unroll
+    for (int t = 0; t < TOK; ++t)
+        if (t < it.ntok) yv[t].add_store(y, yoff[t], acc[t]);
+}
+
+template <int DT, bool Y16>
+__global__ __launch_bounds__(kSmallWaves *kWave) void lora_vec_small_kernel(const Item *__restrict__ items,
+                                                                            const int32_t *__restrict__ arena,
+                                                                            const uint16_t *__restrict__ pool,
+                                                                            const int32_t *__restrict__ tok_idx, int H,
+                                                                            int v_stride, MultiArgs args)
+{
+    extern __shared__ u32x4 smem[]; // x rows [TOK][H/8], v [TOK][kSmallRanks], the expand's partial sums
+    const int cs = blockIdx.x % args.n;
+    const Item it = items[blockIdx.x / args.n];
+    const int32_t *pa = arena + it.arena_off + (int64_t)args.slot[cs] * 2 * it.rank;
+    const uint16_t *x = static_cast<const uint16_t *>(args.x[cs]);
+    if (it.ntok == 1)
+        small_body<DT, Y16, 1>(it, pa, pool, x, tok_idx, H, v_stride, args.y[cs], args.v[cs], smem);
+    else if (it.ntok == 2)
+        small_body<DT, Y16, 2>(it, pa, pool, x, tok_idx, H, v_stride, args.y[cs], args.v[cs], smem);
+    else
+        small_body<DT, Y16, kExpandTok>(it, pa, pool, x, tok_idx, H, v_stride, args.y[cs], args.v[cs], smem);
+}
+
+// ---------------------------------------------------------------------------------------
 // prefill path (MFMA).  Matrix blocks are 32 x 32 with 16 k-values per instruction
 // (v_mfma_f32_32x32x16_{f16,bf16}): lane l supplies, for row/column l % 32, the 8 k-values
 // 8*(l / 32) .. +7 of both operands, and receives D[8*(v/4) + 4*(l/32) + v%4][l % 32] in
@@ -625,15 +763,6 @@ constexpr int kExpMin = -24, kExpMax = 40;           // range of the row exponen
 static_assert(kMsGranule % kPiece == 0 && kMsTok == 128 && kMsRanks == 128, "pieces and tiles are tied");
 
 __device__ __forceinline__ float pow2f(int e) { return __uint_as_float((uint32_t)(e + 127) << 23); }
-
-// 64 lanes x 16 bytes from per-lane addresses to 1 KiB of LDS at a wave-uniform address
-template <int AUX>
-__device__ __forceinline__ void load_to_lds(const unsigned char *src, unsigned char *dst)
-{
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)src,
-                                     (__attribute__((address_space(3))) void *)dst, 16, 0, AUX);
-}
-constexpr int kLoadStreaming = 2; // cache policy "nt"
 
 // N 16-byte LDS reads, waited for together.  Reads and wait are one asm block because the compiler
 // cannot tell which stage of a ring filled by global_load_lds a read touches: before an ordinary
@@ -1579,9 +1708,34 @@ static int shrink_loads_per_block(int H)
     return std::max(4, (per_lane + nblk - 1) / nblk);
 }
 
+static int32_t launch_small(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, bool y16)
+{
+    slora_pool *pool = plan->pool;
+    const uint16_t *base = static_cast<const uint16_t *>(pool->dev_base);
+    hipStream_t st = (hipStream_t)stream;
+    const int H = pool->H;
+    const dim3 grid((unsigned)(plan->ve_items.size() * (size_t)n));
+    const int tok = plan->max_expand_tok <= 2 ? plan->max_expand_tok : kExpandTok;
+    // at most 4 x (8 KiB of x + 6.1 KiB): below the 64 KiB that every kernel may have
+    const size_t lds = (size_t)tok * (H * 2 + (kSmallRanks + (kSplitWaves - 1) * 8 * kWave) * sizeof(float));
+#define SLORA_SMALL(DT, Y)                                                                                      \
+    hipLaunchKernelGGL((lora_vec_small_kernel<DT, Y>), grid, dim3(kSmallWaves *kWave), lds, st, plan->d_ve,     \
+                       pool->d_arena, base, plan->d_tok_idx, H, plan->v_stride, args)
+    if (pool->dtype == SLORA_F16) {
+        if (y16) SLORA_SMALL(SLORA_F16, true);
+        else SLORA_SMALL(SLORA_F16, false);
+    } else {
+        if (y16) SLORA_SMALL(SLORA_BF16, true);
+        else SLORA_SMALL(SLORA_BF16, false);
+    }
+#undef SLORA_SMALL
+    return check_launch("lora_vec_small");
+}
+
 int32_t launch_fused(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, bool y16)
 {
     slora_pool *pool = plan->pool;
+    if (plan->small_used) return launch_small(plan, n, args, stream, y16);
     if (plan->vf_items.empty()) return SLORA_OK;
     const uint16_t *base = static_cast<const uint16_t *>(pool->dev_base);
     hipStream_t st = (hipStream_t)stream;

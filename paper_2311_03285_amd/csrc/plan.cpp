@@ -320,6 +320,18 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
             return (int64_t)(a.ntok + a.nj) * (a.c1 - a.c0) > (int64_t)(b.ntok + b.nj) * (b.c1 - b.c0);
         });
         plan->T_act = (int32_t)plan->tok_idx.size();
+        // Small batches in one launch, every workgroup computing v for itself: while that is a page or two per
+        // wavefront and token.  Measured, us per call, two kernels / one: rank x H x tokens of the largest item
+        // 32 Ki 10.4 / 6.0, 64 Ki 9.8 / 6.2, 128 Ki 11.8 / 10.0 (19 groups of rank 8), 10.5 / 10.0 (H = 2048),
+        // 9.8 / 9.3 (7 groups of rank 16); 256 Ki 11.3 / 12.6; H = 8192 (two blocks of loads per page) 9.1 / 10.1.
+        // Only calls of at most 256 workgroups: a larger launch streams the A pages eight times.
+        plan->max_expand_tok = 0;
+        bool few_pages = true;
+        for (const Item &i : plan->ve_items) {
+            plan->max_expand_tok = std::max(plan->max_expand_tok, i.ntok);
+            few_pages = few_pages && i.rank <= kSmallRanks && (int64_t)i.rank * H * i.ntok <= 128 * 1024;
+        }
+        plan->small = plan->expand_split && plan->ms_items.empty() && plan->vf_items.empty() && few_pages && H <= 4096;
         plan->v_stride = std::max(kRankPad, (max_rank + kRankPad - 1) / kRankPad * kRankPad);
         plan->n_rank_blocks = (plan->v_stride + kMsRanks - 1) / kMsRanks;
     } catch (const std::bad_alloc &) {
@@ -451,12 +463,13 @@ int32_t do_shrink(slora_plan *plan, int32_t n, const int32_t *slots, const void 
     if (rc != SLORA_OK) return rc;
     plan->fill_args(a, n, v);
     const bool fused = y != nullptr && !plan->vf_items.empty();
-    if (fused) {
+    plan->small_used = y != nullptr && plan->small && (int64_t)plan->ve_items.size() * n <= 256;
+    if (fused || plan->small_used) {
         for (int32_t k = 0; k < n; ++k) a.y[k] = y[k];
         rc = launch_fused(plan, n, a, stream, y16);
         if (rc != SLORA_OK) return rc;
     }
-    rc = launch_shrink(plan, n, a, stream, fused);
+    if (!plan->small_used) rc = launch_shrink(plan, n, a, stream, fused);
     if (rc == SLORA_OK) {
         plan->v_slots = n;
         plan->v_used = v;
@@ -491,6 +504,7 @@ int32_t do_expand(slora_plan *plan, int32_t n, const int32_t *slots, void *const
     }
     if (plan->v_slots != n || !plan->v_used || (!after_fused && !plan->v_complete))
         return fail(SLORA_EINVAL, "expand of %d slot(s) needs a preceding slora_lora_shrink of %d slot(s)", n, n);
+    if (after_fused && plan->small_used) return SLORA_OK; // both stages ran in one launch
     DeviceScope dev(plan->pool->device);
     if (dev.status() != SLORA_OK) return dev.status();
     rc = plan->enter(stream);

@@ -70,6 +70,7 @@ struct MultiArgs {
 // Tile constants the scheduler and the kernels must agree on.
 constexpr int kShrinkTok = 4;     // tokens per vector-shrink item (x rows staged in LDS)
 constexpr int kExpandTok = 4;     // tokens per vector-expand item (accumulators in registers)
+constexpr int kSmallRanks = 32;   // most ranks of an adapter in a batch that runs in the one-launch kernel for small batches
 constexpr int kExpandColsMax = 1024; // most columns per vector-expand item (a multiple of 512, <= 4096; measured best on cfg4: 1024)
 constexpr int kMfmaTok = 32;      // tokens per v tile = per MFMA-expand item (one 32-row MFMA block)
 constexpr int kMsTok = 128;       // most tokens per MFMA-shrink item
@@ -186,6 +187,9 @@ struct slora_plan {
     int32_t max_shrink_tok = 0;
     int32_t n_mfma_tiles = 0;
     int32_t expand_threads = 64; // workgroup size of the vector expand (columns per item / 8)
+    int32_t max_expand_tok = 0;
+    bool small = false;          // small calls on the plan may take the one-launch kernel for small batches
+    bool small_used = false;     // ... and the latest shrink did: its expand is done
     int32_t expand_split = 0;    // small batch: 512-column items, ranks split over four wavefronts
     int64_t sum_rank = 0;
     int32_t n_groups = 0, n_groups_vec = 0, n_groups_mfma = 0;
@@ -259,6 +263,7 @@ int32_t static_scratch_address(int device, void **out); // `device` must be curr
 // heads_only: the vector lists without the groups that launch_fused has served
 int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, bool heads_only = false);
 int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, bool y16, bool heads_only = false);
+// the groups of the one-launch decode kernel or, if small_used is set, the whole (small) batch
 int32_t launch_fused(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, bool y16);
 
 } // namespace slora
