@@ -9,6 +9,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <atomic>
 #include <mutex>
 #include <type_traits>
 
@@ -1700,6 +1701,17 @@ int32_t launch_gather(slora_pool *pool, int64_t arena_entry, int32_t rank, void 
     return check_launch("gather_pages");
 }
 
+// A launch with more than 64 KiB of dynamic LDS has to be allowed once per kernel instance and device;
+// `done` holds a bit per device.
+static hipError_t allow_lds(std::atomic<uint64_t> &done, int device, const void *kernel, size_t lds)
+{
+    const uint64_t bit = uint64_t(1) << (device & 63);
+    if (lds <= 65536 || (done.load() & bit)) return hipSuccess;
+    const hipError_t e = hipFuncSetAttribute(kernel, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e == hipSuccess) done.fetch_or(bit);
+    return e;
+}
+
 // loads per block of the vector shrink: as few blocks per page as 8 loads allow, then the smallest U that fits
 static int shrink_loads_per_block(int H)
 {
@@ -1746,16 +1758,11 @@ int32_t launch_fused(slora_plan *plan, int32_t n, const MultiArgs &args, void *s
     const int v_pad = plan->v_stride;
     const size_t lds = (size_t)kExpandTok * H * 2 + (size_t)kExpandTok * v_pad * sizeof(float);
     const int U = shrink_loads_per_block(H);
-    // more than 64 KiB of dynamic LDS (H = 8192) has to be allowed once per kernel instance
     hipError_t attr = hipSuccess;
 #define SLORA_FUSED(DT, Y, UU)                                                                                       \
     {                                                                                                                \
-        static bool allowed = false;                                                                                 \
-        if (!allowed && lds > 65536) {                                                                               \
-            attr = hipFuncSetAttribute(reinterpret_cast<const void *>(&lora_vec_fused_kernel<DT, Y, UU>),           \
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);                      \
-            allowed = attr == hipSuccess;                                                                            \
-        }                                                                                                            \
+        static std::atomic<uint64_t> done{0};                                                                        \
+        attr = allow_lds(done, pool->device, reinterpret_cast<const void *>(&lora_vec_fused_kernel<DT, Y, UU>), lds); \
         if (attr == hipSuccess)                                                                                      \
             hipLaunchKernelGGL((lora_vec_fused_kernel<DT, Y, UU>), grid, block, lds, st, plan->d_vf, pool->d_arena, \
                                base, plan->d_tok_idx, H, v_pad, args);                                               \
@@ -1813,16 +1820,11 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *
     if (!plan->ms_items.empty() && plan->mfma_on()) {
         const dim3 grid((unsigned)(plan->ms_items.size() * (size_t)(kMsTok / plan->ms_sub_tok) * (size_t)n));
         const size_t lds = (size_t)plan->ms_lds_bytes;
-        // more than 64 KiB of dynamic LDS has to be allowed once per kernel instance
 #define SLORA_MSK(DT)                                                                                                \
     {                                                                                                                \
-        static bool allowed = false;                                                                                 \
-        if (!allowed && lds > 65536) {                                                                               \
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&shrink_mfma_kernel<DT>),             \
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);              \
-            if (e != hipSuccess) return fail(SLORA_EHIP, "hipFuncSetAttribute(LDS size): %s", hipGetErrorString(e)); \
-            allowed = true;                                                                                          \
-        }                                                                                                            \
+        static std::atomic<uint64_t> done{0};                                                                        \
+        hipError_t e = allow_lds(done, pool->device, reinterpret_cast<const void *>(&shrink_mfma_kernel<DT>), lds);            \
+        if (e != hipSuccess) return fail(SLORA_EHIP, "hipFuncSetAttribute(LDS size): %s", hipGetErrorString(e));     \
         hipLaunchKernelGGL(shrink_mfma_kernel<DT>, grid, dim3(kMfmaThreads), lds, st, plan->d_ms, pool->d_arena,     \
                            base, plan->d_tok_idx, pool->H, plan->v_stride, plan->ms_sub_tok, args);                  \
     }
@@ -1872,13 +1874,9 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *
         const size_t lds = (size_t)2 * plan->me_stages * 2 * (pool->dtype == SLORA_F16 ? 2 : 3) * 1024 + 4 * kWaveLds;
 #define SLORA_MEK(DT, Y)                                                                                             \
     {                                                                                                                \
-        static bool allowed = false;                                                                                 \
-        if (!allowed && lds > 65536) {                                                                               \
-            hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void *>(&expand_mfma_kernel<DT, Y>),          \
-                                               hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);              \
-            if (e != hipSuccess) return fail(SLORA_EHIP, "hipFuncSetAttribute(LDS size): %s", hipGetErrorString(e)); \
-            allowed = true;                                                                                          \
-        }                                                                                                            \
+        static std::atomic<uint64_t> done{0};                                                                        \
+        hipError_t e = allow_lds(done, pool->device, reinterpret_cast<const void *>(&expand_mfma_kernel<DT, Y>), lds);         \
+        if (e != hipSuccess) return fail(SLORA_EHIP, "hipFuncSetAttribute(LDS size): %s", hipGetErrorString(e));     \
         hipLaunchKernelGGL((expand_mfma_kernel<DT, Y>), grid, dim3(kMfmaThreads), lds, st, plan->d_me,               \
                            pool->d_arena, base, plan->d_tok_idx, pool->H, plan->v_stride, plan->me_run, args);       \
     }
