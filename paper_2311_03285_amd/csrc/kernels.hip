@@ -1621,12 +1621,12 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void expand_mfma_kernel(const Item
                                                                     const int32_t *__restrict__ arena,
                                                                     const uint16_t *__restrict__ pool,
                                                                     const int32_t *__restrict__ tok_idx, int H,
-                                                                    int v_stride, int run, MultiArgs args)
+                                                                    int v_stride, MultiArgs args)
 {
     // two buffers of V for the plan's widest adapter of up to 128 ranks, then each wavefront's own part
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int cs = blockIdx.x % args.n;
-    const Item it = items[(int64_t)(blockIdx.x / args.n) * run]; // the first tile of the run stands for all of them
+    const Item it = items[blockIdx.x / args.n]; // the first tile of a run stands for all of them
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int32_t *pbl = arena + it.arena_off + (int64_t)args.slot[cs] * 2 * it.rank + it.rank;
     const uint16_t *vfrag = reinterpret_cast<const uint16_t *>(args.v[cs] + args.vfrag_off);
@@ -1869,7 +1869,7 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *
         if (rc != SLORA_OK) return rc;
     }
     if (!plan->me_items.empty() && plan->mfma_on()) {
-        const dim3 grid((unsigned)(plan->me_items.size() / (size_t)plan->me_run * (size_t)n));
+        const dim3 grid((unsigned)((size_t)plan->n_me_runs * (size_t)n));
         // LDS: two buffers of V fragments (the plan's most 32-rank stages) and the wavefronts' own parts
         const size_t lds = (size_t)2 * plan->me_stages * 2 * (pool->dtype == SLORA_F16 ? 2 : 3) * 1024 + 4 * kWaveLds;
 #define SLORA_MEK(DT, Y)                                                                                             \
@@ -1878,7 +1878,7 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *
         hipError_t e = allow_lds(done, pool->device, reinterpret_cast<const void *>(&expand_mfma_kernel<DT, Y>), lds);         \
         if (e != hipSuccess) return fail(SLORA_EHIP, "hipFuncSetAttribute(LDS size): %s", hipGetErrorString(e));     \
         hipLaunchKernelGGL((expand_mfma_kernel<DT, Y>), grid, dim3(kMfmaThreads), lds, st, plan->d_me,               \
-                           pool->d_arena, base, plan->d_tok_idx, pool->H, plan->v_stride, plan->me_run, args);       \
+                           pool->d_arena, base, plan->d_tok_idx, pool->H, plan->v_stride, args);                     \
     }
         if (pool->dtype == SLORA_F16) {
             if (y16) SLORA_MEK(SLORA_F16, true) else SLORA_MEK(SLORA_F16, false)

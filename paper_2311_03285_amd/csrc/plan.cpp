@@ -156,7 +156,6 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         }
         const int64_t me_wgs = me_tiles * ((H + kMfmaExpandCols - 1) / kMfmaExpandCols) * launch_slots;
         const int32_t me_run = (int32_t)std::min<int64_t>(kMfmaRunMax, std::max<int64_t>(1, me_wgs / 1024));
-        plan->me_run = me_run;
         plan->me_stages = 0;
         int32_t n_vec_groups = 0;
         for (int32_t gi : order)
@@ -192,7 +191,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         const bool fuse = pool->fuse_decode != 0 && H <= 8192 &&
                           (pool->fuse_decode > 1 ||
                            (n_small * launch_slots >= 3 * 256 && small_bytes >= n_small * (int64_t(1) << 20)));
-        std::vector<Item> vs_tail, ve_tail, vs_dual, ve_dual;
+        std::vector<Item> vs_tail, ve_tail, vs_dual, ve_dual, me_rest;
         plan->vf_items.clear();
         for (int32_t gi : order) {
             const Group &g = groups[(size_t)gi];
@@ -258,10 +257,10 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                     const int32_t last = std::min(kMfmaTok, n - (t1 - 1) * kMfmaTok);
                     for (int32_t c = 0; c < H; c += kMfmaExpandCols) {
                         for (int32_t t = t0; t < t1; ++t)
-                            plan->me_items.push_back(Item{off, g.rank, c, std::min(kMfmaExpandCols, H - c), pos_base + t * kMfmaTok,
-                                                          std::min(kMfmaTok, n - t * kMfmaTok), tile0 + t,
-                                                          t == t0 ? (t1 - t0) + 256 * last : 0});
-                        plan->me_items.resize(plan->me_items.size() + (size_t)(me_run - (t1 - t0)), Item{0, 0, 0, 0, 0, 0, 0, 0});
+                            (t == t0 ? plan->me_items : me_rest)
+                                .push_back(Item{off, g.rank, c, std::min(kMfmaExpandCols, H - c), pos_base + t * kMfmaTok,
+                                                std::min(kMfmaTok, n - t * kMfmaTok), tile0 + t,
+                                                t == t0 ? (t1 - t0) + 256 * last : 0});
                     }
                 }
             }
@@ -289,6 +288,8 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                 }
             }
         }
+        plan->n_me_runs = (int32_t)plan->me_items.size(); // the runs' first tiles, then the others
+        plan->me_items.insert(plan->me_items.end(), me_rest.begin(), me_rest.end());
         plan->n_vs_plain = (int32_t)plan->vs_items.size();
         plan->n_ve_plain = (int32_t)plan->ve_items.size();
         plan->vs_items.insert(plan->vs_items.end(), vs_dual.begin(), vs_dual.end());
@@ -564,11 +565,6 @@ int32_t slora_plan_info(const slora_plan *plan, int64_t *out, int32_t n)
 {
     clear_error();
     if (!plan || !out || n < 0 || n > SLORA_PLAN_INFO_N) return fail(SLORA_EINVAL, "bad arguments");
-    auto live = [](const std::vector<Item> &l) { // without the padding of the per-XCD columns
-        int64_t c = 0;
-        for (const Item &i : l) c += i.ntok > 0;
-        return c;
-    };
     const int64_t v[SLORA_PLAN_INFO_N] = {plan->T_act,
                                           plan->n_groups,
                                           plan->n_groups_vec,
@@ -576,7 +572,7 @@ int32_t slora_plan_info(const slora_plan *plan, int64_t *out, int32_t n)
                                           (int64_t)plan->vs_items.size(),
                                           (int64_t)plan->ve_items.size(),
                                           (int64_t)plan->ms_items.size(),
-                                          live(plan->me_items),
+                                          (int64_t)plan->me_items.size(),
                                           plan->v_stride,
                                           plan->sum_rank,
                                           plan->n_sync,

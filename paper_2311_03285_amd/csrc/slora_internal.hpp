@@ -209,7 +209,7 @@ struct slora_plan {
     std::vector<slora::MsItem> mj_items; // one record per split tile, for the kernel that joins the shares
     int32_t ms_sub_tok = slora::kMsTok;  // tokens of an MFMA shrink item that one workgroup takes
     int32_t ms_lds_bytes = 0;  // LDS of the MFMA shrink's largest tile
-    int32_t me_run = 1;        // list entries per MFMA expand workgroup (a run of tiles, padded with empty entries)
+    int32_t n_me_runs = 0;     // MFMA expand workgroups per slot: the first entries of me, one per run of tiles
     int32_t me_stages = 0;     // most 32-rank stages an MFMA expand workgroup keeps in registers (sizes its LDS)
     int32_t n_sync = 0;        // split tiles
     int64_t part_floats = 0;   // partial sums of the split tiles, per slot
