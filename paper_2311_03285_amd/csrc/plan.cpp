@@ -108,70 +108,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
             if (n >= pool->mfma_min_tokens) mfma_tiles += (n + kMfmaTok - 1) / kMfmaTok;
         }
         const int64_t min_tokens = mfma_tiles >= pool->mfma_min_tiles ? pool->mfma_min_tokens : INT64_MAX;
-        // Fewer tiles than that: applies to fp32 y take the MFMA kernels all the same where the vector kernels
-        // would read very much again - every four tokens of a group read all of its pages, while an MFMA
-        // tile of a small batch is spread over many workgroups (shares of H, quarters of its tokens).
-        // Measured, vector / MFMA, us per call, for pages read (all slots): 30 MB 18.0 / 16.2, 67 MB 43 / 27,
-        // 134 MB 35 / 18, 268 MB 60 / 22, 537 MB (512 tokens of rank 64, 4 slots) 110 / 32.  Groups that stay
-        // on the vector kernels put the three MFMA launches behind theirs: 59 MB 26 / 34, 214 MB 85 / 67,
-        // 236 MB 116 / 103.  A plan does not know the type of y: it holds both forms (dual), and 16-bit y and the
-        // two-stage calls keep the vector kernels, whose sums 16-bit results are rounded from.
-        int64_t reread = 0;
-        bool few_tokens = false;
         const int64_t launch_slots = std::min<int64_t>(pool->n_slots, SLORA_MAX_MULTI);
-        for (int32_t gi : order) {
-            const int64_t n = (int64_t)groups[(size_t)gi].toks.size();
-            if (n >= pool->mfma_min_tokens)
-                reread += (n + kExpandTok - 1) / kExpandTok * groups[(size_t)gi].rank * (int64_t)H * 4 * launch_slots;
-            else
-                few_tokens = true;
-        }
-        plan->dual = min_tokens == INT64_MAX && reread >= (few_tokens ? 128000000 : 30000000);
-        const int64_t mfma_tokens = plan->dual ? pool->mfma_min_tokens : min_tokens; // groups with MFMA items
-        // Size of a share of an MFMA shrink tile (see below): mfma_split_bytes, or more when the
-        // batch is so large that shares of that size would be far more than the GPU can hold at a
-        // time (every share of a split tile costs a set of partial sums) - about three workgroups
-        // per compute unit for a launch of up to eight slots.
-        int64_t ms_bytes = 0;
-        for (int32_t gi : order) {
-            const Group &g = groups[(size_t)gi];
-            const int64_t n = (int64_t)g.toks.size();
-            if (n < mfma_tokens) continue;
-            const int64_t n_tok_tiles = (n + kMsTok - 1) / kMsTok, n_rank_blocks = (g.rank + kMsRanks - 1) / kMsRanks;
-            ms_bytes += (n * n_rank_blocks + (int64_t)g.rank * n_tok_tiles) * H * 2;
-        }
-        // A dual batch is small: there the shares are as short as pays, 256 elements of H (512 tokens of rank 64,
-        // H = 4096, 4 slots: 24 us for the stage with shares of 1 MiB, 18 at 512 KiB, 15 from 256 KiB on).  Short
-        // chains also keep the error where the vector kernels have it: 1.08e-7 against 1.09e-7 for these
-        // tokens in binary16 (2.9e-7 unsplit), 1.25e-7 against 1.41e-7 for rank 128 and H = 8192.
-        const int64_t split_bytes = plan->dual ? std::min<int64_t>(pool->mfma_split_bytes, 32 << 10) : pool->mfma_split_bytes;
-        const int64_t split_min_h = plan->dual ? std::min<int64_t>(pool->mfma_split_min_h, 256) : pool->mfma_split_min_h;
-        const int64_t share_bytes = std::max<int64_t>(split_bytes, ms_bytes * launch_slots / (3 * 256));
-        // MFMA expand: a workgroup keeps the B operands of its columns and walks a run of tiles.  Long runs
-        // pay for them once, but the launch still needs several workgroups per compute unit.
-        int64_t me_tiles = 0;
-        for (int32_t gi : order) {
-            const int64_t n = (int64_t)groups[(size_t)gi].toks.size();
-            if (n >= mfma_tokens) me_tiles += (n + kMfmaTok - 1) / kMfmaTok;
-        }
-        const int64_t me_wgs = me_tiles * ((H + kMfmaExpandCols - 1) / kMfmaExpandCols) * launch_slots;
-        const int32_t me_run = (int32_t)std::min<int64_t>(kMfmaRunMax, std::max<int64_t>(1, me_wgs / 1024));
-        plan->me_stages = 0;
-        int32_t n_vec_groups = 0;
-        for (int32_t gi : order)
-            if ((int64_t)groups[(size_t)gi].toks.size() < min_tokens) n_vec_groups++;
-        // vector-expand items: long runs of columns, halved while a launch would have fewer
-        // workgroups than the GPU has CUs
-        int32_t chunks = (H + kExpandColsMax - 1) / kExpandColsMax;
-        auto cols_of = [&](int32_t c) { return ((H + c - 1) / c + 511) / 512 * 512; };
-        while ((int64_t)n_vec_groups * chunks < 256 && cols_of(chunks) > 512) chunks *= 2;
-        int32_t ecols = cols_of(chunks);
-        // still short of workgroups at the smallest items: split the ranks over the wavefronts
-        plan->expand_split = ecols == 512 && (int64_t)n_vec_groups * chunks < 512;
-        // the vector shrink stages its tokens' x rows in LDS: at most 64 KiB of them per item
-        const int32_t shrink_tok = std::max(1, std::min(kShrinkTok, 65536 / (H * 2)));
-        const int32_t shrink_pages = (int32_t)pool->shrink_pages;
-        plan->expand_threads = ecols / 8;
         // One launch for both stages of decode groups (at most kExpandTok tokens): a workgroup per
         // group streams the whole adapter.  That pays when the batch has enough groups to fill
         // the GPU about three times over with whole-group workgroups AND the groups are large
@@ -191,6 +128,72 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         const bool fuse = pool->fuse_decode != 0 && H <= 8192 &&
                           (pool->fuse_decode > 1 ||
                            (n_small * launch_slots >= 3 * 256 && small_bytes >= n_small * (int64_t(1) << 20)));
+        // ... these groups run in that launch whatever else the plan holds
+        auto fused_group = [&](int64_t n) { return fuse && n < min_tokens && n <= kExpandTok; };
+        // Fewer tiles than that: applies to fp32 y take the MFMA kernels all the same where the vector kernels
+        // would read very much again - every four tokens of a group read all of its pages, while an MFMA
+        // tile of a small batch is spread over many workgroups (shares of H, quarters of its tokens).
+        // Measured, vector / MFMA, us per call, for pages read (all slots): 30 MB 18.0 / 16.2, 67 MB 43 / 27,
+        // 134 MB 35 / 18, 268 MB 60 / 22, 537 MB (512 tokens of rank 64, 4 slots) 110 / 32.  Groups that stay
+        // on the vector kernels put the three MFMA launches behind theirs: 59 MB 26 / 34, 214 MB 85 / 67,
+        // 236 MB 116 / 103.  A plan does not know the type of y: it holds both forms (dual), and 16-bit y and the
+        // two-stage calls keep the vector kernels, whose sums 16-bit results are rounded from.
+        int64_t reread = 0;
+        bool few_tokens = false;
+        for (int32_t gi : order) {
+            const int64_t n = (int64_t)groups[(size_t)gi].toks.size();
+            if (n >= pool->mfma_min_tokens && !fused_group(n))
+                reread += (n + kExpandTok - 1) / kExpandTok * groups[(size_t)gi].rank * (int64_t)H * 4 * launch_slots;
+            else
+                few_tokens = true;
+        }
+        plan->dual = min_tokens == INT64_MAX && reread >= (few_tokens ? 128000000 : 30000000);
+        const int64_t mfma_tokens = plan->dual ? pool->mfma_min_tokens : min_tokens;
+        auto mfma_group = [&](int64_t n) { return n >= mfma_tokens && !fused_group(n); }; // has MFMA items
+        // Size of a share of an MFMA shrink tile (see below): mfma_split_bytes, or more when the
+        // batch is so large that shares of that size would be far more than the GPU can hold at a
+        // time (every share of a split tile costs a set of partial sums) - about three workgroups
+        // per compute unit for a launch of up to eight slots.
+        int64_t ms_bytes = 0;
+        for (int32_t gi : order) {
+            const Group &g = groups[(size_t)gi];
+            const int64_t n = (int64_t)g.toks.size();
+            if (!mfma_group(n)) continue;
+            const int64_t n_tok_tiles = (n + kMsTok - 1) / kMsTok, n_rank_blocks = (g.rank + kMsRanks - 1) / kMsRanks;
+            ms_bytes += (n * n_rank_blocks + (int64_t)g.rank * n_tok_tiles) * H * 2;
+        }
+        // A dual batch is small: there the shares are as short as pays, 256 elements of H (512 tokens of rank 64,
+        // H = 4096, 4 slots: 24 us for the stage with shares of 1 MiB, 18 at 512 KiB, 15 from 256 KiB on).  Short
+        // chains also keep the error where the vector kernels have it: 1.08e-7 against 1.09e-7 for these
+        // tokens in binary16 (2.9e-7 unsplit), 1.25e-7 against 1.41e-7 for rank 128 and H = 8192.
+        const int64_t split_bytes = plan->dual ? std::min<int64_t>(pool->mfma_split_bytes, 32 << 10) : pool->mfma_split_bytes;
+        const int64_t split_min_h = plan->dual ? std::min<int64_t>(pool->mfma_split_min_h, 256) : pool->mfma_split_min_h;
+        const int64_t share_bytes = std::max<int64_t>(split_bytes, ms_bytes * launch_slots / (3 * 256));
+        // MFMA expand: a workgroup keeps the B operands of its columns and walks a run of tiles.  Long runs
+        // pay for them once, but the launch still needs several workgroups per compute unit.
+        int64_t me_tiles = 0;
+        for (int32_t gi : order) {
+            const int64_t n = (int64_t)groups[(size_t)gi].toks.size();
+            if (mfma_group(n)) me_tiles += (n + kMfmaTok - 1) / kMfmaTok;
+        }
+        const int64_t me_wgs = me_tiles * ((H + kMfmaExpandCols - 1) / kMfmaExpandCols) * launch_slots;
+        const int32_t me_run = (int32_t)std::min<int64_t>(kMfmaRunMax, std::max<int64_t>(1, me_wgs / 1024));
+        plan->me_stages = 0;
+        int32_t n_vec_groups = 0;
+        for (int32_t gi : order)
+            if ((int64_t)groups[(size_t)gi].toks.size() < min_tokens) n_vec_groups++;
+        // vector-expand items: long runs of columns, halved while a launch would have fewer
+        // workgroups than the GPU has CUs
+        int32_t chunks = (H + kExpandColsMax - 1) / kExpandColsMax;
+        auto cols_of = [&](int32_t c) { return ((H + c - 1) / c + 511) / 512 * 512; };
+        while ((int64_t)n_vec_groups * chunks < 256 && cols_of(chunks) > 512) chunks *= 2;
+        int32_t ecols = cols_of(chunks);
+        // still short of workgroups at the smallest items: split the ranks over the wavefronts
+        plan->expand_split = ecols == 512 && (int64_t)n_vec_groups * chunks < 512;
+        // the vector shrink stages its tokens' x rows in LDS: at most 64 KiB of them per item
+        const int32_t shrink_tok = std::max(1, std::min(kShrinkTok, 65536 / (H * 2)));
+        const int32_t shrink_pages = (int32_t)pool->shrink_pages;
+        plan->expand_threads = ecols / 8;
         std::vector<Item> vs_tail, ve_tail, vs_dual, ve_dual, me_rest;
         plan->vf_items.clear();
         for (int32_t gi : order) {
@@ -201,7 +204,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
             plan->sum_rank += g.rank;
             max_rank = std::max(max_rank, g.rank);
             const int32_t off = (int32_t)g.arena_off;
-            if ((int64_t)n >= mfma_tokens) {
+            if (mfma_group(n)) {
                 // v tiles of 32 tokens, numbered in order; an expand item covers one tile, a shrink
                 // item up to four consecutive ones (its pages are then read once for them all)
                 const int32_t tile0 = plan->n_mfma_tiles;
@@ -270,8 +273,8 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                 plan->n_groups_vec++;
                 // a group the one-launch decode kernel can take goes to the end of the two lists
                 // (the two-stage calls run the whole lists, a fused apply only their heads)
-                const bool fused = fuse && n <= kExpandTok;
-                const bool both = (int64_t)n >= mfma_tokens; // has MFMA items as well
+                const bool fused = fused_group(n);
+                const bool both = mfma_group(n); // in the MFMA lists as well
                 std::vector<Item> &vs = fused ? vs_tail : both ? vs_dual : plan->vs_items;
                 std::vector<Item> &ve = fused ? ve_tail : both ? ve_dual : plan->ve_items;
                 if (fused) plan->vf_items.push_back(Item{off, g.rank, 0, H, pos_base, n, 0, 0});

@@ -85,3 +85,20 @@ def test_small_batch_with_both_kernels_lists(dtype, few):
         slora.set_option(dw.pool, "mfma_min_tokens", 1 << 40)  # vector kernels throughout
         assert np.array_equal(gpu_slot(dw, 1, dw.plan()), two)
         assert np.array_equal(gpu_y16(dw, [1])[0], got)
+
+
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+def test_one_launch_groups_beside_mfma_groups_are_added_once(dtype):
+    """Groups of one to four tokens that the options allow on the MFMA kernels and on the one-launch kernel."""
+    ids = np.repeat([0, 1, 2, 3], [290, 1, 4, 5]).astype(np.int32)
+    w = synth.make_workload("once", 690, 4096, dtype, 2 * 2 * (128 + 8 + 16 + 8) + 16, 2, [128, 8, 16, 8], ids, int_valued=True)
+    with DeviceWorkload(w, real_adapters="all") as dw:
+        route(dw.pool, 1, 32)
+        slora.set_option(dw.pool, "fuse_decode", 2)
+        plan = dw.plan()
+        info = slora.plan_info(plan)
+        assert info["groups_fused"] == 2 and info["mfma_expand_items"] > 0
+        xs, ys = [dw.x_dev(s) for s in (0, 1)], [dw.y_dev(s) for s in (0, 1)]
+        slora.lora_apply_multi(plan, [0, 1], [t.data_ptr() for t in xs], [t.data_ptr() for t in ys])
+        for s in (0, 1):
+            assert np.array_equal(ys[s].cpu().numpy().astype(np.float64), oracle_slot(w, s))

@@ -38,3 +38,15 @@ def test_rule(groups, options, dual):
     assert (info["mfma_expand_items"] > 0) == (dual or on_mfma)
     if not on_mfma:                                            # every group keeps its vector items
         assert info["vec_shrink_items"] == sum((t + 3) // 4 * ((r + 3) // 4) for r, t in groups)
+
+
+@pytest.mark.parametrize("H,n_slots,groups,options,fused,tiles", [
+    (4096, 4, [(64, 512), (8, 1)], {"mfma_min_tokens": 1, "fuse_decode": 2}, 1, 16),
+    (8192, 8, [(64, 512)] + [(64, 4)] * 4 + [(64, 1)] * 120, {"mfma_min_tokens": 4}, 124, 16),
+    (4096, 4, [(64, 512), (8, 3)], {"mfma_min_tokens": 1, "fuse_decode": 0}, 0, 17),
+])
+def test_no_group_is_in_the_one_launch_list_and_the_mfma_lists(H, n_slots, groups, options, fused, tiles):
+    """An apply runs both: such a group's delta would be added twice."""
+    info = plan_of(H, n_slots, groups, **options)
+    assert info["groups_fused"] == fused
+    assert info["mfma_expand_items"] == tiles * (H // 256)
