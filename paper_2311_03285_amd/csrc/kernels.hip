@@ -1744,10 +1744,10 @@ static int32_t launch_small(slora_plan *plan, int32_t n, const MultiArgs &args, 
     return check_launch("lora_vec_small");
 }
 
-int32_t launch_fused(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, bool y16)
+int32_t launch_fused(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, bool y16, const Route &route)
 {
     slora_pool *pool = plan->pool;
-    if (plan->small_used) return launch_small(plan, n, args, stream, y16);
+    if (route.small) return launch_small(plan, n, args, stream, y16);
     if (plan->vf_items.empty()) return SLORA_OK;
     const uint16_t *base = static_cast<const uint16_t *>(pool->dev_base);
     hipStream_t st = (hipStream_t)stream;
@@ -1786,12 +1786,12 @@ int32_t launch_fused(slora_plan *plan, int32_t n, const MultiArgs &args, void *s
     return check_launch("lora_vec_fused");
 }
 
-int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, bool heads_only)
+int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, const Route &route)
 {
     slora_pool *pool = plan->pool;
     const uint16_t *base = static_cast<const uint16_t *>(pool->dev_base);
     hipStream_t st = (hipStream_t)stream;
-    const size_t n_vs = plan->wide ? (size_t)plan->n_vs_plain : heads_only ? (size_t)plan->n_vs_head : plan->vs_items.size();
+    const size_t n_vs = plan->n_vs(route);
     if (n_vs > 0) {
         const dim3 grid((unsigned)(n_vs * (size_t)n));
         const size_t lds = (size_t)plan->max_shrink_tok * pool->H * 2;
@@ -1817,7 +1817,7 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *
         int32_t rc = check_launch("shrink_vec");
         if (rc != SLORA_OK) return rc;
     }
-    if (!plan->ms_items.empty() && plan->mfma_on()) {
+    if (!plan->ms_items.empty() && plan->mfma_on(route)) {
         const dim3 grid((unsigned)(plan->ms_items.size() * (size_t)(kMsTok / plan->ms_sub_tok) * (size_t)n));
         const size_t lds = (size_t)plan->ms_lds_bytes;
 #define SLORA_MSK(DT)                                                                                                \
@@ -1847,7 +1847,7 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *
     return SLORA_OK;
 }
 
-int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, bool y16, bool heads_only)
+int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, bool y16, const Route &route)
 {
     slora_pool *pool = plan->pool;
     const uint16_t *base = static_cast<const uint16_t *>(pool->dev_base);
@@ -1856,7 +1856,7 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *
 #define SLORA_PICK(KERNEL)                                                                   \
     (pool->dtype == SLORA_F16 ? (y16 ? KERNEL<SLORA_F16, true> : KERNEL<SLORA_F16, false>)   \
                               : (y16 ? KERNEL<SLORA_BF16, true> : KERNEL<SLORA_BF16, false>))
-    const size_t n_ve = plan->wide ? (size_t)plan->n_ve_plain : heads_only ? (size_t)plan->n_ve_head : plan->ve_items.size();
+    const size_t n_ve = plan->n_ve(route);
     if (n_ve > 0) {
         const dim3 grid((unsigned)(n_ve * (size_t)n));
         if (plan->expand_split)
@@ -1868,7 +1868,7 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *
         int32_t rc = check_launch("expand_vec");
         if (rc != SLORA_OK) return rc;
     }
-    if (!plan->me_items.empty() && plan->mfma_on()) {
+    if (!plan->me_items.empty() && plan->mfma_on(route)) {
         const dim3 grid((unsigned)((size_t)plan->n_me_runs * (size_t)n));
         // LDS: two buffers of V fragments (the plan's most 32-rank stages) and the wavefronts' own parts
         const size_t lds = (size_t)2 * plan->me_stages * 2 * (pool->dtype == SLORA_F16 ? 2 : 3) * 1024 + 4 * kWaveLds;

@@ -399,9 +399,9 @@ int32_t slora_plan::upload()
     return SLORA_OK;
 }
 
-void slora_plan::fill_args(MultiArgs &a, int32_t n, float *v) const
+void slora_plan::fill_args(MultiArgs &a, int32_t n, float *v, const Route &r) const
 {
-    const int64_t per_slot = v_slot_floats(pool->dtype, mfma_on());
+    const int64_t per_slot = v_slot_floats(pool->dtype, mfma_on(r));
     for (int32_t k = 0; k < n; ++k) a.v[k] = v + (int64_t)k * per_slot;
     a.vfrag_off = (int64_t)T_act * v_stride;
     a.vexp_off = a.vfrag_off + vfrag_floats(pool->dtype);
@@ -455,29 +455,29 @@ int32_t do_shrink(slora_plan *plan, int32_t n, const int32_t *slots, const void 
     }
     DeviceScope dev(plan->pool->device);
     if (dev.status() != SLORA_OK) return dev.status();
-    plan->wide = plan->dual && y != nullptr && !y16 && !narrow;
+    Route route;
+    route.wide = plan->dual && y != nullptr && !y16 && !narrow;
+    route.fused = y != nullptr && !plan->vf_items.empty();
+    route.small = y != nullptr && plan->small && (int64_t)plan->ve_items.size() * n <= 256;
     // the page lists of every adapter the plan names went to the device when it was built
     float *v = scratch;
     int32_t rc = SLORA_OK;
     if (!v) {
-        rc = plan->pool->grow_v(plan->set, (size_t)plan->v_total_floats(n, plan->pool->dtype, plan->mfma_on()));
+        rc = plan->pool->grow_v(plan->set, (size_t)plan->v_total_floats(n, plan->pool->dtype, plan->mfma_on(route)));
         v = plan->set->v;
     }
     if (rc == SLORA_OK) rc = plan->enter(stream);
     if (rc != SLORA_OK) return rc;
-    plan->fill_args(a, n, v);
-    const bool fused = y != nullptr && !plan->vf_items.empty();
-    plan->small_used = y != nullptr && plan->small && (int64_t)plan->ve_items.size() * n <= 256;
-    if (fused || plan->small_used) {
+    plan->fill_args(a, n, v, route);
+    if (route.fused || route.small) {
         for (int32_t k = 0; k < n; ++k) a.y[k] = y[k];
-        rc = launch_fused(plan, n, a, stream, y16);
-        if (rc != SLORA_OK) return rc;
+        rc = launch_fused(plan, n, a, stream, y16, route);
     }
-    if (!plan->small_used) rc = launch_shrink(plan, n, a, stream, fused);
+    if (rc == SLORA_OK && !route.small) rc = launch_shrink(plan, n, a, stream, route);
     if (rc == SLORA_OK) {
         plan->v_slots = n;
         plan->v_used = v;
-        plan->v_complete = !fused; // after a fused apply the v of the fused groups never reached memory
+        plan->v_route = route;
     }
     return rc;
 }
@@ -495,7 +495,7 @@ int32_t check_y(int32_t n, void *const *y)
 }
 
 int32_t do_expand(slora_plan *plan, int32_t n, const int32_t *slots, void *const *y, void *stream, bool y16,
-                  bool after_fused = false)
+                  bool after_apply = false)
 {
     int32_t rc = check_y(n, y);
     if (rc != SLORA_OK) return rc;
@@ -506,15 +506,16 @@ int32_t do_expand(slora_plan *plan, int32_t n, const int32_t *slots, void *const
         a.y[k] = y[k];
         a.slot[k] = slots[k];
     }
-    if (plan->v_slots != n || !plan->v_used || (!after_fused && !plan->v_complete))
+    const Route route = plan->v_route;
+    if (plan->v_slots != n || !plan->v_used || (!after_apply && route.fused))
         return fail(SLORA_EINVAL, "expand of %d slot(s) needs a preceding slora_lora_shrink of %d slot(s)", n, n);
-    if (after_fused && plan->small_used) return SLORA_OK; // both stages ran in one launch
+    if (after_apply && route.small) return SLORA_OK; // both stages ran in one launch
     DeviceScope dev(plan->pool->device);
     if (dev.status() != SLORA_OK) return dev.status();
     rc = plan->enter(stream);
     if (rc != SLORA_OK) return rc;
-    plan->fill_args(a, n, plan->v_used);
-    return launch_expand(plan, n, a, stream, y16, after_fused && !plan->vf_items.empty());
+    plan->fill_args(a, n, plan->v_used, route);
+    return launch_expand(plan, n, a, stream, y16, route);
 }
 
 } // namespace

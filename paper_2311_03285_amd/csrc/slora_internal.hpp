@@ -67,6 +67,13 @@ struct MultiArgs {
     int64_t part_off;  // floats from v[k] to the partial sums of split tiles
 };
 
+// Which kernels one call of a plan takes.  The expand follows the shrink whose v it reads.
+struct Route {
+    bool wide = false;  // a dual plan's groups of many tokens on the MFMA kernels
+    bool small = false; // both stages in the one-launch kernel for small batches
+    bool fused = false; // an apply: launch_fused serves the groups of the one-launch decode kernel
+};
+
 // Tile constants the scheduler and the kernels must agree on.
 constexpr int kShrinkTok = 4;     // tokens per vector-shrink item (x rows staged in LDS)
 constexpr int kExpandTok = 4;     // tokens per vector-expand item (accumulators in registers)
@@ -189,7 +196,6 @@ struct slora_plan {
     int32_t expand_threads = 64; // workgroup size of the vector expand (columns per item / 8)
     int32_t max_expand_tok = 0;
     bool small = false;          // small calls on the plan may take the one-launch kernel for small batches
-    bool small_used = false;     // ... and the latest shrink did: its expand is done
     int32_t expand_split = 0;    // small batch: 512-column items, ranks split over four wavefronts
     int64_t sum_rank = 0;
     int32_t n_groups = 0, n_groups_vec = 0, n_groups_mfma = 0;
@@ -202,9 +208,11 @@ struct slora_plan {
     // A dual plan's groups of many tokens are in both kernels' lists: in vs / ve between the plain groups'
     // items and n_vs_head / n_ve_head, and in the MFMA lists.  fp32-y applies take the latter (wide).
     bool dual = false;
-    bool wide = false;                    // the latest shrink did, and so does the expand that follows it
     int32_t n_vs_plain = 0, n_ve_plain = 0;
-    bool mfma_on() const { return !dual || wide; }
+    bool mfma_on(const slora::Route &r) const { return !dual || r.wide; }
+    // items of the two vector lists that a call runs beside the other kernels
+    size_t n_vs(const slora::Route &r) const { return r.wide ? (size_t)n_vs_plain : r.fused ? (size_t)n_vs_head : vs_items.size(); }
+    size_t n_ve(const slora::Route &r) const { return r.wide ? (size_t)n_ve_plain : r.fused ? (size_t)n_ve_head : ve_items.size(); }
     std::vector<slora::MsItem> ms_items;
     std::vector<slora::MsItem> mj_items; // one record per split tile, for the kernel that joins the shares
     int32_t ms_sub_tok = slora::kMsTok;  // tokens of an MFMA shrink item that one workgroup takes
@@ -234,9 +242,11 @@ struct slora_plan {
         return (int64_t)T_act * v_stride + (mfma ? vfrag_floats(dtype) + vexp_floats() + part_floats : 0);
     }
     int64_t v_total_floats(int32_t n, int32_t dtype, bool mfma) const { return (int64_t)n * v_slot_floats(dtype, mfma); }
-    float *v_used = nullptr; // where the latest shrink left v
-    int32_t v_slots = 0;     // n of the latest shrink
-    bool v_complete = false; // the latest shrink left v for every group (not so after an apply that fused decode groups)
+    // The latest shrink whose launches succeeded.  Written together, after them: a call that fails on the
+    // way must not change how an expand reads the v that is there.
+    float *v_used = nullptr; // where it left v
+    int32_t v_slots = 0;     // its n
+    slora::Route v_route;    // and its kernels: the layout of v (fused: v of those groups never reached memory)
 
     // Stream order.  Every launch of a plan reads its work lists and reads or writes its v, so
     // all of a plan's work is kept in ONE order: when a call names another stream than the
@@ -246,7 +256,7 @@ struct slora_plan {
 
     int32_t upload();
     int32_t enter(void *stream);
-    void fill_args(slora::MultiArgs &a, int32_t n, float *v) const;
+    void fill_args(slora::MultiArgs &a, int32_t n, float *v, const slora::Route &r) const;
 };
 
 namespace slora {
@@ -260,10 +270,9 @@ int32_t launch_write_pages(slora_pool *pool, const int32_t *d_idx, int64_t n, co
                            void *stream, int32_t max_groups = 0); // max_groups > 0 caps the grid
 int32_t launch_gather(slora_pool *pool, int64_t arena_entry, int32_t rank, void *dev_out, void *stream);
 int32_t static_scratch_address(int device, void **out); // `device` must be current
-// heads_only: the vector lists without the groups that launch_fused has served
-int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, bool heads_only = false);
-int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, bool y16, bool heads_only = false);
-// the groups of the one-launch decode kernel or, if small_used is set, the whole (small) batch
-int32_t launch_fused(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, bool y16);
+int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, const Route &route);
+int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, bool y16, const Route &route);
+// the groups of the one-launch decode kernel or, on a small route, the whole batch
+int32_t launch_fused(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, bool y16, const Route &route);
 
 } // namespace slora

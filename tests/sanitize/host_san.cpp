@@ -6,14 +6,17 @@
 // always complete - and (2) stand-ins for the kernel launchers that do not compute anything
 // but CHECK what the kernels assume about their work lists and touch every byte of scratch the
 // kernels would touch, so that a list entry out of range or an undersized buffer is reported by
-// the sanitizer or by an explicit check.  Then a seeded random sequence of API calls runs.
+// the sanitizer or by an explicit check.  Then a seeded random sequence of API calls runs, or, named
+// on the command line, one of the directed cases.
 #include <hip/hip_runtime_api.h>
 
+#include <algorithm>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
 #include <random>
 #include <set>
+#include <utility>
 #include <vector>
 
 #include "slora_internal.hpp"
@@ -29,13 +32,21 @@
 // ---------------------------------------------------------------------------------------------
 // stand-in HIP runtime
 // ---------------------------------------------------------------------------------------------
+static long g_device_mallocs = 0;  // hipMalloc calls so far
+static bool g_fail_malloc = false; // hipMalloc is out of memory
+
 extern "C" {
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
 hipError_t hipSetDevice(int) { return hipSuccess; }
 hipError_t hipDeviceSynchronize(void) { return hipSuccess; }
 hipError_t hipGetLastError(void) { return hipSuccess; }
 const char *hipGetErrorString(hipError_t) { return "stand-in"; }
-hipError_t hipMalloc(void **p, size_t n) { *p = std::malloc(n ? n : 1); return *p ? hipSuccess : hipErrorOutOfMemory; }
+hipError_t hipMalloc(void **p, size_t n)
+{
+    g_device_mallocs++;
+    *p = g_fail_malloc ? nullptr : std::malloc(n ? n : 1);
+    return *p ? hipSuccess : hipErrorOutOfMemory;
+}
 hipError_t hipFree(void *p) { std::free(p); return hipSuccess; }
 hipError_t hipHostMalloc(void **p, size_t n, unsigned) { *p = std::malloc(n ? n : 1); return *p ? hipSuccess : hipErrorOutOfMemory; }
 hipError_t hipHostFree(void *p) { std::free(p); return hipSuccess; }
@@ -116,18 +127,41 @@ static void check_tokens(const slora_plan *plan, int32_t pos0, int32_t ntok)
     }
 }
 
-int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &a, void *, bool heads_only)
+// the v of all slots, in the layout of the route, lies inside the plan's buffer or the static scratch
+static void check_scratch(const slora_plan *plan, int32_t n, const MultiArgs &a, const Route &route)
+{
+    const size_t floats = (size_t)plan->v_total_floats(n, plan->pool->dtype, plan->mfma_on(route));
+    if (a.v[0] == plan->set->v)
+        REQUIRE(floats <= plan->set->v_cap);
+    else if (a.v[0] == (float *)g_static_scratch.data())
+        REQUIRE(floats * sizeof(float) <= SLORA_STATIC_SCRATCH_BYTES);
+    for (int32_t k = 1; k < n; ++k) REQUIRE(a.v[k] - a.v[0] == k * plan->v_slot_floats(plan->pool->dtype, plan->mfma_on(route)));
+}
+
+// what the latest apply, shrink or expand launched
+struct Log {
+    bool small = false, fused = false, mfma_shrink = false, mfma_expand = false;
+    size_t vec_shrink = 0, vec_expand = 0; // items
+};
+static Log g_log;
+static volatile float g_sink; // reads of the stand-in kernels end here
+
+int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &a, void *, const Route &route)
 {
     const slora_pool *pool = plan->pool;
     const int32_t np = pool->dtype == SLORA_F16 ? 2 : 3;
     const int n_gran = (pool->H + kMsGranule - 1) / kMsGranule;
     const int n_kk = plan->v_stride / 16;
     REQUIRE(a.n == n && plan->v_stride % kRankPad == 0);
+    REQUIRE(0 <= plan->n_vs_plain && plan->n_vs_plain <= plan->n_vs_head && (size_t)plan->n_vs_head <= plan->vs_items.size());
+    const size_t n_vs = plan->n_vs(route);
+    check_scratch(plan, n, a, route);
+    g_log.vec_shrink = n_vs;
+    g_log.mfma_shrink = plan->mfma_on(route) && !plan->ms_items.empty();
     for (int32_t k = 0; k < n; ++k) {
         REQUIRE(a.x[k] && a.v[k]);
         float *v = a.v[k];
-        REQUIRE(plan->n_vs_head >= 0 && (size_t)plan->n_vs_head <= plan->vs_items.size());
-        for (size_t i = 0; i < (heads_only ? (size_t)plan->n_vs_head : plan->vs_items.size()); ++i) {
+        for (size_t i = 0; i < n_vs; ++i) {
             const Item &it = plan->d_vs[i];
             REQUIRE(std::memcmp(&it, &plan->vs_items[i], sizeof it) == 0);
             check_pages(plan, it.arena_off, it.rank, a.slot[k]);
@@ -139,7 +173,7 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &a, void *, b
         uint16_t *frag = reinterpret_cast<uint16_t *>(v + a.vfrag_off);
         int8_t *vexp = reinterpret_cast<int8_t *>(v + a.vexp_off);
         float *part = v + a.part_off;
-        for (size_t i = 0; i < plan->ms_items.size(); ++i) {
+        for (size_t i = 0; plan->mfma_on(route) && i < plan->ms_items.size(); ++i) {
             const MsItem &it = plan->d_ms[i];
             REQUIRE(std::memcmp(&it, &plan->ms_items[i], sizeof it) == 0);
             check_pages(plan, it.arena_off, it.rank, a.slot[k]);
@@ -171,38 +205,57 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &a, void *, b
     return SLORA_OK;
 }
 
-int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &a, void *, bool, bool heads_only)
+int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &a, void *, bool, const Route &route)
 {
     const slora_pool *pool = plan->pool;
     REQUIRE(a.n == n);
+    REQUIRE(0 <= plan->n_ve_plain && plan->n_ve_plain <= plan->n_ve_head && (size_t)plan->n_ve_head <= plan->ve_items.size());
+    const size_t n_ve = plan->n_ve(route);
+    check_scratch(plan, n, a, route);
+    g_log.vec_expand = n_ve;
+    g_log.mfma_expand = plan->mfma_on(route) && !plan->me_items.empty();
+    const int n_kk = plan->v_stride / 16, np = pool->dtype == SLORA_F16 ? 2 : 3;
     for (int32_t k = 0; k < n; ++k) {
         REQUIRE(a.y[k] && a.v[k]);
-        REQUIRE(plan->n_ve_head >= 0 && (size_t)plan->n_ve_head <= plan->ve_items.size());
-        for (size_t i = 0; i < (heads_only ? (size_t)plan->n_ve_head : plan->ve_items.size()); ++i) {
+        for (size_t i = 0; i < n_ve; ++i) {
             const Item &it = plan->d_ve[i];
             REQUIRE(std::memcmp(&it, &plan->ve_items[i], sizeof it) == 0);
             check_pages(plan, it.arena_off, it.rank, a.slot[k]);
             check_tokens(plan, it.pos0, it.ntok);
             REQUIRE(it.ntok <= kExpandTok && it.a >= 0 && it.b > 0 && it.a % 8 == 0 && it.a + it.b <= pool->H);
             REQUIRE(it.b <= plan->expand_threads * 8 || plan->expand_split);
+            for (int32_t t = 0; t < it.ntok; ++t)
+                for (int32_t j = 0; j < it.rank; ++j) g_sink = a.v[k][(int64_t)(it.pos0 + t) * plan->v_stride + j];
         }
-        for (size_t i = 0; i < plan->me_items.size(); ++i) {
+        for (size_t i = 0; plan->mfma_on(route) && i < plan->me_items.size(); ++i) {
             const Item &it = plan->d_me[i];
             REQUIRE(std::memcmp(&it, &plan->me_items[i], sizeof it) == 0);
-            if (it.ntok == 0) continue; // padding of a per-die column
             check_pages(plan, it.arena_off, it.rank, a.slot[k]);
             check_tokens(plan, it.pos0, it.ntok);
             REQUIRE(it.ntok <= kMfmaTok && it.a >= 0 && it.b > 0 && it.b <= kMfmaExpandCols && it.a + it.b <= pool->H);
             REQUIRE(it.tile >= 0 && it.tile < plan->n_mfma_tiles);
+            const unsigned char *frag = reinterpret_cast<const unsigned char *>(a.v[k] + a.vfrag_off);
+            for (int kk = 0; kk < (it.rank + 31) / 32 * 2; ++kk)
+                for (int b = 0; b < np * 1024; b += 64) g_sink = frag[((int64_t)it.tile * n_kk + kk) * np * 1024 + b];
+            const int8_t *vexp = reinterpret_cast<const int8_t *>(a.v[k] + a.vexp_off);
+            for (int b = 0; b < 32 * plan->n_rank_blocks; ++b) g_sink = vexp[(int64_t)it.tile * plan->n_rank_blocks * 32 + b];
         }
     }
     return SLORA_OK;
 }
 
-int32_t launch_fused(slora_plan *plan, int32_t n, const MultiArgs &a, void *, bool)
+int32_t launch_fused(slora_plan *plan, int32_t n, const MultiArgs &a, void *, bool, const Route &route)
 {
     const slora_pool *pool = plan->pool;
     REQUIRE(a.n == n && pool->H <= 8192);
+    if (route.small) { // the whole batch, from the items of the rank-split expand
+        g_log.small = true;
+        REQUIRE(plan->small && plan->ms_items.empty() && plan->vf_items.empty() && plan->expand_split && pool->H <= 4096);
+        for (const Item &it : plan->ve_items)
+            REQUIRE(it.rank <= kSmallRanks && it.ntok <= kExpandTok && it.ntok <= plan->max_expand_tok);
+        return SLORA_OK;
+    }
+    g_log.fused = true;
     // every fused group is a whole group of at most kExpandTok tokens, and the tails of the two
     // vector lists are exactly these groups' two-stage items
     std::set<int32_t> fused_pos;
@@ -227,10 +280,89 @@ int32_t launch_fused(slora_plan *plan, int32_t n, const MultiArgs &a, void *, bo
 } // namespace slora
 
 // ---------------------------------------------------------------------------------------------
+// directed cases
+// ---------------------------------------------------------------------------------------------
+using namespace slora;
+
+// A pool of one adapter per (rank, tokens) pair, its batch, and one x and y per slot.
+struct Bench {
+    int32_t H, n_slots, T = 0;
+    std::vector<uint16_t> mem;
+    slora_pool *pool = nullptr;
+    slora_plan *plan = nullptr;
+    std::vector<std::vector<uint16_t>> x;
+    std::vector<std::vector<float>> y;
+    std::vector<int32_t> ids;
+    std::vector<const void *> xs;
+    std::vector<float *> ys;
+    int32_t slots[SLORA_MAX_MULTI] = {0, 1, 2, 3, 4, 5, 6, 7};
+
+    Bench(int32_t H_, int32_t n_slots_, int32_t dtype, const std::vector<std::pair<int, int>> &groups,
+          const std::vector<std::pair<const char *, int64_t>> &options = {})
+        : H(H_), n_slots(n_slots_)
+    {
+        int64_t pages = 0;
+        int32_t max_rank = 1;
+        for (auto &g : groups) {
+            pages += 2 * (int64_t)n_slots * g.first;
+            max_rank = std::max(max_rank, g.first);
+        }
+        mem.assign((size_t)pages * H, 0);
+        REQUIRE(slora_pool_init(&pool, H, pages, dtype, mem.data(), n_slots, max_rank) == SLORA_OK);
+        for (auto &o : options) REQUIRE(slora_set_option(pool, o.first, o.second) == SLORA_OK);
+        for (size_t a = 0; a < groups.size(); ++a) {
+            REQUIRE(slora_adapter_alloc(pool, (int32_t)a, groups[a].first, nullptr) == SLORA_OK);
+            ids.insert(ids.end(), (size_t)groups[a].second, (int32_t)a);
+        }
+        T = (int32_t)ids.size();
+        for (int k = 0; k < n_slots; ++k) {
+            x.emplace_back((size_t)T * H);
+            y.emplace_back((size_t)T * H);
+            xs.push_back(x.back().data());
+            ys.push_back(y.back().data());
+        }
+        REQUIRE(slora_batch_plan(pool, &plan, ids.data(), T, nullptr, 0) == SLORA_OK);
+    }
+    ~Bench()
+    {
+        REQUIRE(slora_plan_destroy(plan) == SLORA_OK);
+        REQUIRE(slora_pool_destroy(pool) == SLORA_OK);
+    }
+    int32_t apply(int32_t n) { g_log = {}; return slora_lora_apply_multi(plan, n, slots, xs.data(), ys.data(), nullptr); }
+    int32_t apply_static(int32_t n) { g_log = {}; return slora_lora_apply_multi_static(plan, n, slots, xs.data(), ys.data(), nullptr); }
+    int32_t apply16(int32_t n) { g_log = {}; return slora_lora_apply_multi_y16(plan, n, slots, xs.data(), (void *const *)ys.data(), nullptr); }
+    int32_t shrink(int32_t n) { g_log = {}; return slora_lora_shrink(plan, n, slots, xs.data(), nullptr); }
+    int32_t expand(int32_t n) { g_log = {}; return slora_lora_expand(plan, n, slots, ys.data(), nullptr); }
+};
+
+// An apply that fails leaves v as the shrink before it did: the expand that follows reads THAT layout.
+static void failed_apply()
+{
+    Bench b(4096, 4, SLORA_F16, {{64, 512}});
+    REQUIRE(b.shrink(4) == SLORA_OK && !g_log.mfma_shrink);
+    g_fail_malloc = true; // whatever the apply wants to allocate
+    const int32_t rc = b.apply(4);
+    g_fail_malloc = false;
+    REQUIRE(rc == SLORA_OK || rc == SLORA_EHIP);
+    REQUIRE(b.expand(4) == SLORA_OK);
+    REQUIRE(g_log.mfma_expand == (rc == SLORA_OK));
+}
+
+static const struct { const char *name; void (*run)(); } kCases[] = {
+    {"failed_apply", failed_apply},
+};
+
+// ---------------------------------------------------------------------------------------------
 // driver
 // ---------------------------------------------------------------------------------------------
 int main(int argc, char **argv)
 {
+    for (auto &c : kCases)
+        if (argc > 1 && !std::strcmp(argv[1], c.name)) {
+            c.run();
+            std::printf("host_san OK: %s\n", c.name);
+            return 0;
+        }
     const unsigned seed = argc > 1 ? (unsigned)std::atoi(argv[1]) : 1u;
     std::mt19937 rng(seed);
     auto rnd = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
