@@ -257,8 +257,11 @@ int32_t slora_lora_apply_multi(slora_plan *plan, int32_t n, const int32_t *slots
  * SLORA_STATIC_SCRATCH_BYTES, held until the process ends) instead of the plan's own buffer.
  * The call makes no hipMalloc / hipFree and no other allocating call, on any path.
  * Limit: n * (tokens with an adapter * v row stride * 4 bytes + the MFMA tiles' operand
- * fragments) must fit the scratch, else SLORA_ERANGE and nothing is enqueued (slora_plan_info
- * gives tokens and stride; 8 slots of 4096 decode tokens at rank <= 128 need 16 MiB).
+ * fragments and partial sums) must fit the scratch, else SLORA_ERANGE and nothing is enqueued
+ * (slora_plan_info gives tokens, stride and the whole per slot; 8 slots of 4096 decode tokens at
+ * rank <= 128 need 16 MiB).  Batches that may take either kernel family (few tiles, see
+ * "mfma_min_tiles" below) take the vector kernels, in this call and in slora_lora_apply_multi,
+ * where only the rows of v fit.
  * Every call on a GPU uses that GPU's one array: calls whose device work may overlap (two
  * streams, two plans, two pools) race on it - order them on one stream or by events.  Nothing
  * in the array has to be cleared between calls: the expand reads only what the shrink of the

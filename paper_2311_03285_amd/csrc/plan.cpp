@@ -399,6 +399,16 @@ int32_t slora_plan::upload()
     return SLORA_OK;
 }
 
+Route slora_plan::route(int32_t n, bool apply, bool y16) const
+{
+    Route r;
+    r.wide = dual && apply && !y16 &&
+             v_total_floats(n, pool->dtype, true) * (int64_t)sizeof(float) <= (int64_t)SLORA_STATIC_SCRATCH_BYTES;
+    r.fused = apply && !vf_items.empty();
+    r.small = apply && small && (int64_t)ve_items.size() * n <= 256;
+    return r;
+}
+
 void slora_plan::fill_args(MultiArgs &a, int32_t n, float *v, const Route &r) const
 {
     const int64_t per_slot = v_slot_floats(pool->dtype, mfma_on(r));
@@ -439,9 +449,8 @@ int32_t check_plan(slora_plan *plan, int32_t n, const int32_t *slots)
 // scratch: where v goes; NULL = the plan's own buffer (grown on demand)
 // y != NULL: part of an apply - decode groups the plan marked for it run both stages in one
 // launch here, and the two-stage launches (here and in do_expand) cover the other groups only.
-// narrow: a dual plan stays on the vector kernels.
 int32_t do_shrink(slora_plan *plan, int32_t n, const int32_t *slots, const void *const *x, void *stream,
-                  float *scratch = nullptr, void *const *y = nullptr, bool y16 = false, bool narrow = false)
+                  float *scratch = nullptr, void *const *y = nullptr, bool y16 = false)
 {
     if (!x) return fail(SLORA_EINVAL, "x is NULL");
     if (plan->T_act == 0) return SLORA_OK;
@@ -455,10 +464,7 @@ int32_t do_shrink(slora_plan *plan, int32_t n, const int32_t *slots, const void 
     }
     DeviceScope dev(plan->pool->device);
     if (dev.status() != SLORA_OK) return dev.status();
-    Route route;
-    route.wide = plan->dual && y != nullptr && !y16 && !narrow;
-    route.fused = y != nullptr && !plan->vf_items.empty();
-    route.small = y != nullptr && plan->small && (int64_t)plan->ve_items.size() * n <= 256;
+    const Route route = plan->route(n, y != nullptr, y16);
     // the page lists of every adapter the plan names went to the device when it was built
     float *v = scratch;
     int32_t rc = SLORA_OK;
@@ -617,11 +623,9 @@ int32_t apply_multi(slora_plan *plan, int32_t n, const int32_t *slots, const voi
     rc = check_y(n, y); // validate the y side before the shrink is enqueued
     if (rc != SLORA_OK) return rc;
     float *scratch = nullptr;
-    bool narrow = false;
     if (static_scratch) {
-        auto bytes = [&](bool mfma) { return plan->v_total_floats(n, plan->pool->dtype, mfma) * (int64_t)sizeof(float); };
-        narrow = plan->dual && bytes(true) > (int64_t)SLORA_STATIC_SCRATCH_BYTES; // rows of v alone may still fit
-        const int64_t need = bytes(!narrow);
+        const bool mfma = plan->mfma_on(plan->route(n, true, y16));
+        const int64_t need = plan->v_total_floats(n, plan->pool->dtype, mfma) * (int64_t)sizeof(float);
         if (need > (int64_t)SLORA_STATIC_SCRATCH_BYTES)
             return fail(SLORA_ERANGE,
                         "this batch needs %lld bytes of scratch for %d slot(s), the static scratch holds %lld: use "
@@ -630,7 +634,7 @@ int32_t apply_multi(slora_plan *plan, int32_t n, const int32_t *slots, const voi
         scratch = static_cast<float *>(plan->pool->static_scratch);
         if (!scratch) return fail(SLORA_EHIP, "the static scratch was not resolved for this pool's device");
     }
-    rc = do_shrink(plan, n, slots, x, stream, scratch, y, y16, narrow);
+    rc = do_shrink(plan, n, slots, x, stream, scratch, y, y16);
     if (rc != SLORA_OK) return rc;
     return do_expand(plan, n, slots, y, stream, y16, true);
 }

@@ -348,8 +348,24 @@ static void failed_apply()
     REQUIRE(g_log.mfma_expand == (rc == SLORA_OK));
 }
 
+// The apply that allocates nothing takes the kernels of the one that does, also where the MFMA form is larger
+// than the static scratch (512 tokens of rank 1024 on 8 slots: 80 MiB).
+static void static_route()
+{
+    for (int32_t n : {1, 4, 8}) {
+        Bench b(1024, 8, SLORA_F16, {{1024, 512}});
+        REQUIRE(b.apply(n) == SLORA_OK);
+        const Log multi = g_log;
+        REQUIRE(b.apply_static(n) == SLORA_OK);
+        REQUIRE(g_log.mfma_shrink == multi.mfma_shrink && g_log.mfma_expand == multi.mfma_expand);
+        REQUIRE(g_log.vec_shrink == multi.vec_shrink && g_log.vec_expand == multi.vec_expand);
+        REQUIRE(multi.mfma_expand == (n < 8) && (multi.vec_expand > 0) == (n == 8));
+    }
+}
+
 static const struct { const char *name; void (*run)(); } kCases[] = {
     {"failed_apply", failed_apply},
+    {"static_route", static_route},
 };
 
 // ---------------------------------------------------------------------------------------------

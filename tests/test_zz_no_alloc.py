@@ -52,6 +52,17 @@ def test_static_scratch_matches_the_allocating_entry_point_twice_in_a_row(dtype)
         both_ways(dw, small, [2, 0])
 
 
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+def test_static_scratch_matches_where_the_mfma_form_of_a_small_batch_exceeds_it(dtype):
+    """Few tiles of a very high rank: the MFMA form (operand fragments, partial sums) of eight slots is larger than
+    the static scratch, that of one slot is not."""
+    w = synth.make_workload("wide", 1210, 1024, dtype, 8 * 2 * 1024 + 32, 8, [1024], np.zeros(512, dtype=np.int32))
+    with DeviceWorkload(w, real_adapters="all", max_rank=1024) as dw:
+        assert 8 * slora.plan_info(dw.plan())["scratch_bytes_per_slot"] > slora.STATIC_SCRATCH_BYTES
+        both_ways(dw, w, list(range(8)))
+        both_ways(dw, w, [6])
+
+
 def test_static_scratch_rejects_a_batch_beyond_its_size():
     H, T, r = 64, 2100, 1024
     w = synth.make_workload("too-big", 5, H, synth.F16, 4096, 1, [r], np.zeros(T, dtype=np.int32))
