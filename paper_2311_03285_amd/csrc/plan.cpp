@@ -409,6 +409,14 @@ Route slora_plan::route(int32_t n, bool apply, bool y16) const
     return r;
 }
 
+int64_t slora_plan::v_most_floats(int32_t n, int32_t dtype) const
+{
+    int64_t most = v_total_floats(n, dtype, !dual);
+    for (int32_t m = 1; dual && m <= n; ++m) // more slots may need less: not every call of a dual plan takes the MFMA form
+        if (route(m, true, false).wide) most = std::max(most, v_total_floats(m, dtype, true));
+    return most;
+}
+
 void slora_plan::fill_args(MultiArgs &a, int32_t n, float *v, const Route &r) const
 {
     const int64_t per_slot = v_slot_floats(pool->dtype, mfma_on(r));
@@ -469,7 +477,7 @@ int32_t do_shrink(slora_plan *plan, int32_t n, const int32_t *slots, const void 
     float *v = scratch;
     int32_t rc = SLORA_OK;
     if (!v) {
-        rc = plan->pool->grow_v(plan->set, (size_t)plan->v_total_floats(n, plan->pool->dtype, plan->mfma_on(route)));
+        rc = plan->pool->grow_v(plan->set, (size_t)plan->v_most_floats(n, plan->pool->dtype));
         v = plan->set->v;
     }
     if (rc == SLORA_OK) rc = plan->enter(stream);

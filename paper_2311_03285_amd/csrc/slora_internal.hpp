@@ -242,6 +242,8 @@ struct slora_plan {
         return (int64_t)T_act * v_stride + (mfma ? vfrag_floats(dtype) + vexp_floats() + part_floats : 0);
     }
     int64_t v_total_floats(int32_t n, int32_t dtype, bool mfma) const { return (int64_t)n * v_slot_floats(dtype, mfma); }
+    // scratch of any call with at most n slots, whatever the type of y: a plan's buffer is grown once
+    int64_t v_most_floats(int32_t n, int32_t dtype) const;
     // The kernels of a call with n slots.  A dual plan's MFMA form is taken only where it fits the static scratch,
     // so that an apply gives the same bits wherever v is kept.
     slora::Route route(int32_t n, bool apply, bool y16) const;

@@ -104,10 +104,15 @@ int32_t launch_gather(slora_pool *pool, int64_t entry, int32_t rank, void *out, 
     return SLORA_OK;
 }
 
+static int64_t g_seen; // consecutive items of an adapter: its list is checked once per launch
+
 // every page number an item can reach through the device image of the arena
 static void check_pages(const slora_plan *plan, int32_t arena_off, int32_t rank, int32_t slot)
 {
     const slora_pool *pool = plan->pool;
+    const int64_t key = (int64_t)arena_off * 64 + slot;
+    if (key == g_seen) return;
+    g_seen = key;
     REQUIRE(arena_off >= 0 && rank > 0);
     const int64_t first = arena_off + (int64_t)slot * 2 * rank;
     REQUIRE(first + 2 * rank <= pool->d_arena_cap);
@@ -155,6 +160,7 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &a, void *, c
     REQUIRE(a.n == n && plan->v_stride % kRankPad == 0);
     REQUIRE(0 <= plan->n_vs_plain && plan->n_vs_plain <= plan->n_vs_head && (size_t)plan->n_vs_head <= plan->vs_items.size());
     const size_t n_vs = plan->n_vs(route);
+    g_seen = -1;
     check_scratch(plan, n, a, route);
     g_log.vec_shrink = n_vs;
     g_log.mfma_shrink = plan->mfma_on(route) && !plan->ms_items.empty();
@@ -211,6 +217,7 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &a, void *, b
     REQUIRE(a.n == n);
     REQUIRE(0 <= plan->n_ve_plain && plan->n_ve_plain <= plan->n_ve_head && (size_t)plan->n_ve_head <= plan->ve_items.size());
     const size_t n_ve = plan->n_ve(route);
+    g_seen = -1;
     check_scratch(plan, n, a, route);
     g_log.vec_expand = n_ve;
     g_log.mfma_expand = plan->mfma_on(route) && !plan->me_items.empty();
@@ -225,7 +232,7 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &a, void *, b
             REQUIRE(it.ntok <= kExpandTok && it.a >= 0 && it.b > 0 && it.a % 8 == 0 && it.a + it.b <= pool->H);
             REQUIRE(it.b <= plan->expand_threads * 8 || plan->expand_split);
             for (int32_t t = 0; t < it.ntok; ++t)
-                for (int32_t j = 0; j < it.rank; ++j) g_sink = a.v[k][(int64_t)(it.pos0 + t) * plan->v_stride + j];
+                for (int32_t j = 0; j < it.rank; j += 16) g_sink = a.v[k][(int64_t)(it.pos0 + t) * plan->v_stride + j];
         }
         for (size_t i = 0; plan->mfma_on(route) && i < plan->me_items.size(); ++i) {
             const Item &it = plan->d_me[i];
@@ -256,6 +263,7 @@ int32_t launch_fused(slora_plan *plan, int32_t n, const MultiArgs &a, void *, bo
         return SLORA_OK;
     }
     g_log.fused = true;
+    g_seen = -1;
     // every fused group is a whole group of at most kExpandTok tokens, and the tails of the two
     // vector lists are exactly these groups' two-stage items
     std::set<int32_t> fused_pos;
@@ -363,9 +371,25 @@ static void static_route()
     }
 }
 
+// Once a plan has been applied (or shrunk) with n slots, whatever the type of y, further calls with at most n
+// slots allocate nothing.
+static void scratch_is_sized_once()
+{
+    for (int32_t H : {1024, 4096})
+        for (int first = 0; first < 3; ++first) {
+            Bench b(H, 8, SLORA_F16, {{H == 1024 ? 1024 : 64, 512}}); // H = 1024: 8 slots are too large for the MFMA form
+            REQUIRE((first == 0 ? b.apply(8) : first == 1 ? b.apply16(8) : b.shrink(8)) == SLORA_OK);
+            const long before = g_device_mallocs;
+            for (int32_t n : {7, 1})
+                REQUIRE(b.apply(n) == SLORA_OK && b.apply16(n) == SLORA_OK && b.shrink(n) == SLORA_OK && b.expand(n) == SLORA_OK);
+            REQUIRE(g_device_mallocs == before);
+        }
+}
+
 static const struct { const char *name; void (*run)(); } kCases[] = {
     {"failed_apply", failed_apply},
     {"static_route", static_route},
+    {"scratch_is_sized_once", scratch_is_sized_once},
 };
 
 // ---------------------------------------------------------------------------------------------

@@ -7,9 +7,10 @@ compared bit for bit; 16-bit y as elsewhere: the correctly rounded oracle result
 """
 import numpy as np
 import pytest
+import torch
 
 from paper_2311_03285_amd import slora, synth
-from paper_2311_03285_amd.harness import DeviceWorkload
+from paper_2311_03285_amd.harness import DeviceWorkload, bits_to_device
 from gpu_util import assert_close, gpu_slot, oracle_slot
 from test_gpu_mfma import MFMA_ALL, route
 from test_gpu_y16 import assert_y16_close, gpu_y16, oracle_y16
@@ -102,3 +103,37 @@ def test_one_launch_groups_beside_mfma_groups_are_added_once(dtype):
         slora.lora_apply_multi(plan, [0, 1], [t.data_ptr() for t in xs], [t.data_ptr() for t in ys])
         for s in (0, 1):
             assert np.array_equal(ys[s].cpu().numpy().astype(np.float64), oracle_slot(w, s))
+
+
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+def test_fp32_apply_captured_after_a_16_bit_apply(dtype):
+    """The plan's first apply sizes the scratch of both kernel families: the other one may follow under capture."""
+    ids = np.repeat([0, 1], [190, 40]).astype(np.int32)
+    w = synth.make_workload("capture", 695, 4096, dtype, 2 * 2 * (128 + 65) + 16, 2, [128, 65], ids)
+    with DeviceWorkload(w, real_adapters="all") as dw:
+        plan = dw.plan()
+        x = [dw.x_dev(s) for s in (0, 1)]
+        y16 = [bits_to_device(w.y16_bits(s), dw.device) for s in (0, 1)]
+        y0 = [dw.y_dev(s) for s in (0, 1)]
+        y = [t.clone() for t in y0]
+        xp, yp = [t.data_ptr() for t in x], [t.data_ptr() for t in y]
+        st = torch.cuda.Stream()
+        torch.cuda.synchronize()
+        slora.lora_apply_multi_y16(plan, [0, 1], xp, [t.data_ptr() for t in y16], st)
+        torch.cuda.synchronize()
+        before = slora.pool_stats(dw.pool)
+        g = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(g, stream=st):
+            slora.lora_apply_multi(plan, [0, 1], xp, yp, torch.cuda.current_stream())
+        assert slora.pool_stats(dw.pool) == before
+        for rep in range(3):
+            for k in (0, 1):
+                y[k].copy_(y0[k])
+            torch.cuda.synchronize()
+            g.replay()
+            torch.cuda.synchronize()
+            got = [t.cpu().numpy() for t in y]
+            for k in (0, 1):
+                assert np.array_equal(got[k], gpu_slot(dw, k)), (rep, k)
+                rel, _ = assert_close(got[k], oracle_slot(w, k), f"replay {rep}, slot {k}")
+                assert rel <= 5e-6, rel
