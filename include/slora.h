@@ -330,6 +330,8 @@ int32_t slora_lora_shrink_expand(slora_pool *pool, int32_t slot, const void *x,
  *                      fill the GPU and they average 1 MiB of pages or more, 0 never, 2 always.  Applies only (the two-stage calls
  *                      slora_lora_shrink / slora_lora_expand always use the two kernels, and an
  *                      expand on its own needs a slora_lora_shrink before it, not an apply).
+ *                      With 1, calls on very small decode batches (a page or two of A per wavefront)
+ *                      run in one launch too, a workgroup per 512 columns; 0 rules that out as well.
  *   "shrink_pages"     pages of A per work item of the decode shrink (default 4)
  *   "upload_groups"    workgroups of slora_adapter_upload when the source is host memory (default
  *                      32: enough requests in flight to fill the host link; many more delay the

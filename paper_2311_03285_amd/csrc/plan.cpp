@@ -335,7 +335,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
             plan->max_expand_tok = std::max(plan->max_expand_tok, i.ntok);
             few_pages = few_pages && i.rank <= kSmallRanks && (int64_t)i.rank * H * i.ntok <= 128 * 1024;
         }
-        plan->small = plan->expand_split && plan->ms_items.empty() && plan->vf_items.empty() && few_pages && H <= 4096;
+        plan->small = pool->fuse_decode != 0 && plan->expand_split && plan->ms_items.empty() && plan->vf_items.empty() && few_pages && H <= 4096;
         plan->v_stride = std::max(kRankPad, (max_rank + kRankPad - 1) / kRankPad * kRankPad);
         plan->n_rank_blocks = (plan->v_stride + kMsRanks - 1) / kMsRanks;
     } catch (const std::bad_alloc &) {

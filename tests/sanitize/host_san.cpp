@@ -386,10 +386,22 @@ static void scratch_is_sized_once()
         }
 }
 
+// "fuse_decode" 0: never one launch for both stages.
+static void fuse_decode_never()
+{
+    for (int64_t mode : {0, 1, 2}) {
+        Bench b(4096, 2, SLORA_BF16, {{8, 1}, {16, 2}}, {{"fuse_decode", mode}});
+        REQUIRE(b.apply(2) == SLORA_OK);
+        REQUIRE(g_log.small == (mode == 1) && g_log.fused == (mode == 2));
+        REQUIRE((g_log.vec_expand > 0) == (mode == 0));
+    }
+}
+
 static const struct { const char *name; void (*run)(); } kCases[] = {
     {"failed_apply", failed_apply},
     {"static_route", static_route},
     {"scratch_is_sized_once", scratch_is_sized_once},
+    {"fuse_decode_never", fuse_decode_never},
 };
 
 // ---------------------------------------------------------------------------------------------

@@ -22,6 +22,6 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("case", ["failed_apply", "static_route", "scratch_is_sized_once"])
+@pytest.mark.parametrize("case", ["failed_apply", "static_route", "scratch_is_sized_once", "fuse_decode_never"])
 def test_case(exe, case):
     assert f"host_san OK: {case}" in run(exe, case)
