@@ -243,7 +243,8 @@ int32_t slora_lora_apply(slora_plan *plan, int32_t slot, const void *x, float *y
 /*
  * The same for n slots (1 <= n <= SLORA_MAX_MULTI) in one pair of launches, e.g. the q, k, v
  * projections of a layer.  slots, x, y: HOST arrays of n entries; x[k] / y[k] are DEVICE
- * pointers as in slora_lora_apply (entries of x may be equal; entries of y must not overlap).
+ * pointers as in slora_lora_apply (entries of x may be equal; entries of y must not overlap; a
+ * y[k] in 16 bits may be the buffer of x[k], updated in place, if no other entry of x names it).
  */
 #define SLORA_MAX_MULTI 8
 int32_t slora_lora_apply_multi(slora_plan *plan, int32_t n, const int32_t *slots,

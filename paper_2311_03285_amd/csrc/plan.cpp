@@ -454,6 +454,18 @@ int32_t check_plan(slora_plan *plan, int32_t n, const int32_t *slots)
     return SLORA_OK;
 }
 
+// whether a y of the call shares memory with an x
+bool y_overlaps_x(const slora_plan *plan, int32_t n, const void *const *x, void *const *y, bool y16)
+{
+    const uintptr_t x_bytes = (uintptr_t)plan->T * (uintptr_t)plan->pool->H * 2, y_bytes = y16 ? x_bytes : 2 * x_bytes;
+    for (int32_t k = 0; k < n; ++k)
+        for (int32_t m = 0; m < n; ++m) {
+            const uintptr_t xa = reinterpret_cast<uintptr_t>(x[k]), ya = reinterpret_cast<uintptr_t>(y[m]);
+            if (xa < ya + y_bytes && ya < xa + x_bytes) return true;
+        }
+    return false;
+}
+
 // scratch: where v goes; NULL = the plan's own buffer (grown on demand)
 // y != NULL: part of an apply - decode groups the plan marked for it run both stages in one
 // launch here, and the two-stage launches (here and in do_expand) cover the other groups only.
@@ -472,7 +484,10 @@ int32_t do_shrink(slora_plan *plan, int32_t n, const int32_t *slots, const void 
     }
     DeviceScope dev(plan->pool->device);
     if (dev.status() != SLORA_OK) return dev.status();
-    const Route route = plan->route(n, y != nullptr, y16);
+    Route route = plan->route(n, y != nullptr, y16);
+    // the two kernels have read all of x before y is written; in the one-launch kernel for small batches the
+    // workgroups of other columns still read it
+    if (route.small && y_overlaps_x(plan, n, x, y, y16)) route.small = false;
     // the page lists of every adapter the plan names went to the device when it was built
     float *v = scratch;
     int32_t rc = SLORA_OK;

@@ -397,11 +397,31 @@ static void fuse_decode_never()
     }
 }
 
+// A workgroup of the one-launch kernel for small batches writes y while others still read x: calls in which a
+// y overlaps an x take the two kernels.
+static void y_in_the_buffer_of_x()
+{
+    Bench b(4096, 2, SLORA_BF16, {{8, 1}, {16, 2}});
+    const size_t row = (size_t)b.H * 2; // bytes of a row of x, and of a 16-bit y
+    std::vector<unsigned char> room(12 * row);
+    b.xs = {room.data() + 3 * row, b.xs[1]};
+    const auto one_launch = [&](int64_t y_off, bool y16) { // y of slot 1 at this offset from x of slot 0
+        b.ys[1] = (float *)(room.data() + 3 * row + y_off);
+        REQUIRE((y16 ? b.apply16(2) : b.apply(2)) == SLORA_OK);
+        REQUIRE(g_log.small == (g_log.vec_expand == 0));
+        return g_log.small;
+    };
+    REQUIRE(!one_launch(0, true) && !one_launch((int64_t)(2 * row), true) && !one_launch(-(int64_t)(2 * row), true));
+    REQUIRE(one_launch((int64_t)(3 * row), true) && one_launch(-(int64_t)(3 * row), true));
+    REQUIRE(!one_launch(-(int64_t)(3 * row), false) && one_launch((int64_t)(3 * row), false)); // fp32: rows twice as long
+}
+
 static const struct { const char *name; void (*run)(); } kCases[] = {
     {"failed_apply", failed_apply},
     {"static_route", static_route},
     {"scratch_is_sized_once", scratch_is_sized_once},
     {"fuse_decode_never", fuse_decode_never},
+    {"y_in_the_buffer_of_x", y_in_the_buffer_of_x},
 };
 
 // ---------------------------------------------------------------------------------------------

@@ -44,3 +44,19 @@ def test_one_launch_is_bit_identical_to_two(dtype, H, ranks):
         torch.cuda.synchronize()
         for g, t in zip(got, ys):
             assert np.array_equal(g, t.cpu().numpy().view(np.uint16).reshape(g.shape))
+
+
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+def test_y_in_the_buffer_of_x(dtype):
+    """x += (x A) B in place, on a batch small enough for one launch, against the call with an x of its own."""
+    ids = np.array([0, 1, 1, 2], np.int32)
+    w = synth.make_workload("in-place", 790, 4096, dtype, 2 * 2 * 40 + 8, 2, [16, 8, 16], ids)
+    with DeviceWorkload(w, real_adapters="all") as dw:
+        plan = dw.plan()
+        xs = [dw.x_dev(s) for s in (0, 1)]
+        apart, place = [x.clone() for x in xs], [x.clone() for x in xs]
+        slora.lora_apply_multi_y16(plan, [0, 1], [t.data_ptr() for t in xs], [t.data_ptr() for t in apart])
+        slora.lora_apply_multi_y16(plan, [0, 1], [t.data_ptr() for t in place], [t.data_ptr() for t in place])
+        torch.cuda.synchronize()
+        for x, a, p in zip(xs, apart, place):
+            assert torch.equal(a, p) and not torch.equal(a, x)

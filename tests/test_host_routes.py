@@ -22,6 +22,7 @@ def exe(tmp_path_factory):
     return out
 
 
-@pytest.mark.parametrize("case", ["failed_apply", "static_route", "scratch_is_sized_once", "fuse_decode_never"])
+@pytest.mark.parametrize("case", ["failed_apply", "static_route", "scratch_is_sized_once", "fuse_decode_never",
+                                  "y_in_the_buffer_of_x"])
 def test_case(exe, case):
     assert f"host_san OK: {case}" in run(exe, case)
