@@ -31,7 +31,9 @@
  *     ranks) lies in [2^-42, 2^35) are carried to 22 bits relative to that largest value, like
  *     the fp32 sums they come from; smaller rows keep an absolute error of 2^-64; from 2^40 on
  *     the pieces overflow and y becomes inf/NaN where the vector kernels and a plain fp32
- *     evaluation would still be finite.
+ *     evaluation would still be finite.  Batches of few tiles whose applies to fp32 y run there
+ *     all the same ("mfma_min_tiles" below) carry three pieces: the 24 bits of every value down to
+ *     2^-39 of its row's largest, over the whole range of finite sums.
  *   - Page j of an adapter's A list holds column j of A (an H-vector), page j of its B list
  *     holds row j of B.  All projections map H -> H.
  *   - The pool memory is borrowed from the caller and never allocated, freed or cleared here.

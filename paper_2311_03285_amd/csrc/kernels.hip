@@ -669,35 +669,52 @@ __device__ __forceinline__ int mfma_row(int v, int lane) { return 8 * (v >> 2) +
 
 // v = x*A of the MFMA path is handed from shrink to expand already in the layout of the expand's
 // first MFMA operand, split into 16-bit pieces whose sum is the fp32 value (so nothing is lost to
-// the operand format): hi + lo for binary16 (22+ bits), hi + mid + lo by truncation for bfloat16
-// (exactly 24 bits).  One fragment = 64 lanes x 8 values (1 KiB) = the operand of one MFMA:
+// the operand format): hi + lo for binary16 (22+ bits; or three pieces, below), hi + mid + lo by truncation
+// for bfloat16 (exactly 24 bits).  One fragment = 64 lanes x 8 values (1 KiB) = the operand of one MFMA:
 // tokens 0..31 of the tile x ranks 16*kk .. 16*kk+15, lane = token + 32 * ((rank % 16) / 8).
 // Fragments are ordered [tile][kk][piece]; the expand reads each with one coalesced 16-byte load
 // per lane and does no conversion work.
+//
+// Three pieces for binary16 (NP = 3) are for calls that would else keep v in fp32 rows: the second and third
+// are stored 2^12 and 2^24 times as large, so that neither meets the end of the format's range, and the expand
+// scales its sums back from piece to piece.  They hold all 24 bits of values down to 2^-39 of the row's largest;
+// two pieces hold 22 bits, of values near the largest.  512 tokens of rank 64, H = 4096, 4 slots: error against
+// 64 bits 1.1e-7 -> 1.0e-7, 31.1 -> 32.1 us per call; rows whose ranks differ by 2^22, 1.5e-5 -> 1.6e-7.
 template <int DT>
 struct VPieces {
     static constexpr int N = DT == SLORA_F16 ? 2 : 3;
 };
+template <int DT, int NP>
+constexpr bool kScaledPieces = DT == SLORA_F16 && NP == 3;
+constexpr float kPieceUp = 4096.f, kPieceDown = 1.f / 4096.f;
 __device__ __forceinline__ int64_t vfrag_index(int tile, int kk, int piece, int n_kk, int n_piece)
 {
     return (((int64_t)tile * n_kk + kk) * n_piece + piece) * (kWave * 8);
 }
-// eight consecutive ranks of one token -> the 16-bit pieces whose sum is the fp32 value, packed as
-// the 16 bytes a lane owns in each piece's fragment
-template <int DT>
-__device__ __forceinline__ void split_pieces(const float (&f)[8], u32x4 (&piece)[VPieces<DT>::N])
+// Eight consecutive ranks of one token -> the 16-bit pieces whose sum is the fp32 value, packed as
+// the 16 bytes a lane owns in each piece's fragment.  An infinite or NaN value is all in the first piece (the
+// differences that make the others would be NaN).
+template <int DT, int NP>
+__device__ __forceinline__ void split_pieces(const float (&f)[8], u32x4 (&piece)[NP])
 {
-    uint16_t h[VPieces<DT>::N][8];
+    uint16_t h[NP][8];
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
+        const bool finite = fabsf(f[e]) < __builtin_inff();
         if constexpr (DT == SLORA_F16) {
             const _Float16 a = (_Float16)f[e];
-            const _Float16 b = (_Float16)(f[e] - (float)a);
+            float r = finite ? f[e] - (float)a : 0.f;
             h[0][e] = __builtin_bit_cast(uint16_t, a);
-            h[1][e] = __builtin_bit_cast(uint16_t, b);
+#pragma unroll
+            for (int p = 1; p < NP; ++p) {
+                if constexpr (kScaledPieces<DT, NP>) r *= kPieceUp;
+                const _Float16 c = (_Float16)r;
+                h[p][e] = __builtin_bit_cast(uint16_t, c);
+                r -= (float)c;
+            }
         } else {
-            const uint32_t hi = __float_as_uint(f[e]) & 0xffff0000u;
-            const float r1 = f[e] - __uint_as_float(hi);
+            const uint32_t hi = (__float_as_uint(f[e]) & 0xffff0000u) | (f[e] != f[e] ? 0x00400000u : 0u); // a NaN stays one
+            const float r1 = finite ? f[e] - __uint_as_float(hi) : 0.f;
             const uint32_t mid = __float_as_uint(r1) & 0xffff0000u;
             const float r2 = r1 - __uint_as_float(mid);
             h[0][e] = (uint16_t)(hi >> 16);
@@ -706,7 +723,7 @@ __device__ __forceinline__ void split_pieces(const float (&f)[8], u32x4 (&piece)
         }
     }
 #pragma unroll
-    for (int p = 0; p < VPieces<DT>::N; ++p)
+    for (int p = 0; p < NP; ++p)
 #pragma unroll
         for (int k = 0; k < 4; ++k) piece[p][k] = (uint32_t)h[p][2 * k] | ((uint32_t)h[p][2 * k + 1] << 16);
 }
@@ -750,7 +767,8 @@ __device__ __forceinline__ void split_pieces(const float (&f)[8], u32x4 (&piece)
 // pools every token row is first scaled by a power of two, 2^e, that puts its largest |v| into
 // [2^10, 2^11): the hi piece then holds 11 bits and the lo piece 11 more whatever the magnitude
 // of v (row maxima in [2^-42, 2^35); the pieces overflow from 2^40 on).  e (clamped to [-24, 40]) is left
-// beside the fragments; the expand scales its accumulators back.
+// beside the fragments; the expand scales its accumulators back.  The tiles of a dual plan, whose v would
+// otherwise be fp32 rows, always pass through the join kernel, which gives binary16 three pieces (see RowScale).
 // Token rows beyond the item and ranks beyond the adapter's are read from a valid row instead;
 // their results are not stored, or stored as zero (ranks up to the next multiple of 32, so the
 // expand can read whole blocks).
@@ -760,7 +778,12 @@ constexpr int kPiece = 64;                           // elements of H per piece
 constexpr int kPieceBytes = kPiece * 2;              // bytes of a row per piece
 constexpr int kPieceBlock = kMsBlockBytes;           // bytes of 32 rows of a piece in LDS
 static_assert(kMsBlockBytes == 32 * kPieceBytes, "the ring is laid out in pieces");
-constexpr int kExpMin = -24, kExpMax = 40;           // range of the row exponents of binary16 pools
+// Row exponents of binary16 pools: where they put a row's largest |v|, and their range.  With three pieces the
+// range covers every finite sum of products of binary16 values (|v| < 2^47, multiples of 2^-48).
+template <int NP>
+struct RowScale {
+    static constexpr int kTop = NP == 3 ? 14 : 10, kMin = NP == 3 ? -34 : -24, kMax = 40;
+};
 static_assert(kMsGranule % kPiece == 0 && kMsTok == 128 && kMsRanks == 128, "pieces and tiles are tied");
 
 __device__ __forceinline__ float pow2f(int e) { return __uint_as_float((uint32_t)(e + 127) << 23); }
@@ -856,16 +879,18 @@ __device__ __forceinline__ uint32_t lds_address(const unsigned char *p)
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char *)p;
 }
 
-// Exponent e of the power of two that scales a token row of a binary16 pool: the row's largest
-// |v| lands in [2^10, 2^11).  Zero, subnormal, infinite and NaN maxima get e = 0.
+// Exponent e of the power of two that scales a token row of a binary16 pool: the row's largest finite
+// |v| lands in [2^kTop, 2^(kTop + 1)).  Zero and subnormal maxima get e = 0.
+template <int NP>
 __device__ __forceinline__ int row_exponent(float vmax)
 {
+    typedef RowScale<NP> S;
     const int be = (int)((__float_as_uint(vmax) >> 23) & 0xffu); // biased exponent of the row maximum
-    if (be == 0 || be == 255) return 0;
-    return min(max(10 - (be - 127), kExpMin), kExpMax);
+    if (be == 0) return 0;
+    return min(max(S::kTop - (be - 127), S::kMin), S::kMax);
 }
 
-// Ranks beyond the adapter's become zero; returns the largest |value| of the eight.
+// Ranks beyond the adapter's become zero; returns the largest finite |value| of the eight.
 __device__ __forceinline__ float mask_octet(const MsItem &it, int oct, float (&val)[8])
 {
     float vmax = 0.f;
@@ -873,18 +898,17 @@ __device__ __forceinline__ float mask_octet(const MsItem &it, int oct, float (&v
     for (int e = 0; e < 8; ++e) {
         const float f = oct * 8 + e < it.nj ? val[e] : 0.f;
         val[e] = f;
-        vmax = fmaxf(vmax, fabsf(f));
+        vmax = fabsf(f) < __builtin_inff() ? fmaxf(vmax, fabsf(f)) : vmax;
     }
     return vmax;
 }
 
 // Ranks 8 * oct .. + 7 of the item, finished, of token row `row` of v tile `tile` -> the 16 bytes
 // they fill in each piece's operand fragment, scaled by `sc` first.
-template <int DT>
+template <int DT, int NP>
 __device__ __forceinline__ void store_octet(const MsItem &it, int tile, int row, int oct, const float (&val)[8],
                                             float sc, int v_stride, uint16_t *__restrict__ vfrag)
 {
-    constexpr int NP = VPieces<DT>::N;
     const int n_kk = v_stride >> 4;
     const int kk = (it.j0 >> 4) + (oct >> 1);
     if (kk >= n_kk) return;
@@ -893,7 +917,7 @@ __device__ __forceinline__ void store_octet(const MsItem &it, int tile, int row,
     for (int k = 0; k < 8; ++k) f[k] = DT == SLORA_F16 ? val[k] * sc : val[k];
     uint16_t *dst = vfrag + vfrag_index(tile, kk, 0, n_kk, NP) + (row + 32 * (oct & 1)) * 8;
     u32x4 piece[NP];
-    split_pieces<DT>(f, piece);
+    split_pieces<DT, NP>(f, piece);
 #pragma unroll
     for (int p = 0; p < NP; ++p) *reinterpret_cast<u32x4 *>(dst + p * (kWave * 8)) = piece[p];
 }
@@ -1083,7 +1107,7 @@ __device__ __forceinline__ void shrink_mfma_tile(const MsItem &it, unsigned item
         }
     }
     // ---- a share of a split tile: leave the partial sums for join_shares_kernel -------------------
-    if (it.n_parts > 1) {
+    if (it.sync >= 0) {
         if (trow < ((it.ntok + 31) & ~31)) {
 #pragma unroll
             for (int i = 0; i < NI; ++i) {
@@ -1106,14 +1130,14 @@ __device__ __forceinline__ void shrink_mfma_tile(const MsItem &it, unsigned item
     if constexpr (DT == SLORA_F16) {
 #pragma unroll
         for (int m = R; m < kWave; m <<= 1) vmax = fmaxf(vmax, __shfl_xor(vmax, m, kWave)); // the token's other ranks
-        const int e = row_exponent(vmax);
+        const int e = row_exponent<VPieces<DT>::N>(vmax);
         sc = pow2f(e);
         if (o0 == 0 && trow < ((it.ntok + 31) & ~31)) *vexp_row(vexp, it, tile, v_stride, r) = (int8_t)(token_ok ? e : 0);
     }
     if (!token_ok) return;
 #pragma unroll
     for (int i = 0; i < NI; ++i)
-        if (o0 + OL * i < nb_act * 4) store_octet<DT>(it, tile, r, o0 + OL * i, val[i], sc, v_stride, vfrag);
+        if (o0 + OL * i < nb_act * 4) store_octet<DT, VPieces<DT>::N>(it, tile, r, o0 + OL * i, val[i], sc, v_stride, vfrag);
 }
 
 template <int DT>
@@ -1156,7 +1180,7 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void shrink_mfma_kernel(const MsIt
 // block nb in the order of their numbers (a fixed order: the same bits on every run; the loads of
 // four shares are in flight at a time) and finishes the block as the shrink itself does for a
 // tile that was not split.  Binary16: the row maximum over the rank blocks meets in LDS.
-template <int DT>
+template <int DT, int NP>
 __global__ __launch_bounds__(kMfmaThreads) void join_shares_kernel(const MsItem *__restrict__ tiles, int v_stride,
                                                                     MultiArgs args)
 {
@@ -1214,7 +1238,7 @@ __global__ __launch_bounds__(kMfmaThreads) void join_shares_kernel(const MsItem 
         __syncthreads();
 #pragma unroll
         for (int k = 0; k < kMsRanks / 32; ++k) vmax = fmaxf(vmax, smax[k][row]);
-        const int e = row_exponent(vmax);
+        const int e = row_exponent<NP>(vmax);
         sc = pow2f(e);
         if (nb == 0 && q == 0)
             *vexp_row(reinterpret_cast<int8_t *>(args.v[cs] + args.vexp_off), it, it.tile + tb, v_stride, row) = (int8_t)(token_ok ? e : 0);
@@ -1222,7 +1246,7 @@ __global__ __launch_bounds__(kMfmaThreads) void join_shares_kernel(const MsItem 
     if (live && token_ok) {
         uint16_t *vfrag = reinterpret_cast<uint16_t *>(args.v[cs] + args.vfrag_off);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) store_octet<DT>(it, it.tile + tb, row, nb * 4 + q + 2 * i, val[i], sc, v_stride, vfrag);
+        for (int i = 0; i < 2; ++i) store_octet<DT, NP>(it, it.tile + tb, row, nb * 4 + q + 2 * i, val[i], sc, v_stride, vfrag);
     }
 }
 
@@ -1278,10 +1302,11 @@ __device__ __forceinline__ void wave_lds_fence() // LDS written by one lane is r
 
 // One wavefront's view of a run: its columns, the rows of y it moves, and the ways of B and of the
 // finished deltas through its LDS.
-template <int DT, bool Y16>
+template <int DT, bool Y16, int NP>
 struct ExpandWave {
     typedef int32_t i32x4 __attribute__((ext_vector_type(4)));
-    static constexpr int NP = VPieces<DT>::N;
+    static constexpr bool kScaled = kScaledPieces<DT, NP>;
+    static constexpr bool kFromZero = !Y16 || kScaled;   // y is added to the finished sum of products
     static constexpr int kElem = Y16 ? 2 : 4;
     static constexpr int kYVec = 16 / kElem;             // elements per 16-byte access
     static constexpr int kYLanes = 64 / kYVec;           // lanes per tile row
@@ -1359,29 +1384,36 @@ struct ExpandWave {
             for (int nb = 0; nb < 2; ++nb)
                 op[s][nb] = *reinterpret_cast<const u32x4 *>(slab + slab_col(nb * 32 + n) + 8 * s + 4 * q);
     }
-    __device__ __forceinline__ void multiply(const u32x4 &piece, const u32x4 (&op)[2])
+    static __device__ __forceinline__ void multiply(f32x16 (&sum)[2], const u32x4 &piece, const u32x4 (&op)[2])
     {
 #pragma unroll
-        for (int nb = 0; nb < 2; ++nb) acc[nb] = mfma32<DT>(piece, op[nb], acc[nb]);
+        for (int nb = 0; nb < 2; ++nb) sum[nb] = mfma32<DT>(piece, op[nb], sum[nb]);
     }
     // Binary16 pools: the shrink scaled token row i of a block of kMsRanks ranks by 2^e[i].  The accumulators
     // follow: they hold (16-bit y + products so far) * 2^e of the CURRENT block - scaled up before the first
     // block, re-scaled where the block changes, scaled back at the end.  Powers of two: every step is exact.
-    __device__ __forceinline__ void scale_rows(const i32x4 &from, const i32x4 &to)
+    static __device__ __forceinline__ void scale_rows(f32x16 (&sum)[2], const i32x4 &from, const i32x4 &to)
     {
 #pragma unroll
         for (int g = 0; g < 4; ++g)
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const float f = pow2f((int)(int8_t)(to[g] >> (8 * k)) - (int)(int8_t)(from[g] >> (8 * k)));
-                acc[0][4 * g + k] *= f;
-                acc[1][4 * g + k] *= f;
+                sum[0][4 * g + k] *= f;
+                sum[1][4 * g + k] *= f;
             }
+    }
+    __device__ __forceinline__ void times(float f) // of all sums
+    {
+#pragma unroll
+        for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[nb][v] *= f;
     }
     // Accumulators at the start of a tile: y itself if it is 16-bit (widened, through LDS), zero if fp32.
     __device__ __forceinline__ void begin(const u32x4 (&w)[kYLoads], [[maybe_unused]] const i32x4 &scale)
     {
-        if constexpr (!Y16) {
+        if constexpr (kFromZero) {
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb)
 #pragma unroll
@@ -1407,7 +1439,7 @@ struct ExpandWave {
 #pragma unroll
                     for (int nb = 0; nb < 2; ++nb) acc[nb][8 * h + v] = half[mfma_row(v, lane) * kTileStride + nb * 32 + n];
             }
-            if constexpr (DT == SLORA_F16) scale_rows(i32x4{0, 0, 0, 0}, scale);
+            if constexpr (DT == SLORA_F16) scale_rows(acc, i32x4{0, 0, 0, 0}, scale);
         }
     }
     // Accumulators -> row pieces of the finished y tile: rounded once if y is 16-bit, added to y if fp32
@@ -1416,7 +1448,7 @@ struct ExpandWave {
     // as they always were, so that they stay the same bit for bit.
     __device__ __forceinline__ void end(u32x4 (&w)[kYLoads], [[maybe_unused]] const i32x4 &scale)
     {
-        if constexpr (DT == SLORA_F16) scale_rows(scale, i32x4{0, 0, 0, 0});
+        if constexpr (DT == SLORA_F16) scale_rows(acc, scale, i32x4{0, 0, 0, 0});
         float *half = reinterpret_cast<float *>(slab);
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
@@ -1430,11 +1462,18 @@ struct ExpandWave {
             for (int i = 0; i < kYLoads / 2; ++i) {
                 const float *src = half + (yrow + kYRows * i) * kTileStride + kYVec * ygrp;
                 u32x4 &o = w[h * (kYLoads / 2) + i];
-                const f32x4 a = *reinterpret_cast<const f32x4 *>(src);
                 if constexpr (Y16) {
-                    const f32x4 b = *reinterpret_cast<const f32x4 *>(src + 4);
+                    f32x4 a = *reinterpret_cast<const f32x4 *>(src), b = *reinterpret_cast<const f32x4 *>(src + 4);
+                    if constexpr (kFromZero) {
+                        float f[8];
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) widen2<DT>(o[e], f[2 * e], f[2 * e + 1]);
+                        a += f32x4{f[0], f[1], f[2], f[3]};
+                        b += f32x4{f[4], f[5], f[6], f[7]};
+                    }
                     o = u32x4{narrow2<DT>(a.x, a.y), narrow2<DT>(a.z, a.w), narrow2<DT>(b.x, b.y), narrow2<DT>(b.z, b.w)};
                 } else {
+                    const f32x4 a = *reinterpret_cast<const f32x4 *>(src);
 #pragma unroll
                     for (int e = 0; e < 4; ++e) o[e] = __float_as_uint(__uint_as_float(o[e]) + a[e]);
                 }
@@ -1454,16 +1493,16 @@ struct ExpandWave {
     }
 };
 
-template <int DT, bool Y16, int RegStages>
+template <int DT, bool Y16, int NP, int RegStages>
 __device__ __forceinline__ void expand_mfma_run(const Item &it, int wave, const int32_t *__restrict__ pbl,
                                                 const uint16_t *__restrict__ pool,
                                                 const int32_t *__restrict__ tok_idx, int H, int v_stride,
                                                 const uint16_t *__restrict__ vfrag, const int8_t *__restrict__ vexp,
                                                 void *__restrict__ y, unsigned char *lds)
 {
-    typedef ExpandWave<DT, Y16> W;
+    typedef ExpandWave<DT, Y16, NP> W;
     typedef typename W::i32x4 i32x4;
-    constexpr int NP = W::NP, kYLoads = W::kYLoads;
+    constexpr int kYLoads = W::kYLoads;
     constexpr int kFrags = 2 * RegStages * NP;    // operand fragments (1 KiB) of V per tile
     const int n_kk = v_stride >> 4, n_rb = (v_stride + kMsRanks - 1) / kMsRanks;
     const int lane = threadIdx.x & (kWave - 1);
@@ -1532,11 +1571,17 @@ __device__ __forceinline__ void expand_mfma_run(const Item &it, int wave, const 
                 for (int f = 0; f < 2 * N; ++f) at[f] = buf_at + ((2 * s + f / N) * NP + P0 + f % N) * 1024;
                 lds_read(at, piece);
 #pragma unroll
-                for (int f = 0; f < 2 * N; ++f) w.multiply(piece[f], bop[s][f / N]);
+                for (int f = 0; f < 2 * N; ++f) W::multiply(w.acc, piece[f], bop[s][f / N]);
             }
         };
-        if constexpr (Y16) {
+        if constexpr (!W::kFromZero) {
             products(std::integral_constant<int, 0>{}, std::integral_constant<int, NP>{});
+        } else if constexpr (W::kScaled) {
+            products(std::integral_constant<int, 2>{}, std::integral_constant<int, 3>{});
+            w.times(kPieceDown);
+            products(std::integral_constant<int, 1>{}, std::integral_constant<int, 2>{});
+            w.times(kPieceDown);
+            products(std::integral_constant<int, 0>{}, std::integral_constant<int, 1>{});
         } else {
             // from zero: first the small pieces of all ranks, then the leading ones, so that only the latter's
             // additions round at the size of the sum (512 tokens of rank 64, H = 4096, error against 64 bits: 1.24e-7 -> 1.17e-7
@@ -1564,16 +1609,16 @@ __device__ __forceinline__ void expand_mfma_run(const Item &it, int wave, const 
 }
 
 // adapters of more than 128 ranks: V and B come from memory for every tile
-template <int DT, bool Y16>
+template <int DT, bool Y16, int NP>
 __device__ __forceinline__ void expand_mfma_stream(const Item &it, int wave, const int32_t *__restrict__ pbl,
                                                    const uint16_t *__restrict__ pool,
                                                    const int32_t *__restrict__ tok_idx, int H, int v_stride,
                                                    const uint16_t *__restrict__ vfrag, const int8_t *__restrict__ vexp,
                                                    void *__restrict__ y, unsigned char *lds)
 {
-    typedef ExpandWave<DT, Y16> W;
+    typedef ExpandWave<DT, Y16, NP> W;
     typedef typename W::i32x4 i32x4;
-    constexpr int NP = W::NP, kYLoads = W::kYLoads;
+    constexpr int kYLoads = W::kYLoads;
     const int n_kk = v_stride >> 4, n_rb = (v_stride + kMsRanks - 1) / kMsRanks;
     const int colw = it.a + wave * 64;            // this wavefront's first column
     if (colw >= it.a + it.b) return;              // whole wavefront; no barrier is used below
@@ -1590,11 +1635,23 @@ __device__ __forceinline__ void expand_mfma_stream(const Item &it, int wave, con
         if constexpr (DT == SLORA_F16) e_cur = et[0];
         w.load_y(row, yt);
         w.begin(yt, e_cur);
+        // pieces of a scale of their own have a sum of their own
+        [[maybe_unused]] f32x16 mid[2], low[2];
+        if constexpr (W::kScaled) {
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) mid[nb][v] = low[nb][v] = 0.f;
+        }
         for (int k0 = 0; k0 < it.rank; k0 += 32) {
             if constexpr (DT == SLORA_F16) {
                 if (k0 > 0 && (k0 & (kMsRanks - 1)) == 0) { // the sums so far follow the next block's scale
                     const i32x4 e_next = et[(k0 / kMsRanks) * 2];
-                    w.scale_rows(e_cur, e_next);
+                    W::scale_rows(w.acc, e_cur, e_next);
+                    if constexpr (W::kScaled) {
+                        W::scale_rows(mid, e_cur, e_next);
+                        W::scale_rows(low, e_cur, e_next);
+                    }
                     e_cur = e_next;
                 }
             }
@@ -1609,14 +1666,25 @@ __device__ __forceinline__ void expand_mfma_stream(const Item &it, int wave, con
 #pragma unroll
             for (int s = 0; s < 2; ++s)
 #pragma unroll
-                for (int p = 0; p < NP; ++p) w.multiply(piece[s][p], op[s]);
+                for (int p = 0; p < NP; ++p) {
+                    if constexpr (W::kScaled)
+                        W::multiply(p == 0 ? w.acc : p == 1 ? mid : low, piece[s][p], op[s]);
+                    else
+                        W::multiply(w.acc, piece[s][p], op[s]);
+                }
+        }
+        if constexpr (W::kScaled) {
+#pragma unroll
+            for (int nb = 0; nb < 2; ++nb)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) w.acc[nb][v] += kPieceDown * (mid[nb][v] + kPieceDown * low[nb][v]);
         }
         w.end(yt, e_cur);
         w.store_y(t, row, yt);
     }
 }
 
-template <int DT, bool Y16>
+template <int DT, bool Y16, int NP>
 __global__ __launch_bounds__(kMfmaThreads, 2) void expand_mfma_kernel(const Item *__restrict__ items,
                                                                     const int32_t *__restrict__ arena,
                                                                     const uint16_t *__restrict__ pool,
@@ -1631,12 +1699,12 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void expand_mfma_kernel(const Item
     const int32_t *pbl = arena + it.arena_off + (int64_t)args.slot[cs] * 2 * it.rank + it.rank;
     const uint16_t *vfrag = reinterpret_cast<const uint16_t *>(args.v[cs] + args.vfrag_off);
     const int8_t *vexp = reinterpret_cast<const int8_t *>(args.v[cs] + args.vexp_off);
-#define SLORA_ME(S) expand_mfma_run<DT, Y16, S>(it, wave, pbl, pool, tok_idx, H, v_stride, vfrag, vexp, args.y[cs], lds)
+#define SLORA_ME(S) expand_mfma_run<DT, Y16, NP, S>(it, wave, pbl, pool, tok_idx, H, v_stride, vfrag, vexp, args.y[cs], lds)
     if (it.rank <= 32) SLORA_ME(1);
     else if (it.rank <= 64) SLORA_ME(2);
     else if (it.rank <= 96) SLORA_ME(3);
     else if (it.rank <= 128) SLORA_ME(4);
-    else expand_mfma_stream<DT, Y16>(it, wave, pbl, pool, tok_idx, H, v_stride, vfrag, vexp, args.y[cs], lds);
+    else expand_mfma_stream<DT, Y16, NP>(it, wave, pbl, pool, tok_idx, H, v_stride, vfrag, vexp, args.y[cs], lds);
 #undef SLORA_ME
 }
 
@@ -1834,12 +1902,10 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *
         if (rc != SLORA_OK) return rc;
         if (plan->n_sync > 0) {
             const dim3 jgrid((unsigned)((size_t)plan->n_sync * (kMsTok / 32) * (size_t)n));
-            if (pool->dtype == SLORA_F16)
-                hipLaunchKernelGGL(join_shares_kernel<SLORA_F16>, jgrid, dim3(kMfmaThreads), 0, st, plan->d_mj,
-                                   plan->v_stride, args);
-            else
-                hipLaunchKernelGGL(join_shares_kernel<SLORA_BF16>, jgrid, dim3(kMfmaThreads), 0, st, plan->d_mj,
-                                   plan->v_stride, args);
+            auto *join = pool->dtype != SLORA_F16   ? &join_shares_kernel<SLORA_BF16, 3>
+                         : plan->pieces(SLORA_F16) == 2 ? &join_shares_kernel<SLORA_F16, 2>
+                                                        : &join_shares_kernel<SLORA_F16, 3>;
+            hipLaunchKernelGGL(join, jgrid, dim3(kMfmaThreads), 0, st, plan->d_mj, plan->v_stride, args);
             rc = check_launch("join_shares");
             if (rc != SLORA_OK) return rc;
         }
@@ -1871,19 +1937,21 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *
     if (!plan->me_items.empty() && plan->mfma_on(route)) {
         const dim3 grid((unsigned)((size_t)plan->n_me_runs * (size_t)n));
         // LDS: two buffers of V fragments (the plan's most 32-rank stages) and the wavefronts' own parts
-        const size_t lds = (size_t)2 * plan->me_stages * 2 * (pool->dtype == SLORA_F16 ? 2 : 3) * 1024 + 4 * kWaveLds;
-#define SLORA_MEK(DT, Y)                                                                                             \
+        const size_t lds = (size_t)2 * plan->me_stages * 2 * plan->pieces(pool->dtype) * 1024 + 4 * kWaveLds;
+#define SLORA_MEK(DT, Y, NP)                                                                                           \
     {                                                                                                                \
         static std::atomic<uint64_t> done{0};                                                                        \
-        hipError_t e = allow_lds(done, pool->device, reinterpret_cast<const void *>(&expand_mfma_kernel<DT, Y>), lds);         \
+        hipError_t e = allow_lds(done, pool->device, reinterpret_cast<const void *>(&expand_mfma_kernel<DT, Y, NP>), lds);     \
         if (e != hipSuccess) return fail(SLORA_EHIP, "hipFuncSetAttribute(LDS size): %s", hipGetErrorString(e));     \
-        hipLaunchKernelGGL((expand_mfma_kernel<DT, Y>), grid, dim3(kMfmaThreads), lds, st, plan->d_me,               \
+        hipLaunchKernelGGL((expand_mfma_kernel<DT, Y, NP>), grid, dim3(kMfmaThreads), lds, st, plan->d_me,           \
                            pool->d_arena, base, plan->d_tok_idx, pool->H, plan->v_stride, args);                     \
     }
-        if (pool->dtype == SLORA_F16) {
-            if (y16) SLORA_MEK(SLORA_F16, true) else SLORA_MEK(SLORA_F16, false)
+        if (pool->dtype == SLORA_BF16) {
+            if (y16) SLORA_MEK(SLORA_BF16, true, 3) else SLORA_MEK(SLORA_BF16, false, 3)
+        } else if (plan->pieces(SLORA_F16) == 2) {
+            if (y16) SLORA_MEK(SLORA_F16, true, 2) else SLORA_MEK(SLORA_F16, false, 2)
         } else {
-            if (y16) SLORA_MEK(SLORA_BF16, true) else SLORA_MEK(SLORA_BF16, false)
+            if (y16) SLORA_MEK(SLORA_F16, true, 3) else SLORA_MEK(SLORA_F16, false, 3)
         }
 #undef SLORA_MEK
         int32_t rc = check_launch("expand_mfma");

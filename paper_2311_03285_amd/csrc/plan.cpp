@@ -138,16 +138,20 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         // on the vector kernels put the three MFMA launches behind theirs: 59 MB 26 / 34, 214 MB 85 / 67,
         // 236 MB 116 / 103.  A plan does not know the type of y: it holds both forms (dual), and 16-bit y and the
         // two-stage calls keep the vector kernels, whose sums 16-bit results are rounded from.
-        int64_t reread = 0;
+        int64_t reread = 0, sums = 0; // sums: floats of one set of partial sums
         bool few_tokens = false;
         for (int32_t gi : order) {
             const int64_t n = (int64_t)groups[(size_t)gi].toks.size();
-            if (n >= pool->mfma_min_tokens && !fused_group(n))
+            if (n >= pool->mfma_min_tokens && !fused_group(n)) {
                 reread += (n + kExpandTok - 1) / kExpandTok * groups[(size_t)gi].rank * (int64_t)H * 4 * launch_slots;
-            else
+                sums += (n + kMfmaTok - 1) / kMfmaTok * kMfmaTok * ((groups[(size_t)gi].rank + kRankPad - 1) / kRankPad * kRankPad);
+            } else {
                 few_tokens = true;
+            }
         }
-        plan->dual = min_tokens == INT64_MAX && reread >= (few_tokens ? 128000000 : 30000000);
+        // (a form whose partial sums of one slot exceed the static scratch is never taken: see route)
+        plan->dual = min_tokens == INT64_MAX && reread >= (few_tokens ? 128000000 : 30000000) &&
+                     sums * (int64_t)sizeof(float) <= (int64_t)SLORA_STATIC_SCRATCH_BYTES;
         const int64_t mfma_tokens = plan->dual ? pool->mfma_min_tokens : min_tokens;
         auto mfma_group = [&](int64_t n) { return n >= mfma_tokens && !fused_group(n); }; // has MFMA items
         // Size of a share of an MFMA shrink tile (see below): mfma_split_bytes, or more when the
@@ -238,7 +242,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                         it.tile = tile0 + p / kMfmaTok;
                         it.n_parts = (int32_t)parts;
                         it.sync = -1;
-                        if (parts > 1) {
+                        if (parts > 1 || plan->dual) {
                             it.sync = plan->n_sync++;
                             it.part_off = (int32_t)plan->part_floats;
                             plan->part_floats += parts * mb * nb * 1024;

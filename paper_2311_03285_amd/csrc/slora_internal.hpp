@@ -49,7 +49,7 @@ struct MsItem {
     int32_t tile;      // v tile (32 tokens) of the first token; the item covers up to 4 consecutive tiles
     int32_t c0, c1;    // granules [c0, c1) of H, kMsGranule elements each
     int32_t part, n_parts;
-    int32_t sync;      // number of the tile among the plan's split tiles (-1: not split)
+    int32_t sync;      // number of the tile among those the join kernel finishes (-1: the shrink finishes it)
     int32_t part_off;  // floats from the slot's partial area to the tile's partial sums
     int32_t pad[3];
 };
@@ -219,7 +219,7 @@ struct slora_plan {
     int32_t ms_lds_bytes = 0;  // LDS of the MFMA shrink's largest tile
     int32_t n_me_runs = 0;     // MFMA expand workgroups per slot: the first entries of me, one per run of tiles
     int32_t me_stages = 0;     // most 32-rank stages an MFMA expand workgroup keeps in registers (sizes its LDS)
-    int32_t n_sync = 0;        // split tiles
+    int32_t n_sync = 0;        // tiles that the join kernel finishes: those in several shares, all of a dual plan
     int64_t part_floats = 0;   // partial sums of the split tiles, per slot
     int32_t n_rank_blocks = 1; // kMsRanks-blocks per row of v (exponent sets per tile)
 
@@ -234,8 +234,10 @@ struct slora_plan {
     // partial sums of split tiles
     int64_t vfrag_floats(int32_t dtype) const
     {
-        return (int64_t)n_mfma_tiles * (v_stride / 16) * (dtype == SLORA_F16 ? 2 : 3) * 256;
+        return (int64_t)n_mfma_tiles * (v_stride / 16) * pieces(dtype) * 256;
     }
+    // 16-bit pieces that carry v to the MFMA expand: three where the vector kernels would keep it in fp32
+    int32_t pieces(int32_t dtype) const { return dual || dtype != SLORA_F16 ? 3 : 2; }
     int64_t vexp_floats() const { return (int64_t)n_mfma_tiles * n_rank_blocks * 8; } // one byte per row
     int64_t v_slot_floats(int32_t dtype, bool mfma) const
     {

@@ -154,7 +154,7 @@ static volatile float g_sink; // reads of the stand-in kernels end here
 int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &a, void *, const Route &route)
 {
     const slora_pool *pool = plan->pool;
-    const int32_t np = pool->dtype == SLORA_F16 ? 2 : 3;
+    const int32_t np = plan->pieces(pool->dtype);
     const int n_gran = (pool->H + kMsGranule - 1) / kMsGranule;
     const int n_kk = plan->v_stride / 16;
     REQUIRE(a.n == n && plan->v_stride % kRankPad == 0);
@@ -188,7 +188,8 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &a, void *, c
             REQUIRE(it.c0 >= 0 && it.c0 < it.c1 && it.c1 <= n_gran && it.part >= 0 && it.part < it.n_parts);
             const int mb = (it.ntok + 31) / 32, nb = (it.nj + 31) / 32;
             REQUIRE(it.tile >= 0 && it.tile + mb <= plan->n_mfma_tiles);
-            if (it.n_parts > 1) {
+            REQUIRE((it.sync >= 0) == (it.n_parts > 1 || plan->dual));
+            if (it.sync >= 0) {
                 REQUIRE(it.sync >= 0 && it.sync < plan->n_sync);
                 REQUIRE(it.part_off >= 0 && it.part_off + (int64_t)it.n_parts * mb * nb * 1024 <= plan->part_floats);
                 std::memset(part + it.part_off + (int64_t)it.part * mb * nb * 1024, 0, (size_t)mb * nb * 1024 * sizeof(float));
@@ -221,7 +222,7 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &a, void *, b
     check_scratch(plan, n, a, route);
     g_log.vec_expand = n_ve;
     g_log.mfma_expand = plan->mfma_on(route) && !plan->me_items.empty();
-    const int n_kk = plan->v_stride / 16, np = pool->dtype == SLORA_F16 ? 2 : 3;
+    const int n_kk = plan->v_stride / 16, np = plan->pieces(pool->dtype);
     for (int32_t k = 0; k < n; ++k) {
         REQUIRE(a.y[k] && a.v[k]);
         for (size_t i = 0; i < n_ve; ++i) {
