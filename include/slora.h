@@ -216,7 +216,8 @@ int32_t slora_plan_destroy(slora_plan *plan);
  * Schedule statistics, for tests and tuning: fills out[0..n) (n <= SLORA_PLAN_INFO_N) with
  *  [0] tokens with an adapter of rank > 0   [1] adapter groups        [2] groups on the vector path
  *  [3] groups on the MFMA path              [4] vector shrink items   [5] vector expand items
- *  [6] MFMA shrink items                    [7] MFMA expand items     [8] v row stride (floats)
+ *  [6] MFMA shrink items                    [7] MFMA expand tiles     [8] v row stride (floats)
+ *      (a workgroup walks several)              (32 tokens x 256 columns)
  *  [9] sum over groups of rank (pages of A read per slot)
  *  [10] MFMA shrink tiles whose H range is shared out over several workgroups
  *  [11] bytes of v scratch one slot of an apply needs

@@ -1694,7 +1694,7 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void expand_mfma_kernel(const Item
     // two buffers of V for the plan's widest adapter of up to 128 ranks, then each wavefront's own part
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int cs = blockIdx.x % args.n;
-    const Item it = items[blockIdx.x / args.n]; // the first tile of a run stands for all of them
+    const Item it = items[blockIdx.x / args.n]; // a run of tiles
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int32_t *pbl = arena + it.arena_off + (int64_t)args.slot[cs] * 2 * it.rank + it.rank;
     const uint16_t *vfrag = reinterpret_cast<const uint16_t *>(args.v[cs] + args.vfrag_off);
@@ -1935,7 +1935,7 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *
         if (rc != SLORA_OK) return rc;
     }
     if (!plan->me_items.empty() && plan->mfma_on(route)) {
-        const dim3 grid((unsigned)((size_t)plan->n_me_runs * (size_t)n));
+        const dim3 grid((unsigned)(plan->me_items.size() * (size_t)n));
         // LDS: two buffers of V fragments (the plan's most 32-rank stages) and the wavefronts' own parts
         const size_t lds = (size_t)2 * plan->me_stages * 2 * plan->pieces(pool->dtype) * 1024 + 4 * kWaveLds;
 #define SLORA_MEK(DT, Y, NP)                                                                                           \

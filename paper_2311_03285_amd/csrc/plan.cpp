@@ -198,7 +198,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         const int32_t shrink_tok = std::max(1, std::min(kShrinkTok, 65536 / (H * 2)));
         const int32_t shrink_pages = (int32_t)pool->shrink_pages;
         plan->expand_threads = ecols / 8;
-        std::vector<Item> vs_tail, ve_tail, vs_dual, ve_dual, me_rest;
+        std::vector<Item> vs_tail, ve_tail, vs_dual, ve_dual;
         plan->vf_items.clear();
         for (int32_t gi : order) {
             const Group &g = groups[(size_t)gi];
@@ -263,11 +263,8 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                     const int32_t t0 = n_tiles * k / n_runs, t1 = n_tiles * (k + 1) / n_runs;
                     const int32_t last = std::min(kMfmaTok, n - (t1 - 1) * kMfmaTok);
                     for (int32_t c = 0; c < H; c += kMfmaExpandCols) {
-                        for (int32_t t = t0; t < t1; ++t)
-                            (t == t0 ? plan->me_items : me_rest)
-                                .push_back(Item{off, g.rank, c, std::min(kMfmaExpandCols, H - c), pos_base + t * kMfmaTok,
-                                                std::min(kMfmaTok, n - t * kMfmaTok), tile0 + t,
-                                                t == t0 ? (t1 - t0) + 256 * last : 0});
+                        plan->me_items.push_back(Item{off, g.rank, c, std::min(kMfmaExpandCols, H - c), pos_base + t0 * kMfmaTok,
+                                                      std::min(kMfmaTok, n - t0 * kMfmaTok), tile0 + t0, (t1 - t0) + 256 * last});
                     }
                 }
             }
@@ -295,8 +292,6 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                 }
             }
         }
-        plan->n_me_runs = (int32_t)plan->me_items.size(); // the runs' first tiles, then the others
-        plan->me_items.insert(plan->me_items.end(), me_rest.begin(), me_rest.end());
         plan->n_vs_plain = (int32_t)plan->vs_items.size();
         plan->n_ve_plain = (int32_t)plan->ve_items.size();
         plan->vs_items.insert(plan->vs_items.end(), vs_dual.begin(), vs_dual.end());
@@ -609,7 +604,7 @@ int32_t slora_plan_info(const slora_plan *plan, int64_t *out, int32_t n)
                                           (int64_t)plan->vs_items.size(),
                                           (int64_t)plan->ve_items.size(),
                                           (int64_t)plan->ms_items.size(),
-                                          (int64_t)plan->me_items.size(),
+                                          (int64_t)plan->n_mfma_tiles * ((plan->pool->H + kMfmaExpandCols - 1) / kMfmaExpandCols),
                                           plan->v_stride,
                                           plan->sum_rank,
                                           plan->n_sync,

@@ -23,7 +23,7 @@ const char *last_error_cstr();
 // One record type serves the four work lists; `a` and `b` mean
 //   vector shrink : a = first page j0 of the A list, b = number of pages
 //   vector expand : a = first column (element index),  b = number of columns
-//   MFMA   expand : a = first column (element index),  b = number of columns
+//   MFMA   expand : a = first column (element index),  b = number of columns, of a run of tiles
 // (the MFMA shrink has its own record, MsItem)
 struct Item {
     int32_t arena_off; // adapter's first entry in the page-list arena ([slot][A r][B r])
@@ -31,9 +31,9 @@ struct Item {
     int32_t a;
     int32_t b;
     int32_t pos0;      // first position in the sorted token list (also the row of v)
-    int32_t ntok;      // tokens handled by this item
+    int32_t ntok;      // tokens handled by this item (MFMA expand: by its first tile)
     int32_t tile;      // MFMA lists: number of the (adapter, 32-token) tile, shared by shrink and expand
-    int32_t run;       // MFMA expand: first item of a run: tiles of the run + 256 * tokens of its last tile
+    int32_t run;       // MFMA expand: tiles the workgroup walks from `tile` on + 256 * tokens of the last one
 };
 static_assert(sizeof(Item) == 32, "Item must stay 32 bytes");
 
@@ -217,7 +217,6 @@ struct slora_plan {
     std::vector<slora::MsItem> mj_items; // one record per split tile, for the kernel that joins the shares
     int32_t ms_sub_tok = slora::kMsTok;  // tokens of an MFMA shrink item that one workgroup takes
     int32_t ms_lds_bytes = 0;  // LDS of the MFMA shrink's largest tile
-    int32_t n_me_runs = 0;     // MFMA expand workgroups per slot: the first entries of me, one per run of tiles
     int32_t me_stages = 0;     // most 32-rank stages an MFMA expand workgroup keeps in registers (sizes its LDS)
     int32_t n_sync = 0;        // tiles that the join kernel finishes: those in several shares, all of a dual plan
     int64_t part_floats = 0;   // partial sums of the split tiles, per slot

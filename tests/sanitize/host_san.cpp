@@ -235,19 +235,26 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &a, void *, b
             for (int32_t t = 0; t < it.ntok; ++t)
                 for (int32_t j = 0; j < it.rank; j += 16) g_sink = a.v[k][(int64_t)(it.pos0 + t) * plan->v_stride + j];
         }
+        std::set<std::pair<int, int>> done; // every tile and column range is in one run
         for (size_t i = 0; plan->mfma_on(route) && i < plan->me_items.size(); ++i) {
             const Item &it = plan->d_me[i];
             REQUIRE(std::memcmp(&it, &plan->me_items[i], sizeof it) == 0);
             check_pages(plan, it.arena_off, it.rank, a.slot[k]);
-            check_tokens(plan, it.pos0, it.ntok);
-            REQUIRE(it.ntok <= kMfmaTok && it.a >= 0 && it.b > 0 && it.b <= kMfmaExpandCols && it.a + it.b <= pool->H);
-            REQUIRE(it.tile >= 0 && it.tile < plan->n_mfma_tiles);
+            REQUIRE(it.a >= 0 && it.b > 0 && it.b <= kMfmaExpandCols && it.a % kMfmaExpandCols == 0 && it.a + it.b <= pool->H);
+            const int tiles = it.run & 0xff, last = it.run >> 8; // a run: whole tiles, then one of `last` tokens
+            REQUIRE(tiles >= 1 && tiles <= kMfmaRunMax && last >= 1 && last <= kMfmaTok && it.ntok == (tiles == 1 ? last : kMfmaTok));
+            check_tokens(plan, it.pos0, (tiles - 1) * kMfmaTok + last);
+            REQUIRE(it.tile >= 0 && it.tile + tiles <= plan->n_mfma_tiles);
             const unsigned char *frag = reinterpret_cast<const unsigned char *>(a.v[k] + a.vfrag_off);
-            for (int kk = 0; kk < (it.rank + 31) / 32 * 2; ++kk)
-                for (int b = 0; b < np * 1024; b += 64) g_sink = frag[((int64_t)it.tile * n_kk + kk) * np * 1024 + b];
             const int8_t *vexp = reinterpret_cast<const int8_t *>(a.v[k] + a.vexp_off);
-            for (int b = 0; b < 32 * plan->n_rank_blocks; ++b) g_sink = vexp[(int64_t)it.tile * plan->n_rank_blocks * 32 + b];
+            for (int t = it.tile; t < it.tile + tiles; ++t) {
+                REQUIRE(done.insert({t, it.a}).second);
+                for (int kk = 0; kk < (it.rank + 31) / 32 * 2; ++kk)
+                    for (int b = 0; b < np * 1024; b += 64) g_sink = frag[((int64_t)t * n_kk + kk) * np * 1024 + b];
+                for (int b = 0; b < 32 * plan->n_rank_blocks; ++b) g_sink = vexp[(int64_t)t * plan->n_rank_blocks * 32 + b];
+            }
         }
+        REQUIRE(!g_log.mfma_expand || (int64_t)done.size() == (int64_t)plan->n_mfma_tiles * ((pool->H + kMfmaExpandCols - 1) / kMfmaExpandCols));
     }
     return SLORA_OK;
 }
@@ -417,12 +424,26 @@ static void y_in_the_buffer_of_x()
     REQUIRE(!one_launch(-(int64_t)(3 * row), false) && one_launch((int64_t)(3 * row), false)); // fp32: rows twice as long
 }
 
+// The MFMA expand list holds what its workgroups read: one record per run of tiles and column range, in runs that
+// leave the launch at least 1024 workgroups.
+static void expand_runs()
+{
+    std::vector<std::pair<int, int>> groups;
+    for (int g = 0; g < 16; ++g) groups.push_back({32, 283}); // 16 x 9 tiles
+    Bench b(4096, 4, SLORA_F16, groups);
+    REQUIRE(b.plan->n_mfma_tiles == 144 && b.apply(4) == SLORA_OK && g_log.mfma_expand);
+    REQUIRE(b.plan->me_items.size() == 16 * 16); // runs of 9 tiles: 144 x 16 x 4 / 1024
+    int64_t info[SLORA_PLAN_INFO_N];
+    REQUIRE(slora_plan_info(b.plan, info, SLORA_PLAN_INFO_N) == SLORA_OK && info[7] == 144 * 16);
+}
+
 static const struct { const char *name; void (*run)(); } kCases[] = {
     {"failed_apply", failed_apply},
     {"static_route", static_route},
     {"scratch_is_sized_once", scratch_is_sized_once},
     {"fuse_decode_never", fuse_decode_never},
     {"y_in_the_buffer_of_x", y_in_the_buffer_of_x},
+    {"expand_runs", expand_runs},
 };
 
 // ---------------------------------------------------------------------------------------------
