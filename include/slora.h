@@ -231,7 +231,9 @@ int32_t slora_plan_info(const slora_plan *plan, int64_t *out, int32_t n);
  * x: DEVICE, T*H elements of the pool's storage type, row-major.  y: DEVICE, T*H fp32,
  * row-major, updated in place.  Asynchronous on `stream`; x and y must stay valid until the
  * stream has run the work.  Rows of tokens with id -1 or a rank-0 adapter are not accessed.
- * Results are deterministic: no floating-point atomics, fixed reduction order per plan.
+ * Results are deterministic: no floating-point atomics, fixed reduction order per plan - and, in
+ * batches that hold both kernel families' lists ("mfma_min_tiles" below), per type of y and
+ * number of slots in the call, which decide between the two.
  * All launches of one plan share its work lists and its v scratch and therefore run in ONE
  * order: a call that names another stream than the plan's previous call makes the new stream
  * wait (on the device, through an event) for the work enqueued before.  To run projections
@@ -320,9 +322,10 @@ int32_t slora_lora_shrink_expand(slora_pool *pool, int32_t slot, const void *x,
  *                      (default 16; 1 forces everything onto MFMA, a value > 2^30 disables it)
  *   "mfma_min_tiles"   the MFMA kernels are used only if such groups make up at least this many
  *                      32-token tiles in the batch (default 32: fewer tiles cannot fill the GPU
- *                      and run faster on the vector kernels - except where those would read 30 MB
- *                      of pages again, 128 MB beside groups of few tokens: applies to fp32 y then
- *                      take the MFMA kernels all the same, with shorter shares of H)
+ *                      and run faster on the vector kernels - except where those, in all slots of a
+ *                      call, would read 30 MB of pages again, 128 MB beside groups of few tokens:
+ *                      applies to fp32 y then take the MFMA kernels all the same, with shorter
+ *                      shares of H; 16-bit y and the two-stage calls never do)
  *   "mfma_split_bytes" the MFMA shrink hands the H range of a tile (up to 128 tokens x up to 128 ranks)
  *                      to several workgroups, each taking about this many bytes of x and page rows
  *                      (default 1 MiB); their partial sums are added in a fixed order by a small

@@ -1689,12 +1689,21 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void expand_mfma_kernel(const Item
                                                                     const int32_t *__restrict__ arena,
                                                                     const uint16_t *__restrict__ pool,
                                                                     const int32_t *__restrict__ tok_idx, int H,
-                                                                    int v_stride, MultiArgs args)
+                                                                    int v_stride, int parts, MultiArgs args)
 {
     // two buffers of V for the plan's widest adapter of up to 128 ranks, then each wavefront's own part
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int cs = blockIdx.x % args.n;
-    const Item it = items[blockIdx.x / args.n]; // a run of tiles
+    // a run of tiles, or this workgroup's part of it
+    Item it = items[blockIdx.x / args.n / parts];
+    if (parts > 1) {
+        const int part = (int)(blockIdx.x / args.n % parts), tiles = it.run & 0xff;
+        const int t0 = tiles * part / parts, t1 = tiles * (part + 1) / parts;
+        if (t0 == t1) return; // the whole workgroup
+        it.pos0 += t0 * kMfmaTok;
+        it.tile += t0;
+        it.run = (t1 - t0) + 256 * (t1 == tiles ? it.run >> 8 : kMfmaTok);
+    }
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int32_t *pbl = arena + it.arena_off + (int64_t)args.slot[cs] * 2 * it.rank + it.rank;
     const uint16_t *vfrag = reinterpret_cast<const uint16_t *>(args.v[cs] + args.vfrag_off);
@@ -1886,15 +1895,15 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *
         if (rc != SLORA_OK) return rc;
     }
     if (!plan->ms_items.empty() && plan->mfma_on(route)) {
-        const dim3 grid((unsigned)(plan->ms_items.size() * (size_t)(kMsTok / plan->ms_sub_tok) * (size_t)n));
-        const size_t lds = (size_t)plan->ms_lds_bytes;
+        const dim3 grid((unsigned)((plan->ms_items.size() << route.sub) * (size_t)n));
+        const size_t lds = (size_t)plan->ms_lds[route.sub];
 #define SLORA_MSK(DT)                                                                                                \
     {                                                                                                                \
         static std::atomic<uint64_t> done{0};                                                                        \
         hipError_t e = allow_lds(done, pool->device, reinterpret_cast<const void *>(&shrink_mfma_kernel<DT>), lds);            \
         if (e != hipSuccess) return fail(SLORA_EHIP, "hipFuncSetAttribute(LDS size): %s", hipGetErrorString(e));     \
         hipLaunchKernelGGL(shrink_mfma_kernel<DT>, grid, dim3(kMfmaThreads), lds, st, plan->d_ms, pool->d_arena,     \
-                           base, plan->d_tok_idx, pool->H, plan->v_stride, plan->ms_sub_tok, args);                  \
+                           base, plan->d_tok_idx, pool->H, plan->v_stride, kMsTok >> route.sub, args);               \
     }
         if (pool->dtype == SLORA_F16) SLORA_MSK(SLORA_F16) else SLORA_MSK(SLORA_BF16)
 #undef SLORA_MSK
@@ -1935,7 +1944,7 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *
         if (rc != SLORA_OK) return rc;
     }
     if (!plan->me_items.empty() && plan->mfma_on(route)) {
-        const dim3 grid((unsigned)(plan->me_items.size() * (size_t)n));
+        const dim3 grid((unsigned)(plan->me_items.size() * (size_t)route.parts * (size_t)n));
         // LDS: two buffers of V fragments (the plan's most 32-rank stages) and the wavefronts' own parts
         const size_t lds = (size_t)2 * plan->me_stages * 2 * plan->pieces(pool->dtype) * 1024 + 4 * kWaveLds;
 #define SLORA_MEK(DT, Y, NP)                                                                                           \
@@ -1944,7 +1953,7 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *
         hipError_t e = allow_lds(done, pool->device, reinterpret_cast<const void *>(&expand_mfma_kernel<DT, Y, NP>), lds);     \
         if (e != hipSuccess) return fail(SLORA_EHIP, "hipFuncSetAttribute(LDS size): %s", hipGetErrorString(e));     \
         hipLaunchKernelGGL((expand_mfma_kernel<DT, Y, NP>), grid, dim3(kMfmaThreads), lds, st, plan->d_me,           \
-                           pool->d_arena, base, plan->d_tok_idx, pool->H, plan->v_stride, args);                     \
+                           pool->d_arena, base, plan->d_tok_idx, pool->H, plan->v_stride, route.parts, args);        \
     }
         if (pool->dtype == SLORA_BF16) {
             if (y16) SLORA_MEK(SLORA_BF16, true, 3) else SLORA_MEK(SLORA_BF16, false, 3)

@@ -33,7 +33,7 @@ int32_t hip_fail(hipError_t e, const char *what) { return fail(SLORA_EHIP, "%s: 
 } // namespace
 
 int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids, int32_t T,
-                          const int32_t *seg_offsets, int32_t n_seg)
+                          const int32_t *seg_offsets, int32_t n_seg, int32_t call_slots)
 {
     // ---- validate ----------------------------------------------------------------------
     if (T < 0) return fail(SLORA_EINVAL, "T=%d must be >= 0", T);
@@ -93,7 +93,6 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         plan->n_groups_vec = plan->n_groups_mfma = 0;
         plan->n_mfma_tiles = 0;
         plan->n_sync = 0;
-        plan->ms_lds_bytes = 0;
         plan->part_floats = 0;
         plan->max_shrink_tok = 0;
         const int32_t n_chunks = (pool->H + kMsGranule - 1) / kMsGranule;
@@ -109,6 +108,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         }
         const int64_t min_tokens = mfma_tiles >= pool->mfma_min_tiles ? pool->mfma_min_tokens : INT64_MAX;
         const int64_t launch_slots = std::min<int64_t>(pool->n_slots, SLORA_MAX_MULTI);
+        const int64_t most_slots = call_slots > 0 ? call_slots : launch_slots; // ... of a call
         // One launch for both stages of decode groups (at most kExpandTok tokens): a workgroup per
         // group streams the whole adapter.  That pays when the batch has enough groups to fill
         // the GPU about three times over with whole-group workgroups AND the groups are large
@@ -136,21 +136,24 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         // Measured, vector / MFMA, us per call, for pages read (all slots): 30 MB 18.0 / 16.2, 67 MB 43 / 27,
         // 134 MB 35 / 18, 268 MB 60 / 22, 537 MB (512 tokens of rank 64, 4 slots) 110 / 32.  Groups that stay
         // on the vector kernels put the three MFMA launches behind theirs: 59 MB 26 / 34, 214 MB 85 / 67,
-        // 236 MB 116 / 103.  A plan does not know the type of y: it holds both forms (dual), and 16-bit y and the
-        // two-stage calls keep the vector kernels, whose sums 16-bit results are rounded from.
-        int64_t reread = 0, sums = 0; // sums: floats of one set of partial sums
+        // 236 MB 116 / 103.  A plan does not know the type of y nor the slots of its calls: it holds both forms
+        // (dual) if a call of as many slots as it may have reads that much, route() decides call by call, and
+        // 16-bit y and the two-stage calls keep the vector kernels, whose sums 16-bit results are rounded from.
+        int64_t sums = 0; // floats of one set of partial sums
+        plan->reread = 0;
         bool few_tokens = false;
         for (int32_t gi : order) {
             const int64_t n = (int64_t)groups[(size_t)gi].toks.size();
             if (n >= pool->mfma_min_tokens && !fused_group(n)) {
-                reread += (n + kExpandTok - 1) / kExpandTok * groups[(size_t)gi].rank * (int64_t)H * 4 * launch_slots;
+                plan->reread += (n + kExpandTok - 1) / kExpandTok * groups[(size_t)gi].rank * (int64_t)H * 4;
                 sums += (n + kMfmaTok - 1) / kMfmaTok * kMfmaTok * ((groups[(size_t)gi].rank + kRankPad - 1) / kRankPad * kRankPad);
             } else {
                 few_tokens = true;
             }
         }
         // (a form whose partial sums of one slot exceed the static scratch is never taken: see route)
-        plan->dual = min_tokens == INT64_MAX && reread >= (few_tokens ? 128000000 : 30000000) &&
+        plan->reread_min = few_tokens ? 128000000 : 30000000;
+        plan->dual = min_tokens == INT64_MAX && plan->reread * most_slots >= plan->reread_min &&
                      sums * (int64_t)sizeof(float) <= (int64_t)SLORA_STATIC_SCRATCH_BYTES;
         const int64_t mfma_tokens = plan->dual ? pool->mfma_min_tokens : min_tokens;
         auto mfma_group = [&](int64_t n) { return n >= mfma_tokens && !fused_group(n); }; // has MFMA items
@@ -174,14 +177,16 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         const int64_t split_min_h = plan->dual ? std::min<int64_t>(pool->mfma_split_min_h, 256) : pool->mfma_split_min_h;
         const int64_t share_bytes = std::max<int64_t>(split_bytes, ms_bytes * launch_slots / (3 * 256));
         // MFMA expand: a workgroup keeps the B operands of its columns and walks a run of tiles.  Long runs
-        // pay for them once, but the launch still needs several workgroups per compute unit.
+        // pay for them once, but the launch still needs several workgroups per compute unit.  The list's runs are
+        // for calls of the most slots; calls of fewer share a run out over several workgroups (see route).
         int64_t me_tiles = 0;
         for (int32_t gi : order) {
             const int64_t n = (int64_t)groups[(size_t)gi].toks.size();
             if (mfma_group(n)) me_tiles += (n + kMfmaTok - 1) / kMfmaTok;
         }
-        const int64_t me_wgs = me_tiles * ((H + kMfmaExpandCols - 1) / kMfmaExpandCols) * launch_slots;
-        const int32_t me_run = (int32_t)std::min<int64_t>(kMfmaRunMax, std::max<int64_t>(1, me_wgs / 1024));
+        const int64_t me_pairs = me_tiles * ((H + kMfmaExpandCols - 1) / kMfmaExpandCols) * most_slots;
+        const int32_t me_run = (int32_t)std::min<int64_t>(kMfmaRunMax, std::max<int64_t>(1, me_pairs / 1024));
+        plan->me_run = me_run;
         plan->me_stages = 0;
         int32_t n_vec_groups = 0;
         for (int32_t gi : order)
@@ -300,22 +305,16 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         plan->n_ve_head = (int32_t)plan->ve_items.size();
         plan->vs_items.insert(plan->vs_items.end(), vs_tail.begin(), vs_tail.end());
         plan->ve_items.insert(plan->ve_items.end(), ve_tail.begin(), ve_tail.end());
-        // Tokens of an item per workgroup of the MFMA shrink.  The items of a batch of modest size are too
-        // few for the GPU; halves or quarters of their tokens read the pages two or four times as often,
-        // which pays only while compute units stand idle: 111 items 62 us in as many workgroups, 48 in 153,
-        // 35 in 222, but 236 items 47 -> 52 and 252 items 55 -> 58 us (launches of three or four slots).
-        plan->ms_sub_tok = kMsTok;
-        auto ms_wgs = [&](int32_t sub) {
-            int64_t c = 0;
-            for (const MsItem &i : plan->ms_items) c += (i.ntok + sub - 1) / sub;
-            return c * launch_slots;
-        };
-        while (plan->ms_sub_tok > 32 && ms_wgs(plan->ms_sub_tok) < 192) plan->ms_sub_tok /= 2;
-        for (const MsItem &i : plan->ms_items)
-            for (int32_t p = 0; p < i.ntok; p += plan->ms_sub_tok) {
-                const int32_t rows = std::min(plan->ms_sub_tok, i.ntok - p);
-                plan->ms_lds_bytes = std::max(plan->ms_lds_bytes, ms_lds_bytes((rows <= 32 ? 1 : rows <= 64 ? 2 : 4) + (i.nj + 31) / 32));
-            }
+        for (int32_t sub = 0; sub < kMsSubs; ++sub) {
+            plan->ms_wgs[sub] = 0;
+            plan->ms_lds[sub] = 0;
+            for (const MsItem &i : plan->ms_items)
+                for (int32_t p = 0; p < i.ntok; p += kMsTok >> sub) {
+                    const int32_t rows = std::min(kMsTok >> sub, i.ntok - p);
+                    plan->ms_wgs[sub]++;
+                    plan->ms_lds[sub] = std::max(plan->ms_lds[sub], ms_lds_bytes((rows <= 32 ? 1 : rows <= 64 ? 2 : 4) + (i.nj + 31) / 32));
+                }
+        }
         // longest first: the hardware hands a workgroup to a compute unit as one becomes free, so
         // with the big shares at the head of the list and the small ones at its end the launch
         // ends on every unit at about the same time
@@ -401,10 +400,24 @@ int32_t slora_plan::upload()
 Route slora_plan::route(int32_t n, bool apply, bool y16) const
 {
     Route r;
-    r.wide = dual && apply && !y16 &&
+    r.wide = dual && apply && !y16 && reread * n >= reread_min &&
              v_total_floats(n, pool->dtype, true) * (int64_t)sizeof(float) <= (int64_t)SLORA_STATIC_SCRATCH_BYTES;
     r.fused = apply && !vf_items.empty();
     r.small = apply && small && (int64_t)ve_items.size() * n <= 256;
+    // Tokens of an item per workgroup of the MFMA shrink.  The items of a call of modest size are too
+    // few for the GPU; halves or quarters of their tokens read the pages two or four times as often,
+    // which pays only while compute units stand idle: 111 items 62 us in as many workgroups, 48 in 153,
+    // 35 in 222, but 236 items 47 -> 52 and 252 items 55 -> 58 us (launches of three or four slots).
+    // Between: 177 items of three slots 39 us whole, 44 in halves; 189 halves against 345 quarters 15 us less.
+    while (r.sub + 1 < kMsSubs && ms_wgs[r.sub] * n < 160) r.sub++;
+    // Calls of fewer slots than the list's runs are made for share a run out until there are 1024 workgroups.  Sixteen
+    // prompts in a pool of 64 slots, us per call of one slot in 256 / 768 / 1024 / 1536 / 2048 workgroups 84 / 63 /
+    // 63 / 63 / 67 (16-bit y 81 / 54 / 54 / 55 / 59), of two in 512 / 1024 / 1536 / 2048 101 / 91 / 90 / 93 (87 / 74 / 71 /
+    // 76), of three in 768 / 1536 / 2304 129 / 124 / 127 (96 / 95 / 99).
+    if (!me_items.empty()) {
+        const int64_t wgs = (int64_t)me_items.size() * n;
+        r.parts = (int32_t)std::min<int64_t>(me_run, (1024 + wgs - 1) / wgs);
+    }
     return r;
 }
 
@@ -548,10 +561,9 @@ int32_t do_expand(slora_plan *plan, int32_t n, const int32_t *slots, void *const
 
 } // namespace
 
-extern "C" {
-
-int32_t slora_batch_plan(slora_pool *pool, slora_plan **out, const int32_t *token_adapter_ids, int32_t T,
-                         const int32_t *seg_offsets, int32_t n_seg)
+namespace {
+int32_t make_plan(slora_pool *pool, slora_plan **out, const int32_t *token_adapter_ids, int32_t T,
+                  const int32_t *seg_offsets, int32_t n_seg, int32_t call_slots)
 {
     clear_error();
     if (!pool || !out) return fail(SLORA_EINVAL, "NULL argument");
@@ -560,7 +572,7 @@ int32_t slora_batch_plan(slora_pool *pool, slora_plan **out, const int32_t *toke
     if (!p) return fail(SLORA_ENOMEM, "out of host memory");
     p->pool = pool;
     p->generation = pool->unload_generation;
-    int32_t rc = build_plan(pool, p, token_adapter_ids, T, seg_offsets, n_seg);
+    int32_t rc = build_plan(pool, p, token_adapter_ids, T, seg_offsets, n_seg, call_slots);
     if (rc == SLORA_OK && pool->dev_base) {
         DeviceScope dev(pool->device);
         rc = dev.status();
@@ -575,6 +587,15 @@ int32_t slora_batch_plan(slora_pool *pool, slora_plan **out, const int32_t *toke
     pool->live_plans++;
     *out = p;
     return SLORA_OK;
+}
+} // namespace
+
+extern "C" {
+
+int32_t slora_batch_plan(slora_pool *pool, slora_plan **out, const int32_t *token_adapter_ids, int32_t T,
+                         const int32_t *seg_offsets, int32_t n_seg)
+{
+    return make_plan(pool, out, token_adapter_ids, T, seg_offsets, n_seg, 0);
 }
 
 int32_t slora_plan_destroy(slora_plan *plan)
@@ -604,7 +625,7 @@ int32_t slora_plan_info(const slora_plan *plan, int64_t *out, int32_t n)
                                           (int64_t)plan->vs_items.size(),
                                           (int64_t)plan->ve_items.size(),
                                           (int64_t)plan->ms_items.size(),
-                                          (int64_t)plan->n_mfma_tiles * ((plan->pool->H + kMfmaExpandCols - 1) / kMfmaExpandCols),
+                                          plan->me_wgs(),
                                           plan->v_stride,
                                           plan->sum_rank,
                                           plan->n_sync,
@@ -691,7 +712,7 @@ int32_t slora_lora_shrink_expand(slora_pool *pool, int32_t slot, const void *x, 
                                  const int32_t *seg_offsets, int32_t n_seg, int32_t T, float *y, void *stream)
 {
     slora_plan *plan = nullptr;
-    int32_t rc = slora_batch_plan(pool, &plan, token_adapter_ids, T, seg_offsets, n_seg);
+    int32_t rc = make_plan(pool, &plan, token_adapter_ids, T, seg_offsets, n_seg, 1);
     if (rc != SLORA_OK) return rc;
     rc = slora_lora_apply(plan, slot, x, y, stream);
     std::string keep = last_error_cstr();

@@ -72,6 +72,8 @@ struct Route {
     bool wide = false;  // a dual plan's groups of many tokens on the MFMA kernels
     bool small = false; // both stages in the one-launch kernel for small batches
     bool fused = false; // an apply: launch_fused serves the groups of the one-launch decode kernel
+    int32_t sub = 0;    // MFMA shrink: a workgroup takes kMsTok >> sub tokens of an item
+    int32_t parts = 1;  // MFMA expand: workgroups that share a run of tiles
 };
 
 // Tile constants the scheduler and the kernels must agree on.
@@ -82,6 +84,7 @@ constexpr int kExpandColsMax = 1024; // most columns per vector-expand item (a m
 constexpr int kMfmaTok = 32;      // tokens per v tile = per MFMA-expand item (one 32-row MFMA block)
 constexpr int kMsTok = 128;       // most tokens per MFMA-shrink item
 constexpr int kMsRanks = 128;     // ranks per MFMA-shrink item (up to four blocks of 32)
+constexpr int kMsSubs = 3;        // a workgroup takes an item's tokens whole, in halves or in quarters
 constexpr int kMsGranule = 128;   // shares of H are whole runs of this many elements
 // LDS of the MFMA shrink for a tile of `blocks` 32-row blocks (token rows and page rows): a ring of
 // pieces of 32 rows x 128 bytes per block, at most 80 KiB - two workgroups per compute unit
@@ -208,6 +211,7 @@ struct slora_plan {
     // A dual plan's groups of many tokens are in both kernels' lists: in vs / ve between the plain groups'
     // items and n_vs_head / n_ve_head, and in the MFMA lists.  fp32-y applies take the latter (wide).
     bool dual = false;
+    int64_t reread = 0, reread_min = 0; // bytes of pages the vector kernels would read again, per slot; what it takes per call
     int32_t n_vs_plain = 0, n_ve_plain = 0;
     bool mfma_on(const slora::Route &r) const { return !dual || r.wide; }
     // items of the two vector lists that a call runs beside the other kernels
@@ -215,8 +219,10 @@ struct slora_plan {
     size_t n_ve(const slora::Route &r) const { return r.wide ? (size_t)n_ve_plain : r.fused ? (size_t)n_ve_head : ve_items.size(); }
     std::vector<slora::MsItem> ms_items;
     std::vector<slora::MsItem> mj_items; // one record per split tile, for the kernel that joins the shares
-    int32_t ms_sub_tok = slora::kMsTok;  // tokens of an MFMA shrink item that one workgroup takes
-    int32_t ms_lds_bytes = 0;  // LDS of the MFMA shrink's largest tile
+    // MFMA shrink with kMsTok >> sub tokens per workgroup: workgroups per slot, LDS of the largest tile
+    int64_t ms_wgs[slora::kMsSubs] = {};
+    int32_t ms_lds[slora::kMsSubs] = {};
+    int32_t me_run = 1;        // most tiles of a run of the MFMA expand list
     int32_t me_stages = 0;     // most 32-rank stages an MFMA expand workgroup keeps in registers (sizes its LDS)
     int32_t n_sync = 0;        // tiles that the join kernel finishes: those in several shares, all of a dual plan
     int64_t part_floats = 0;   // partial sums of the split tiles, per slot
@@ -245,6 +251,7 @@ struct slora_plan {
     int64_t v_total_floats(int32_t n, int32_t dtype, bool mfma) const { return (int64_t)n * v_slot_floats(dtype, mfma); }
     // scratch of any call with at most n slots, whatever the type of y: a plan's buffer is grown once
     int64_t v_most_floats(int32_t n, int32_t dtype) const;
+    int64_t me_wgs() const { return (int64_t)n_mfma_tiles * ((pool->H + slora::kMfmaExpandCols - 1) / slora::kMfmaExpandCols); } // one per tile
     // The kernels of a call with n slots.  A dual plan's MFMA form is taken only where it fits the static scratch,
     // so that an apply gives the same bits wherever v is kept.
     slora::Route route(int32_t n, bool apply, bool y16) const;
@@ -268,8 +275,9 @@ struct slora_plan {
 namespace slora {
 
 // scheduler (plan.cpp)
+// call_slots: slots of the plan's only call, if that is known; 0: calls may have as many as the pool
 int32_t build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids, int32_t T,
-                   const int32_t *seg_offsets, int32_t n_seg);
+                   const int32_t *seg_offsets, int32_t n_seg, int32_t call_slots);
 
 // kernel launchers (kernels.hip); all return a SLORA_* code
 int32_t launch_write_pages(slora_pool *pool, const int32_t *d_idx, int64_t n, const void *d_src,

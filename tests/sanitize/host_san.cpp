@@ -147,6 +147,7 @@ static void check_scratch(const slora_plan *plan, int32_t n, const MultiArgs &a,
 struct Log {
     bool small = false, fused = false, mfma_shrink = false, mfma_expand = false;
     size_t vec_shrink = 0, vec_expand = 0; // items
+    size_t mfma_shrink_wgs = 0, mfma_expand_wgs = 0; // workgroups with work
 };
 static Log g_log;
 static volatile float g_sink; // reads of the stand-in kernels end here
@@ -187,6 +188,12 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &a, void *, c
             REQUIRE(it.ntok <= kMsTok && it.nj > 0 && it.nj <= kMsRanks && it.j0 % kMsRanks == 0 && it.j0 + it.nj <= it.rank);
             REQUIRE(it.c0 >= 0 && it.c0 < it.c1 && it.c1 <= n_gran && it.part >= 0 && it.part < it.n_parts);
             const int mb = (it.ntok + 31) / 32, nb = (it.nj + 31) / 32;
+            const int sub_tok = kMsTok >> route.sub;
+            for (int p = 0; p < it.ntok; p += sub_tok) { // one workgroup each: its ring must fit
+                const int rows = std::min(sub_tok, it.ntok - p);
+                g_log.mfma_shrink_wgs++;
+                REQUIRE(ms_lds_bytes((rows <= 32 ? 1 : rows <= 64 ? 2 : 4) + nb) <= plan->ms_lds[route.sub] && plan->ms_lds[route.sub] <= 80 * 1024);
+            }
             REQUIRE(it.tile >= 0 && it.tile + mb <= plan->n_mfma_tiles);
             REQUIRE((it.sync >= 0) == (it.n_parts > 1 || plan->dual));
             if (it.sync >= 0) {
@@ -242,7 +249,8 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &a, void *, b
             check_pages(plan, it.arena_off, it.rank, a.slot[k]);
             REQUIRE(it.a >= 0 && it.b > 0 && it.b <= kMfmaExpandCols && it.a % kMfmaExpandCols == 0 && it.a + it.b <= pool->H);
             const int tiles = it.run & 0xff, last = it.run >> 8; // a run: whole tiles, then one of `last` tokens
-            REQUIRE(tiles >= 1 && tiles <= kMfmaRunMax && last >= 1 && last <= kMfmaTok && it.ntok == (tiles == 1 ? last : kMfmaTok));
+            g_log.mfma_expand_wgs += (size_t)std::min(tiles, route.parts);
+            REQUIRE(tiles >= 1 && tiles <= plan->me_run && tiles <= kMfmaRunMax && last >= 1 && last <= kMfmaTok && it.ntok == (tiles == 1 ? last : kMfmaTok));
             check_tokens(plan, it.pos0, (tiles - 1) * kMfmaTok + last);
             REQUIRE(it.tile >= 0 && it.tile + tiles <= plan->n_mfma_tiles);
             const unsigned char *frag = reinterpret_cast<const unsigned char *>(a.v[k] + a.vfrag_off);
@@ -437,6 +445,28 @@ static void expand_runs()
     REQUIRE(slora_plan_info(b.plan, info, SLORA_PLAN_INFO_N) == SLORA_OK && info[7] == 144 * 16);
 }
 
+// What a call takes depends on its own slots, not on the pool's: tokens per workgroup of the MFMA shrink, tiles per
+// workgroup of the MFMA expand, and which kernels serve a batch of few tiles.
+static void slots_of_the_call()
+{
+    const std::vector<std::pair<int, int>> prompts(8, {32, 283}); // 8 x 9 tiles, not dual
+    for (int32_t n : {1, 3, 4, 8}) {
+        Bench one(4096, n, SLORA_F16, prompts), all(4096, 8, SLORA_F16, prompts);
+        REQUIRE(one.apply(n) == SLORA_OK && one.plan->mfma_on({}));
+        const Log want = g_log;
+        REQUIRE(all.apply(n) == SLORA_OK);
+        REQUIRE(g_log.mfma_expand_wgs >= (size_t)std::min(1024, 72 * 16 * n));
+        REQUIRE(g_log.mfma_expand_wgs <= 2 * want.mfma_expand_wgs);
+        REQUIRE(g_log.mfma_shrink_wgs >= (size_t)std::min(160, 72 * n)); // 72: the items in quarters
+    }
+    Bench few(4096, 8, SLORA_F16, {{64, 32}}); // 8.4 MB of pages read again per slot: 30 MB from four slots on
+    for (int32_t n = 1; n <= 8; ++n) REQUIRE(few.apply(n) == SLORA_OK && g_log.mfma_expand == (n >= 4));
+    few.ids.assign(32, 0);
+    g_log = {};
+    REQUIRE(slora_lora_shrink_expand(few.pool, 0, few.xs[0], few.ids.data(), nullptr, 0, 32, few.ys[0], nullptr) == SLORA_OK);
+    REQUIRE(!g_log.mfma_expand && g_log.vec_expand > 0);
+}
+
 static const struct { const char *name; void (*run)(); } kCases[] = {
     {"failed_apply", failed_apply},
     {"static_route", static_route},
@@ -444,6 +474,7 @@ static const struct { const char *name; void (*run)(); } kCases[] = {
     {"fuse_decode_never", fuse_decode_never},
     {"y_in_the_buffer_of_x", y_in_the_buffer_of_x},
     {"expand_runs", expand_runs},
+    {"slots_of_the_call", slots_of_the_call},
 };
 
 // ---------------------------------------------------------------------------------------------
