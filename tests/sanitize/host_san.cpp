@@ -14,6 +14,7 @@
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
+#include <map>
 #include <random>
 #include <set>
 #include <utility>
@@ -150,6 +151,7 @@ struct Log {
     size_t mfma_shrink_wgs = 0, mfma_expand_wgs = 0; // workgroups with work
 };
 static Log g_log;
+static std::map<const slora_plan *, bool> g_wide; // whether the latest shrink of a plan left v in the MFMA layout of a dual plan
 static volatile float g_sink; // reads of the stand-in kernels end here
 
 int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &a, void *, const Route &route)
@@ -164,6 +166,7 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &a, void *, c
     g_seen = -1;
     check_scratch(plan, n, a, route);
     g_log.vec_shrink = n_vs;
+    g_wide[plan] = route.wide;
     g_log.mfma_shrink = plan->mfma_on(route) && !plan->ms_items.empty();
     for (int32_t k = 0; k < n; ++k) {
         REQUIRE(a.x[k] && a.v[k]);
@@ -228,6 +231,7 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &a, void *, b
     g_seen = -1;
     check_scratch(plan, n, a, route);
     g_log.vec_expand = n_ve;
+    REQUIRE(g_wide.count(plan) && g_wide[plan] == route.wide);
     g_log.mfma_expand = plan->mfma_on(route) && !plan->me_items.empty();
     const int n_kk = plan->v_stride / 16, np = plan->pieces(pool->dtype);
     for (int32_t k = 0; k < n; ++k) {
@@ -273,6 +277,7 @@ int32_t launch_fused(slora_plan *plan, int32_t n, const MultiArgs &a, void *, bo
     REQUIRE(a.n == n && pool->H <= 8192);
     if (route.small) { // the whole batch, from the items of the rank-split expand
         g_log.small = true;
+        g_wide[plan] = false;
         REQUIRE(plan->small && plan->ms_items.empty() && plan->vf_items.empty() && plan->expand_split && pool->H <= 4096);
         for (const Item &it : plan->ve_items)
             REQUIRE(it.rank <= kSmallRanks && it.ntok <= kExpandTok && it.ntok <= plan->max_expand_tok);
@@ -362,14 +367,15 @@ struct Bench {
 // An apply that fails leaves v as the shrink before it did: the expand that follows reads THAT layout.
 static void failed_apply()
 {
-    Bench b(4096, 4, SLORA_F16, {{64, 512}});
-    REQUIRE(b.shrink(4) == SLORA_OK && !g_log.mfma_shrink);
-    g_fail_malloc = true; // whatever the apply wants to allocate
-    const int32_t rc = b.apply(4);
-    g_fail_malloc = false;
-    REQUIRE(rc == SLORA_OK || rc == SLORA_EHIP);
-    REQUIRE(b.expand(4) == SLORA_OK);
-    REQUIRE(g_log.mfma_expand == (rc == SLORA_OK));
+    for (int32_t n : {1, 2, 3, 4}) { // slots of the shrink; the apply of all eight needs a larger scratch
+        Bench b(4096, 8, SLORA_F16, {{64, 512}});
+        REQUIRE(b.shrink(n) == SLORA_OK && !g_log.mfma_shrink);
+        g_fail_malloc = true;
+        REQUIRE(b.apply(8) == SLORA_EHIP);
+        g_fail_malloc = false;
+        REQUIRE(b.expand(n) == SLORA_OK && !g_log.mfma_expand && g_log.vec_expand > 0);
+        REQUIRE(b.apply(n) == SLORA_OK && g_log.mfma_expand);
+    }
 }
 
 // The apply that allocates nothing takes the kernels of the one that does, also where the MFMA form is larger
@@ -491,7 +497,7 @@ int main(int argc, char **argv)
     const unsigned seed = argc > 1 ? (unsigned)std::atoi(argv[1]) : 1u;
     std::mt19937 rng(seed);
     auto rnd = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
-    long calls = 0, plans_made = 0;
+    long calls = 0, plans_made = 0, both_families = 0;
     for (int round = 0; round < 12; ++round) {
         const int32_t H = 8 * rnd(8, 160);
         const int64_t n_pages = rnd(200, 3000);
@@ -501,7 +507,7 @@ int main(int argc, char **argv)
         slora_pool *pool = nullptr;
         REQUIRE(slora_pool_init(&pool, H, n_pages, dtype, mem.data(), n_slots, max_rank) == SLORA_OK);
         REQUIRE(slora_set_option(pool, "mfma_min_tokens", rnd(1, 40)) == SLORA_OK);
-        REQUIRE(slora_set_option(pool, "mfma_min_tiles", rnd(1, 4)) == SLORA_OK);
+        REQUIRE(slora_set_option(pool, "mfma_min_tiles", rnd(0, 2) ? rnd(1, 4) : 1000) == SLORA_OK); // 1000: plans of both families
         REQUIRE(slora_set_option(pool, "mfma_split_bytes", 4096 << rnd(0, 6)) == SLORA_OK);
         REQUIRE(slora_set_option(pool, "mfma_split_min_h", 128 << rnd(0, 3)) == SLORA_OK);
         REQUIRE(slora_set_option(pool, "xcd_group", rnd(0, 3)) == SLORA_OK);
@@ -511,6 +517,36 @@ int main(int argc, char **argv)
         std::vector<slora_plan *> plans;
         std::vector<uint16_t> x((size_t)4096 * H, 0x3800), w;
         std::vector<float> y((size_t)SLORA_MAX_MULTI * 4096 * H, 0.f);
+        // one to four calls on a plan, any entry point, now and then without device memory to be had
+        auto use = [&](slora_plan *plan, int32_t most) {
+            int32_t slots[SLORA_MAX_MULTI];
+            const void *xs[SLORA_MAX_MULTI];
+            float *ys[SLORA_MAX_MULTI];
+            for (int k = 0; k < most; ++k) {
+                slots[k] = rnd(0, n_slots - 1);
+                xs[k] = x.data();
+                ys[k] = y.data() + (size_t)k * 4096 * H;
+            }
+            for (int c = rnd(1, 4); c > 0; --c) {
+                const int32_t n = rnd(0, 1) ? most : (most + 1) / 2;
+                const bool no_memory = g_fail_malloc = rnd(0, 7) == 0;
+                g_log = {};
+                int32_t rc = SLORA_OK;
+                const int entry = rnd(0, 6);
+                switch (entry) {
+                case 0: rc = slora_lora_apply_multi_static(plan, n, slots, xs, ys, nullptr); break;
+                case 1: rc = slora_lora_apply_multi_y16(plan, n, slots, xs, (void *const *)ys, nullptr); break;
+                case 2: rc = slora_lora_shrink(plan, n, slots, xs, nullptr); break;
+                case 3: rc = slora_lora_expand(plan, n, slots, ys, nullptr); break;
+                case 4: rc = slora_lora_expand_y16(plan, n, slots, (void *const *)ys, nullptr); break;
+                default: rc = slora_lora_apply_multi(plan, n, slots, xs, ys, nullptr);
+                }
+                g_fail_malloc = false;
+                both_families += plan->dual && g_log.mfma_expand;
+                REQUIRE(rc == SLORA_OK || rc == SLORA_EBUSY || (rc == SLORA_ERANGE && entry == 0) ||
+                        (rc == SLORA_EINVAL && (entry == 3 || entry == 4)) || (rc == SLORA_EHIP && no_memory));
+            }
+        };
         for (int step = 0; step < 120; ++step, ++calls) {
             const int what = rnd(0, 9);
             if (what <= 2) { // make an adapter resident on pages of the library's choice, then fill them
@@ -551,18 +587,7 @@ int main(int argc, char **argv)
                 REQUIRE(slora_batch_plan(pool, &plan, ids.data(), (int32_t)ids.size(), decode ? nullptr : seg.data(),
                                          (int32_t)seg.size() - 1) == SLORA_OK);
                 plans_made++;
-                const int32_t n = rnd(1, SLORA_MAX_MULTI);
-                int32_t slots[SLORA_MAX_MULTI];
-                const void *xs[SLORA_MAX_MULTI];
-                float *ys[SLORA_MAX_MULTI];
-                for (int k = 0; k < n; ++k) {
-                    slots[k] = rnd(0, n_slots - 1);
-                    xs[k] = x.data();
-                    ys[k] = y.data() + (size_t)k * 4096 * H;
-                }
-                const int32_t rc = rnd(0, 3) ? slora_lora_apply_multi(plan, n, slots, xs, ys, nullptr)
-                                             : slora_lora_apply_multi_static(plan, n, slots, xs, ys, nullptr);
-                REQUIRE(rc == SLORA_OK || rc == SLORA_ERANGE);
+                use(plan, rnd(1, SLORA_MAX_MULTI));
                 int64_t info[SLORA_PLAN_INFO_N];
                 REQUIRE(slora_plan_info(plan, info, SLORA_PLAN_INFO_N) == SLORA_OK);
                 if (rnd(0, 2))
@@ -571,11 +596,7 @@ int main(int argc, char **argv)
                     plans.push_back(plan);
             } else if (what == 8 && !plans.empty()) { // an older plan again: stale after an eviction, else fine
                 slora_plan *plan = plans[rng() % plans.size()];
-                int32_t slot = 0;
-                const void *xs[1] = {x.data()};
-                float *ys[1] = {y.data()};
-                const int32_t rc = slora_lora_apply_multi(plan, 1, &slot, xs, ys, nullptr);
-                REQUIRE(rc == SLORA_OK || rc == SLORA_EBUSY);
+                use(plan, rnd(1, 2));
             } else if (!loaded.empty()) { // gather a matrix back
                 const int32_t id = loaded[rng() % loaded.size()];
                 std::vector<uint16_t> out((size_t)(max_rank + 2) * H + 8);
@@ -588,6 +609,7 @@ int main(int argc, char **argv)
         REQUIRE(slora_pool_stats(pool, stats, SLORA_POOL_STATS_N) == SLORA_OK);
         REQUIRE(slora_pool_destroy(pool) == SLORA_OK);
     }
-    std::printf("host_san OK: seed %u, %ld calls, %ld plans\n", seed, calls, plans_made);
+    REQUIRE(both_families > 0); // MFMA calls on plans that hold both kernel families' lists
+    std::printf("host_san OK: seed %u, %ld calls, %ld plans, %ld on both families\n", seed, calls, plans_made, both_families);
     return 0;
 }
