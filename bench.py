@@ -32,11 +32,11 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 MEASURED_TRAFFIC = {("cfg4-large-pool-decode", "power", "fused", 8): {"expand_vec": 332880461,
                                                                         "shrink_vec": 312123908,
                                                                         "source": "profiles/cfg4_decode_hbm_traffic.md"},
-                    ("cfg3-prefill", "power", "fused", 8): {"expand_mfma": 690047714,
-                                                            "shrink_mfma": 209097830 + 7899366,
+                    ("cfg3-prefill", "power", "fused", 8): {"expand_mfma": 659094527,
+                                                            "shrink_mfma": 206237601 + 7616027,
                                                             "source": "profiles/cfg3_prefill_hbm_traffic.md"},
-                    ("cfg5-mixed", "power", "fused", 8): {"expand_vec+mfma": 2804682598 + 1373456197,
-                                                          "shrink_vec+mfma": 768431054 + 36335013 + 1299029045,
+                    ("cfg5-mixed", "power", "fused", 8): {"expand_vec+mfma": 2434973348 + 1373480688,
+                                                          "shrink_vec+mfma": 762422317 + 36343393 + 1299132088,
                                                           "source": "profiles/cfg5_mixed_hbm_traffic.md"}}
 MFMA_PEAK_TFLOPS = 2500.0      # dense fp16 / bf16 MFMA, published
 

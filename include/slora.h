@@ -216,12 +216,16 @@ int32_t slora_plan_destroy(slora_plan *plan);
  * Schedule statistics, for tests and tuning: fills out[0..n) (n <= SLORA_PLAN_INFO_N) with
  *  [0] tokens with an adapter of rank > 0   [1] adapter groups        [2] groups on the vector path
  *  [3] groups on the MFMA path              [4] vector shrink items   [5] vector expand items
+ *      ([2], [3]: of every call; a plan with MFMA items although [3] is 0 holds both families'
+ *      lists, and applies to fp32 y may run its large groups on the MFMA kernels)
  *  [6] MFMA shrink items                    [7] MFMA expand tiles     [8] v row stride (floats)
  *      (a workgroup walks several)              (32 tokens x 256 columns)
  *  [9] sum over groups of rank (pages of A read per slot)
- *  [10] MFMA shrink tiles whose H range is shared out over several workgroups
+ *  [10] MFMA shrink tiles whose H range is shared out over several workgroups (of a plan that
+ *       holds both families' lists: all tiles)
  *  [11] bytes of v scratch one slot of an apply needs
- *  [12] adapter groups an apply serves with the one-launch decode kernel
+ *  [12] adapter groups an apply serves with the one-launch decode kernel, a workgroup per group (not
+ *       the kernel for very small batches, which is chosen call by call)
  */
 #define SLORA_PLAN_INFO_N 13
 int32_t slora_plan_info(const slora_plan *plan, int64_t *out, int32_t n);
@@ -246,7 +250,8 @@ int32_t slora_plan_info(const slora_plan *plan, int64_t *out, int32_t n);
 int32_t slora_lora_apply(slora_plan *plan, int32_t slot, const void *x, float *y, void *stream);
 
 /*
- * The same for n slots (1 <= n <= SLORA_MAX_MULTI) in one pair of launches, e.g. the q, k, v
+ * The same for n slots (1 <= n <= SLORA_MAX_MULTI) in the launches of one (one to six kernels,
+ * each over all slots), e.g. the q, k, v
  * projections of a layer.  slots, x, y: HOST arrays of n entries; x[k] / y[k] are DEVICE
  * pointers as in slora_lora_apply (entries of x may be equal; entries of y must not overlap; a
  * y[k] in 16 bits may be the buffer of x[k], updated in place, if no other entry of x names it).

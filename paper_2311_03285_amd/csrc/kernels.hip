@@ -520,10 +520,10 @@ __global__ __launch_bounds__(1024) void lora_vec_fused_kernel(const Item *__rest
 // itself.  Its eight wavefronts share out the A pages and leave v in LDS; the first four then do the
 // rank-split expand, whose B rows and y were requested before the first A page.  A is read once per 512
 // columns - from L2 but for the first.  What bounds such a batch is the chain of dependent round trips
-// and the two launches: one token of rank 16, H = 4096, 4 slots 9.8 -> 6.2 us per call, rank 8 10.4 -> 6.0.
-// Beyond a page or two per wavefront and token the repeated A reads cost more than the launch (rank 32
-// 9.9 / 9.7, ten groups of rank 16 and up to four tokens 11.3 / 12.6, H = 8192 9.1 / 10.1): see the plan's
-// rule.  Sixteen wavefronts (128 registers each, B rows through LDS) were slower: 7.1 us.
+// and the two launches: one token of rank 8 or 16, H = 4096, 4 slots 9.6 -> 6.6 us per call, rank 32 9.4 -> 7.8.
+// Beyond a page or two per wavefront and token the repeated A reads cost more than the launch (ten groups
+// of rank 16 and up to four tokens 11.3 / 12.6, H = 8192 9.1 / 10.1): see the plan's
+// rule.  Sixteen wavefronts (128 registers each, B rows through LDS) were slower, 0.5 to 0.9 us.
 // The first column range's workgroup also leaves v in memory, where a later expand expects it.
 // Results are bit-identical to the two kernels'.
 // ---------------------------------------------------------------------------------------
@@ -1280,8 +1280,7 @@ __global__ __launch_bounds__(kMfmaThreads) void join_shares_kernel(const MsItem 
 // 24675 tokens (4 slots, H = 4096, binary16 y): a workgroup per tile, everything read per tile
 // 132 / 110 / 395 us; runs of tiles with B in registers 130 / 116 / 345; V shared through LDS
 // 131 / 97 / 340; y moved with streaming (non-temporal) loads AND stores 111 / 83 / 311 us = 5.6 / 4.2 /
-// 5.3 TB/s of y, B and V (streaming on one side only changes nothing: y otherwise displaces, line by line,
-// what the other side still needs in L2).  Workgroups per launch 1024-4096 measure alike, fewer than
+// 5.3 TB/s of y, B and V (streaming on one side only changes nothing).  Workgroups per launch 1024-4096 measure alike, fewer than
 // 1024 and runs of 32 tiles gain nothing; three wavefronts per SIMD need registers that spill (+25 %).
 // ---------------------------------------------------------------------------------------
 constexpr int kSlabStride = 20; // dwords per column in LDS: 16 (32 ranks) + 4 pad, keeps 16-byte alignment

@@ -324,7 +324,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         plan->T_act = (int32_t)plan->tok_idx.size();
         // Small batches in one launch, every workgroup computing v for itself: while that is a page or two per
         // wavefront and token.  Measured, us per call, two kernels / one: rank x H x tokens of the largest item
-        // 32 Ki 10.4 / 6.0, 64 Ki 9.8 / 6.2, 128 Ki 11.8 / 10.0 (19 groups of rank 8), 10.5 / 10.0 (H = 2048),
+        // 32 Ki and 64 Ki 9.6 / 6.6 (one token of 4 slots), 128 Ki 11.8 / 10.0 (19 groups of rank 8), 10.5 / 10.0 (H = 2048),
         // 9.8 / 9.3 (7 groups of rank 16); 256 Ki 11.3 / 12.6; H = 8192 (two blocks of loads per page) 9.1 / 10.1.
         // Only calls of at most 256 workgroups: a larger launch streams the A pages eight times.
         plan->max_expand_tok = 0;
