@@ -26,8 +26,8 @@
  *     (Eq. 2 has none): fold any scale into B before upload.
  *     Range of v: adapter groups that run on the matrix cores (prefill segments, Sec. 5.3) hand
  *     v to the second product as 16-bit pieces whose sum is the fp32 value.  For bfloat16 pools
- *     that holds over the whole fp32 range.  For binary16 pools every token row of v is scaled
- *     by a power of two first (exponent clamped to [-24, 40]): rows whose largest |v| (per 128
+ *     that holds for |v| of 2^-109 and more (smaller ones keep an absolute error of 2^-133).  For
+ *     binary16 pools every token row of v is scaled by a power of two first (exponent clamped to [-24, 40]): rows whose largest |v| (per 128
  *     ranks) lies in [2^-42, 2^35) are carried to 22 bits relative to that largest value, like
  *     the fp32 sums they come from; smaller rows keep an absolute error of 2^-64; from 2^40 on
  *     the pieces overflow and y becomes inf/NaN where the vector kernels and a plain fp32
