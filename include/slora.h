@@ -329,8 +329,9 @@ int32_t slora_lora_shrink_expand(slora_pool *pool, int32_t slot, const void *x,
  *                      32-token tiles in the batch (default 32: fewer tiles cannot fill the GPU
  *                      and run faster on the vector kernels - except where those, in all slots of a
  *                      call, would read 30 MB of pages again, 128 MB beside groups of few tokens:
- *                      applies to fp32 y then take the MFMA kernels all the same, with shorter
- *                      shares of H; 16-bit y and the two-stage calls never do)
+ *                      applies to fp32 y then take the MFMA kernels all the same, with shares of H
+ *                      of 32 KiB and 256 elements (or what the next two options say, if that is
+ *                      less); 16-bit y and the two-stage calls never do)
  *   "mfma_split_bytes" the MFMA shrink hands the H range of a tile (up to 128 tokens x up to 128 ranks)
  *                      to several workgroups, each taking about this many bytes of x and page rows
  *                      (default 1 MiB); their partial sums are added in a fixed order by a small
