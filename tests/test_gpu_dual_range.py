@@ -127,3 +127,23 @@ def test_bfloat16_sums_of_extreme_size(log2):
     x, A, B = g.standard_normal((150, H)), g.standard_normal((64, H)), g.standard_normal((64, H))
     x, A, B = (quantized(a * 2.0**e, slora.BF16) for a, e in ((x, log2), (A, log2), (B, -2 * log2)))
     against_the_vector_kernels(slora.BF16, x, A, B)
+
+
+@pytest.mark.parametrize("dtype", [slora.F16, slora.BF16])
+@pytest.mark.parametrize("rank", [60, 128, 160])
+def test_16_bit_expand_after_an_fp32_apply(dtype, rank):
+    """It reads v as that apply left it, in pieces.  Binary16: the sum from zero, added to y and rounded once, which is
+    the fp32 result added and rounded; bfloat16 starts from y, so a few of the sums round differently."""
+    g = np.random.default_rng(rank + 7)
+    T, tt = 150, torch.float16 if dtype == slora.F16 else torch.bfloat16
+    x, A, B = (quantized(a, dtype) for a in (g.standard_normal((T, H)), g.standard_normal((rank, H)) / 64, g.standard_normal((rank, H)) / 8))
+    b = Batch(dtype, x, A, B, np.zeros((T, H)))
+    delta = torch.from_numpy(b.apply()).cuda()
+    y = torch.from_numpy(g.standard_normal((T, H)).astype(np.float32)).cuda().to(tt)
+    want = (y.float() + delta).to(tt)
+    slora.lora_expand_y16(b.plan, [0], [y.data_ptr()])
+    torch.cuda.synchronize()
+    b.close()
+    differ = (y != want).float().mean().item()
+    assert differ <= (0.0 if dtype == slora.F16 else 1e-3), differ
+    assert (y.float() - want.float()).abs().max().item() <= 2.0**-4
