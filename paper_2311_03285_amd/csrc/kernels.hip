@@ -141,22 +141,32 @@ struct Y8<DT, true> {
 // the steps 32 to 8 the sums repeat every 8 lanes, so a rotation by 4 brings what ^ 4 would - and quad permutes.
 // Six dependent exchanges through LDS were a part of every decode kernel's chain: 32 tokens of ranks 8-64,
 // H = 4096, 13.8 -> 12.9 us per call, 39 tokens of rank 32, H = 824, 18.2 -> 15.5.  The sums are the same bits.
-__device__ __forceinline__ float wave_sum(float v)
+__device__ __forceinline__ float row_sum(float v) // over 16 lanes
 {
-    {
-        const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-        v = __uint_as_float(s[0]) + __uint_as_float(s[1]);
-    }
-    {
-        const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
-        v = __uint_as_float(s[0]) + __uint_as_float(s[1]);
-    }
     constexpr int kRor8 = 0x128, kRor4 = 0x124, kXor2 = 0x4e, kXor1 = 0xb1; // DPP controls
     v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), kRor8, 0xf, 0xf, true));
     v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), kRor4, 0xf, 0xf, true));
     v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), kXor2, 0xf, 0xf, true));
     v += __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), kXor1, 0xf, 0xf, true));
     return v;
+}
+__device__ __forceinline__ float wave_sum(float v)
+{
+    const auto s = __builtin_amdgcn_permlane32_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    v = __uint_as_float(s[0]) + __uint_as_float(s[1]);
+    const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v), __float_as_uint(v), false, false);
+    return row_sum(__uint_as_float(r[0]) + __uint_as_float(r[1]));
+}
+
+// Sums over the lanes of four values at a time: row r of 16 lanes (in every lane of it) gets the sum of a, c, b, d
+__device__ __forceinline__ float wave_sum4(float a, float b, float c, float d)
+{
+    const auto ab = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    const auto cd = __builtin_amdgcn_permlane32_swap(__float_as_uint(c), __float_as_uint(d), false, false);
+    const float x = __uint_as_float(ab[0]) + __uint_as_float(ab[1]); // lanes 0 .. 31: a, others: b
+    const float y = __uint_as_float(cd[0]) + __uint_as_float(cd[1]);
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(y), false, false);
+    return row_sum(__uint_as_float(s[0]) + __uint_as_float(s[1]));
 }
 
 // 64 lanes x 16 bytes from per-lane addresses to 1 KiB of LDS at a wave-uniform address
@@ -278,22 +288,13 @@ __device__ __forceinline__ void shrink_vec_core(const int32_t *__restrict__ pa, 
     }
 }
 
-template <int DT, int U>
-__global__ __launch_bounds__(kShrinkThreads) void shrink_vec_kernel(const Item *__restrict__ items,
-                                                                     const int32_t *__restrict__ arena,
-                                                                     const uint16_t *__restrict__ pool,
-                                                                     const int32_t *__restrict__ tok_idx, int H,
-                                                                     int v_stride, MultiArgs args)
+// an item of the vector shrink: pa is its first entry of the A list, put(t, j, s) as above
+template <int DT, int U, class Put>
+__device__ __forceinline__ void shrink_vec_item(const Item &it, const int32_t *__restrict__ pa, const uint16_t *__restrict__ pool,
+                                                const uint16_t *__restrict__ x, const int32_t *__restrict__ tok_idx, int H,
+                                                u32x4 *xs, Put put) // xs: [ntok][H/8]
 {
-    extern __shared__ u32x4 xs[]; // [ntok][H/8]
-    // slots vary fastest, so workgroups are dispatched in the order of the work list (by rank)
-    const int cs = blockIdx.x % args.n;
-    const Item it = items[blockIdx.x / args.n];
-    const uint16_t *__restrict__ x = static_cast<const uint16_t *>(args.x[cs]);
-    float *__restrict__ v = args.v[cs];
-    const int nch = H >> 3;
-    const int tid = threadIdx.x;
-    const int32_t *pa = arena + it.arena_off + (int64_t)args.slot[cs] * 2 * it.rank + it.a;
+    const int nch = H >> 3, tid = threadIdx.x;
     shrink_vec_core<DT, U>(
         pa, it.b, it.ntok, tid / kWave, kShrinkWaves, tid & (kWave - 1), pool, H, xs,
         [&]() {
@@ -303,7 +304,24 @@ __global__ __launch_bounds__(kShrinkThreads) void shrink_vec_kernel(const Item *
             }
             __syncthreads();
         },
-        [&](int t, int j, float s) { v[(int64_t)(it.pos0 + t) * v_stride + it.a + j] = s; });
+        put);
+}
+
+template <int DT, int U>
+__global__ __launch_bounds__(kShrinkThreads) void shrink_vec_kernel(const Item *__restrict__ items,
+                                                                     const int32_t *__restrict__ arena,
+                                                                     const uint16_t *__restrict__ pool,
+                                                                     const int32_t *__restrict__ tok_idx, int H,
+                                                                     int v_stride, MultiArgs args)
+{
+    extern __shared__ u32x4 xs[];
+    // slots vary fastest, so workgroups are dispatched in the order of the work list (by rank)
+    const int cs = blockIdx.x % args.n;
+    const Item it = items[blockIdx.x / args.n];
+    float *__restrict__ v = args.v[cs];
+    shrink_vec_item<DT, U>(it, arena + it.arena_off + (int64_t)args.slot[cs] * 2 * it.rank + it.a, pool,
+                           static_cast<const uint16_t *>(args.x[cs]), tok_idx, H, xs,
+                           [&](int t, int j, float s) { v[(int64_t)(it.pos0 + t) * v_stride + it.a + j] = s; });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -317,23 +335,14 @@ __global__ __launch_bounds__(kShrinkThreads) void shrink_vec_kernel(const Item *
 // wave-uniform and comes in through scalar loads); then one read-modify-write of y per token,
 // whose loads are issued before the row loop when there are at most two tokens.
 // ---------------------------------------------------------------------------------------
-//
-// SPLIT (small batches, where a launch has fewer workgroups than the GPU can hold): the four
-// wavefronts of a workgroup own the SAME 512 columns and take every fourth block of ranks, which
-// cuts the chain of dependent round trips of a high-rank item by four; their partial sums meet
-// in LDS (fixed order) and wavefront 0 does the read-modify-write of y.
-constexpr int kSplitWaves = 4;
-
-template <int DT, bool Y16, int TOK, int U, bool PREFETCH_Y, bool SPLIT>
+template <int DT, bool Y16, int TOK, int U, bool PREFETCH_Y>
 __device__ __forceinline__ void expand_vec_body(const Item &it, const int32_t *__restrict__ pb,
                                                 const uint16_t *__restrict__ pool,
                                                 const int32_t *__restrict__ tok_idx, int H, int v_stride,
                                                 void *__restrict__ y, const float *v, int col, bool live,
-                                                float *red, int v_pos0 = -1)
+                                                int v_pos0 = -1)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    const int wave = SPLIT ? (int)(threadIdx.x / kWave) : 0;
-    constexpr int kStep = SPLIT ? kSplitWaves : 1;
     const float *vrow = v + (int64_t)(v_pos0 < 0 ? it.pos0 : v_pos0) * v_stride; // row of v of the item's first token
     float acc[TOK][8];
 #pragma unroll
@@ -346,7 +355,7 @@ __device__ __forceinline__ void expand_vec_body(const Item &it, const int32_t *_
 #pragma unroll
     for (int t = 0; t < TOK; ++t) {
         yoff[t] = (int64_t)tok_idx[it.pos0 + (t < it.ntok ? t : 0)] * H + col;
-        if (PREFETCH_Y && t < it.ntok && live && wave == 0) yv[t].load(y, yoff[t]);
+        if (PREFETCH_Y && t < it.ntok && live) yv[t].load(y, yoff[t]);
     }
 
     const int col_ld = live ? col : it.a;
@@ -393,28 +402,10 @@ __device__ __forceinline__ void expand_vec_body(const Item &it, const int32_t *_
         };
 
         u32x4 w[U];
-        for (int b = wave; b < nb; b += kStep) {
+        for (int b = 0; b < nb; ++b) {
             load_block(b, w);
             consume(b, w);
         }
-    }
-
-    if constexpr (SPLIT) {
-        // red[wave - 1][t][e][lane]; every wavefront of the workgroup reaches both barriers
-        if (wave > 0) {
-#pragma unroll
-            for (int t = 0; t < TOK; ++t)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) red[(((wave - 1) * TOK + t) * 8 + e) * kWave + lane] = acc[t][e];
-        }
-        __syncthreads();
-        if (wave > 0) return;
-#pragma unroll
-        for (int k = 0; k < kSplitWaves - 1; ++k)
-#pragma unroll
-            for (int t = 0; t < TOK; ++t)
-#pragma unroll
-                for (int e = 0; e < 8; ++e) acc[t][e] += red[((k * TOK + t) * 8 + e) * kWave + lane];
     }
 
     if (!live) return;
@@ -445,34 +436,12 @@ __global__ __launch_bounds__(512) void expand_vec_kernel(const Item *__restrict_
     const bool live = col < col_end;
     const int32_t *pb = arena + it.arena_off + (int64_t)args.slot[cs] * 2 * it.rank + it.rank;
     if (it.ntok == 1)
-        expand_vec_body<DT, Y16, 1, 8, true, false>(it, pb, pool, tok_idx, H, v_stride, args.y[cs], args.v[cs], col, live, nullptr);
+        expand_vec_body<DT, Y16, 1, 8, true>(it, pb, pool, tok_idx, H, v_stride, args.y[cs], args.v[cs], col, live);
     else if (it.ntok == 2)
-        expand_vec_body<DT, Y16, 2, 8, true, false>(it, pb, pool, tok_idx, H, v_stride, args.y[cs], args.v[cs], col, live, nullptr);
+        expand_vec_body<DT, Y16, 2, 8, true>(it, pb, pool, tok_idx, H, v_stride, args.y[cs], args.v[cs], col, live);
     else
-        expand_vec_body<DT, Y16, kExpandTok, 8, false, false>(it, pb, pool, tok_idx, H, v_stride, args.y[cs], args.v[cs], col, live, nullptr);
+        expand_vec_body<DT, Y16, kExpandTok, 8, false>(it, pb, pool, tok_idx, H, v_stride, args.y[cs], args.v[cs], col, live);
 }
-
-template <int DT, bool Y16>
-__global__ __launch_bounds__(kSplitWaves *kWave) void expand_vec_split_kernel(const Item *__restrict__ items,
-                                                                              const int32_t *__restrict__ arena,
-                                                                              const uint16_t *__restrict__ pool,
-                                                                              const int32_t *__restrict__ tok_idx,
-                                                                              int H, int v_stride, MultiArgs args)
-{
-    __shared__ float red[(kSplitWaves - 1) * kExpandTok * 8 * kWave];
-    const int cs = blockIdx.x % args.n;
-    const Item it = items[blockIdx.x / args.n];
-    const int col = it.a + (int)(threadIdx.x & (kWave - 1)) * 8; // all four wavefronts: the same 512 columns
-    const bool live = col < it.a + it.b;
-    const int32_t *pb = arena + it.arena_off + (int64_t)args.slot[cs] * 2 * it.rank + it.rank;
-    if (it.ntok == 1)
-        expand_vec_body<DT, Y16, 1, 16, true, true>(it, pb, pool, tok_idx, H, v_stride, args.y[cs], args.v[cs], col, live, red);
-    else if (it.ntok == 2)
-        expand_vec_body<DT, Y16, 2, 16, true, true>(it, pb, pool, tok_idx, H, v_stride, args.y[cs], args.v[cs], col, live, red);
-    else
-        expand_vec_body<DT, Y16, kExpandTok, 8, false, true>(it, pb, pool, tok_idx, H, v_stride, args.y[cs], args.v[cs], col, live, red);
-}
-
 
 // ---------------------------------------------------------------------------------------
 // decode path, both stages in ONE launch: a workgroup = one adapter group of at most kExpandTok
@@ -522,11 +491,11 @@ __global__ __launch_bounds__(1024) void lora_vec_fused_kernel(const Item *__rest
         Item strip = it;
         strip.a = c0;   // lanes beyond H read the strip's first column and are dropped at the store
         if (it.ntok == 1)
-            expand_vec_body<DT, Y16, 1, 8, true, false>(strip, pb, pool, tok_idx, H, v_pad, args.y[cs], vl, col, live, nullptr, 0);
+            expand_vec_body<DT, Y16, 1, 8, true>(strip, pb, pool, tok_idx, H, v_pad, args.y[cs], vl, col, live, 0);
         else if (it.ntok == 2)
-            expand_vec_body<DT, Y16, 2, 8, true, false>(strip, pb, pool, tok_idx, H, v_pad, args.y[cs], vl, col, live, nullptr, 0);
+            expand_vec_body<DT, Y16, 2, 8, true>(strip, pb, pool, tok_idx, H, v_pad, args.y[cs], vl, col, live, 0);
         else
-            expand_vec_body<DT, Y16, kExpandTok, 8, false, false>(strip, pb, pool, tok_idx, H, v_pad, args.y[cs], vl, col, live, nullptr, 0);
+            expand_vec_body<DT, Y16, kExpandTok, 8, false>(strip, pb, pool, tok_idx, H, v_pad, args.y[cs], vl, col, live, 0);
     }
 }
 
@@ -657,6 +626,331 @@ __global__ __launch_bounds__(kSmallWaves *kWave) void lora_vec_small_kernel(cons
         small_body<DT, Y16, 2>(it, pa, pool, x, tok_idx, H, v_stride, args.y[cs], args.v[cs], smem);
     else
         small_body<DT, Y16, kExpandTok>(it, pa, pool, x, tok_idx, H, v_stride, args.y[cs], args.v[cs], smem);
+}
+
+// ---------------------------------------------------------------------------------------
+// decode path, shrink for groups of many tokens: an item is up to kGangTok tokens x kGangPages pages of one adapter.
+// The rows are walked in pieces of kGangPiece elements; a wavefront has up to four pages, requested together with
+// the piece of x that goes to LDS, and keeps a sum per page and token, so that a read of x from LDS serves four
+// pages and a pair of token and page costs little more than a third of the row bytes that an item of 4 x 4 reads.
+// Every lane adds the same products in the same order as there and the lanes' sums meet in the same tree:
+// bit-identical.  142 tokens of ranks 5-130, H = 4096, 2 slots: 22 -> 13.7 us; 960 tokens of rank 8, H = 2928, 3 slots:
+// 15.2 -> 13.1; 173 tokens of ranks 8-128, H = 1128, 3 slots: 12.4 -> 9.6.  Tried: 8 x 16 items on the code of
+// the 4 x 4 ones (a read of x from LDS per page) 21-24 us on the first of these; pieces of 1024 elements, two in flight, 15;
+// a workgroup for a quarter of an item (those without work still claim their LDS first: 10.7 -> 27 us where three of
+// four had none).
+// ---------------------------------------------------------------------------------------
+constexpr int kGangPiece = 2048;
+constexpr int kGangChunks = kGangPiece / 8;
+static_assert(kGangChunks == kShrinkThreads, "a thread copies one 16-byte chunk of a row's piece");
+constexpr int kGangWavePages = kGangPages / kShrinkWaves;
+constexpr size_t kGangLds = (size_t)kGangTok * kGangPiece * 2;
+
+template <int DT, class Put>
+__device__ __forceinline__ void shrink_gang(const Item &it, const int32_t *__restrict__ pa, const uint16_t *__restrict__ pool,
+                                            const uint16_t *__restrict__ x, const int32_t *__restrict__ tok_idx, int H,
+                                            u32x4 *xs, Put put)
+{
+    const int n_pages = it.b;
+    const int tid = threadIdx.x, lane = tid & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(tid / kWave);
+    const int nch = H >> 3;
+    const u32x4 zero = u32x4{0u, 0u, 0u, 0u};
+    const u32x4 *page[kGangWavePages];
+#pragma unroll
+    for (int i = 0; i < kGangWavePages; ++i) // pages wave, wave + 4, ... of the item's
+        page[i] = reinterpret_cast<const u32x4 *>(pool + (int64_t)pa[min(wave + kShrinkWaves * i, n_pages - 1)] * H);
+    const u32x4 *row[kGangTok];
+#pragma unroll
+    for (int t = 0; t < kGangTok; ++t)
+        row[t] = reinterpret_cast<const u32x4 *>(x + (int64_t)tok_idx[it.pos0 + min(t, it.ntok - 1)] * H);
+    float acc[kGangWavePages][kGangTok];
+#pragma unroll
+    for (int i = 0; i < kGangWavePages; ++i)
+#pragma unroll
+        for (int t = 0; t < kGangTok; ++t) acc[i][t] = 0.f;
+    for (int c0 = 0; c0 < nch; c0 += kGangChunks) {
+        u32x4 xr[kGangTok], w[kGangWavePages][4];
+#pragma unroll
+        for (int t = 0; t < kGangTok; ++t)
+            if (t < it.ntok) xr[t] = c0 + tid < nch ? row[t][c0 + tid] : zero;
+#pragma unroll
+        for (int i = 0; i < kGangWavePages; ++i)
+            if (wave + kShrinkWaves * i < n_pages) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const int c = c0 + u * kWave + lane;
+                    w[i][u] = c < nch ? page[i][c] : zero;
+                }
+            }
+        __syncthreads(); // the piece before this one has been read
+#pragma unroll
+        for (int t = 0; t < kGangTok; ++t)
+            if (t < it.ntok) xs[t * kGangChunks + tid] = xr[t];
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < kGangTok; ++t)
+            if (t < it.ntok) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const u32x4 xv = xs[t * kGangChunks + u * kWave + lane];
+#pragma unroll
+                    for (int i = 0; i < kGangWavePages; ++i)
+                        if (wave + kShrinkWaves * i < n_pages) acc[i][t] = dot8<DT>(w[i][u], xv, acc[i][t]);
+                }
+            }
+    }
+    const int r = lane >> 4, t_of_row = r == 1 ? 2 : r == 2 ? 1 : r; // see wave_sum4
+#pragma unroll
+    for (int i = 0; i < kGangWavePages; ++i) {
+        const int j = wave + kShrinkWaves * i;
+        if (j < n_pages) {
+#pragma unroll
+            for (int t = 0; t < kGangTok; t += 4) {
+                if (t < it.ntok) {
+                    const float s = wave_sum4(acc[i][t], acc[i][t + 1], acc[i][t + 2], acc[i][t + 3]);
+                    if ((lane & 15) == 0 && t + t_of_row < it.ntok) put(t + t_of_row, j, s);
+                }
+            }
+        }
+    }
+}
+
+// Workgroup `no` of a slot: the items of this kernel, then the vector-shrink items of the groups that are not in them.
+struct GangArgs {
+    const Item *items, *plain;
+    unsigned n_items;
+};
+template <int DT, int U, class Put>
+__device__ __forceinline__ void shrink_crowd(const GangArgs &g, unsigned no, const int32_t *__restrict__ arena, int slot,
+                                             const uint16_t *__restrict__ pool, const uint16_t *__restrict__ x,
+                                             const int32_t *__restrict__ tok_idx, int H, u32x4 *smem, Put put)
+{
+    const bool gang = no < g.n_items;
+    const Item it = gang ? g.items[no] : g.plain[no - g.n_items];
+    const int32_t *pa = arena + it.arena_off + (int64_t)slot * 2 * it.rank + it.a;
+    auto at = [&](int t, int j, float s) { put(it.pos0 + t, it.a + j, s); };
+    if (gang)
+        shrink_gang<DT>(it, pa, pool, x, tok_idx, H, smem, at);
+    else
+        shrink_vec_item<DT, U>(it, pa, pool, x, tok_idx, H, smem, at);
+}
+
+template <int DT, int U>
+__global__ __launch_bounds__(kShrinkThreads) void shrink_gang_kernel(GangArgs g, const int32_t *__restrict__ arena,
+                                                                         const uint16_t *__restrict__ pool,
+                                                                      const int32_t *__restrict__ tok_idx, int H,
+                                                                      int v_stride, MultiArgs args)
+{
+    extern __shared__ u32x4 smem[]; // a piece of kGangTok rows of x, or the rows of a vector-shrink item
+    const int cs = blockIdx.x % args.n;
+    float *v = args.v[cs];
+    shrink_crowd<DT, U>(g, blockIdx.x / args.n, arena, args.slot[cs], pool, static_cast<const uint16_t *>(args.x[cs]), tok_idx, H,
+                        smem, [&](int pos, int j, float s) { v[(int64_t)pos * v_stride + j] = s; });
+}
+
+// ---------------------------------------------------------------------------------------
+// decode path, expand for batches whose launch has fewer workgroups than the GPU can hold ("rank-split"): a
+// workgroup = 512 columns (a lane owns 8) of some tokens of one adapter group.  A sum over the ranks is made of the
+// sums of four rows of blocks - blocks of 8 ranks, 16 where a token is one of at most two left over from the
+// group's fours; row w has the blocks w, w + 4, ... - which are added in the order of w.  Who forms them does not matter:
+//   up to kOwnRanks ranks: a wavefront keeps all B rows of its columns in registers and forms whole sums, of
+//     every fourth token of the workgroup's;
+//   more: wavefront w forms row w for four tokens, the parts meet in LDS, and wavefront t finishes token t.
+// B rows, page numbers and y are requested before v is needed.  Bound by the chain of round trips in small calls, by
+// the fp32 additions and 16-bit conversions where groups have many tokens.  Before, every item was four tokens with
+// its ranks shared out and wavefront 0 finished them all: 45 tokens of ranks 3-100, H = 3080, 3 slots 13.7 -> 9.4 us;
+// 51 tokens of ranks 30-130, H = 1168, 4 slots 15.2 -> 9.2; 142 tokens of ranks 5-130, H = 4096, 2 slots 17.0 -> 13.5; 376
+// tokens of rank 1, H = 4096, 8 slots 39.5 -> 22.6, with 16 tokens per workgroup 15.8; 960 tokens of rank 8, H = 2928, 3 slots
+// 31.4 -> 16.0 -> 11.1.  kOwnRanks = 16 (fewer registers, four workgroups per compute unit instead of three): up to 20 %
+// slower, half as fast on groups of many tokens (spills).
+// ---------------------------------------------------------------------------------------
+// v of ranks w0 + lane, where `mine`, of tokens t0 .. t0 + TOK - 1 of an item
+template <int DT, int TOK>
+struct StoredV {
+    const float *v;
+    __device__ __forceinline__ void get(const Item &it, int t0, int w0, bool mine, int v_stride, float (&out)[TOK])
+    {
+        const float *at = v + (int64_t)(it.pos0 + t0) * v_stride + w0 + (threadIdx.x & (kWave - 1));
+#pragma unroll
+        for (int t = 0; t < TOK; ++t) out[t] = t0 + t < it.ntok && mine ? at[(int64_t)t * v_stride] : 0.f;
+    }
+};
+// keeps the compiler from widening rows once and holding them at twice the size
+template <int N>
+__device__ __forceinline__ void stay_narrow(u32x4 (&w)[N])
+{
+#pragma unroll
+    for (int j = 0; j < N; ++j) asm volatile("" : "+v"(w[j]));
+}
+
+// R: ranks in registers.  Tokens t0, t0 + 4, ... of the item.
+template <int DT, bool Y16, int R, class V>
+__device__ __forceinline__ void expand_own(const Item &it, int t0, const int32_t *__restrict__ pb,
+                                           const uint16_t *__restrict__ pool, const int32_t *__restrict__ tok_idx, int H,
+                                           int v_stride, void *__restrict__ y, V from)
+{
+    if (t0 >= it.ntok) return;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int col = it.a + lane * 8;
+    const bool live = col < it.a + it.b;
+    const int col_ld = live ? col : it.a; // lanes beyond the item's columns are dropped at the store
+    const int pwin = lane < it.rank ? pb[lane] : 0;
+    u32x4 w[R];
+#pragma unroll
+    for (int j = 0; j < R; ++j) { // ranks beyond the last: the last one's row meets v = 0
+        const int64_t page = __builtin_amdgcn_readlane(pwin, min(j, it.rank - 1));
+        w[j] = *reinterpret_cast<const u32x4 *>(pool + page * H + col_ld);
+    }
+    const int left = it.ntok & 3; // one or two: their blocks are of 16 ranks
+    for (int t = t0; t < it.ntok; t += kSplitWaves) {
+        Y8<DT, Y16> yv;
+        const int64_t yoff = (int64_t)tok_idx[it.pos0 + t] * H + col;
+        if (live) yv.load(y, yoff);
+        float v[1];
+        from.get(it, t, 0, lane < it.rank, v_stride, v);
+        stay_narrow(w);
+        const bool by16 = left > 0 && left <= 2 && t >= it.ntok - left;
+        float sum[8], acc[8];
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sum[e] = acc[e] = 0.f;
+#pragma unroll
+        for (int b = 0; b < R / 8; ++b) {
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int j = 8 * b + u;
+                const float vv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[0]), j));
+                float f[8];
+                widen2<DT>(w[j].x, f[0], f[1]);
+                widen2<DT>(w[j].y, f[2], f[3]);
+                widen2<DT>(w[j].z, f[4], f[5]);
+                widen2<DT>(w[j].w, f[6], f[7]);
+#pragma unroll
+                for (int e = 0; e < 8; ++e) acc[e] = fmaf(vv, f[e], acc[e]);
+            }
+            if (!by16 || (b & 1) || b == R / 8 - 1) { // the end of a block
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    sum[e] += acc[e];
+                    acc[e] = 0.f;
+                }
+            }
+        }
+        if (live) yv.add_store(y, yoff, sum);
+    }
+}
+
+// An item of at most TOK tokens; UB: ranks per block
+template <int DT, bool Y16, int TOK, int UB, class V>
+__device__ __forceinline__ void expand_shared(const Item &it, const int32_t *__restrict__ pb,
+                                              const uint16_t *__restrict__ pool, const int32_t *__restrict__ tok_idx,
+                                              int H, int v_stride, void *__restrict__ y, V from, float *red)
+{
+    constexpr int NB = 16 / UB; // blocks of a wavefront in a window of 64 ranks
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int col = it.a + lane * 8;
+    const bool live = col < it.a + it.b;
+    const int col_ld = live ? col : it.a;
+    const bool finishes = wave < it.ntok; // token `wave`
+    Y8<DT, Y16> yv;
+    const int64_t yoff = (int64_t)tok_idx[it.pos0 + (finishes ? wave : 0)] * H + col;
+    if (finishes && live) yv.load(y, yoff);
+    float acc[TOK][8];
+#pragma unroll
+    for (int t = 0; t < TOK; ++t)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[t][e] = 0.f;
+    for (int w0 = 0; w0 < it.rank && wave * UB < it.rank - w0; w0 += kWave) {
+        const int wr = min(kWave, it.rank - w0);
+        const int pwin = lane < wr ? pb[w0 + lane] : 0;
+        u32x4 w[NB][UB];
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int j0 = (wave + kSplitWaves * i) * UB;
+            if (i == 0 || j0 < wr) {
+#pragma unroll
+                for (int u = 0; u < UB; ++u) { // ranks beyond the last: the last one's row meets v = 0
+                    const int64_t page = __builtin_amdgcn_readlane(pwin, min(j0 + u, wr - 1));
+                    w[i][u] = *reinterpret_cast<const u32x4 *>(pool + page * H + col_ld);
+                }
+            }
+        }
+        float v[TOK]; // rank w0 + lane, if it is in one of this wavefront's blocks
+        from.get(it, 0, w0, lane < wr && lane / UB % kSplitWaves == wave, v_stride, v);
+#pragma unroll
+        for (int i = 0; i < NB; ++i) {
+            const int j0 = (wave + kSplitWaves * i) * UB;
+            if (i == 0 || j0 < wr) {
+#pragma unroll
+                for (int u = 0; u < UB; ++u) {
+                    float f[8];
+                    widen2<DT>(w[i][u].x, f[0], f[1]);
+                    widen2<DT>(w[i][u].y, f[2], f[3]);
+                    widen2<DT>(w[i][u].z, f[4], f[5]);
+                    widen2<DT>(w[i][u].w, f[6], f[7]);
+#pragma unroll
+                    for (int t = 0; t < TOK; ++t) {
+                        if (t < it.ntok) {
+                            const float vv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[t]), j0 + u));
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) acc[t][e] = fmaf(vv, f[e], acc[t][e]);
+                        }
+                    }
+                }
+            }
+        }
+    }
+    // red[wave][t][e][lane]
+#pragma unroll
+    for (int t = 0; t < TOK; ++t)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) red[((wave * TOK + t) * 8 + e) * kWave + lane] = acc[t][e];
+    __syncthreads();
+    if (!finishes) return;
+    float d[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+        d[e] = red[(wave * 8 + e) * kWave + lane];
+#pragma unroll
+        for (int k = 1; k < kSplitWaves; ++k) d[e] += red[((k * TOK + wave) * 8 + e) * kWave + lane];
+    }
+    if (live) yv.add_store(y, yoff, d);
+}
+
+// An item: up to kGangExpandTok tokens of an adapter of at most kOwnRanks ranks, kExpandTok of another;
+// make(std::integral_constant<int, TOK>) gives the source of v
+template <int DT, bool Y16, class Make>
+__device__ __forceinline__ void expand_split(const Item &it, const int32_t *__restrict__ pb, const uint16_t *__restrict__ pool,
+                                             const int32_t *__restrict__ tok_idx, int H, int v_stride, void *__restrict__ y,
+                                             float *red, Make make)
+{
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if (it.rank <= 8)
+        expand_own<DT, Y16, 8>(it, wave, pb, pool, tok_idx, H, v_stride, y, make(std::integral_constant<int, 1>{}));
+    else if (it.rank <= 16)
+        expand_own<DT, Y16, 16>(it, wave, pb, pool, tok_idx, H, v_stride, y, make(std::integral_constant<int, 1>{}));
+    else if (it.rank <= kOwnRanks)
+        expand_own<DT, Y16, kOwnRanks>(it, wave, pb, pool, tok_idx, H, v_stride, y, make(std::integral_constant<int, 1>{}));
+    else if (it.ntok <= 2)
+        expand_shared<DT, Y16, 2, 16>(it, pb, pool, tok_idx, H, v_stride, y, make(std::integral_constant<int, 2>{}), red);
+    else
+        expand_shared<DT, Y16, kExpandTok, 8>(it, pb, pool, tok_idx, H, v_stride, y, make(std::integral_constant<int, kExpandTok>{}), red);
+}
+
+template <int DT, bool Y16>
+__global__ __launch_bounds__(kSplitWaves *kWave, 3) void expand_vec_split_kernel(const Item *__restrict__ items,
+                                                                              const int32_t *__restrict__ arena,
+                                                                              const uint16_t *__restrict__ pool,
+                                                                              const int32_t *__restrict__ tok_idx,
+                                                                              int H, int v_stride, MultiArgs args)
+{
+    extern __shared__ u32x4 smem[];
+    const int cs = blockIdx.x % args.n;
+    const Item it = items[blockIdx.x / args.n];
+    const int32_t *pb = arena + it.arena_off + (int64_t)args.slot[cs] * 2 * it.rank + it.rank;
+    expand_split<DT, Y16>(it, pb, pool, tok_idx, H, v_stride, args.y[cs],
+                          reinterpret_cast<float *>(smem), [&](auto tok) { return StoredV<DT, decltype(tok)::value>{args.v[cs]}; });
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1878,13 +2172,54 @@ int32_t launch_fused(slora_plan *plan, int32_t n, const MultiArgs &args, void *s
     return check_launch("lora_vec_fused");
 }
 
+// LDS of the rank-split expand: its partial sums
+constexpr size_t kSplitLds = (size_t)kSplitWaves * kExpandTok * 8 * kWave * sizeof(float);
+
+// LDS of the vector shrink: its items' rows of x, at most 64 KiB, or a piece of the gang's
+static size_t vec_shrink_lds(const slora_plan *plan, const Route &route)
+{
+    const size_t row = (size_t)plan->pool->H * 2;
+    return route.gang ? std::max(kGangLds, plan->max_gv_tok * row) : plan->max_shrink_tok * row;
+}
+
+static GangArgs gang_args(const slora_plan *plan, const Route &route)
+{
+    if (!route.gang) return GangArgs{nullptr, plan->d_vs, 0};
+    return GangArgs{plan->d_gs, plan->d_gv, (unsigned)plan->n_gs(route)};
+}
+
 int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, const Route &route)
 {
     slora_pool *pool = plan->pool;
     const uint16_t *base = static_cast<const uint16_t *>(pool->dev_base);
     hipStream_t st = (hipStream_t)stream;
     const size_t n_vs = plan->n_vs(route);
-    if (n_vs > 0) {
+    int32_t rc = SLORA_OK;
+    if (n_vs > 0 && route.gang) {
+        const GangArgs g = gang_args(plan, route);
+        const dim3 grid((unsigned)(plan->shrink_wgs(route) * (size_t)n));
+        const size_t lds = vec_shrink_lds(plan, route);
+        const int U = shrink_loads_per_block(pool->H);
+#define SLORA_GANG(DT, UU) \
+    hipLaunchKernelGGL((shrink_gang_kernel<DT, UU>), grid, dim3(kShrinkThreads), lds, st, g, pool->d_arena, base, plan->d_tok_idx, pool->H, plan->v_stride, args)
+#define SLORA_GANG_U(DT)                      \
+    switch (U) {                              \
+    case 4: SLORA_GANG(DT, 4); break;         \
+    case 5: SLORA_GANG(DT, 5); break;         \
+    case 6: SLORA_GANG(DT, 6); break;         \
+    case 7: SLORA_GANG(DT, 7); break;         \
+    default: SLORA_GANG(DT, 8); break;        \
+    }
+        if (pool->dtype == SLORA_F16) {
+            SLORA_GANG_U(SLORA_F16)
+        } else {
+            SLORA_GANG_U(SLORA_BF16)
+        }
+#undef SLORA_GANG_U
+#undef SLORA_GANG
+        rc = check_launch("shrink_gang");
+        if (rc != SLORA_OK) return rc;
+    } else if (n_vs > 0) {
         const dim3 grid((unsigned)(n_vs * (size_t)n));
         const size_t lds = (size_t)plan->max_shrink_tok * pool->H * 2;
         const int U = shrink_loads_per_block(pool->H);
@@ -1906,7 +2241,7 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *
         }
 #undef SLORA_SHRINK_U
 #undef SLORA_LAUNCH_SHRINK
-        int32_t rc = check_launch("shrink_vec");
+        rc = check_launch("shrink_vec");
         if (rc != SLORA_OK) return rc;
     }
     if (!plan->ms_items.empty() && plan->mfma_on(route)) {
@@ -1922,7 +2257,7 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *
     }
         if (pool->dtype == SLORA_F16) SLORA_MSK(SLORA_F16) else SLORA_MSK(SLORA_BF16)
 #undef SLORA_MSK
-        int32_t rc = check_launch("shrink_mfma");
+        rc = check_launch("shrink_mfma");
         if (rc != SLORA_OK) return rc;
         if (plan->n_sync > 0) {
             const dim3 jgrid((unsigned)((size_t)plan->n_sync * (kMsTok / 32) * (size_t)n));
@@ -1948,10 +2283,11 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *
                               : (y16 ? KERNEL<SLORA_BF16, true> : KERNEL<SLORA_BF16, false>))
     const size_t n_ve = plan->n_ve(route);
     if (n_ve > 0) {
-        const dim3 grid((unsigned)(n_ve * (size_t)n));
+        const dim3 grid((unsigned)(plan->expand_wgs(route) * (size_t)n));
         if (plan->expand_split)
-            hipLaunchKernelGGL(SLORA_PICK(expand_vec_split_kernel), grid, dim3(kSplitWaves * kWave), 0, st, plan->d_ve,
-                               pool->d_arena, base, plan->d_tok_idx, pool->H, plan->v_stride, args);
+            hipLaunchKernelGGL(SLORA_PICK(expand_vec_split_kernel), grid, dim3(kSplitWaves * kWave), kSplitLds, st,
+                               route.gang_expand ? plan->d_ge : plan->d_ve, pool->d_arena, base, plan->d_tok_idx, pool->H,
+                               plan->v_stride, args);
         else
             hipLaunchKernelGGL(SLORA_PICK(expand_vec_kernel), grid, dim3((unsigned)plan->expand_threads), 0, st,
                                plan->d_ve, pool->d_arena, base, plan->d_tok_idx, pool->H, plan->v_stride, args);

@@ -188,9 +188,13 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         const int32_t me_run = (int32_t)std::min<int64_t>(kMfmaRunMax, std::max<int64_t>(1, me_pairs / 1024));
         plan->me_run = me_run;
         plan->me_stages = 0;
-        int32_t n_vec_groups = 0;
-        for (int32_t gi : order)
-            if ((int64_t)groups[(size_t)gi].toks.size() < min_tokens) n_vec_groups++;
+        int32_t n_vec_groups = 0, most_vec_tokens = 0;
+        for (int32_t gi : order) {
+            const int64_t n = (int64_t)groups[(size_t)gi].toks.size();
+            if (n >= min_tokens) continue;
+            n_vec_groups++;
+            most_vec_tokens = std::max(most_vec_tokens, (int32_t)n);
+        }
         // vector-expand items: long runs of columns, halved while a launch would have fewer
         // workgroups than the GPU has CUs
         int32_t chunks = (H + kExpandColsMax - 1) / kExpandColsMax;
@@ -297,6 +301,45 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                 }
             }
         }
+        // Groups of many tokens on the vector kernels: every item of the lists above reads its pages, and its x again for
+        // every few pages, for four tokens.
+        plan->gs_items.clear();
+        plan->gv_items.clear();
+        plan->ge_items.clear();
+        plan->n_gs_plain = plan->n_ge_plain = plan->max_gv_tok = 0;
+        if (plan->expand_split && plan->vf_items.empty() && most_vec_tokens > kExpandTok) {
+            std::vector<Item> gs_dual, ge_dual;
+            int32_t pos = 0;
+            for (int32_t gi : order) {
+                const Group &g = groups[(size_t)gi];
+                const int32_t n = (int32_t)g.toks.size(), off = (int32_t)g.arena_off, pos0 = pos;
+                pos += n;
+                if ((int64_t)n >= min_tokens) continue;
+                std::vector<Item> &gs = mfma_group(n) ? gs_dual : plan->gs_items;
+                std::vector<Item> &ge = mfma_group(n) ? ge_dual : plan->ge_items;
+                if (n <= kExpandTok) {
+                    plan->max_gv_tok = std::max(plan->max_gv_tok, std::min(n, shrink_tok));
+                    for (int32_t p = 0; p < n; p += shrink_tok)
+                        for (int32_t j = 0; j < g.rank; j += shrink_pages)
+                            plan->gv_items.push_back(Item{off, g.rank, j, std::min(shrink_pages, g.rank - j), pos0 + p, std::min(shrink_tok, n - p), 0, 0});
+                } else {
+                    const int32_t runs = (g.rank + kGangPages - 1) / kGangPages; // of about equal length
+                    for (int32_t p = 0; p < n; p += kGangTok)
+                        for (int32_t k = 0; k < runs; ++k) {
+                            const int32_t j0 = (int32_t)((int64_t)g.rank * k / runs), j1 = (int32_t)((int64_t)g.rank * (k + 1) / runs);
+                            gs.push_back(Item{off, g.rank, j0, j1 - j0, pos0 + p, std::min(kGangTok, n - p), 0, 0});
+                        }
+                }
+                const int32_t step = g.rank <= kOwnRanks ? kGangExpandTok : kExpandTok;
+                for (int32_t p = 0; p < n; p += step)
+                    for (int32_t c = 0; c < H; c += ecols)
+                        ge.push_back(Item{off, g.rank, c, std::min(ecols, H - c), pos0 + p, std::min(step, n - p), 0, 0});
+            }
+            plan->n_gs_plain = (int32_t)plan->gs_items.size();
+            plan->n_ge_plain = (int32_t)plan->ge_items.size();
+            plan->gs_items.insert(plan->gs_items.end(), gs_dual.begin(), gs_dual.end());
+            plan->ge_items.insert(plan->ge_items.end(), ge_dual.begin(), ge_dual.end());
+        }
         plan->n_vs_plain = (int32_t)plan->vs_items.size();
         plan->n_ve_plain = (int32_t)plan->ve_items.size();
         plan->vs_items.insert(plan->vs_items.end(), vs_dual.begin(), vs_dual.end());
@@ -349,7 +392,7 @@ int32_t slora_plan::upload()
     if (n_tok == 0) return SLORA_OK;
     const size_t tok_bytes = (n_tok * sizeof(int32_t) + 63) / 64 * 64;
     const size_t bytes = tok_bytes + (ms_items.size() + mj_items.size()) * sizeof(MsItem) +
-                         (vs_items.size() + ve_items.size() + me_items.size() + vf_items.size()) * sizeof(Item);
+                         (vs_items.size() + ve_items.size() + me_items.size() + vf_items.size() + gs_items.size() + gv_items.size() + ge_items.size()) * sizeof(Item);
     // The image is assembled in the pinned half of a recycled buffer set and copied to the
     // device half on the pool's own upload stream: the copy runs beside whatever the caller's
     // streams are doing, and the first launch of the plan waits for it through an event.
@@ -369,6 +412,9 @@ int32_t slora_plan::upload()
     put(ve_items);
     put(me_items);
     put(vf_items);
+    put(gs_items);
+    put(gv_items);
+    put(ge_items);
     void *up_v = nullptr;
     rc = pool->uploads(&up_v);
     if (rc != SLORA_OK) {
@@ -394,6 +440,9 @@ int32_t slora_plan::upload()
     d_ve = d_vs + vs_items.size();
     d_me = d_ve + ve_items.size();
     d_vf = d_me + me_items.size();
+    d_gs = d_vf + vf_items.size();
+    d_gv = d_gs + gs_items.size();
+    d_ge = d_gv + gv_items.size();
     return SLORA_OK;
 }
 
@@ -404,6 +453,12 @@ Route slora_plan::route(int32_t n, bool apply, bool y16) const
              v_total_floats(n, pool->dtype, true) * (int64_t)sizeof(float) <= (int64_t)SLORA_STATIC_SCRATCH_BYTES;
     r.fused = apply && !vf_items.empty();
     r.small = apply && small && (int64_t)ve_items.size() * n <= 256;
+    // Larger vector items, where the small ones are more workgroups than the GPU holds at a time.  us per kernel, small / large:
+    // shrink, 2066 / 294 workgroups 22.1 / 13.7, 2604 / 333 12.4 / 9.6, 1446 / 363 15.2 / 13.1, but 1520 / 208 7.6 / 8.1,
+    // 792 / 748 9.2 / 12.5, 752 / 376 8.4 / 10.6, 744 / 96 9.6 / 13.1; expand, 6016 / 1536 22.6 / 15.8, 4338 / 1098 16.0 / 11.1,
+    // 912 / 792 7.8 / 7.5, but 600 / 288 8.3 / 11.2, 414 / 333 10.4 / 12.8.
+    r.gang = n_gs(r) > 0 && (int64_t)n_vs(r) * n >= 1400 && (int64_t)(n_gs(r) + gv_items.size()) * n >= 256;
+    r.gang_expand = !ge_items.empty() && (int64_t)n_ve(r) * n >= 2000 && (int64_t)n_ge(r) * n >= 512;
     // Tokens of an item per workgroup of the MFMA shrink.  The items of a call of modest size are too
     // few for the GPU; halves or quarters of their tokens read the pages two or four times as often,
     // which pays only while compute units stand idle: 111 items 62 us in as many workgroups, 48 in 153,

@@ -71,6 +71,8 @@ struct MultiArgs {
 struct Route {
     bool wide = false;  // a dual plan's groups of many tokens on the MFMA kernels
     bool small = false; // both stages in the one-launch kernel for small batches
+    bool gang = false;        // vector groups of many tokens: the shrink for them,
+    bool gang_expand = false; // the expand's longer items
     bool fused = false; // an apply: launch_fused serves the groups of the one-launch decode kernel
     int32_t sub = 0;    // MFMA shrink: a workgroup takes kMsTok >> sub tokens of an item
     int32_t parts = 1;  // MFMA expand: workgroups that share a run of tiles
@@ -81,6 +83,11 @@ constexpr int kShrinkTok = 4;     // tokens per vector-shrink item (x rows stage
 constexpr int kExpandTok = 4;     // tokens per vector-expand item (accumulators in registers)
 constexpr int kSmallRanks = 32;   // most ranks of an adapter in a batch that runs in the one-launch kernel for small batches
 constexpr int kExpandColsMax = 1024; // most columns per vector-expand item (a multiple of 512, <= 4096; measured best on cfg4: 1024)
+constexpr int kSplitWaves = 4;    // rank-split expand: wavefronts of a workgroup, and parts of a sum over the ranks
+constexpr int kOwnRanks = 32;     // ... up to this many ranks a wavefront forms whole sums
+constexpr int kGangTok = 8;       // tokens per item of the shrink for groups of many tokens,
+constexpr int kGangPages = 16;    // pages, at most
+constexpr int kGangExpandTok = 16; // tokens per item of the rank-split expand for such groups of at most kOwnRanks ranks
 constexpr int kMfmaTok = 32;      // tokens per v tile = per MFMA-expand item (one 32-row MFMA block)
 constexpr int kMsTok = 128;       // most tokens per MFMA-shrink item
 constexpr int kMsRanks = 128;     // ranks per MFMA-shrink item (up to four blocks of 32)
@@ -217,6 +224,16 @@ struct slora_plan {
     // items of the two vector lists that a call runs beside the other kernels
     size_t n_vs(const slora::Route &r) const { return r.wide ? (size_t)n_vs_plain : r.fused ? (size_t)n_vs_head : vs_items.size(); }
     size_t n_ve(const slora::Route &r) const { return r.wide ? (size_t)n_ve_plain : r.fused ? (size_t)n_ve_head : ve_items.size(); }
+    // The vector lists once more, in larger items, if the expand is rank-split and a group has more than kExpandTok tokens
+    std::vector<slora::Item> gs_items, gv_items; // shrink: groups of more than that; vector-shrink items of the others
+    std::vector<slora::Item> ge_items;           // expand: all groups
+    int32_t n_gs_plain = 0, n_ge_plain = 0;      // without a dual plan's groups of many tokens
+    int32_t max_gv_tok = 0;                      // most tokens of an item of gv
+    size_t n_gs(const slora::Route &r) const { return r.wide ? (size_t)n_gs_plain : gs_items.size(); }
+    size_t n_ge(const slora::Route &r) const { return r.wide ? (size_t)n_ge_plain : ge_items.size(); }
+    // workgroups of the vector kernels, per slot
+    size_t shrink_wgs(const slora::Route &r) const { return r.gang ? n_gs(r) + gv_items.size() : n_vs(r); }
+    size_t expand_wgs(const slora::Route &r) const { return r.gang_expand ? n_ge(r) : n_ve(r); }
     std::vector<slora::MsItem> ms_items;
     std::vector<slora::MsItem> mj_items; // one record per split tile, for the kernel that joins the shares
     // MFMA shrink with kMsTok >> sub tokens per workgroup: workgroups per slot, LDS of the largest tile
@@ -231,7 +248,7 @@ struct slora_plan {
     // device image: tok_idx and the four lists in one buffer of the plan's buffer set
     slora::Buffers *set = nullptr;
     int32_t *d_tok_idx = nullptr;
-    slora::Item *d_vs = nullptr, *d_ve = nullptr, *d_me = nullptr, *d_vf = nullptr;
+    slora::Item *d_vs = nullptr, *d_ve = nullptr, *d_me = nullptr, *d_vf = nullptr, *d_gs = nullptr, *d_gv = nullptr, *d_ge = nullptr;
     slora::MsItem *d_ms = nullptr, *d_mj = nullptr;
 
     // scratch for v = x*A (set->v, or the library's static scratch), per slot: T_act * v_stride floats (vector path rows), n_mfma_tiles * (v_stride/16) *

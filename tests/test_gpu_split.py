@@ -1,0 +1,59 @@
+"""GPU parity of the rank-split vector kernels: whole sums in a wavefront up to 32 ranks, shared ones beyond, blocks of
+8 ranks or (one or two tokens left over) 16, and the larger items that calls of many workgroups take (shrink: 8
+tokens x 16 pages in pieces of 2048 elements; expand: 16 tokens).  Ranks and tokens per group at the edges of all
+of these.  Who forms a sum never changes its bits."""
+import numpy as np
+import pytest
+import torch
+
+from paper_2311_03285_amd import slora, synth
+from paper_2311_03285_amd.harness import DeviceWorkload, bits_to_device
+from gpu_util import assert_close, oracle_slot
+from test_gpu_y16 import assert_y16_close, oracle_y16
+
+pytestmark = pytest.mark.gpu
+
+RANKS = (1, 8, 9, 16, 17, 32, 33, 40, 64, 65, 100, 130)
+TOKENS = (17, 5, 33, 6, 19, 18, 7, 9, 10, 4, 2, 1)
+
+
+def crowd(H, dtype):
+    ids = np.concatenate([np.repeat(np.arange(len(RANKS)), TOKENS), [-1, -1]])
+    ids = ids[np.random.default_rng(H).permutation(ids.size)].astype(np.int32)
+    return synth.make_workload("crowd", 800 + H, H, dtype, 2 * 2 * sum(RANKS) + 8, 2, RANKS, ids)
+
+
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+@pytest.mark.parametrize("H", [1032, 2056, 3080, 4096])   # one piece and a bit, two and a chunk; 3080, 4096: the expand's larger items too
+def test_larger_items_are_bit_identical(H, dtype):
+    w = crowd(H, dtype)
+    with DeviceWorkload(w, real_adapters="all") as dw:
+        plan = dw.plan()
+        info = slora.plan_info(plan)
+        assert info["groups_mfma"] == 0 and info["vec_shrink_items"] < 1400 <= 8 * info["vec_shrink_items"]
+        assert (8 * info["vec_expand_items"] >= 2000) == (H >= 3080)
+        xs = [dw.x_dev(s) for s in (0, 1)]
+        slots = [0, 1] * 4
+        for y16 in (False, True):
+            def new(s):
+                return bits_to_device(w.y16_bits(s), dw.device) if y16 else dw.y_dev(s)
+
+            def two_kernels(which, ys):
+                ptrs = [t.data_ptr() for t in ys]
+                slora.lora_shrink(plan, which, [xs[s].data_ptr() for s in which])
+                (slora.lora_expand_y16 if y16 else slora.lora_expand)(plan, which, ptrs)
+
+            many, one = [new(s) for s in slots], [new(s) for s in (0, 1)]
+            two_kernels(slots, many)
+            for s in (0, 1):
+                two_kernels([s], [one[s]])
+            torch.cuda.synchronize()
+            for s, got in zip(slots, many):
+                assert torch.equal(got, one[s]), (y16, s)
+            for s in (0, 1):
+                if y16:
+                    ref, exact = oracle_y16(w, s)
+                    assert_y16_close(one[s].cpu().numpy().view(np.uint16).reshape(w.T, w.H), ref, exact, w.y16_bits(s), dtype, f"slot {s}")
+                else:
+                    rel, _ = assert_close(one[s].cpu().numpy(), oracle_slot(w, s), f"slot {s}")
+                    assert rel <= 2e-6, rel
