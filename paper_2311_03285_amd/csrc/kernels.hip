@@ -1204,6 +1204,30 @@ __device__ __forceinline__ void lds_read(const uint32_t (&a)[N], u32x4 (&o)[N])
             : "v"(a[0]), "v"(a[1]), "v"(a[2]), "v"(a[3]), "v"(a[4]), "v"(a[5]), "v"(a[6]), "v"(a[7]), "v"(a[8]), "v"(a[9]), "v"(a[10]), "v"(a[11])
             : "memory");
 }
+// The NP fragments of a k-step, kWave * 16 bytes apart, from byte OFF past `at` on; offsets in the instructions, so that
+// unrolled reads hold no address registers
+template <int NP, int OFF>
+__device__ __forceinline__ void lds_read_pieces(uint32_t at, u32x4 (&o)[NP])
+{
+    static_assert((NP == 2 || NP == 3) && OFF >= 0 && OFF + 2 * kWave * 16 < 65536, "offset field");
+    if constexpr (NP == 2)
+        asm volatile(
+            "ds_read_b128 %0, %2 offset:%3\n\t"
+            "ds_read_b128 %1, %2 offset:%4\n\t"
+            "s_waitcnt lgkmcnt(0)"
+            : "=&v"(o[0]), "=&v"(o[1])
+            : "v"(at), "n"(OFF), "n"(OFF + kWave * 16)
+            : "memory");
+    else
+        asm volatile(
+            "ds_read_b128 %0, %3 offset:%4\n\t"
+            "ds_read_b128 %1, %3 offset:%5\n\t"
+            "ds_read_b128 %2, %3 offset:%6\n\t"
+            "s_waitcnt lgkmcnt(0)"
+            : "=&v"(o[0]), "=&v"(o[1]), "=&v"(o[2])
+            : "v"(at), "n"(OFF), "n"(OFF + kWave * 16), "n"(OFF + 2 * kWave * 16)
+            : "memory");
+}
 __device__ __forceinline__ uint32_t lds_address(const unsigned char *p)
 {
     return (uint32_t)(uintptr_t)(__attribute__((address_space(3))) const unsigned char *)p;
@@ -1592,7 +1616,8 @@ __global__ __launch_bounds__(kMfmaThreads) void join_shares_kernel(const MsItem 
 // every wavefront for itself it was a larger part of the kernel's requests than y.  V and y of the
 // next tile are requested before the current one is computed; one barrier per tile hands the
 // buffers over, and the stores of a tile are only waited for a tile later.
-// Adapters of more ranks (expand_mfma_stream) read V and B again for every tile, without barriers.
+// Adapters of up to 256 ranks do the same with V in two halves (expand_mfma_halves); those of more
+// (expand_mfma_stream) read V and B again for every tile, without barriers.
 //
 // The first operand is V (tokens x ranks, fp32 precision), split by the shrink into 16-bit pieces
 // (see VPieces); each piece costs one more MFMA on a path that is bound by memory, not by the
@@ -1712,6 +1737,27 @@ struct ExpandWave {
 #pragma unroll
             for (int nb = 0; nb < 2; ++nb)
                 op[s][nb] = *reinterpret_cast<const u32x4 *>(slab + slab_col(nb * 32 + n) + 8 * s + 4 * q);
+    }
+    // B of the run, `stages` <= N stages of 32 ranks: all page numbers first, then the rows of up to AHEAD stages in flight
+    // (registers that the tiles need later); first() runs behind the first rows' requests
+    template <int N, class First>
+    __device__ __forceinline__ void load_operands(int stages, u32x4 (&op)[N][2][2], First first) const
+    {
+        constexpr int kAhead = N < 4 ? N : 4;
+        int pg[N][4];
+        u32x4 b[kAhead][4];
+#pragma unroll
+        for (int s = 0; s < N; ++s)
+            if (s < kAhead || s < stages) load_pg(32 * s, pg[s]);
+#pragma unroll
+        for (int s = 0; s < kAhead; ++s) load_b(pg[s], b[s]);
+        first();
+#pragma unroll
+        for (int s = 0; s < N; ++s) {
+            if (s >= kAhead && s >= stages) break;
+            transpose_b(b[s % kAhead], op[s]);
+            if (s + kAhead < N && s + kAhead < stages) load_b(pg[s + kAhead], b[s % kAhead]);
+        }
     }
     static __device__ __forceinline__ void multiply(f32x16 (&sum)[2], const u32x4 &piece, const u32x4 (&op)[2])
     {
@@ -1861,21 +1907,7 @@ __device__ __forceinline__ void expand_mfma_run(const Item &it, int wave, const 
     [[maybe_unused]] i32x4 e_cur = i32x4{0, 0, 0, 0}, e_next = i32x4{0, 0, 0, 0};
     if constexpr (DT == SLORA_F16) e_cur = exponents(0);
     w.load_rows(0, row_cur);
-    constexpr int kAhead = RegStages < 2 ? RegStages : 2; // stages of B in flight
-#pragma unroll
-    for (int s0 = 0; s0 < RegStages; s0 += kAhead) {
-        int pg[kAhead][4];
-        u32x4 b[kAhead][4];
-#pragma unroll
-        for (int s = 0; s < kAhead; ++s) w.load_pg(32 * (s0 + s), pg[s]);
-#pragma unroll
-        for (int s = 0; s < kAhead; ++s) w.load_b(pg[s], b[s]);
-        if (s0 == 0) w.load_y(row_cur, yt);
-#pragma unroll
-        for (int s = 0; s < kAhead; ++s)
-            if (s0 + s < RegStages) w.transpose_b(b[s], bop[s0 + s]);
-        if constexpr (RegStages > kAhead) __builtin_amdgcn_sched_barrier(0);
-    }
+    w.load_operands(RegStages, bop, [&]() { w.load_y(row_cur, yt); });
     w.load_rows(min(1, tiles - 1), row_next);
     const uint32_t frag_at = lds_address(lds) + lane * 16;
     asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -1937,7 +1969,121 @@ __device__ __forceinline__ void expand_mfma_run(const Item &it, int wave, const 
     }
 }
 
-// adapters of more than 128 ranks: V and B come from memory for every tile
+// Adapters of 129 to 256 ranks: B of up to eight stages in registers, V of a tile through LDS in two halves of four
+// stages, one buffer each: while a half is multiplied the next is on its way.  A barrier per half.  No registers are left for the y of
+// the next tile if it is fp32.  The sums are formed as in expand_mfma_stream, which read V in every wavefront and B per
+// tile, stage after stage, a chain of
+// dependent loads: 2615 tokens of ranks 5-200 (a third of them 200), H = 2568, 3 slots, fp32 y 57.8 -> 53.6 us; all of rank 200 109 -> 85.
+template <int DT, bool Y16, int NP>
+__device__ __forceinline__ void expand_mfma_halves(const Item &it, int wave, const int32_t *__restrict__ pbl,
+                                                   const uint16_t *__restrict__ pool,
+                                                   const int32_t *__restrict__ tok_idx, int H, int v_stride,
+                                                   const uint16_t *__restrict__ vfrag, const int8_t *__restrict__ vexp,
+                                                   void *__restrict__ y, unsigned char *lds)
+{
+    typedef ExpandWave<DT, Y16, NP> W;
+    typedef typename W::i32x4 i32x4;
+    static_assert(!W::kScaled, "pieces of a scale of their own need sums of their own");
+    constexpr int kYLoads = W::kYLoads;
+    constexpr int kHalf = kMsRanks / 32;          // stages of a half
+    constexpr int kFrags = 2 * kHalf * NP;        // operand fragments (1 KiB) of a half
+    constexpr bool kAheadY = !W::kFromZero;       // y starts in the accumulators: requested a tile ahead
+    const int n_kk = v_stride >> 4, n_rb = (v_stride + kMsRanks - 1) / kMsRanks;
+    const int lane = threadIdx.x & (kWave - 1);
+    const int tiles = it.run & 0xff;
+    const int stages = (it.rank + 31) >> 5;       // kHalf + 1 .. 2 * kHalf
+    auto load_v = [&](int t, int h) { // this wavefront's part of a half of tile t
+        const unsigned char *src = reinterpret_cast<const unsigned char *>(vfrag + vfrag_index(it.tile + t, 2 * kHalf * h, 0, n_kk, NP)) + lane * 16;
+        unsigned char *dst = lds + h * (kFrags * 1024);
+        const int n = h == 0 ? kFrags : 2 * (stages - kHalf) * NP;
+        for (int f = wave; f < n; f += 4) load_to_lds<0>(src + f * 1024, dst + f * 1024);
+    };
+    auto hand_over = [&]() { // what was requested has arrived, in every wavefront
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __builtin_amdgcn_s_barrier();
+        asm volatile("" ::: "memory");
+    };
+    const int colw = it.a + wave * 64;            // this wavefront's first column
+    load_v(0, 0);
+    if (colw >= it.a + it.b) {                    // no columns: it only does its part of the copying
+        hand_over();
+        for (int t = 0; t < tiles; ++t) {
+            load_v(t, 1);
+            hand_over();
+            if (t + 1 < tiles) {
+                load_v(t + 1, 0);
+                hand_over();
+            }
+        }
+        return;
+    }
+    W w(it, colw, pbl, pool, tok_idx, H, y, reinterpret_cast<uint32_t *>(lds + 2 * kFrags * 1024 + wave * kWaveLds));
+    int row_cur[kYLoads], row_next[kYLoads];
+    u32x4 yt[kYLoads];
+    [[maybe_unused]] u32x4 y_next[kYLoads];
+    u32x4 bop[2 * kHalf][2][2];
+    w.load_rows(0, row_cur);
+    w.load_operands(stages, bop, [&]() {
+        if constexpr (kAheadY) w.load_y(row_cur, yt);
+    });
+    const uint32_t frag_at = lds_address(lds) + lane * 16;
+    hand_over();
+    for (int t = 0; t < tiles; ++t) {
+        load_v(t, 1);
+        if constexpr (!kAheadY) w.load_y(row_cur, yt);
+        [[maybe_unused]] const i32x4 *et = reinterpret_cast<const i32x4 *>(vexp + (int64_t)(it.tile + t) * n_rb * 32 + w.q * 16);
+        [[maybe_unused]] i32x4 scale = i32x4{0, 0, 0, 0};
+        if constexpr (DT == SLORA_F16) scale = et[0];
+        w.begin(yt, scale);
+        auto products = [&](auto stage) {
+            constexpr int st = decltype(stage)::value;
+#pragma unroll
+            for (int k = 0; k < 2; ++k) {
+                u32x4 piece[NP];
+                if (k == 0)
+                    lds_read_pieces<NP, 2 * NP * st * 1024>(frag_at, piece);
+                else
+                    lds_read_pieces<NP, (2 * NP * st + NP) * 1024>(frag_at, piece);
+#pragma unroll
+                for (int p = 0; p < NP; ++p) W::multiply(w.acc, piece[p], bop[st][k]);
+            }
+        };
+        products(std::integral_constant<int, 0>{});
+        products(std::integral_constant<int, 1>{});
+        products(std::integral_constant<int, 2>{});
+        products(std::integral_constant<int, 3>{});
+        if constexpr (kAheadY) w.load_rows(min(t + 1, tiles - 1), row_next);
+        hand_over(); // the second half is in LDS, the first has been read
+        if (t + 1 < tiles) {
+            load_v(t + 1, 0);
+            if constexpr (kAheadY) w.load_y(row_next, y_next);
+        }
+        if constexpr (DT == SLORA_F16) { // the sums so far follow the next block's scale
+            const i32x4 to = et[2];
+            W::scale_rows(w.acc, scale, to);
+            scale = to;
+        }
+        products(std::integral_constant<int, 4>{});
+        if (stages > 5) products(std::integral_constant<int, 5>{});
+        if (stages > 6) products(std::integral_constant<int, 6>{});
+        if (stages > 7) products(std::integral_constant<int, 7>{});
+        if constexpr (!kAheadY) w.load_rows(min(t + 1, tiles - 1), row_next);
+        w.end(yt, scale);
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // the stores that follow are waited for a half later
+        w.store_y(t, row_cur, yt);
+        if (t + 1 < tiles) {
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+#pragma unroll
+            for (int i = 0; i < kYLoads; ++i) {
+                row_cur[i] = row_next[i];
+                if constexpr (kAheadY) yt[i] = y_next[i];
+            }
+        }
+    }
+}
+
+// adapters of more ranks: V and B come from memory for every tile
 template <int DT, bool Y16, int NP>
 __device__ __forceinline__ void expand_mfma_stream(const Item &it, int wave, const int32_t *__restrict__ pbl,
                                                    const uint16_t *__restrict__ pool,
@@ -2042,6 +2188,10 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void expand_mfma_kernel(const Item
     else if (it.rank <= 64) SLORA_ME(2);
     else if (it.rank <= 96) SLORA_ME(3);
     else if (it.rank <= 128) SLORA_ME(4);
+    else if (it.rank <= 2 * kMsRanks && !kScaledPieces<DT, NP>) {
+        if constexpr (!kScaledPieces<DT, NP>)
+            expand_mfma_halves<DT, Y16, NP>(it, wave, pbl, pool, tok_idx, H, v_stride, vfrag, vexp, args.y[cs], lds);
+    }
     else expand_mfma_stream<DT, Y16, NP>(it, wave, pbl, pool, tok_idx, H, v_stride, vfrag, vexp, args.y[cs], lds);
 #undef SLORA_ME
 }

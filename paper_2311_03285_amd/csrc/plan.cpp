@@ -266,7 +266,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                     }
                 }
                 // expand: the tiles in runs of equal length; a run of one column range is one workgroup
-                if (g.rank <= kMsRanks) plan->me_stages = std::max(plan->me_stages, (g.rank + 31) / 32);
+                if (g.rank <= 2 * kMsRanks) plan->me_stages = std::max(plan->me_stages, (std::min(g.rank, kMsRanks) + 31) / 32);
                 const int32_t n_runs = (n_tiles + me_run - 1) / me_run;
                 for (int32_t k = 0; k < n_runs; ++k) {
                     const int32_t t0 = n_tiles * k / n_runs, t1 = n_tiles * (k + 1) / n_runs;
