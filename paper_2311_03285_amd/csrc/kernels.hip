@@ -203,6 +203,12 @@ __global__ __launch_bounds__(256) void gather_pages_kernel(const uint16_t *__res
     for (int c = threadIdx.x; c < H / 8; c += blockDim.x) d[c] = s[c];
 }
 
+// Work lists of a plan for one call, from pinned host memory: 16 bytes per lane and trip
+__global__ __launch_bounds__(256) void copy_kernel(u32x4 *__restrict__ dst, const u32x4 *__restrict__ src, int64_t n)
+{
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) dst[i] = src[i];
+}
+
 // ---------------------------------------------------------------------------------------
 // decode path, shrink: v[pos, j] = sum_h x[tok, h] * Apage_j[h]
 //
@@ -2247,6 +2253,14 @@ int32_t launch_write_pages(slora_pool *pool, const int32_t *d_idx, int64_t n, co
     hipLaunchKernelGGL(write_pages_kernel, dim3((unsigned)groups), dim3(256), 0, (hipStream_t)stream,
                        static_cast<uint16_t *>(pool->dev_base), d_idx, static_cast<const uint16_t *>(d_src), pool->H, n);
     return check_launch("write_pages");
+}
+
+int32_t launch_copy(void *dst, const void *src, size_t bytes, void *stream)
+{
+    const int64_t n = (int64_t)(bytes / 16); // whole work items: a multiple of 32 bytes
+    hipLaunchKernelGGL(copy_kernel, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 64)), dim3(256), 0, (hipStream_t)stream,
+                       static_cast<u32x4 *>(dst), static_cast<const u32x4 *>(src), n);
+    return check_launch("copy_lists");
 }
 
 int32_t launch_gather(slora_pool *pool, int64_t arena_entry, int32_t rank, void *dev_out, void *stream)

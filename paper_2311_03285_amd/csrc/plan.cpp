@@ -307,7 +307,11 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         plan->gv_items.clear();
         plan->ge_items.clear();
         plan->n_gs_plain = plan->n_ge_plain = plan->max_gv_tok = 0;
-        if (plan->expand_split && plan->vf_items.empty() && most_vec_tokens > kExpandTok) {
+        // (only if a call may be large enough to take them, see route: a call may name a slot more than once)
+        const int64_t most_n = call_slots > 0 ? call_slots : SLORA_MAX_MULTI;
+        const bool gang = (int64_t)(plan->vs_items.size() + vs_dual.size()) * most_n >= kGangFrom;
+        const bool gang_expand = (int64_t)(plan->ve_items.size() + ve_dual.size()) * most_n >= kGangExpandFrom;
+        if (plan->expand_split && plan->vf_items.empty() && most_vec_tokens > kExpandTok && (gang || gang_expand)) {
             std::vector<Item> gs_dual, ge_dual;
             int32_t pos = 0;
             for (int32_t gi : order) {
@@ -317,7 +321,8 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                 if ((int64_t)n >= min_tokens) continue;
                 std::vector<Item> &gs = mfma_group(n) ? gs_dual : plan->gs_items;
                 std::vector<Item> &ge = mfma_group(n) ? ge_dual : plan->ge_items;
-                if (n <= kExpandTok) {
+                if (!gang) {
+                } else if (n <= kExpandTok) {
                     plan->max_gv_tok = std::max(plan->max_gv_tok, std::min(n, shrink_tok));
                     for (int32_t p = 0; p < n; p += shrink_tok)
                         for (int32_t j = 0; j < g.rank; j += shrink_pages)
@@ -331,7 +336,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                         }
                 }
                 const int32_t step = g.rank <= kOwnRanks ? kGangExpandTok : kExpandTok;
-                for (int32_t p = 0; p < n; p += step)
+                for (int32_t p = 0; gang_expand && p < n; p += step)
                     for (int32_t c = 0; c < H; c += ecols)
                         ge.push_back(Item{off, g.rank, c, std::min(ecols, H - c), pos0 + p, std::min(step, n - p), 0, 0});
             }
@@ -385,7 +390,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
     return SLORA_OK;
 }
 
-int32_t slora_plan::upload()
+int32_t slora_plan::upload(bool once, void *stream)
 {
     if (!pool->dev_base) return SLORA_OK; // host-only pool: the plan stays on the host
     const size_t n_tok = tok_idx.size();
@@ -415,6 +420,25 @@ int32_t slora_plan::upload()
     put(gs_items);
     put(gv_items);
     put(ge_items);
+    d_tok_idx = (int32_t *)set->d;
+    d_ms = (MsItem *)((unsigned char *)set->d + tok_bytes);
+    d_mj = d_ms + ms_items.size();
+    d_vs = (Item *)(d_mj + mj_items.size());
+    d_ve = d_vs + vs_items.size();
+    d_me = d_ve + ve_items.size();
+    d_vf = d_me + me_items.size();
+    d_gs = d_vf + vf_items.size();
+    d_gv = d_gs + gs_items.size();
+    d_ge = d_gv + gv_items.size();
+    if (once) {
+        // A plan of one call: its lists travel on that call's own stream, by a kernel that reads the pinned image, so
+        // there is no copy engine to start and no event between two streams, both of which cost the host more than the
+        // launch.  236 decode and prompt tokens, H = 4096: 51.3 -> 27.0 us per call back to back.
+        rc = pool->arena_ready(stream);
+        if (rc == SLORA_OK) rc = launch_copy(set->d, set->h, bytes, stream);
+        last_stream = stream;
+        return rc;
+    }
     void *up_v = nullptr;
     rc = pool->uploads(&up_v);
     if (rc != SLORA_OK) {
@@ -433,16 +457,6 @@ int32_t slora_plan::upload()
     }
     last_stream = pool->upload_stream;
     order_recorded = true;
-    d_tok_idx = (int32_t *)set->d;
-    d_ms = (MsItem *)((unsigned char *)set->d + tok_bytes);
-    d_mj = d_ms + ms_items.size();
-    d_vs = (Item *)(d_mj + mj_items.size());
-    d_ve = d_vs + vs_items.size();
-    d_me = d_ve + ve_items.size();
-    d_vf = d_me + me_items.size();
-    d_gs = d_vf + vf_items.size();
-    d_gv = d_gs + gs_items.size();
-    d_ge = d_gv + gv_items.size();
     return SLORA_OK;
 }
 
@@ -457,8 +471,8 @@ Route slora_plan::route(int32_t n, bool apply, bool y16) const
     // shrink, 2066 / 294 workgroups 22.1 / 13.7, 2604 / 333 12.4 / 9.6, 1446 / 363 15.2 / 13.1, but 1520 / 208 7.6 / 8.1,
     // 792 / 748 9.2 / 12.5, 752 / 376 8.4 / 10.6, 744 / 96 9.6 / 13.1; expand, 6016 / 1536 22.6 / 15.8, 4338 / 1098 16.0 / 11.1,
     // 912 / 792 7.8 / 7.5, but 600 / 288 8.3 / 11.2, 414 / 333 10.4 / 12.8.
-    r.gang = n_gs(r) > 0 && (int64_t)n_vs(r) * n >= 1400 && (int64_t)(n_gs(r) + gv_items.size()) * n >= 256;
-    r.gang_expand = !ge_items.empty() && (int64_t)n_ve(r) * n >= 2000 && (int64_t)n_ge(r) * n >= 512;
+    r.gang = n_gs(r) > 0 && (int64_t)n_vs(r) * n >= kGangFrom && (int64_t)(n_gs(r) + gv_items.size()) * n >= 256;
+    r.gang_expand = !ge_items.empty() && (int64_t)n_ve(r) * n >= kGangExpandFrom && (int64_t)n_ge(r) * n >= 512;
     // Tokens of an item per workgroup of the MFMA shrink.  The items of a call of modest size are too
     // few for the GPU; halves or quarters of their tokens read the pages two or four times as often,
     // which pays only while compute units stand idle: 111 items 62 us in as many workgroups, 48 in 153,
@@ -618,7 +632,7 @@ int32_t do_expand(slora_plan *plan, int32_t n, const int32_t *slots, void *const
 
 namespace {
 int32_t make_plan(slora_pool *pool, slora_plan **out, const int32_t *token_adapter_ids, int32_t T,
-                  const int32_t *seg_offsets, int32_t n_seg, int32_t call_slots)
+                  const int32_t *seg_offsets, int32_t n_seg, int32_t call_slots, void *stream = nullptr)
 {
     clear_error();
     if (!pool || !out) return fail(SLORA_EINVAL, "NULL argument");
@@ -633,9 +647,17 @@ int32_t make_plan(slora_pool *pool, slora_plan **out, const int32_t *token_adapt
         rc = dev.status();
         // page lists of adapters loaded since the last plan, then this plan's work lists
         if (rc == SLORA_OK) rc = pool->sync_device();
-        if (rc == SLORA_OK) rc = p->upload();
+        // (a capturing stream takes no copy that reads an image which is recycled: such a call is refused when it waits)
+        bool once = call_slots > 0 && rc == SLORA_OK;
+        if (once) {
+            hipStreamCaptureStatus capture = hipStreamCaptureStatusNone;
+            once = hipStreamIsCapturing((hipStream_t)stream, &capture) == hipSuccess && capture == hipStreamCaptureStatusNone;
+            if (!once) (void)hipGetLastError();
+        }
+        if (rc == SLORA_OK) rc = p->upload(once, stream);
     }
     if (rc != SLORA_OK) {
+        if (p->set) pool->give_set(p->set, p->last_stream);
         delete p;
         return rc;
     }
@@ -767,7 +789,7 @@ int32_t slora_lora_shrink_expand(slora_pool *pool, int32_t slot, const void *x, 
                                  const int32_t *seg_offsets, int32_t n_seg, int32_t T, float *y, void *stream)
 {
     slora_plan *plan = nullptr;
-    int32_t rc = make_plan(pool, &plan, token_adapter_ids, T, seg_offsets, n_seg, 1);
+    int32_t rc = make_plan(pool, &plan, token_adapter_ids, T, seg_offsets, n_seg, 1, stream);
     if (rc != SLORA_OK) return rc;
     rc = slora_lora_apply(plan, slot, x, y, stream);
     std::string keep = last_error_cstr();

@@ -246,9 +246,23 @@ int32_t slora_pool::sync_device()
         if (e == hipSuccess) arena_event = ev;
     }
     if (e == hipSuccess) e = hipEventRecord((hipEvent_t)arena_event, (hipStream_t)up);
+    arena_done = false;
     give_set(set, up);
     if (e != hipSuccess) return hip_fail(e, "uploading page lists");
     dirty_lo = dirty_hi = 0;
+    return SLORA_OK;
+}
+
+int32_t slora_pool::arena_ready(void *stream)
+{
+    if (arena_done) return SLORA_OK;
+    const hipError_t q = hipEventQuery((hipEvent_t)arena_event);
+    if (q == hipErrorNotReady) {
+        (void)hipGetLastError();
+        return await_arena(stream);
+    }
+    if (q != hipSuccess) return hip_fail(q, "hipEventQuery");
+    arena_done = true;
     return SLORA_OK;
 }
 

@@ -87,6 +87,7 @@ constexpr int kSplitWaves = 4;    // rank-split expand: wavefronts of a workgrou
 constexpr int kOwnRanks = 32;     // ... up to this many ranks a wavefront forms whole sums
 constexpr int kGangTok = 8;       // tokens per item of the shrink for groups of many tokens,
 constexpr int kGangPages = 16;    // pages, at most
+constexpr int kGangFrom = 1400, kGangExpandFrom = 2000; // least workgroups of the small items at which a call takes them (see route)
 constexpr int kGangExpandTok = 16; // tokens per item of the rank-split expand for such groups of at most kOwnRanks ranks
 constexpr int kMfmaTok = 32;      // tokens per v tile = per MFMA-expand item (one 32-row MFMA block)
 constexpr int kMsTok = 128;       // most tokens per MFMA-shrink item
@@ -183,6 +184,8 @@ struct slora_pool {
     void *upload_stream = nullptr;                    // hipStream_t, created on first use
     void *arena_event = nullptr;                      // hipEvent_t: the device page-list image is complete after it
     int32_t uploads(void **out);                      // the upload stream
+    bool arena_done = true;                           // ... which is known to have happened
+    int32_t arena_ready(void *stream);                // await_arena, unless it has happened
     int32_t await_arena(void *stream);                // make `stream` wait for the latest page-list upload
 
     int32_t take_set(slora::Buffers **out, size_t h_bytes, size_t d_bytes); // an idle set whose last use has completed, or a new one
@@ -284,7 +287,7 @@ struct slora_plan {
     void *last_stream = nullptr; // hipStream_t of the latest upload or launch
     bool order_recorded = false; // set->order already marks the end of the work on last_stream
 
-    int32_t upload();
+    int32_t upload(bool once, void *stream); // once: for a single call, on `stream`
     int32_t enter(void *stream);
     void fill_args(slora::MultiArgs &a, int32_t n, float *v, const slora::Route &r) const;
 };
@@ -299,6 +302,7 @@ int32_t build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids, int32
 // kernel launchers (kernels.hip); all return a SLORA_* code
 int32_t launch_write_pages(slora_pool *pool, const int32_t *d_idx, int64_t n, const void *d_src,
                            void *stream, int32_t max_groups = 0); // max_groups > 0 caps the grid
+int32_t launch_copy(void *dst, const void *src, size_t bytes, void *stream); // 16-byte aligned; src may be pinned host memory
 int32_t launch_gather(slora_pool *pool, int64_t arena_entry, int32_t rank, void *dev_out, void *stream);
 int32_t static_scratch_address(int device, void **out); // `device` must be current
 int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, const Route &route);

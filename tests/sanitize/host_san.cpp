@@ -60,6 +60,7 @@ hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)std::malloc(1); return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { std::free((void *)s); return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) { *s = hipStreamCaptureStatusNone; return hipSuccess; }
 hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p)
 {
     std::memset(a, 0, sizeof *a);
@@ -91,6 +92,13 @@ int32_t launch_write_pages(slora_pool *pool, const int32_t *d_idx, int64_t n, co
         std::memcpy(static_cast<uint16_t *>(pool->dev_base) + (int64_t)d_idx[i] * pool->H,
                     static_cast<const uint16_t *>(d_src) + i * pool->H, (size_t)pool->H * 2);
     }
+    return SLORA_OK;
+}
+
+int32_t launch_copy(void *dst, const void *src, size_t bytes, void *)
+{
+    REQUIRE(bytes > 0 && bytes % 16 == 0);
+    std::memcpy(dst, src, bytes);
     return SLORA_OK;
 }
 
