@@ -1536,50 +1536,58 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void shrink_mfma_kernel(const MsIt
 #undef SLORA_MS
 }
 
-// One workgroup per split tile, token block and slot; its wavefront nb adds up the shares of rank
-// block nb in the order of their numbers (a fixed order: the same bits on every run; the loads of
-// four shares are in flight at a time) and finishes the block as the shrink itself does for a
-// tile that was not split.  Binary16: the row maximum over the rank blocks meets in LDS.
-template <int DT, int NP>
-__global__ __launch_bounds__(kMfmaThreads) void join_shares_kernel(const MsItem *__restrict__ tiles, int v_stride,
-                                                                    MultiArgs args)
+// One workgroup per split tile, token block and slot; its wavefronts add up the shares of a rank block, or
+// of half of one (Wide), in the order of their numbers (a fixed order: the same bits on every run) and finish it as the
+// shrink itself does for a tile that was not split.  Binary16: the row maximum over the rank blocks meets in LDS.
+// Bound by the round trips.  The tiles of a dual plan have up to 32 shares: Wide requests 16 of them at a time (512
+// tokens of rank 64, H = 4096, 4 slots: 6.6 -> 5.6 us); others have two to five, and more threads only make their many
+// small workgroups dearer (5.4 -> 6.4 us for sixteen prompts, 10.6 -> 12.7 us for 2251 tokens of rank 128 among others).
+constexpr int join_waves(bool wide) { return kMsRanks / 32 * (wide ? 2 : 1); }
+template <int DT, int NP, bool Wide>
+__global__ __launch_bounds__(join_waves(Wide) * kWave) void join_shares_kernel(const MsItem *__restrict__ tiles, int v_stride,
+                                                                               MultiArgs args)
 {
-    constexpr int kBlocks = kMsTok / 32;
-    __shared__ float smax[kMsRanks / 32][32];
+    constexpr int kBlocks = kMsTok / 32, kWaves = join_waves(Wide);
+    constexpr int NO = Wide ? 1 : 2;                          // octets of ranks of a lane
+    constexpr int kBatch = Wide ? 16 : 4;
+    __shared__ float smax[kWaves][32];
     const int cs = blockIdx.x % args.n;
     const int tb = (blockIdx.x / args.n) % kBlocks;          // token block
     const MsItem it = tiles[blockIdx.x / args.n / kBlocks];
     const int lane = threadIdx.x & (kWave - 1);
-    const int nb = threadIdx.x / kWave;                       // rank block of this wavefront
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int nb = Wide ? wave >> 1 : wave, half = Wide ? wave & 1 : 0; // rank block of this wavefront, its first half
     const int row = lane & 31, q = lane >> 5;
+    const int oct = nb * 4 + q + 2 * half;                    // first octet of this lane; the other is two further on
     const int mb_act = (it.ntok + 31) >> 5, nb_act = (it.nj + 31) >> 5;
     if (tb >= mb_act) return;                                 // the whole workgroup
     const bool live = nb < nb_act;
-    float val[2][8];
+    float val[NO][8];
 #pragma unroll
-    for (int i = 0; i < 2; ++i)
+    for (int i = 0; i < NO; ++i)
 #pragma unroll
         for (int e = 0; e < 8; ++e) val[i][e] = 0.f;
     if (live) {
         const int64_t blk = share_block(it);
-        const float *base = args.v[cs] + args.part_off + it.part_off + (int64_t)(tb * nb_act + nb) * 1024 + lane * 8;
-        constexpr int kBatch = 4;
+        const float *base = args.v[cs] + args.part_off + it.part_off + (int64_t)(tb * nb_act + nb) * 1024 + half * 512 + lane * 8;
         for (int p0 = 0; p0 < it.n_parts; p0 += kBatch) {
-            f32x4 w[kBatch][4];
+            f32x4 w[kBatch][2 * NO];
 #pragma unroll
             for (int k = 0; k < kBatch; ++k) {
-                const float *srcp = base + (int64_t)min(p0 + k, it.n_parts - 1) * blk;
+                if (p0 + k < it.n_parts) {
+                    const float *src = base + (int64_t)(p0 + k) * blk;
 #pragma unroll
-                for (int i = 0; i < 2; ++i) {
-                    w[k][2 * i] = *reinterpret_cast<const f32x4 *>(srcp + i * 512);
-                    w[k][2 * i + 1] = *reinterpret_cast<const f32x4 *>(srcp + i * 512 + 4);
+                    for (int i = 0; i < NO; ++i) {
+                        w[k][2 * i] = *reinterpret_cast<const f32x4 *>(src + i * 512);
+                        w[k][2 * i + 1] = *reinterpret_cast<const f32x4 *>(src + i * 512 + 4);
+                    }
                 }
             }
 #pragma unroll
             for (int k = 0; k < kBatch; ++k) {
                 if (p0 + k < it.n_parts) {
 #pragma unroll
-                    for (int i = 0; i < 2; ++i)
+                    for (int i = 0; i < NO; ++i)
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
                             val[i][e] += w[k][2 * i][e];
@@ -1591,22 +1599,24 @@ __global__ __launch_bounds__(kMfmaThreads) void join_shares_kernel(const MsItem 
     }
     float sc = 1.f;
     const bool token_ok = tb * 32 + row < it.ntok;
-    float vmax = fmaxf(mask_octet(it, nb * 4 + q, val[0]), mask_octet(it, nb * 4 + q + 2, val[1]));
+    float vmax = 0.f;
+#pragma unroll
+    for (int i = 0; i < NO; ++i) vmax = fmaxf(vmax, mask_octet(it, oct + 2 * i, val[i]));
     if constexpr (DT == SLORA_F16) {
         vmax = fmaxf(vmax, __shfl_xor(vmax, 32, kWave));
-        if (q == 0) smax[nb][row] = vmax;
+        if (q == 0) smax[wave][row] = vmax;
         __syncthreads();
 #pragma unroll
-        for (int k = 0; k < kMsRanks / 32; ++k) vmax = fmaxf(vmax, smax[k][row]);
+        for (int k = 0; k < kWaves; ++k) vmax = fmaxf(vmax, smax[k][row]);
         const int e = row_exponent<NP>(vmax);
         sc = pow2f(e);
-        if (nb == 0 && q == 0)
+        if (wave == 0 && q == 0)
             *vexp_row(reinterpret_cast<int8_t *>(args.v[cs] + args.vexp_off), it, it.tile + tb, v_stride, row) = (int8_t)(token_ok ? e : 0);
     }
     if (live && token_ok) {
         uint16_t *vfrag = reinterpret_cast<uint16_t *>(args.v[cs] + args.vfrag_off);
 #pragma unroll
-        for (int i = 0; i < 2; ++i) store_octet<DT, NP>(it, it.tile + tb, row, nb * 4 + q + 2 * i, val[i], sc, v_stride, vfrag);
+        for (int i = 0; i < NO; ++i) store_octet<DT, NP>(it, it.tile + tb, row, oct + 2 * i, val[i], sc, v_stride, vfrag);
     }
 }
 
@@ -2445,10 +2455,10 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *
         if (rc != SLORA_OK) return rc;
         if (plan->n_sync > 0) {
             const dim3 jgrid((unsigned)((size_t)plan->n_sync * (kMsTok / 32) * (size_t)n));
-            auto *join = pool->dtype != SLORA_F16   ? &join_shares_kernel<SLORA_BF16, 3>
-                         : plan->pieces(SLORA_F16) == 2 ? &join_shares_kernel<SLORA_F16, 2>
-                                                        : &join_shares_kernel<SLORA_F16, 3>;
-            hipLaunchKernelGGL(join, jgrid, dim3(kMfmaThreads), 0, st, plan->d_mj, plan->v_stride, args);
+            auto *join = pool->dtype != SLORA_F16 ? (plan->dual ? &join_shares_kernel<SLORA_BF16, 3, true> : &join_shares_kernel<SLORA_BF16, 3, false>)
+                         : plan->dual             ? &join_shares_kernel<SLORA_F16, 3, true>
+                                                  : &join_shares_kernel<SLORA_F16, 2, false>;
+            hipLaunchKernelGGL(join, jgrid, dim3((unsigned)(join_waves(plan->dual) * kWave)), 0, st, plan->d_mj, plan->v_stride, args);
             rc = check_launch("join_shares");
             if (rc != SLORA_OK) return rc;
         }
