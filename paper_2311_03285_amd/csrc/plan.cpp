@@ -478,7 +478,9 @@ Route slora_plan::route(int32_t n, bool apply, bool y16) const
     // which pays only while compute units stand idle: 111 items 62 us in as many workgroups, 48 in 153,
     // 35 in 222, but 236 items 47 -> 52 and 252 items 55 -> 58 us (launches of three or four slots).
     // Between: 177 items of three slots 39 us whole, 44 in halves; 189 halves against 345 quarters 15 us less.
-    while (r.sub + 1 < kMsSubs && ms_wgs[r.sub] * n < 160) r.sub++;
+    // Quarters pay a little less long than halves: 126 halves 31.6, 252 quarters 29.0 us; 132 / 264 38.4 / 36.2, but 148 / 296
+    // 33.4 / 41.0, 184 / 368 34.0 / 43.6 us; 148 whole / 296 halves 63.8 / 51.2.
+    while (r.sub + 1 < kMsSubs && ms_wgs[r.sub] * n < (r.sub == 0 ? 160 : 140)) r.sub++;
     // Calls of fewer slots than the list's runs are made for share a run out until there are 1024 workgroups.  Sixteen
     // prompts in a pool of 64 slots, us per call of one slot in 256 / 768 / 1024 / 1536 / 2048 workgroups 84 / 63 /
     // 63 / 63 / 67 (16-bit y 81 / 54 / 54 / 55 / 59), of two in 512 / 1024 / 1536 / 2048 101 / 91 / 90 / 93 (87 / 74 / 71 /
