@@ -842,17 +842,19 @@ __device__ __forceinline__ void expand_own(const Item &it, int t0, const int32_t
         for (int e = 0; e < 8; ++e) sum[e] = acc[e] = 0.f;
 #pragma unroll
         for (int b = 0; b < R / 8; ++b) {
+            if (b < 3 || it.rank > 24) { // up to 24 ranks: no fourth block, all of whose rows would be the last one, times zero (NaN if it is infinite)
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int j = 8 * b + u;
-                const float vv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[0]), j));
-                float f[8];
-                widen2<DT>(w[j].x, f[0], f[1]);
-                widen2<DT>(w[j].y, f[2], f[3]);
-                widen2<DT>(w[j].z, f[4], f[5]);
-                widen2<DT>(w[j].w, f[6], f[7]);
+                for (int u = 0; u < 8; ++u) {
+                    const int j = 8 * b + u;
+                    const float vv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[0]), j));
+                    float f[8];
+                    widen2<DT>(w[j].x, f[0], f[1]);
+                    widen2<DT>(w[j].y, f[2], f[3]);
+                    widen2<DT>(w[j].z, f[4], f[5]);
+                    widen2<DT>(w[j].w, f[6], f[7]);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) acc[e] = fmaf(vv, f[e], acc[e]);
+                    for (int e = 0; e < 8; ++e) acc[e] = fmaf(vv, f[e], acc[e]);
+                }
             }
             if (!by16 || (b & 1) || b == R / 8 - 1) { // the end of a block
 #pragma unroll
