@@ -782,8 +782,11 @@ __global__ __launch_bounds__(kShrinkThreads) void shrink_gang_kernel(GangArgs g,
 // group's fours; row w has the blocks w, w + 4, ... - which are added in the order of w.  Who forms them does not matter:
 //   up to kOwnRanks ranks: a wavefront keeps all B rows of its columns in registers and forms whole sums, of
 //     every fourth token of the workgroup's;
-//   more: wavefront w forms row w for four tokens, the parts meet in LDS, and wavefront t finishes token t.
-// B rows, page numbers and y are requested before v is needed.  Bound by the chain of round trips in small calls, by
+//   more, or one or two tokens of more than 16: wavefront w forms row w for up to four tokens, the parts meet in LDS, and wavefront t
+//     finishes token t (48 tokens of rank 32, 12 groups of one / two on 4 slots: 5.6 -> 5.2 / 6.3 -> 5.5 us).
+// B rows and page numbers are requested before v is needed; y, v and the token of a whole sum before its B rows: 4.2 -> 4.5 us for 24 tokens of
+// rank 24, 6.4 -> 8.6 for 240 in twenties.  B rows are kept in the caches: items of one group share them, and streaming loads cost
+// 0.3-1 us (which leaves the L2 less of the A rows of a call that is repeated: 5.5 -> 5.9 us for the shrink of 24 tokens of rank 64).  Bound by the chain of round trips in small calls, by
 // the fp32 additions and 16-bit conversions where groups have many tokens.  Before, every item was four tokens with
 // its ranks shared out and wavefront 0 finished them all: 45 tokens of ranks 3-100, H = 3080, 3 slots 13.7 -> 9.4 us;
 // 51 tokens of ranks 30-130, H = 1168, 4 slots 15.2 -> 9.2; 142 tokens of ranks 5-130, H = 4096, 2 slots 17.0 -> 13.5; 376
@@ -868,7 +871,10 @@ __device__ __forceinline__ void expand_own(const Item &it, int t0, const int32_t
     }
 }
 
-// An item of at most TOK tokens; UB: ranks per block
+// An item of at most TOK tokens (1 or 2: exactly); UB: ranks per block.  One token has an instance of its own: with the
+// two-token one it requested, multiplied and passed through LDS a second token of zeros.  v is requested beside the page numbers, which
+// the B rows wait for anyway.  us of the expand, 24 tokens of rank 64, H = 4096: 5.8 -> 4.9; 8 of rank 128: 7.2 -> 5.5; 37 of ranks 16-128,
+// H = 3072: 7.8 -> 6.1.
 template <int DT, bool Y16, int TOK, int UB, class V>
 __device__ __forceinline__ void expand_shared(const Item &it, const int32_t *__restrict__ pb,
                                               const uint16_t *__restrict__ pool, const int32_t *__restrict__ tok_idx,
@@ -892,6 +898,8 @@ __device__ __forceinline__ void expand_shared(const Item &it, const int32_t *__r
     for (int w0 = 0; w0 < it.rank && wave * UB < it.rank - w0; w0 += kWave) {
         const int wr = min(kWave, it.rank - w0);
         const int pwin = lane < wr ? pb[w0 + lane] : 0;
+        float v[TOK]; // rank w0 + lane, if it is in one of this wavefront's blocks
+        from.get(it, 0, w0, lane < wr && lane / UB % kSplitWaves == wave, v_stride, v);
         u32x4 w[NB][UB];
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
@@ -904,8 +912,6 @@ __device__ __forceinline__ void expand_shared(const Item &it, const int32_t *__r
                 }
             }
         }
-        float v[TOK]; // rank w0 + lane, if it is in one of this wavefront's blocks
-        from.get(it, 0, w0, lane < wr && lane / UB % kSplitWaves == wave, v_stride, v);
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
             const int j0 = (wave + kSplitWaves * i) * UB;
@@ -919,7 +925,7 @@ __device__ __forceinline__ void expand_shared(const Item &it, const int32_t *__r
                     widen2<DT>(w[i][u].w, f[6], f[7]);
 #pragma unroll
                     for (int t = 0; t < TOK; ++t) {
-                        if (t < it.ntok) {
+                        if (TOK <= 2 || t < it.ntok) {
                             const float vv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v[t]), j0 + u));
 #pragma unroll
                             for (int e = 0; e < 8; ++e) acc[t][e] = fmaf(vv, f[e], acc[t][e]);
@@ -958,11 +964,14 @@ __device__ __forceinline__ void expand_split(const Item &it, const int32_t *__re
         expand_own<DT, Y16, 8>(it, wave, pb, pool, tok_idx, H, v_stride, y, make(std::integral_constant<int, 1>{}));
     else if (it.rank <= 16)
         expand_own<DT, Y16, 16>(it, wave, pb, pool, tok_idx, H, v_stride, y, make(std::integral_constant<int, 1>{}));
-    else if (it.rank <= kOwnRanks)
+    else if (it.rank <= kOwnRanks && it.ntok > 2)
         expand_own<DT, Y16, kOwnRanks>(it, wave, pb, pool, tok_idx, H, v_stride, y, make(std::integral_constant<int, 1>{}));
-    else if (it.ntok <= 2)
-        expand_shared<DT, Y16, 2, 16>(it, pb, pool, tok_idx, H, v_stride, y, make(std::integral_constant<int, 2>{}), red);
-    else
+    else if (it.ntok <= 2) { // two blocks or more: a wavefront each, while whole sums would keep one of them busy
+        if (it.ntok == 1)
+            expand_shared<DT, Y16, 1, 16>(it, pb, pool, tok_idx, H, v_stride, y, make(std::integral_constant<int, 1>{}), red);
+        else
+            expand_shared<DT, Y16, 2, 16>(it, pb, pool, tok_idx, H, v_stride, y, make(std::integral_constant<int, 2>{}), red);
+    } else
         expand_shared<DT, Y16, kExpandTok, 8>(it, pb, pool, tok_idx, H, v_stride, y, make(std::integral_constant<int, kExpandTok>{}), red);
 }
 

@@ -8,8 +8,8 @@ import torch
 
 from paper_2311_03285_amd import slora, synth
 from paper_2311_03285_amd.harness import DeviceWorkload, bits_to_device
-from gpu_util import assert_close, oracle_slot
-from test_gpu_y16 import assert_y16_close, oracle_y16
+from gpu_util import assert_close, gpu_slot, oracle_slot
+from test_gpu_y16 import assert_y16_close, gpu_y16, oracle_y16
 
 pytestmark = pytest.mark.gpu
 
@@ -57,3 +57,20 @@ def test_larger_items_are_bit_identical(H, dtype):
                 else:
                     rel, _ = assert_close(one[s].cpu().numpy(), oracle_slot(w, s), f"slot {s}")
                     assert rel <= 2e-6, rel
+
+
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+@pytest.mark.parametrize("H", [520, 2056])
+def test_one_and_two_tokens(dtype, H):
+    """Items of one and two tokens on both sides of 16 and 32 ranks, of a window of 64 and of blocks of 16."""
+    ranks = (16, 17, 24, 31, 32, 33, 48, 64, 65, 80, 128, 130)
+    ids = np.concatenate([np.arange(12), np.arange(0, 12, 2)]).astype(np.int32)     # every other adapter: two
+    ids = ids[np.random.default_rng(H).permutation(ids.size)]
+    w = synth.make_workload("few", 870 + H, H, dtype, 2 * 2 * sum(ranks) + 8, 2, ranks, ids)
+    with DeviceWorkload(w, real_adapters="all") as dw:
+        plan = dw.plan()
+        rel, _ = assert_close(gpu_slot(dw, 1, plan), oracle_slot(w, 1), "fp32 y")
+        assert rel <= 2e-6, rel
+        got = gpu_y16(dw, [1], plan)[0]
+        ref, exact = oracle_y16(w, 1)
+        assert_y16_close(got, ref, exact, w.y16_bits(1), dtype, "16-bit y")
