@@ -152,9 +152,46 @@ static void check_scratch(const slora_plan *plan, int32_t n, const MultiArgs &a,
     for (int32_t k = 1; k < n; ++k) REQUIRE(a.v[k] - a.v[0] == k * plan->v_slot_floats(plan->pool->dtype, plan->mfma_on(route)));
 }
 
+// Items of a vector kernel: of every position (token of an adapter) in them each of `units` ranks or columns once
+struct Cover {
+    const size_t row;
+    std::vector<uint8_t> done;
+    std::vector<int32_t> units, count; // of a position: how many there are (0: not in an item yet), how many are done
+    Cover(int32_t positions, size_t most) : row(most), done((size_t)positions * most), units((size_t)positions), count((size_t)positions) {}
+    void add(const Item &it, int32_t of, int32_t lo, int32_t hi)
+    {
+        for (int32_t p = it.pos0; p < it.pos0 + it.ntok; ++p) {
+            REQUIRE(units[(size_t)p] == 0 || units[(size_t)p] == of);
+            units[(size_t)p] = of;
+            for (int32_t u = lo; u < hi; ++u) REQUIRE(!done[(size_t)p * row + (size_t)u]++);
+            count[(size_t)p] += hi - lo;
+        }
+    }
+    // every position is in the vector items, whole, or served elsewhere
+    void check(const std::vector<uint8_t> &elsewhere) const
+    {
+        for (size_t p = 0; p < units.size(); ++p) {
+            REQUIRE((units[p] != 0) != (elsewhere[p] != 0));
+            REQUIRE(count[p] == units[p]);
+        }
+    }
+};
+
+// positions that the MFMA kernels or the one-launch decode kernel serve
+static std::vector<uint8_t> served_elsewhere(const slora_plan *plan, const Route &route)
+{
+    std::vector<uint8_t> out((size_t)plan->T_act);
+    for (size_t i = 0; plan->mfma_on(route) && i < plan->ms_items.size(); ++i)
+        for (int32_t t = 0; t < plan->ms_items[i].ntok; ++t) out[(size_t)(plan->ms_items[i].pos0 + t)] = 1;
+    for (size_t i = 0; route.fused && i < plan->vf_items.size(); ++i)
+        for (int32_t t = 0; t < plan->vf_items[i].ntok; ++t) out[(size_t)(plan->vf_items[i].pos0 + t)] = 1;
+    return out;
+}
+
 // what the latest apply, shrink or expand launched
 struct Log {
     bool small = false, fused = false, mfma_shrink = false, mfma_expand = false;
+    bool wide = false, gang = false, gang_expand = false; // the larger items of the vector kernels
     size_t vec_shrink = 0, vec_expand = 0; // items
     size_t mfma_shrink_wgs = 0, mfma_expand_wgs = 0; // workgroups with work
 };
@@ -171,23 +208,40 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &a, void *, c
     REQUIRE(a.n == n && plan->v_stride % kRankPad == 0);
     REQUIRE(0 <= plan->n_vs_plain && plan->n_vs_plain <= plan->n_vs_head && (size_t)plan->n_vs_head <= plan->vs_items.size());
     const size_t n_vs = plan->n_vs(route);
+    const bool gang = n_vs > 0 && route.gang; // the larger items, then the small ones of the groups that are not in them
+    REQUIRE(0 <= plan->n_gs_plain && (size_t)plan->n_gs_plain <= plan->gs_items.size());
+    const size_t n_gs = gang ? plan->n_gs(route) : 0, n_vec = gang ? n_gs + plan->gv_items.size() : n_vs;
+    REQUIRE(n_vec == plan->shrink_wgs(route));
+    const std::vector<uint8_t> elsewhere = served_elsewhere(plan, route);
     g_seen = -1;
     check_scratch(plan, n, a, route);
     g_log.vec_shrink = n_vs;
+    g_log.wide = route.wide;
+    g_log.gang = gang;
     g_wide[plan] = route.wide;
     g_log.mfma_shrink = plan->mfma_on(route) && !plan->ms_items.empty();
     for (int32_t k = 0; k < n; ++k) {
         REQUIRE(a.x[k] && a.v[k]);
         float *v = a.v[k];
-        for (size_t i = 0; i < n_vs; ++i) {
-            const Item &it = plan->d_vs[i];
-            REQUIRE(std::memcmp(&it, &plan->vs_items[i], sizeof it) == 0);
+        Cover cover(plan->T_act, (size_t)plan->v_stride);
+        for (size_t i = 0; i < n_vec; ++i) {
+            const bool large = i < n_gs;
+            const Item &it = large ? plan->d_gs[i] : gang ? plan->d_gv[i - n_gs] : plan->d_vs[i];
+            REQUIRE(std::memcmp(&it, large ? &plan->gs_items[i] : gang ? &plan->gv_items[i - n_gs] : &plan->vs_items[i], sizeof it) == 0);
             check_pages(plan, it.arena_off, it.rank, a.slot[k]);
             check_tokens(plan, it.pos0, it.ntok);
-            REQUIRE(it.ntok <= kShrinkTok && it.a >= 0 && it.b > 0 && it.b <= pool->shrink_pages && it.a + it.b <= it.rank);
+            REQUIRE(it.a >= 0 && it.b > 0 && it.a + it.b <= it.rank);
+            if (large) {
+                REQUIRE(it.ntok <= kGangTok && it.b <= kGangPages);
+            } else { // its rows of x fit the LDS of the launch
+                REQUIRE(it.ntok <= kShrinkTok && it.ntok <= (gang ? plan->max_gv_tok : plan->max_shrink_tok) && it.b <= pool->shrink_pages);
+                REQUIRE(it.ntok == 1 || it.ntok * pool->H * 2 <= 65536);
+            }
+            cover.add(it, it.rank, it.a, it.a + it.b);
             for (int32_t t = 0; t < it.ntok; ++t)
                 for (int32_t j = it.a; j < it.a + it.b; ++j) v[(int64_t)(it.pos0 + t) * plan->v_stride + j] = 0.f;
         }
+        cover.check(elsewhere);
         uint16_t *frag = reinterpret_cast<uint16_t *>(v + a.vfrag_off);
         int8_t *vexp = reinterpret_cast<int8_t *>(v + a.vexp_off);
         float *part = v + a.part_off;
@@ -236,24 +290,35 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &a, void *, b
     REQUIRE(a.n == n);
     REQUIRE(0 <= plan->n_ve_plain && plan->n_ve_plain <= plan->n_ve_head && (size_t)plan->n_ve_head <= plan->ve_items.size());
     const size_t n_ve = plan->n_ve(route);
+    const bool gang = n_ve > 0 && route.gang_expand;
+    REQUIRE(!gang || plan->expand_split);
+    REQUIRE(0 <= plan->n_ge_plain && (size_t)plan->n_ge_plain <= plan->ge_items.size());
+    const size_t n_vec = gang ? plan->n_ge(route) : n_ve;
+    REQUIRE(n_vec == plan->expand_wgs(route));
+    const std::vector<uint8_t> elsewhere = served_elsewhere(plan, route);
     g_seen = -1;
     check_scratch(plan, n, a, route);
     g_log.vec_expand = n_ve;
+    g_log.gang_expand = gang;
     REQUIRE(g_wide.count(plan) && g_wide[plan] == route.wide);
     g_log.mfma_expand = plan->mfma_on(route) && !plan->me_items.empty();
     const int n_kk = plan->v_stride / 16, np = plan->pieces(pool->dtype);
     for (int32_t k = 0; k < n; ++k) {
         REQUIRE(a.y[k] && a.v[k]);
-        for (size_t i = 0; i < n_ve; ++i) {
-            const Item &it = plan->d_ve[i];
-            REQUIRE(std::memcmp(&it, &plan->ve_items[i], sizeof it) == 0);
+        Cover cover(plan->T_act, (size_t)pool->H / 8);
+        for (size_t i = 0; i < n_vec; ++i) {
+            const Item &it = gang ? plan->d_ge[i] : plan->d_ve[i];
+            REQUIRE(std::memcmp(&it, gang ? &plan->ge_items[i] : &plan->ve_items[i], sizeof it) == 0);
             check_pages(plan, it.arena_off, it.rank, a.slot[k]);
             check_tokens(plan, it.pos0, it.ntok);
-            REQUIRE(it.ntok <= kExpandTok && it.a >= 0 && it.b > 0 && it.a % 8 == 0 && it.a + it.b <= pool->H);
-            REQUIRE(it.b <= plan->expand_threads * 8 || plan->expand_split);
+            REQUIRE(it.ntok <= (gang && it.rank <= kOwnRanks ? kGangExpandTok : kExpandTok));
+            REQUIRE(it.a >= 0 && it.b > 0 && it.a % 8 == 0 && it.b % 8 == 0 && it.a + it.b <= pool->H);
+            REQUIRE(it.b <= (plan->expand_split ? 512 : plan->expand_threads * 8));
+            cover.add(it, pool->H / 8, it.a / 8, (it.a + it.b) / 8);
             for (int32_t t = 0; t < it.ntok; ++t)
                 for (int32_t j = 0; j < it.rank; j += 16) g_sink = a.v[k][(int64_t)(it.pos0 + t) * plan->v_stride + j];
         }
+        cover.check(elsewhere);
         std::set<std::pair<int, int>> done; // every tile and column range is in one run
         for (size_t i = 0; plan->mfma_on(route) && i < plan->me_items.size(); ++i) {
             const Item &it = plan->d_me[i];
@@ -481,7 +546,26 @@ static void slots_of_the_call()
     REQUIRE(!g_log.mfma_expand && g_log.vec_expand > 0);
 }
 
+// The larger items of the vector kernels: every call of a crowded plan covers each token's ranks and columns once,
+// also where the plan's groups of many tokens are on the MFMA kernels (fp32 y) or not (16-bit y, two-stage calls).
+static void larger_items()
+{
+    std::vector<std::pair<int, int>> groups;
+    for (int g = 0; g < 60; ++g) groups.push_back({g % 3 == 0 ? 40 : 32, 7 + g % 9}); // 7 .. 15 tokens
+    for (int g = 0; g < 8; ++g) groups.push_back({32, 1 + g % 4});
+    Bench plain(1024, 8, SLORA_BF16, groups);
+    groups.push_back({32, 800}); // too few tiles for a plan of MFMA groups: in both families' lists
+    Bench dual(1024, 8, SLORA_F16, groups);
+    for (Bench *b : {&plain, &dual}) {
+        REQUIRE(b->plan->dual == (b == &dual));
+        REQUIRE(b->apply(8) == SLORA_OK && g_log.gang && g_log.gang_expand && g_log.wide == (b == &dual));
+        REQUIRE(b->apply16(8) == SLORA_OK && g_log.gang && g_log.gang_expand && !g_log.wide);
+        REQUIRE(b->shrink(8) == SLORA_OK && g_log.gang && b->expand(8) == SLORA_OK && g_log.gang_expand);
+    }
+}
+
 static const struct { const char *name; void (*run)(); } kCases[] = {
+    {"larger_items", larger_items},
     {"failed_apply", failed_apply},
     {"static_route", static_route},
     {"scratch_is_sized_once", scratch_is_sized_once},
@@ -505,7 +589,7 @@ int main(int argc, char **argv)
     const unsigned seed = argc > 1 ? (unsigned)std::atoi(argv[1]) : 1u;
     std::mt19937 rng(seed);
     auto rnd = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
-    long calls = 0, plans_made = 0, both_families = 0;
+    long calls = 0, plans_made = 0, both_families = 0, larger = 0;
     for (int round = 0; round < 12; ++round) {
         const int32_t H = 8 * rnd(8, 160);
         const int64_t n_pages = rnd(200, 3000);
@@ -551,6 +635,7 @@ int main(int argc, char **argv)
                 }
                 g_fail_malloc = false;
                 both_families += plan->dual && g_log.mfma_expand;
+                larger += g_log.gang || g_log.gang_expand;
                 REQUIRE(rc == SLORA_OK || rc == SLORA_EBUSY || (rc == SLORA_ERANGE && entry == 0) ||
                         (rc == SLORA_EINVAL && (entry == 3 || entry == 4)) || (rc == SLORA_EHIP && no_memory));
             }
@@ -618,6 +703,7 @@ int main(int argc, char **argv)
         REQUIRE(slora_pool_destroy(pool) == SLORA_OK);
     }
     REQUIRE(both_families > 0); // MFMA calls on plans that hold both kernel families' lists
-    std::printf("host_san OK: seed %u, %ld calls, %ld plans, %ld on both families\n", seed, calls, plans_made, both_families);
+    REQUIRE(larger > 0);        // calls that take the vector kernels' larger items
+    std::printf("host_san OK: seed %u, %ld calls, %ld plans, %ld on both families, %ld of larger items\n", seed, calls, plans_made, both_families, larger);
     return 0;
 }
