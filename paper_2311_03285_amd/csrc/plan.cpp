@@ -309,9 +309,20 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         plan->n_gs_plain = plan->n_ge_plain = plan->max_gv_tok = 0;
         // (only if a call may be large enough to take them, see route: a call may name a slot more than once)
         const int64_t most_n = call_slots > 0 ? call_slots : SLORA_MAX_MULTI;
-        const bool gang = (int64_t)(plan->vs_items.size() + vs_dual.size()) * most_n >= kGangFrom;
-        const bool gang_expand = (int64_t)(plan->ve_items.size() + ve_dual.size()) * most_n >= kGangExpandFrom;
-        if (plan->expand_split && plan->vf_items.empty() && most_vec_tokens > kExpandTok && (gang || gang_expand)) {
+        const bool crowds = plan->expand_split && plan->vf_items.empty() && most_vec_tokens > kExpandTok;
+        const int64_t n_vs = (int64_t)plan->vs_items.size(), n_vs_all = n_vs + (int64_t)vs_dual.size();
+        bool gang = crowds && n_vs_all * most_n >= kGangFrom;
+        const bool gang_expand = crowds && (int64_t)(plan->ve_items.size() + ve_dual.size()) * most_n >= kGangExpandFrom;
+        if (gang) {
+            int64_t few = 0, few_dual = 0; // shrink items of a call that takes the larger ones
+            for (int32_t gi : order) {
+                const Group &g = groups[(size_t)gi];
+                const int32_t n = (int32_t)g.toks.size(), tok = n > kExpandTok ? kGangTok : shrink_tok, pages = n > kExpandTok ? kGangPages : shrink_pages;
+                if ((int64_t)n < min_tokens) (mfma_group(n) ? few_dual : few) += (int64_t)((n + tok - 1) / tok) * ((g.rank + pages - 1) / pages);
+            }
+            gang = gang_pays(n_vs, few) || gang_pays(n_vs_all, few + few_dual);
+        }
+        if (gang || gang_expand) {
             std::vector<Item> gs_dual, ge_dual;
             int32_t pos = 0;
             for (int32_t gi : order) {
@@ -471,7 +482,12 @@ Route slora_plan::route(int32_t n, bool apply, bool y16) const
     // shrink, 2066 / 294 workgroups 22.1 / 13.7, 2604 / 333 12.4 / 9.6, 1446 / 363 15.2 / 13.1, but 1520 / 208 7.6 / 8.1,
     // 792 / 748 9.2 / 12.5, 752 / 376 8.4 / 10.6, 744 / 96 9.6 / 13.1; expand, 6016 / 1536 22.6 / 15.8, 4338 / 1098 16.0 / 11.1,
     // 912 / 792 7.8 / 7.5, but 600 / 288 8.3 / 11.2, 414 / 333 10.4 / 12.8.
-    r.gang = n_gs(r) > 0 && (int64_t)n_vs(r) * n >= kGangFrom && (int64_t)(n_gs(r) + gv_items.size()) * n >= 256;
+    // The small items beside the larger ones pay for them (fewer of the gang kernel's workgroups fit a compute unit), so the larger ones
+    // must leave half the workgroups at most.  Workgroups small / large, us per call: 4992 / 2016 60 / 53, 4920 / 2085 53.6 / 49.0, 4480 / 2240
+    // 59 / 56, 2880 / 1200 40.9 / 39.1, but 2560 / 1440 44.8 / 46.6, 5056 / 3392 38.8 / 40.8, 10068 / 6993 49 / 52, 2080 / 1800 33.0 / 35.7, 7680 / 6560
+    // 37.5 / 43.5; 2304 / 1408 32.4 / 32.3, 2880 / 1760 39.4 / 39.4, and one composition found the other way round, 3072 / 2064 39.4 / 37.3.
+    const int64_t small_wgs = (int64_t)n_vs(r), large_wgs = (int64_t)(n_gs(r) + gv_items.size());
+    r.gang = n_gs(r) > 0 && small_wgs * n >= kGangFrom && large_wgs * n >= 256 && gang_pays(small_wgs, large_wgs);
     r.gang_expand = !ge_items.empty() && (int64_t)n_ve(r) * n >= kGangExpandFrom && (int64_t)n_ge(r) * n >= 512;
     // Tokens of an item per workgroup of the MFMA shrink.  The items of a call of modest size are too
     // few for the GPU; halves or quarters of their tokens read the pages two or four times as often,

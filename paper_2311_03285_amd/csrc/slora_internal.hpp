@@ -88,6 +88,7 @@ constexpr int kOwnRanks = 32;     // ... up to this many ranks a wavefront forms
 constexpr int kGangTok = 8;       // tokens per item of the shrink for groups of many tokens,
 constexpr int kGangPages = 16;    // pages, at most
 constexpr int kGangFrom = 1400, kGangExpandFrom = 2000; // least workgroups of the small items at which a call takes them (see route)
+constexpr bool gang_pays(int64_t small_items, int64_t large_items) { return 2 * large_items <= small_items; }
 constexpr int kGangExpandTok = 16; // tokens per item of the rank-split expand for such groups of at most kOwnRanks ranks
 constexpr int kMfmaTok = 32;      // tokens per v tile = per MFMA-expand item (one 32-row MFMA block)
 constexpr int kMsTok = 128;       // most tokens per MFMA-shrink item

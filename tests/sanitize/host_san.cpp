@@ -564,7 +564,26 @@ static void larger_items()
     }
 }
 
+// They are taken, and their lists held, where they leave at most half the workgroups: beside many small groups a few
+// larger ones would slow the small items down.
+static void larger_items_pay()
+{
+    const auto with = [](int n_small, int n_large, int toks, bool taken) {
+        std::vector<std::pair<int, int>> groups(n_small, {16, 1});
+        groups.insert(groups.end(), n_large, {16, toks});
+        Bench b(1024, 8, SLORA_F16, groups);
+        REQUIRE(b.apply(8) == SLORA_OK && g_log.vec_shrink * 8 >= 1400 && g_log.gang == taken && b.plan->gs_items.empty() == !taken);
+        REQUIRE(b.apply16(8) == SLORA_OK && g_log.gang == taken);
+    };
+    with(55, 5, 8, false);  // 260 small items / 225 larger and small
+    with(60, 1, 5, false);
+    with(40, 20, 8, false); // 320 / 180
+    with(36, 24, 8, true);  // 336 / 168
+    with(0, 60, 5, true);
+}
+
 static const struct { const char *name; void (*run)(); } kCases[] = {
+    {"larger_items_pay", larger_items_pay},
     {"larger_items", larger_items},
     {"failed_apply", failed_apply},
     {"static_route", static_route},

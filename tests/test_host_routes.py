@@ -23,6 +23,7 @@ def exe(tmp_path_factory):
 
 
 @pytest.mark.parametrize("case", ["failed_apply", "static_route", "scratch_is_sized_once", "fuse_decode_never",
-                                  "y_in_the_buffer_of_x", "expand_runs", "slots_of_the_call", "larger_items"])
+                                  "y_in_the_buffer_of_x", "expand_runs", "slots_of_the_call", "larger_items",
+                                  "larger_items_pay"])
 def test_case(exe, case):
     assert f"host_san OK: {case}" in run(exe, case)
