@@ -188,12 +188,13 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         const int32_t me_run = (int32_t)std::min<int64_t>(kMfmaRunMax, std::max<int64_t>(1, me_pairs / 1024));
         plan->me_run = me_run;
         plan->me_stages = 0;
-        int32_t n_vec_groups = 0, most_vec_tokens = 0;
+        int32_t n_vec_groups = 0, most_vec_tokens = 0, most_own_tokens = 0; // (own: of an adapter of at most kOwnRanks ranks)
         for (int32_t gi : order) {
             const int64_t n = (int64_t)groups[(size_t)gi].toks.size();
             if (n >= min_tokens) continue;
             n_vec_groups++;
             most_vec_tokens = std::max(most_vec_tokens, (int32_t)n);
+            if (groups[(size_t)gi].rank <= kOwnRanks) most_own_tokens = std::max(most_own_tokens, (int32_t)n);
         }
         // vector-expand items: long runs of columns, halved while a launch would have fewer
         // workgroups than the GPU has CUs
@@ -307,12 +308,13 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         plan->gv_items.clear();
         plan->ge_items.clear();
         plan->n_gs_plain = plan->n_ge_plain = plan->max_gv_tok = 0;
-        // (only if a call may be large enough to take them, see route: a call may name a slot more than once)
-        const int64_t most_n = call_slots > 0 ? call_slots : SLORA_MAX_MULTI;
+        // (only if a call of most_slots may take them, see route: they make a plan dearer, 40 groups of eight tokens of rank 64, H = 4096,
+        // 22 -> 27 us on the host.  A call that names a slot twice may have more; it takes the small items.)
         const bool crowds = plan->expand_split && plan->vf_items.empty() && most_vec_tokens > kExpandTok;
         const int64_t n_vs = (int64_t)plan->vs_items.size(), n_vs_all = n_vs + (int64_t)vs_dual.size();
-        bool gang = crowds && n_vs_all * most_n >= kGangFrom;
-        const bool gang_expand = crowds && (int64_t)(plan->ve_items.size() + ve_dual.size()) * most_n >= kGangExpandFrom;
+        bool gang = crowds && n_vs_all * most_slots >= kGangFrom;
+        const bool gang_expand = crowds && most_own_tokens > kExpandTok &&
+                                 (int64_t)(plan->ve_items.size() + ve_dual.size()) * most_slots >= kGangExpandFrom;
         if (gang) {
             int64_t few = 0, few_dual = 0; // shrink items of a call that takes the larger ones
             for (int32_t gi : order) {

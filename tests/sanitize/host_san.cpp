@@ -582,7 +582,20 @@ static void larger_items_pay()
     with(0, 60, 5, true);
 }
 
+// A plan holds no lists that calls of its pool's slots do not take.
+static void larger_items_of_no_call()
+{
+    const std::vector<std::pair<int, int>> low(60, {16, 8}), high(60, {40, 8}); // 8 and 20 shrink items a group, 4 expand items
+    for (int32_t n : {1, 2, 8}) {
+        Bench b(1024, n, SLORA_F16, low), h(1024, n, SLORA_F16, high);
+        REQUIRE(b.plan->gs_items.empty() == (480 * n < 1400) && b.plan->ge_items.empty() == (240 * n < 2000));
+        REQUIRE(h.plan->gs_items.empty() == (1200 * n < 1400) && h.plan->ge_items.empty()); // its expand has no larger items
+        REQUIRE(b.apply(n) == SLORA_OK && h.apply(n) == SLORA_OK);
+    }
+}
+
 static const struct { const char *name; void (*run)(); } kCases[] = {
+    {"larger_items_of_no_call", larger_items_of_no_call},
     {"larger_items_pay", larger_items_pay},
     {"larger_items", larger_items},
     {"failed_apply", failed_apply},

@@ -20,7 +20,7 @@ TOKENS = (17, 5, 33, 6, 19, 18, 7, 9, 10, 4, 2, 1)
 def crowd(H, dtype):
     ids = np.concatenate([np.repeat(np.arange(len(RANKS)), TOKENS), [-1, -1]])
     ids = ids[np.random.default_rng(H).permutation(ids.size)].astype(np.int32)
-    return synth.make_workload("crowd", 800 + H, H, dtype, 2 * 2 * sum(RANKS) + 8, 2, RANKS, ids)
+    return synth.make_workload("crowd", 800 + H, H, dtype, 2 * 8 * sum(RANKS) + 8, 8, RANKS, ids)   # calls of eight slots
 
 
 @pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
