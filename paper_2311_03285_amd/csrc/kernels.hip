@@ -2193,7 +2193,8 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void expand_mfma_kernel(const Item
                                                                     const int32_t *__restrict__ tok_idx, int H,
                                                                     int v_stride, int parts, MultiArgs args)
 {
-    // two buffers of V for the plan's widest adapter of up to 128 ranks, then each wavefront's own part
+    // two buffers of V, for the most 32-rank stages that an adapter of the plan has in one (four from 97 ranks on: 129 to 256 in halves), then each
+    // wavefront's own part
     extern __shared__ __attribute__((aligned(16))) unsigned char lds[];
     const int cs = blockIdx.x % args.n;
     // a run of tiles, or this workgroup's part of it

@@ -267,7 +267,10 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                     }
                 }
                 // expand: the tiles in runs of equal length; a run of one column range is one workgroup
-                if (g.rank <= 2 * kMsRanks) plan->me_stages = std::max(plan->me_stages, (std::min(g.rank, kMsRanks) + 31) / 32);
+                // V of at most kMsRanks ranks at a time passes through LDS; that of an adapter of more ranks than twice as many, or than
+                // kMsRanks if its pieces are scaled (see expand_mfma_kernel), does not
+                if (g.rank <= (plan->dual && pool->dtype == SLORA_F16 ? kMsRanks : 2 * kMsRanks))
+                    plan->me_stages = std::max(plan->me_stages, (std::min(g.rank, kMsRanks) + 31) / 32);
                 const int32_t n_runs = (n_tiles + me_run - 1) / me_run;
                 for (int32_t k = 0; k < n_runs; ++k) {
                     const int32_t t0 = n_tiles * k / n_runs, t1 = n_tiles * (k + 1) / n_runs;

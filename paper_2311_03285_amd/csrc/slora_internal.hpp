@@ -244,7 +244,7 @@ struct slora_plan {
     int64_t ms_wgs[slora::kMsSubs] = {};
     int32_t ms_lds[slora::kMsSubs] = {};
     int32_t me_run = 1;        // most tiles of a run of the MFMA expand list
-    int32_t me_stages = 0;     // most 32-rank stages an MFMA expand workgroup keeps in registers (sizes its LDS)
+    int32_t me_stages = 0;     // most 32-rank stages of V that an MFMA expand workgroup holds in one of its two LDS buffers
     int32_t n_sync = 0;        // tiles that the join kernel finishes: those in several shares, all of a dual plan
     int64_t part_floats = 0;   // partial sums of the split tiles, per slot
     int32_t n_rank_blocks = 1; // kMsRanks-blocks per row of v (exponent sets per tile)

@@ -339,6 +339,11 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &a, void *, b
                 for (int b = 0; b < 32 * plan->n_rank_blocks; ++b) g_sink = vexp[(int64_t)t * plan->n_rank_blocks * 32 + b];
             }
         }
+        int stages = 0; // an LDS buffer of V is as large as its widest user needs, see expand_mfma_kernel
+        for (const Item &it : plan->me_items)
+            if (it.rank <= kMsRanks || (it.rank <= 2 * kMsRanks && !(np == 3 && pool->dtype == SLORA_F16)))
+                stages = std::max(stages, (std::min(it.rank, kMsRanks) + 31) / 32);
+        REQUIRE(plan->me_stages == stages);
         REQUIRE(!g_log.mfma_expand || (int64_t)done.size() == (int64_t)plan->n_mfma_tiles * ((pool->H + kMfmaExpandCols - 1) / kMfmaExpandCols));
     }
     return SLORA_OK;
@@ -594,7 +599,20 @@ static void larger_items_of_no_call()
     }
 }
 
+// LDS of the MFMA expand: adapters of 129 to 256 ranks use its buffers but where v is in scaled pieces
+static void expand_lds()
+{
+    for (int32_t dtype : {SLORA_F16, SLORA_BF16})
+        for (int32_t rank : {32, 128, 129, 200, 256, 257}) {
+            Bench b(1024, 8, dtype, {{rank, 512}});
+            const bool scaled = dtype == SLORA_F16;
+            REQUIRE(b.plan->dual && b.apply(8) == SLORA_OK && g_log.mfma_expand);
+            REQUIRE(b.plan->me_stages == (rank == 32 ? 1 : rank == 128 ? 4 : rank > 256 || scaled ? 0 : 4));
+        }
+}
+
 static const struct { const char *name; void (*run)(); } kCases[] = {
+    {"expand_lds", expand_lds},
     {"larger_items_of_no_call", larger_items_of_no_call},
     {"larger_items_pay", larger_items_pay},
     {"larger_items", larger_items},
