@@ -345,8 +345,8 @@ int32_t slora_lora_shrink_expand(slora_pool *pool, int32_t slot, const void *x,
  *                      expand on its own needs a slora_lora_shrink before it, not an apply).
  *                      With 1, calls on very small decode batches (a page or two of A per wavefront)
  *                      run in one launch too, a workgroup per 512 columns; 0 rules that out as well.
- *   "shrink_pages"     pages of A per work item of the decode shrink (default 4; up to 16 where groups of
- *                      many tokens fill the GPU)
+ *   "shrink_pages"     pages of A per work item of the decode shrink.  Until it is set: 4, or up to 16 where
+ *                      groups of many tokens fill the GPU; a value that is set holds for all items
  *   "upload_groups"    workgroups of slora_adapter_upload when the source is host memory (default
  *                      32: enough requests in flight to fill the host link; many more delay the
  *                      HBM traffic of kernels running on other streams)

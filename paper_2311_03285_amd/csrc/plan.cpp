@@ -206,7 +206,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         plan->expand_split = ecols == 512 && (int64_t)n_vec_groups * chunks < 512;
         // the vector shrink stages its tokens' x rows in LDS: at most 64 KiB of them per item
         const int32_t shrink_tok = std::max(1, std::min(kShrinkTok, 65536 / (H * 2)));
-        const int32_t shrink_pages = (int32_t)pool->shrink_pages;
+        const int32_t shrink_pages = pool->shrink_pages > 0 ? (int32_t)pool->shrink_pages : kShrinkPages;
         plan->expand_threads = ecols / 8;
         std::vector<Item> vs_tail, ve_tail, vs_dual, ve_dual;
         plan->vf_items.clear();
@@ -315,7 +315,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         // 22 -> 27 us on the host.  A call that names a slot twice may have more; it takes the small items.)
         const bool crowds = plan->expand_split && plan->vf_items.empty() && most_vec_tokens > kExpandTok;
         const int64_t n_vs = (int64_t)plan->vs_items.size(), n_vs_all = n_vs + (int64_t)vs_dual.size();
-        bool gang = crowds && n_vs_all * most_slots >= kGangFrom;
+        bool gang = crowds && pool->shrink_pages == 0 && n_vs_all * most_slots >= kGangFrom;
         const bool gang_expand = crowds && most_own_tokens > kExpandTok &&
                                  (int64_t)(plan->ve_items.size() + ve_dual.size()) * most_slots >= kGangExpandFrom;
         if (gang) {

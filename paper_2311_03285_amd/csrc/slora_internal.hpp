@@ -80,6 +80,7 @@ struct Route {
 
 // Tile constants the scheduler and the kernels must agree on.
 constexpr int kShrinkTok = 4;     // tokens per vector-shrink item (x rows staged in LDS)
+constexpr int kShrinkPages = 4;   // pages per vector-shrink item, unless the caller names a number
 constexpr int kExpandTok = 4;     // tokens per vector-expand item (accumulators in registers)
 constexpr int kSmallRanks = 32;   // most ranks of an adapter in a batch that runs in the one-launch kernel for small batches
 constexpr int kExpandColsMax = 1024; // most columns per vector-expand item (a multiple of 512, <= 4096; measured best on cfg4: 1024)
@@ -173,7 +174,7 @@ struct slora_pool {
     int64_t xcd_group = 0;                            // accepted, no effect
     int64_t upload_groups = 32;                       // workgroups of an adapter upload from host memory
     int64_t fuse_decode = 1;                          // 0: never, 1: when the batch has enough small groups, 2: always
-    int64_t shrink_pages = 4;                         // pages of A per vector-shrink item (its x rows are staged once for all of them)
+    int64_t shrink_pages = 0;                         // a caller's pages of A per vector-shrink item (its x rows are staged once for all of them); 0: kShrinkPages, or more
     int64_t mfma_split_bytes = 1 << 20;               // MFMA shrink: a tile's H range is cut into shares of about this many row bytes
     int64_t mfma_split_min_h = 1024;                  // ... but no share is shorter than this many elements of H
 

@@ -232,9 +232,9 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &a, void *, c
             check_tokens(plan, it.pos0, it.ntok);
             REQUIRE(it.a >= 0 && it.b > 0 && it.a + it.b <= it.rank);
             if (large) {
-                REQUIRE(it.ntok <= kGangTok && it.b <= kGangPages);
+                REQUIRE(it.ntok <= kGangTok && it.b <= kGangPages && pool->shrink_pages == 0);
             } else { // its rows of x fit the LDS of the launch
-                REQUIRE(it.ntok <= kShrinkTok && it.ntok <= (gang ? plan->max_gv_tok : plan->max_shrink_tok) && it.b <= pool->shrink_pages);
+                REQUIRE(it.ntok <= kShrinkTok && it.ntok <= (gang ? plan->max_gv_tok : plan->max_shrink_tok) && it.b <= (pool->shrink_pages > 0 ? pool->shrink_pages : kShrinkPages));
                 REQUIRE(it.ntok == 1 || it.ntok * pool->H * 2 <= 65536);
             }
             cover.add(it, it.rank, it.a, it.a + it.b);
@@ -611,7 +611,21 @@ static void expand_lds()
         }
 }
 
+// "shrink_pages" as the caller sets it, be it the default, holds for every item
+static void shrink_pages_of_the_caller()
+{
+    const std::vector<std::pair<int, int>> crowd(60, {32, 9});
+    for (int64_t pages : {0, 1, 4, 12}) {
+        std::vector<std::pair<const char *, int64_t>> options;
+        if (pages > 0) options.push_back({"shrink_pages", pages});
+        Bench b(1024, 8, SLORA_F16, crowd, options);
+        REQUIRE(b.apply(8) == SLORA_OK && g_log.gang == (pages == 0) && g_log.gang_expand);
+        REQUIRE(g_log.vec_shrink == (size_t)(60 * 3 * (pages == 1 ? 32 : pages == 12 ? 3 : 8)));
+    }
+}
+
 static const struct { const char *name; void (*run)(); } kCases[] = {
+    {"shrink_pages_of_the_caller", shrink_pages_of_the_caller},
     {"expand_lds", expand_lds},
     {"larger_items_of_no_call", larger_items_of_no_call},
     {"larger_items_pay", larger_items_pay},
@@ -653,7 +667,8 @@ int main(int argc, char **argv)
         REQUIRE(slora_set_option(pool, "mfma_split_bytes", 4096 << rnd(0, 6)) == SLORA_OK);
         REQUIRE(slora_set_option(pool, "mfma_split_min_h", 128 << rnd(0, 3)) == SLORA_OK);
         REQUIRE(slora_set_option(pool, "xcd_group", rnd(0, 3)) == SLORA_OK);
-        REQUIRE(slora_set_option(pool, "shrink_pages", rnd(1, 12)) == SLORA_OK);
+        const int pages = rnd(1, 12); // the half of the pools that does not set it may take the larger items
+        if (pages % 2) REQUIRE(slora_set_option(pool, "shrink_pages", pages) == SLORA_OK);
         REQUIRE(slora_set_option(pool, "fuse_decode", rnd(0, 2)) == SLORA_OK);
         std::vector<int32_t> loaded;
         std::vector<slora_plan *> plans;
