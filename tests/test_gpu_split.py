@@ -24,7 +24,7 @@ def crowd(H, dtype):
 
 
 @pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
-@pytest.mark.parametrize("H", [1032, 2056, 3080, 4096])   # one piece and a bit, two and a chunk; 3080, 4096: the expand's larger items too
+@pytest.mark.parametrize("H", [1032, 2056, 3080, 4096, 5128])   # half a piece, one and a chunk, one and a half, two, two and a half; the expand's larger items from 3080 on
 def test_larger_items_are_bit_identical(H, dtype):
     w = crowd(H, dtype)
     with DeviceWorkload(w, real_adapters="all") as dw:
@@ -43,13 +43,15 @@ def test_larger_items_are_bit_identical(H, dtype):
                 slora.lora_shrink(plan, which, [xs[s].data_ptr() for s in which])
                 (slora.lora_expand_y16 if y16 else slora.lora_expand)(plan, which, ptrs)
 
-            many, one = [new(s) for s in slots], [new(s) for s in (0, 1)]
+            many, applied, one = [new(s) for s in slots], [new(s) for s in slots], [new(s) for s in (0, 1)]
             two_kernels(slots, many)
+            apply = slora.lora_apply_multi_y16 if y16 else slora.lora_apply_multi
+            apply(plan, slots, [xs[s].data_ptr() for s in slots], [t.data_ptr() for t in applied])
             for s in (0, 1):
                 two_kernels([s], [one[s]])
             torch.cuda.synchronize()
-            for s, got in zip(slots, many):
-                assert torch.equal(got, one[s]), (y16, s)
+            for s, got, got2 in zip(slots, many, applied):
+                assert torch.equal(got, one[s]) and torch.equal(got2, one[s]), (y16, s)
             for s in (0, 1):
                 if y16:
                     ref, exact = oracle_y16(w, s)
@@ -74,3 +76,47 @@ def test_one_and_two_tokens(dtype, H):
         got = gpu_y16(dw, [1], plan)[0]
         ref, exact = oracle_y16(w, 1)
         assert_y16_close(got, ref, exact, w.y16_bits(1), dtype, "16-bit y")
+
+
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+def test_larger_items_beside_groups_of_both_families(dtype):
+    """A crowd of small groups and a few of many tokens that are in both kernel families' lists: an apply to fp32 y serves those
+    on the MFMA kernels, 16-bit y and the two-stage calls everything on the vector kernels - with the larger items each time."""
+    H, n_slots = 3080, 8
+    ranks = [8, 9, 17, 32, 33, 40, 64, 100] * 3 + [40, 17]
+    toks = [5 + g % 8 for g in range(24)] + [600, 19]
+    ids = np.repeat(np.arange(26), toks)[np.random.default_rng(5).permutation(sum(toks))].astype(np.int32)
+    w = synth.make_workload("both", 880, H, dtype, 2 * n_slots * sum(ranks) + 8, n_slots, ranks, ids)
+    few = torch.from_numpy(ids < 24)
+    quads = [-(-t // 4) for t in toks[:24]]
+    assert 8 * sum(q * -(-r // 4) for q, r in zip(quads, ranks)) >= 1400 and 8 * 7 * sum(quads) >= 2000
+    with DeviceWorkload(w, real_adapters="all") as dw:
+        plan = dw.plan()
+        info = slora.plan_info(plan)
+        assert info["groups_mfma"] == 0 and info["mfma_expand_items"] > 0   # both forms
+        slots = list(range(n_slots))
+        xs = [dw.x_dev(s) for s in slots]
+        xp = [x.data_ptr() for x in xs]
+        for y16 in (False, True):
+            def new(s):
+                return bits_to_device(w.y16_bits(s), dw.device) if y16 else dw.y_dev(s)
+
+            expand = slora.lora_expand_y16 if y16 else slora.lora_expand
+            applied, two, one = [new(s) for s in slots], [new(s) for s in slots], [new(s) for s in slots]
+            (slora.lora_apply_multi_y16 if y16 else slora.lora_apply_multi)(plan, slots, xp, [y.data_ptr() for y in applied])
+            slora.lora_shrink(plan, slots, xp)
+            expand(plan, slots, [y.data_ptr() for y in two])
+            for s in slots:
+                slora.lora_shrink(plan, [s], [xp[s]])
+                expand(plan, [s], [one[s].data_ptr()])
+            torch.cuda.synchronize()
+            for s in slots:
+                a, t, o = (v[s].reshape(w.T, w.H).cpu() for v in (applied, two, one))
+                assert torch.equal(t, o), (y16, s)
+                if y16:
+                    assert torch.equal(a, o), s
+                else:   # the others' sums are formed in another order
+                    assert torch.equal(a[few], o[few]) and not torch.equal(a, o), s
+            if not y16:
+                rel, _ = assert_close(applied[3].cpu().numpy(), oracle_slot(w, 3), "applied")
+                assert rel <= 2e-6, rel

@@ -1,6 +1,6 @@
 """GPU parity of the MFMA expand for adapters of more than 128 ranks: up to 256 with B in registers and V in two halves of
 four 32-rank stages, beyond that streamed - at the edges of stages, on both sides of each limit, with column ranges that leave
-wavefronts without columns, runs of one and of several tiles.
+wavefronts without columns, runs of one and of several tiles per workgroup.
 
 Integer-valued inputs have exact sums (below 2^24), so they are compared bit for bit; rows whose ranks differ in size
 by 2^12 from one 128-rank block to the next meet the change of scale between the halves."""
@@ -9,7 +9,7 @@ import pytest
 import torch
 
 from paper_2311_03285_amd import slora, synth
-from paper_2311_03285_amd.harness import DeviceWorkload
+from paper_2311_03285_amd.harness import DeviceWorkload, bits_to_device
 from gpu_util import assert_close, gpu_slot, oracle_slot
 from test_gpu_mfma import MFMA_ALL, route
 from test_gpu_y16 import assert_y16_close, gpu_y16, oracle_y16
@@ -74,3 +74,40 @@ def test_halves_of_different_size(dtype, small_first):
     slora.plan_destroy(plan)
     slora.pool_destroy(pool)
     assert rel <= 2e-6, rel   # sums of 512 + 200 products in 32 bits
+
+
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+def test_runs_of_several_tiles(dtype):
+    """Three tiles per workgroup in a call of eight slots, one in calls of one: the same bits.  The last column range is 72
+    wide, so two of its four wavefronts only copy V."""
+    H, n_slots, lens = 584, 8, (700, 257, 33, 640, 65, 96, 1400, 31, 1200)
+    seg = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    ids = np.repeat(np.random.default_rng(960).permutation(len(RANKS)), lens).astype(np.int32)
+    w = synth.make_workload("runs", 960, H, dtype, 2 * n_slots * sum(RANKS) + 64, n_slots, RANKS, ids, seg)
+    with DeviceWorkload(w, real_adapters="all") as dw:
+        route(dw.pool, MFMA_ALL)
+        plan = dw.plan()
+        tiles, ranges = [-(-n // 32) for n in lens], -(-H // 256)
+        assert slora.plan_info(plan)["mfma_expand_items"] == sum(tiles) * ranges
+        run = sum(tiles) * ranges * n_slots // 1024          # tiles of a run; a run is not shared out from 1024 workgroups on
+        assert run == 3 and sum(-(-t // run) for t in tiles) * ranges * n_slots >= 1024 >= 3 * sum(-(-t // run) for t in tiles) * ranges
+        slots = list(range(n_slots))
+        xs = [dw.x_dev(s) for s in slots]
+        for y16 in (False, True):
+            def apply(which):
+                ys = [bits_to_device(w.y16_bits(s), dw.device) if y16 else dw.y_dev(s) for s in which]
+                fn = slora.lora_apply_multi_y16 if y16 else slora.lora_apply_multi
+                fn(plan, which, [xs[s].data_ptr() for s in which], [y.data_ptr() for y in ys])
+                torch.cuda.synchronize()
+                return ys
+
+            many = apply(slots)
+            for s in slots:
+                assert torch.equal(many[s], apply([s])[0]), (y16, s)
+            got = many[-1].cpu().numpy()
+            if y16:
+                ref, exact = oracle_y16(w, n_slots - 1)
+                assert_y16_close(got.view(np.uint16).reshape(w.T, w.H), ref, exact, w.y16_bits(n_slots - 1), dtype, "16-bit y")
+            else:
+                rel, _ = assert_close(got, oracle_slot(w, n_slots - 1), "fp32 y")
+                assert rel <= 5e-6, rel
