@@ -742,37 +742,28 @@ __device__ __forceinline__ void shrink_gang(const Item &it, const int32_t *__res
     }
 }
 
-// Workgroup `no` of a slot: the items of this kernel, then the vector-shrink items of the groups that are not in them.
-struct GangArgs {
-    const Item *items, *plain;
-    unsigned n_items;
-};
-template <int DT, int U, class Put>
-__device__ __forceinline__ void shrink_crowd(const GangArgs &g, unsigned no, const int32_t *__restrict__ arena, int slot,
-                                             const uint16_t *__restrict__ pool, const uint16_t *__restrict__ x,
-                                             const int32_t *__restrict__ tok_idx, int H, u32x4 *smem, Put put)
-{
-    const bool gang = no < g.n_items;
-    const Item it = gang ? g.items[no] : g.plain[no - g.n_items];
-    const int32_t *pa = arena + it.arena_off + (int64_t)slot * 2 * it.rank + it.a;
-    auto at = [&](int t, int j, float s) { put(it.pos0 + t, it.a + j, s); };
-    if (gang)
-        shrink_gang<DT>(it, pa, pool, x, tok_idx, H, smem, at);
-    else
-        shrink_vec_item<DT, U>(it, pa, pool, x, tok_idx, H, smem, at);
-}
-
+// n_items items of this kernel, then the vector-shrink items (`plain`) of the groups that are not in them
 template <int DT, int U>
-__global__ __launch_bounds__(kShrinkThreads) void shrink_gang_kernel(GangArgs g, const int32_t *__restrict__ arena,
-                                                                         const uint16_t *__restrict__ pool,
+__global__ __launch_bounds__(kShrinkThreads) void shrink_gang_kernel(const Item *__restrict__ items, unsigned n_items,
+                                                                      const Item *__restrict__ plain,
+                                                                      const int32_t *__restrict__ arena,
+                                                                      const uint16_t *__restrict__ pool,
                                                                       const int32_t *__restrict__ tok_idx, int H,
                                                                       int v_stride, MultiArgs args)
 {
     extern __shared__ u32x4 smem[]; // a piece of kGangTok rows of x, or the rows of a vector-shrink item
     const int cs = blockIdx.x % args.n;
+    const unsigned no = blockIdx.x / args.n;
+    const bool gang = no < n_items;
+    const Item it = gang ? items[no] : plain[no - n_items];
+    const int32_t *pa = arena + it.arena_off + (int64_t)args.slot[cs] * 2 * it.rank + it.a;
+    const uint16_t *x = static_cast<const uint16_t *>(args.x[cs]);
     float *v = args.v[cs];
-    shrink_crowd<DT, U>(g, blockIdx.x / args.n, arena, args.slot[cs], pool, static_cast<const uint16_t *>(args.x[cs]), tok_idx, H,
-                        smem, [&](int pos, int j, float s) { v[(int64_t)pos * v_stride + j] = s; });
+    auto put = [&](int t, int j, float s) { v[(int64_t)(it.pos0 + t) * v_stride + it.a + j] = s; };
+    if (gang)
+        shrink_gang<DT>(it, pa, pool, x, tok_idx, H, smem, put);
+    else
+        shrink_vec_item<DT, U>(it, pa, pool, x, tok_idx, H, smem, put);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -795,16 +786,13 @@ __global__ __launch_bounds__(kShrinkThreads) void shrink_gang_kernel(GangArgs g,
 // slower, half as fast on groups of many tokens (spills).
 // ---------------------------------------------------------------------------------------
 // v of ranks w0 + lane, where `mine`, of tokens t0 .. t0 + TOK - 1 of an item
-template <int DT, int TOK>
-struct StoredV {
-    const float *v;
-    __device__ __forceinline__ void get(const Item &it, int t0, int w0, bool mine, int v_stride, float (&out)[TOK])
-    {
-        const float *at = v + (int64_t)(it.pos0 + t0) * v_stride + w0 + (threadIdx.x & (kWave - 1));
+template <int TOK>
+__device__ __forceinline__ void load_v(const Item &it, int t0, int w0, bool mine, const float *__restrict__ v, int v_stride, float (&out)[TOK])
+{
+    const float *at = v + (int64_t)(it.pos0 + t0) * v_stride + w0 + (threadIdx.x & (kWave - 1));
 #pragma unroll
-        for (int t = 0; t < TOK; ++t) out[t] = t0 + t < it.ntok && mine ? at[(int64_t)t * v_stride] : 0.f;
-    }
-};
+    for (int t = 0; t < TOK; ++t) out[t] = t0 + t < it.ntok && mine ? at[(int64_t)t * v_stride] : 0.f;
+}
 // keeps the compiler from widening rows once and holding them at twice the size
 template <int N>
 __device__ __forceinline__ void stay_narrow(u32x4 (&w)[N])
@@ -814,10 +802,10 @@ __device__ __forceinline__ void stay_narrow(u32x4 (&w)[N])
 }
 
 // R: ranks in registers.  Tokens t0, t0 + 4, ... of the item.
-template <int DT, bool Y16, int R, class V>
+template <int DT, bool Y16, int R>
 __device__ __forceinline__ void expand_own(const Item &it, int t0, const int32_t *__restrict__ pb,
                                            const uint16_t *__restrict__ pool, const int32_t *__restrict__ tok_idx, int H,
-                                           int v_stride, void *__restrict__ y, V from)
+                                           int v_stride, void *__restrict__ y, const float *__restrict__ vs)
 {
     if (t0 >= it.ntok) return;
     const int lane = threadIdx.x & (kWave - 1);
@@ -837,7 +825,7 @@ __device__ __forceinline__ void expand_own(const Item &it, int t0, const int32_t
         const int64_t yoff = (int64_t)tok_idx[it.pos0 + t] * H + col;
         if (live) yv.load(y, yoff);
         float v[1];
-        from.get(it, t, 0, lane < it.rank, v_stride, v);
+        load_v(it, t, 0, lane < it.rank, vs, v_stride, v);
         stay_narrow(w);
         const bool by16 = left > 0 && left <= 2 && t >= it.ntok - left;
         float sum[8], acc[8];
@@ -875,10 +863,10 @@ __device__ __forceinline__ void expand_own(const Item &it, int t0, const int32_t
 // two-token one it requested, multiplied and passed through LDS a second token of zeros.  v is requested beside the page numbers, which
 // the B rows wait for anyway.  us of the expand, 24 tokens of rank 64, H = 4096: 5.8 -> 4.9; 8 of rank 128: 7.2 -> 5.5; 37 of ranks 16-128,
 // H = 3072: 7.8 -> 6.1.
-template <int DT, bool Y16, int TOK, int UB, class V>
+template <int DT, bool Y16, int TOK, int UB>
 __device__ __forceinline__ void expand_shared(const Item &it, const int32_t *__restrict__ pb,
                                               const uint16_t *__restrict__ pool, const int32_t *__restrict__ tok_idx,
-                                              int H, int v_stride, void *__restrict__ y, V from, float *red)
+                                              int H, int v_stride, void *__restrict__ y, const float *__restrict__ vs, float *red)
 {
     constexpr int NB = 16 / UB; // blocks of a wavefront in a window of 64 ranks
     const int lane = threadIdx.x & (kWave - 1);
@@ -899,7 +887,7 @@ __device__ __forceinline__ void expand_shared(const Item &it, const int32_t *__r
         const int wr = min(kWave, it.rank - w0);
         const int pwin = lane < wr ? pb[w0 + lane] : 0;
         float v[TOK]; // rank w0 + lane, if it is in one of this wavefront's blocks
-        from.get(it, 0, w0, lane < wr && lane / UB % kSplitWaves == wave, v_stride, v);
+        load_v(it, 0, w0, lane < wr && lane / UB % kSplitWaves == wave, vs, v_stride, v);
         u32x4 w[NB][UB];
 #pragma unroll
         for (int i = 0; i < NB; ++i) {
@@ -952,29 +940,7 @@ __device__ __forceinline__ void expand_shared(const Item &it, const int32_t *__r
     if (live) yv.add_store(y, yoff, d);
 }
 
-// An item: up to kGangExpandTok tokens of an adapter of at most kOwnRanks ranks, kExpandTok of another;
-// make(std::integral_constant<int, TOK>) gives the source of v
-template <int DT, bool Y16, class Make>
-__device__ __forceinline__ void expand_split(const Item &it, const int32_t *__restrict__ pb, const uint16_t *__restrict__ pool,
-                                             const int32_t *__restrict__ tok_idx, int H, int v_stride, void *__restrict__ y,
-                                             float *red, Make make)
-{
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    if (it.rank <= 8)
-        expand_own<DT, Y16, 8>(it, wave, pb, pool, tok_idx, H, v_stride, y, make(std::integral_constant<int, 1>{}));
-    else if (it.rank <= 16)
-        expand_own<DT, Y16, 16>(it, wave, pb, pool, tok_idx, H, v_stride, y, make(std::integral_constant<int, 1>{}));
-    else if (it.rank <= kOwnRanks && it.ntok > 2)
-        expand_own<DT, Y16, kOwnRanks>(it, wave, pb, pool, tok_idx, H, v_stride, y, make(std::integral_constant<int, 1>{}));
-    else if (it.ntok <= 2) { // two blocks or more: a wavefront each, while whole sums would keep one of them busy
-        if (it.ntok == 1)
-            expand_shared<DT, Y16, 1, 16>(it, pb, pool, tok_idx, H, v_stride, y, make(std::integral_constant<int, 1>{}), red);
-        else
-            expand_shared<DT, Y16, 2, 16>(it, pb, pool, tok_idx, H, v_stride, y, make(std::integral_constant<int, 2>{}), red);
-    } else
-        expand_shared<DT, Y16, kExpandTok, 8>(it, pb, pool, tok_idx, H, v_stride, y, make(std::integral_constant<int, kExpandTok>{}), red);
-}
-
+// An item: up to kGangExpandTok tokens of an adapter of at most kOwnRanks ranks, kExpandTok of another
 template <int DT, bool Y16>
 __global__ __launch_bounds__(kSplitWaves *kWave, 3) void expand_vec_split_kernel(const Item *__restrict__ items,
                                                                               const int32_t *__restrict__ arena,
@@ -983,11 +949,26 @@ __global__ __launch_bounds__(kSplitWaves *kWave, 3) void expand_vec_split_kernel
                                                                               int H, int v_stride, MultiArgs args)
 {
     extern __shared__ u32x4 smem[];
+    float *red = reinterpret_cast<float *>(smem);
     const int cs = blockIdx.x % args.n;
     const Item it = items[blockIdx.x / args.n];
     const int32_t *pb = arena + it.arena_off + (int64_t)args.slot[cs] * 2 * it.rank + it.rank;
-    expand_split<DT, Y16>(it, pb, pool, tok_idx, H, v_stride, args.y[cs],
-                          reinterpret_cast<float *>(smem), [&](auto tok) { return StoredV<DT, decltype(tok)::value>{args.v[cs]}; });
+    const float *v = args.v[cs];
+    void *y = args.y[cs];
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    if (it.rank <= 8)
+        expand_own<DT, Y16, 8>(it, wave, pb, pool, tok_idx, H, v_stride, y, v);
+    else if (it.rank <= 16)
+        expand_own<DT, Y16, 16>(it, wave, pb, pool, tok_idx, H, v_stride, y, v);
+    else if (it.rank <= kOwnRanks && it.ntok > 2)
+        expand_own<DT, Y16, kOwnRanks>(it, wave, pb, pool, tok_idx, H, v_stride, y, v);
+    else if (it.ntok <= 2) { // two blocks or more: a wavefront each, while whole sums would keep one of them busy
+        if (it.ntok == 1)
+            expand_shared<DT, Y16, 1, 16>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+        else
+            expand_shared<DT, Y16, 2, 16>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+    } else
+        expand_shared<DT, Y16, kExpandTok, 8>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -2381,19 +2362,6 @@ int32_t launch_fused(slora_plan *plan, int32_t n, const MultiArgs &args, void *s
 // LDS of the rank-split expand: its partial sums
 constexpr size_t kSplitLds = (size_t)kSplitWaves * kExpandTok * 8 * kWave * sizeof(float);
 
-// LDS of the vector shrink: its items' rows of x, at most 64 KiB, or a piece of the gang's
-static size_t vec_shrink_lds(const slora_plan *plan, const Route &route)
-{
-    const size_t row = (size_t)plan->pool->H * 2;
-    return route.gang ? std::max(kGangLds, plan->max_gv_tok * row) : plan->max_shrink_tok * row;
-}
-
-static GangArgs gang_args(const slora_plan *plan, const Route &route)
-{
-    if (!route.gang) return GangArgs{nullptr, plan->d_vs, 0};
-    return GangArgs{plan->d_gs, plan->d_gv, (unsigned)plan->n_gs(route)};
-}
-
 int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, const Route &route)
 {
     slora_pool *pool = plan->pool;
@@ -2402,12 +2370,11 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *
     const size_t n_vs = plan->n_vs(route);
     int32_t rc = SLORA_OK;
     if (n_vs > 0 && route.gang) {
-        const GangArgs g = gang_args(plan, route);
         const dim3 grid((unsigned)(plan->shrink_wgs(route) * (size_t)n));
-        const size_t lds = vec_shrink_lds(plan, route);
+        const size_t lds = std::max(kGangLds, (size_t)plan->max_gv_tok * pool->H * 2);
         const int U = shrink_loads_per_block(pool->H);
 #define SLORA_GANG(DT, UU) \
-    hipLaunchKernelGGL((shrink_gang_kernel<DT, UU>), grid, dim3(kShrinkThreads), lds, st, g, pool->d_arena, base, plan->d_tok_idx, pool->H, plan->v_stride, args)
+    hipLaunchKernelGGL((shrink_gang_kernel<DT, UU>), grid, dim3(kShrinkThreads), lds, st, plan->d_gs, (unsigned)plan->n_gs(route), plan->d_gv, pool->d_arena, base, plan->d_tok_idx, pool->H, plan->v_stride, args)
 #define SLORA_GANG_U(DT)                      \
     switch (U) {                              \
     case 4: SLORA_GANG(DT, 4); break;         \
