@@ -294,10 +294,12 @@ __device__ __forceinline__ void shrink_vec_core(const int32_t *__restrict__ pa, 
     }
 }
 
-// The x rows of `ntok` <= TOK tokens to LDS, [ntok][H/8] chunks.  All rows are requested before any is stored: one round trip
-// instead of one per token.  Vector shrink, us: 45 tokens of ranks 3-100, H = 3080, 3 slots 9.5 -> 8.4; 96 tokens of 4 adapters, H = 4096,
-// 3 slots 9.5 -> 8.7; 100 tokens of ranks 8-64, 1 slot 7.9 -> 6.5.
-template <int TOK>
+// The x rows of `ntok` <= TOK tokens to LDS, [ntok][H/8] chunks, CH chunks of a row per thread and trip.  All rows are requested before any is
+// stored: one round trip instead of one per token.  Vector shrink, us: 45 tokens of ranks 3-100, H = 3080, 3 slots 9.5 -> 8.4; 96 tokens of
+// 4 adapters, H = 4096, 3 slots 9.5 -> 8.7; 100 tokens of ranks 8-64, 1 slot 7.9 -> 6.5.  CH = 1 wherever the threads cover a row: with a
+// second chunk the vector shrink of H <= 2048 had 75 registers instead of 59, six wavefronts per SIMD instead of eight: 250 tokens of rank 64, H = 1024,
+// 4 slots 34 / 39 us, 250 pairs of rank 32, H = 2048 26.7 / 32.5.
+template <int TOK, int CH>
 __device__ __forceinline__ void stage_rows(const uint16_t *__restrict__ x, const int32_t *__restrict__ tok_idx, int pos0, int ntok,
                                            int H, int n_threads, u32x4 *xs)
 {
@@ -305,20 +307,20 @@ __device__ __forceinline__ void stage_rows(const uint16_t *__restrict__ x, const
     const u32x4 *row[TOK];
 #pragma unroll
     for (int t = 0; t < TOK; ++t) row[t] = reinterpret_cast<const u32x4 *>(x + (int64_t)tok_idx[pos0 + min(t, ntok - 1)] * H);
-    for (int c = threadIdx.x; c < nch; c += 2 * n_threads) {
-        const int d = c + n_threads;
-        u32x4 a[TOK], b[TOK];
+    for (int c = threadIdx.x; c < nch; c += CH * n_threads) {
+        u32x4 a[TOK][CH];
 #pragma unroll
         for (int t = 0; t < TOK; ++t)
             if (t < ntok) {
-                a[t] = row[t][c];
-                b[t] = row[t][min(d, nch - 1)];
+#pragma unroll
+                for (int i = 0; i < CH; ++i) a[t][i] = row[t][i == 0 ? c : min(c + i * n_threads, nch - 1)];
             }
 #pragma unroll
         for (int t = 0; t < TOK; ++t)
             if (t < ntok) {
-                xs[t * nch + c] = a[t];
-                if (d < nch) xs[t * nch + d] = b[t];
+#pragma unroll
+                for (int i = 0; i < CH; ++i)
+                    if (i == 0 || c + i * n_threads < nch) xs[t * nch + c + i * n_threads] = a[t][i];
             }
     }
 }
@@ -333,7 +335,7 @@ __device__ __forceinline__ void shrink_vec_item(const Item &it, const int32_t *_
     shrink_vec_core<DT, U>(
         pa, it.b, it.ntok, tid / kWave, kShrinkWaves, tid & (kWave - 1), pool, H, xs,
         [&]() {
-            stage_rows<kShrinkTok>(x, tok_idx, it.pos0, it.ntok, H, kShrinkThreads, xs);
+            stage_rows<kShrinkTok, U <= 4 ? 1 : 2>(x, tok_idx, it.pos0, it.ntok, H, kShrinkThreads, xs);
             __syncthreads();
         },
         put);
@@ -484,10 +486,11 @@ __global__ __launch_bounds__(512) void expand_vec_kernel(const Item *__restrict_
 // two dependent ones (each of which spends its first microseconds waiting for work items,
 // page lists and the first pages).  Used when a batch has enough such groups to fill the GPU
 // with whole-group workgroups (the scheduler decides); results are bit-identical to the two
-// kernels' - the same sums in the same order.
+// kernels' - the same sums in the same order.  Five wavefronts per SIMD instead of four fit three workgroups of
+// H = 3072 on a compute unit instead of two: 800 workgroups of rank 100, bf16 200 -> 177 us (16-bit y 194 -> 173); U >= 7 needs the registers.
 // ---------------------------------------------------------------------------------------
 template <int DT, bool Y16, int U>
-__global__ __launch_bounds__(1024) void lora_vec_fused_kernel(const Item *__restrict__ items,
+__global__ __launch_bounds__(1024, U <= 6 ? 5 : 4) void lora_vec_fused_kernel(const Item *__restrict__ items,
                                                                const int32_t *__restrict__ arena,
                                                                const uint16_t *__restrict__ pool,
                                                                const int32_t *__restrict__ tok_idx, int H,
@@ -507,7 +510,7 @@ __global__ __launch_bounds__(1024) void lora_vec_fused_kernel(const Item *__rest
     shrink_vec_core<DT, U>(
         pa, it.rank, it.ntok, wave, nw, lane, pool, H, smem,
         [&]() {
-            stage_rows<kExpandTok>(x, tok_idx, it.pos0, it.ntok, H, (int)blockDim.x, smem);
+            stage_rows<kExpandTok, 1>(x, tok_idx, it.pos0, it.ntok, H, (int)blockDim.x, smem);
             __syncthreads();
         },
         [&](int t, int j, float s) { vl[t * v_pad + j] = s; });
@@ -584,7 +587,7 @@ __device__ __forceinline__ void small_body(const Item &it, const int32_t *__rest
     shrink_vec_core<DT, 8>(
         pa, it.rank, it.ntok, wave, kSmallWaves, lane, pool, H, xs,
         [&]() {
-            stage_rows<TOK>(x, tok_idx, it.pos0, it.ntok, H, kSmallWaves * kWave, xs);
+            stage_rows<TOK, 1>(x, tok_idx, it.pos0, it.ntok, H, kSmallWaves * kWave, xs);
             __syncthreads();
         },
         [&](int t, int j, float s) {

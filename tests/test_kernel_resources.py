@@ -1,8 +1,8 @@
 """The compiled kernels' resources, read from the compiler's own report (no GPU needed): no kernel
 may spill registers or use scratch memory (the runtime would allocate scratch for a queue at the
 kernel's first launch, behind the back of the entry point that promises to allocate nothing),
-none may contain a packed-fp32 VALU instruction, and the MFMA shrink must leave room for two
-workgroups per compute unit."""
+none may contain a packed-fp32 VALU instruction, the MFMA shrink must leave room for two
+workgroups per compute unit, and the streaming kernels of short rows for as many as hide their latency."""
 import os
 import re
 import shutil
@@ -54,6 +54,18 @@ def test_mfma_shrink_fits_two_workgroups_per_compute_unit(report):
     assert len(ms) == 2
     for k, v in ms.items():
         assert v["VGPRs"] + v.get("AGPRs", 0) <= 256, (k, v)   # 512 registers per SIMD lane, 4 wavefronts per workgroup
+
+
+def test_wavefronts_of_the_streaming_kernels(report):
+    """H <= 2048 in the vector shrink (its calls are of up to 16 000 workgroups), H <= 3072 in the one-launch decode kernel."""
+    kernels, _ = report
+    shrink = {k: v for k, v in kernels.items() if re.search(r"shrink_vec_kernelILi\dELi4EE", k)}
+    fused = {k: v for k, v in kernels.items() if re.search(r"lora_vec_fused_kernelILi\dELb\dELi[456]EE", k)}
+    assert len(shrink) == 2 and len(fused) == 12
+    for k, v in shrink.items():
+        assert v["Occupancy"] == 8, (k, v)
+    for k, v in fused.items():
+        assert v["Occupancy"] >= 5, (k, v)
 
 
 def test_no_packed_fp32_instructions(report):
