@@ -1535,7 +1535,7 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void shrink_mfma_kernel(const MsIt
 // of half of one (Wide), in the order of their numbers (a fixed order: the same bits on every run) and finish it as the
 // shrink itself does for a tile that was not split.  Binary16: the row maximum over the rank blocks meets in LDS.
 // Bound by the round trips.  The tiles of a dual plan have up to 32 shares: Wide requests 16 of them at a time (512
-// tokens of rank 64, H = 4096, 4 slots: 6.6 -> 5.6 us); others have two to five, and more threads only make their many
+// tokens of rank 64, H = 4096, 4 slots: 6.8 -> 5.2 us); others have two to five, and more threads only make their many
 // small workgroups dearer (5.4 -> 6.4 us for sixteen prompts, 10.6 -> 12.7 us for 2251 tokens of rank 128 among others).
 constexpr int join_waves(bool wide) { return kMsRanks / 32 * (wide ? 2 : 1); }
 template <int DT, int NP, bool Wide>
@@ -1750,7 +1750,8 @@ struct ExpandWave {
                 op[s][nb] = *reinterpret_cast<const u32x4 *>(slab + slab_col(nb * 32 + n) + 8 * s + 4 * q);
     }
     // B of the run, `stages` <= N stages of 32 ranks: all page numbers first, then the rows of up to AHEAD stages in flight
-    // (registers that the tiles need later); first() runs behind the first rows' requests
+    // (registers that the tiles need later); first() runs behind the first rows' requests.  Four stages in flight against two, expand of
+    // sixteen prompts, 4 slots, us: ranks 97-128 135 / 137, with 16-bit y 124 / 129; two stages of 64 ranks 92.3 / 92.2, one slot with 16-bit y 28.2 / 27.7.
     template <int N, class First>
     __device__ __forceinline__ void load_operands(int stages, u32x4 (&op)[N][2][2], First first) const
     {
