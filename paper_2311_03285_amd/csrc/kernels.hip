@@ -779,8 +779,12 @@ __global__ __launch_bounds__(kShrinkThreads) void shrink_gang_kernel(const Item 
 //   more, or one or two tokens of more than 16: wavefront w forms row w for up to four tokens, the parts meet in LDS, and wavefront t
 //     finishes token t (48 tokens of rank 32, 12 groups of one / two on 4 slots: 5.6 -> 5.2 / 6.3 -> 5.5 us).
 // B rows and page numbers are requested before v is needed; y, v and the token of a whole sum before its B rows: 4.2 -> 4.5 us for 24 tokens of
-// rank 24, 6.4 -> 8.6 for 240 in twenties.  B rows are kept in the caches: items of one group share them, and streaming loads cost
-// 0.3-1 us (which leaves the L2 less of the A rows of a call that is repeated: 5.5 -> 5.9 us for the shrink of 24 tokens of rank 64).  Bound by the chain of round trips in small calls, by
+// rank 24, 6.4 -> 8.6 for 240 in twenties.  B rows that one or two tokens read alone are streamed, others are shared by
+// items or wavefronts and stay in the caches.  us, plain / streamed: 17 small groups beside four prompts, H = 4096, 8 slots, 344 MB a call
+// 16.4 / 13.9, and 102 / 95 for the whole call; 40 single tokens of rank 64, 3 slots 15.8 / 14.3 where the pages come from memory (12.0 / 14.3
+// where three batches take turns and the caches still hold them, as a serving loop over many layers' pages does not); leftovers of larger
+// groups streamed as well: 40 groups of six, 2 slots 16.3 / 17.8; rows of three or four tokens: 32 tokens of ranks 8-64 5.4 / 6.2.
+// Bound by the chain of round trips in small calls, by
 // the fp32 additions and 16-bit conversions where groups have many tokens.  Before, every item was four tokens with
 // its ranks shared out and wavefront 0 finished them all: 45 tokens of ranks 3-100, H = 3080, 3 slots 13.7 -> 9.4 us;
 // 51 tokens of ranks 30-130, H = 1168, 4 slots 15.2 -> 9.2; 142 tokens of ranks 5-130, H = 4096, 2 slots 17.0 -> 13.5; 376
@@ -862,11 +866,11 @@ __device__ __forceinline__ void expand_own(const Item &it, int t0, const int32_t
     }
 }
 
-// An item of at most TOK tokens (1 or 2: exactly); UB: ranks per block.  One token has an instance of its own: with the
+// An item of at most TOK tokens (1 or 2: exactly); UB: ranks per block; Once: its B rows are streamed.  One token has an instance of its own: with the
 // two-token one it requested, multiplied and passed through LDS a second token of zeros.  v is requested beside the page numbers, which
-// the B rows wait for anyway.  us of the expand, 24 tokens of rank 64, H = 4096: 5.8 -> 4.9; 8 of rank 128: 7.2 -> 5.5; 37 of ranks 16-128,
-// H = 3072: 7.8 -> 6.1.
-template <int DT, bool Y16, int TOK, int UB>
+// the B rows wait for anyway.  us of the expand, pages from memory, before and with the streaming loads: 24 tokens of rank 64, H = 4096 6.8 -> 5.7; two
+// of rank 128, 8 slots 9.4 -> 7.1; 37 of ranks 16-128, H = 3072 9.5 -> 7.6; pages from the caches 5.9 -> 5.1, 7.7 -> 7.1, 7.9 -> 7.1.
+template <int DT, bool Y16, int TOK, int UB, bool Once>
 __device__ __forceinline__ void expand_shared(const Item &it, const int32_t *__restrict__ pb,
                                               const uint16_t *__restrict__ pool, const int32_t *__restrict__ tok_idx,
                                               int H, int v_stride, void *__restrict__ y, const float *__restrict__ vs, float *red)
@@ -899,7 +903,8 @@ __device__ __forceinline__ void expand_shared(const Item &it, const int32_t *__r
 #pragma unroll
                 for (int u = 0; u < UB; ++u) { // ranks beyond the last: the last one's row meets v = 0
                     const int64_t page = __builtin_amdgcn_readlane(pwin, min(j0 + u, wr - 1));
-                    w[i][u] = *reinterpret_cast<const u32x4 *>(pool + page * H + col_ld);
+                    const u32x4 *row = reinterpret_cast<const u32x4 *>(pool + page * H + col_ld);
+                    w[i][u] = Once ? __builtin_nontemporal_load(row) : *row;
                 }
             }
         }
@@ -966,12 +971,16 @@ __global__ __launch_bounds__(kSplitWaves *kWave, 3) void expand_vec_split_kernel
     else if (it.rank <= kOwnRanks && it.ntok > 2)
         expand_own<DT, Y16, kOwnRanks>(it, wave, pb, pool, tok_idx, H, v_stride, y, v);
     else if (it.ntok <= 2) { // two blocks or more: a wavefront each, while whole sums would keep one of them busy
-        if (it.ntok == 1)
-            expand_shared<DT, Y16, 1, 16>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+        if (it.ntok == 1 && it.tile)
+            expand_shared<DT, Y16, 1, 16, true>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+        else if (it.ntok == 1)
+            expand_shared<DT, Y16, 1, 16, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+        else if (it.tile)
+            expand_shared<DT, Y16, 2, 16, true>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
         else
-            expand_shared<DT, Y16, 2, 16>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+            expand_shared<DT, Y16, 2, 16, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
     } else
-        expand_shared<DT, Y16, kExpandTok, 8>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+        expand_shared<DT, Y16, kExpandTok, 8, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
 }
 
 // ---------------------------------------------------------------------------------------

@@ -301,7 +301,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                 for (int32_t p = 0; p < n; p += kExpandTok) {
                     const int32_t nt = std::min(kExpandTok, n - p);
                     for (int32_t c = 0; c < H; c += ecols)
-                        ve.push_back(Item{off, g.rank, c, std::min(ecols, H - c), pos_base + p, nt, 0, 0});
+                        ve.push_back(Item{off, g.rank, c, std::min(ecols, H - c), pos_base + p, nt, n <= kExpandTok, 0});
                 }
             }
         }
@@ -354,7 +354,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                 const int32_t step = g.rank <= kOwnRanks ? kGangExpandTok : kExpandTok;
                 for (int32_t p = 0; gang_expand && p < n; p += step)
                     for (int32_t c = 0; c < H; c += ecols)
-                        ge.push_back(Item{off, g.rank, c, std::min(ecols, H - c), pos0 + p, std::min(step, n - p), 0, 0});
+                        ge.push_back(Item{off, g.rank, c, std::min(ecols, H - c), pos0 + p, std::min(step, n - p), n <= kExpandTok, 0});
             }
             plan->n_gs_plain = (int32_t)plan->gs_items.size();
             plan->n_ge_plain = (int32_t)plan->ge_items.size();

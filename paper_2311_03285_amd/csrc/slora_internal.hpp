@@ -32,7 +32,8 @@ struct Item {
     int32_t b;
     int32_t pos0;      // first position in the sorted token list (also the row of v)
     int32_t ntok;      // tokens handled by this item (MFMA expand: by its first tile)
-    int32_t tile;      // MFMA lists: number of the (adapter, 32-token) tile, shared by shrink and expand
+    int32_t tile;      // MFMA lists: number of the (adapter, 32-token) tile, shared by shrink and expand; vector expand: 1 if no other item of
+                       // the group reads these B rows
     int32_t run;       // MFMA expand: tiles the workgroup walks from `tile` on + 256 * tokens of the last one
 };
 static_assert(sizeof(Item) == 32, "Item must stay 32 bytes");

@@ -306,6 +306,8 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &a, void *, b
     for (int32_t k = 0; k < n; ++k) {
         REQUIRE(a.y[k] && a.v[k]);
         Cover cover(plan->T_act, (size_t)pool->H / 8);
+        std::map<std::pair<int32_t, int32_t>, int> readers; // of the B rows of an adapter in a column range
+        for (size_t i = 0; i < n_vec; ++i) readers[{(gang ? plan->d_ge : plan->d_ve)[i].arena_off, (gang ? plan->d_ge : plan->d_ve)[i].a}]++;
         for (size_t i = 0; i < n_vec; ++i) {
             const Item &it = gang ? plan->d_ge[i] : plan->d_ve[i];
             REQUIRE(std::memcmp(&it, gang ? &plan->ge_items[i] : &plan->ve_items[i], sizeof it) == 0);
@@ -314,6 +316,8 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &a, void *, b
             REQUIRE(it.ntok <= (gang && it.rank <= kOwnRanks ? kGangExpandTok : kExpandTok));
             REQUIRE(it.a >= 0 && it.b > 0 && it.a % 8 == 0 && it.b % 8 == 0 && it.a + it.b <= pool->H);
             REQUIRE(it.b <= (plan->expand_split ? 512 : plan->expand_threads * 8));
+            REQUIRE(it.tile == 0 || (it.tile == 1 && readers[{it.arena_off, it.a}] == 1)); // streamed: read by this item only
+            REQUIRE(it.tile == 1 || it.ntok > 2 || readers[{it.arena_off, it.a}] > 1);
             cover.add(it, pool->H / 8, it.a / 8, (it.a + it.b) / 8);
             for (int32_t t = 0; t < it.ntok; ++t)
                 for (int32_t j = 0; j < it.rank; j += 16) g_sink = a.v[k][(int64_t)(it.pos0 + t) * plan->v_stride + j];
