@@ -316,8 +316,9 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &a, void *, b
             REQUIRE(it.ntok <= (gang && it.rank <= kOwnRanks ? kGangExpandTok : kExpandTok));
             REQUIRE(it.a >= 0 && it.b > 0 && it.a % 8 == 0 && it.b % 8 == 0 && it.a + it.b <= pool->H);
             REQUIRE(it.b <= (plan->expand_split ? 512 : plan->expand_threads * 8));
-            REQUIRE(it.tile == 0 || (it.tile == 1 && readers[{it.arena_off, it.a}] == 1)); // streamed: read by this item only
-            REQUIRE(it.tile == 1 || it.ntok > 2 || readers[{it.arena_off, it.a}] > 1);
+            const int read_by = readers[std::make_pair(it.arena_off, it.a)];
+            REQUIRE(it.tile == 0 || (it.tile == 1 && read_by == 1)); // streamed: read by this item only
+            REQUIRE(it.tile == 1 || it.ntok > 2 || read_by > 1);
             cover.add(it, pool->H / 8, it.a / 8, (it.a + it.b) / 8);
             for (int32_t t = 0; t < it.ntok; ++t)
                 for (int32_t j = 0; j < it.rank; j += 16) g_sink = a.v[k][(int64_t)(it.pos0 + t) * plan->v_stride + j];
