@@ -1636,8 +1636,8 @@ __global__ __launch_bounds__(join_waves(Wide) * kWave) void join_shares_kernel(c
 // every wavefront for itself it was a larger part of the kernel's requests than y.  V and y of the
 // next tile are requested before the current one is computed; one barrier per tile hands the
 // buffers over, and the stores of a tile are only waited for a tile later.
-// Adapters of up to 256 ranks do the same with V in two halves (expand_mfma_halves); those of more
-// (expand_mfma_stream) read V and B again for every tile, without barriers.
+// Adapters of up to 256 ranks do the same with V in two halves (expand_mfma_halves); those of more, and most single tiles of 129 to 256 ranks
+// (expand_mfma_stream), read V and B again for every tile, without barriers.
 //
 // The first operand is V (tokens x ranks, fp32 precision), split by the shrink into 16-bit pieces
 // (see VPieces); each piece costs one more MFMA on a path that is bound by memory, not by the
@@ -2210,7 +2210,11 @@ __global__ __launch_bounds__(kMfmaThreads, 2) void expand_mfma_kernel(const Item
     else if (it.rank <= 64) SLORA_ME(2);
     else if (it.rank <= 96) SLORA_ME(3);
     else if (it.rank <= 128) SLORA_ME(4);
-    else if (it.rank <= 2 * kMsRanks && !kScaledPieces<DT, NP>) {
+    // One tile has nothing to keep B for, and the halves wait for all of B before the first product, which the stream does not.  us of the expand of
+    // sixteen prompts, one slot, one tile per workgroup, halves / stream, fp32 y: rank 200, H = 1712 29.3 / 26.8 (bf16 35.7 / 31.5), rank 130, H = 2048
+    // 36.3 / 33.5, rank 256, H = 3072 40.4 / 38.2; 16-bit y: rank 160, H = 1496 22.5 / 20.4, rank 256, H = 1536 28.1 / 25.9, rank 160, H = 2568 32.5 / 30.4, but at
+    // multiples of 1024, why is not known, rank 200, H = 1024, bf16 21.7 / 23.7, rank 256, H = 2048, bf16 38.6 / 40.2, rank 130, H = 3072 33.4 / 35.5.
+    else if (it.rank <= 2 * kMsRanks && !kScaledPieces<DT, NP> && ((it.run & 0xff) > 1 || (Y16 && H % 1024 == 0))) {
         if constexpr (!kScaledPieces<DT, NP>)
             expand_mfma_halves<DT, Y16, NP>(it, wave, pbl, pool, tok_idx, H, v_stride, vfrag, vexp, args.y[cs], lds);
     }

@@ -111,3 +111,16 @@ def test_runs_of_several_tiles(dtype):
             else:
                 rel, _ = assert_close(got, oracle_slot(w, n_slots - 1), "fp32 y")
                 assert rel <= 5e-6, rel
+
+
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+@pytest.mark.parametrize("H", [1016, 1024])
+def test_single_tiles(dtype, H):
+    """One tile per workgroup, on both sides of the width at which 16-bit y takes the halves."""
+    w = wide_workload(970 + H, dtype, H, 1)
+    with DeviceWorkload(w, real_adapters="all") as dw:
+        route(dw.pool, MFMA_ALL)
+        rel, _ = assert_close(gpu_slot(dw, 0), oracle_slot(w, 0), "fp32 y")
+        assert rel <= 5e-6, rel
+        ref, exact = oracle_y16(w, 0)
+        assert_y16_close(gpu_y16(dw, [0])[0], ref, exact, w.y16_bits(0), w.dtype, "16-bit y")
