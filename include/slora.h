@@ -344,7 +344,10 @@ int32_t slora_lora_shrink_expand(slora_pool *pool, int32_t slot, const void *x,
  *                      slora_lora_shrink / slora_lora_expand always use the two kernels, and an
  *                      expand on its own needs a slora_lora_shrink before it, not an apply).
  *                      With 1, calls on very small decode batches (a page or two of A per wavefront)
- *                      run in one launch too, a workgroup per 512 columns; 0 rules that out as well.
+ *                      run in one launch too, a workgroup per 512 columns, and so do larger ones (a few
+ *                      thousand workgroups) unless they are captured or use the static scratch: the
+ *                      workgroups of the shrink hand v over to those of the expand.  0 rules both out.
+ *   "hand_polls"       ... how often such a workgroup looks for v (default 256, some 100 us) before it computes v for itself
  *   "shrink_pages"     pages of A per work item of the decode shrink.  Until it is set: 4, or up to 16 where
  *                      groups of many tokens fill the GPU; a value that is set holds for all items
  *   "upload_groups"    workgroups of slora_adapter_upload when the source is host memory (default

@@ -169,6 +169,15 @@ __device__ __forceinline__ float wave_sum4(float a, float b, float c, float d)
     return row_sum(__uint_as_float(s[0]) + __uint_as_float(s[1]));
 }
 
+// ... of two: lanes 0 .. 31 get the sum of a, the others that of b
+__device__ __forceinline__ float wave_sum2(float a, float b)
+{
+    const auto ab = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    const float x = __uint_as_float(ab[0]) + __uint_as_float(ab[1]);
+    const auto s = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return row_sum(__uint_as_float(s[0]) + __uint_as_float(s[1]));
+}
+
 // 64 lanes x 16 bytes from per-lane addresses to 1 KiB of LDS at a wave-uniform address
 template <int AUX>
 __device__ __forceinline__ void load_to_lds(const unsigned char *src, unsigned char *dst)
@@ -981,6 +990,300 @@ __global__ __launch_bounds__(kSplitWaves *kWave, 3) void expand_vec_split_kernel
             expand_shared<DT, Y16, 2, 16, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
     } else
         expand_shared<DT, Y16, kExpandTok, 8, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+}
+
+// ---------------------------------------------------------------------------------------
+// decode path, both stages in ONE launch, v handed over between workgroups ("chain"): first the workgroups of the vector shrink,
+// then those of the expand, in one grid.  What bounds calls of modest size is the chain of dependent round trips and the launches - an empty
+// kernel takes 1.6 us of the GPU and 2.6 to 3.6 us of the host - so the expand's workgroups are there from the start, with their B rows and y
+// requested, when v arrives.  They also run the same few instructions whatever the rank: between the arrival of v and the store of
+// y a wavefront issues a fifth of what the rank-split expand's does for four tokens, whose sums of 64 ranks took 1.1 us.
+//
+// A shrink workgroup leaves every value of v as one 8-byte word {value, number of the launch}, written and read at device scope.  A word that
+// has this launch's number is whole and needs no other order; words of earlier launches have other numbers, so nothing is
+// cleared between calls.  Workgroups are dispatched in order, so those that are waited for run first; where another stream's kernel holds
+// the GPU that may fail, and a wait is bounded: after `polls` reads a wavefront computes what it waits for, with the same sums, leaves it in
+// the words and goes on.  Calls that a HIP graph captures keep the two kernels: a replay would repeat the number.
+//
+// Sums and their order are those of the vector shrink and of the rank-split expand: the same bits.  us per call, two kernels / chain:
+// 32 tokens of ranks 8-64, H = 4096 9.9 / 7.3; 96 tokens of 4 adapters, 3 slots, bf16, 16-bit y 15.5 / 11.9; 45 tokens of ranks 3-100, H = 3080, 3 slots
+// 17.0 / 13.4; two tokens, H = 1368 9.2 / 5.9; 103 tokens of ranks 8-128, H = 4480, 2 slots 22.3 / 18.4.  Large calls: see slora_plan::route.
+// ---------------------------------------------------------------------------------------
+template <int DT>
+struct HandOver {
+    uint64_t *hand; // the slot's words; an item's begin at its `run`, token after token, rank after rank
+    uint32_t launch;
+    int polls;
+    const int32_t *pa; // the item's A list
+    const uint16_t *pool, *x;
+    const int32_t *tok_idx;
+    int H;
+    __device__ __forceinline__ void leave(const Item &it, int t, int j, float s) const
+    {
+        __hip_atomic_store(hand + it.run + (int64_t)t * it.rank + j, (uint64_t)launch << 32 | __float_as_uint(s), __ATOMIC_RELAXED,
+                           __HIP_MEMORY_SCOPE_AGENT);
+    }
+    // the value of a token and a rank of each lane's own, where `mine` and there is such a token; false: not all are there
+    __device__ __forceinline__ bool get(const Item &it, int t, int j, bool mine, float &out) const
+    {
+        const uint64_t *at = hand + it.run + (int64_t)t * it.rank + j;
+        const bool asks = mine && t < it.ntok;
+        for (int k = 0;; ++k) {
+            uint64_t word = (uint64_t)launch << 32;
+            if (asks) word = __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            out = __uint_as_float((uint32_t)word);
+            if (__all((uint32_t)(word >> 32) == launch)) return true;
+            if (k >= polls) return false;
+            __builtin_amdgcn_s_sleep(1);
+        }
+    }
+    // ranks [w0, w0 + wr) of all tokens: each lane adds the products of chunks lane, lane + 64, ... as the shrink's lanes do
+    __device__ __forceinline__ void find(const Item &it, int w0, int wr) const
+    {
+        const int lane = threadIdx.x & (kWave - 1), nch = H >> 3;
+#pragma nounroll
+        for (int j = w0; j < w0 + wr; ++j) {
+            const u32x4 *page = reinterpret_cast<const u32x4 *>(pool + (int64_t)pa[j] * H);
+#pragma nounroll
+            for (int t = 0; t < it.ntok; ++t) {
+                const u32x4 *row = reinterpret_cast<const u32x4 *>(x + (int64_t)tok_idx[it.pos0 + t] * H);
+                float acc = 0.f;
+#pragma nounroll
+                for (int c = lane; c < nch; c += kWave) acc = dot8<DT>(page[c], row[c], acc);
+                acc = wave_sum(acc);
+                if (lane == 0) leave(it, t, j, acc);
+            }
+        }
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // the words are where get() reads them
+    }
+};
+// ... at most: calls that overlap although they use one plan's words could otherwise keep each other's wavefronts
+constexpr int kFinds = 2;
+
+// Chunks of a row that a lane holds: its U-th part, or a little more (the kernel is not made for every number)
+constexpr int chain_chunks(int H)
+{
+    const int u = (H / 8 + kWave - 1) / kWave;
+    return u <= 8 ? u : u <= 10 ? 10 : u <= 12 ? 12 : 16;
+}
+// An item of the vector shrink, rows of at most kWave * U chunks, chain_chunks(H) == U: a wavefront holds a whole page and takes the tokens one
+// after another.
+template <int DT, int U, class Put>
+__device__ __forceinline__ void shrink_page_item(const Item &it, const int32_t *__restrict__ pa, const uint16_t *__restrict__ pool,
+                                                 const uint16_t *__restrict__ x, const int32_t *__restrict__ tok_idx, int H, u32x4 *xs, Put put)
+{
+    constexpr int kFull = U <= 8 ? U - 1 : U == 10 ? 8 : U == 12 ? 10 : 12; // chunks that lie inside every such row
+    const int lane = threadIdx.x & (kWave - 1), nch = H >> 3;
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    auto load_row = [&](const uint16_t *row, bool stream, u32x4(&o)[U]) {
+        const u32x4 *at = reinterpret_cast<const u32x4 *>(row) + lane;
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            o[u] = u32x4{0u, 0u, 0u, 0u};
+            if (u < kFull || u * kWave + lane < nch) o[u] = stream ? __builtin_nontemporal_load(at + u * kWave) : at[u * kWave];
+        }
+    };
+    u32x4 w[U];
+    if (it.ntok == 1) { // no row is shared: no way through LDS
+        const uint16_t *row = x + (int64_t)tok_idx[it.pos0] * H;
+#pragma nounroll
+        for (int j = wave; j < it.b; j += kShrinkWaves) {
+            u32x4 a[U];
+            load_row(pool + (int64_t)pa[j] * H, true, w);
+            load_row(row, false, a);
+            float acc = 0.f;
+#pragma unroll
+            for (int u = 0; u < U; ++u) acc = dot8<DT>(w[u], a[u], acc);
+            acc = wave_sum(acc);
+            if (lane == 0) put(0, j, acc);
+        }
+        return;
+    }
+    if (wave < it.b) load_row(pool + (int64_t)pa[wave] * H, true, w);
+#pragma nounroll
+    for (int t = wave; t < it.ntok; t += kShrinkWaves) {
+        u32x4 a[U];
+        load_row(x + (int64_t)tok_idx[it.pos0 + t] * H, false, a);
+#pragma unroll
+        for (int u = 0; u < U; ++u) xs[(t * U + u) * kWave + lane] = a[u];
+    }
+    __syncthreads();
+#pragma nounroll
+    for (int j = wave; j < it.b; j += kShrinkWaves) {
+        if (j >= kShrinkWaves) load_row(pool + (int64_t)pa[j] * H, true, w);
+#pragma nounroll
+        for (int t = 0; t < it.ntok; t += 2) { // two at a time; the last of an odd number twice
+            const u32x4 *x0 = xs + t * U * kWave + lane, *x1 = t + 1 < it.ntok ? x0 + U * kWave : x0;
+            float a0 = 0.f, a1 = 0.f;
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                a0 = dot8<DT>(w[u], x0[u * kWave], a0);
+                a1 = dot8<DT>(w[u], x1[u * kWave], a1);
+            }
+            const float sum = wave_sum2(a0, a1);
+            if ((lane & 31) == 0 && t + (lane >> 5) < it.ntok) put(t + (lane >> 5), j, sum);
+        }
+    }
+}
+
+// acc[e][t] += v of token t and rank K0 + k of the wavefront's sixteen (lane 4 * (K0 + k) + t of v) times element e of row k, rank after rank.  The matrix
+// instruction is sixteen products of a column of four and a row of four; block K0 + k of its first operand is sent to all of them.
+template <int DT, int K0, int K>
+__device__ __forceinline__ void add_ranks(float v, const u32x4 (&row)[8], float (&f)[8], f32x4 (&acc)[8])
+{
+    // the elements of a rank are widened while the products of the one before run: all in registers of their own first
+    asm volatile("" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]), "+v"(f[6]), "+v"(f[7]));
+    float next[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) acc[e] = __builtin_amdgcn_mfma_f32_4x4x1f32(v, f[e], acc[e], 4, K0 + K, 0);
+    if constexpr (K < 7) {
+        widen2<DT>(row[K + 1].x, next[0], next[1]);
+        widen2<DT>(row[K + 1].y, next[2], next[3]);
+        widen2<DT>(row[K + 1].z, next[4], next[5]);
+        widen2<DT>(row[K + 1].w, next[6], next[7]);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0); // a product,
+            __builtin_amdgcn_sched_group_barrier(0x2, 1, 0); // an element
+        }
+        add_ranks<DT, K0, K + 1>(v, row, next, acc);
+    }
+}
+template <int DT, int K0>
+__device__ __forceinline__ void add_eight(float v, const u32x4 (&row)[8], f32x4 (&acc)[8])
+{
+    float f[8];
+    widen2<DT>(row[0].x, f[0], f[1]);
+    widen2<DT>(row[0].y, f[2], f[3]);
+    widen2<DT>(row[0].z, f[4], f[5]);
+    widen2<DT>(row[0].w, f[6], f[7]);
+    add_ranks<DT, K0, 0>(v, row, f, acc);
+}
+
+// An item of the rank-split expand of one token, or of at most TOK = kExpandTok
+template <int DT, bool Y16, int TOK>
+__device__ __forceinline__ void expand_hand_item(const Item &it, const int32_t *__restrict__ pb, const uint16_t *__restrict__ pool,
+                                                 const int32_t *__restrict__ tok_idx, int H, void *__restrict__ y, const HandOver<DT> &hand,
+                                                 f32x4 *red)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int col = it.a + lane * 8;
+    const bool live = col < it.a + it.b;
+    const int col_ld = live ? col : it.a;
+    const bool finishes = wave < it.ntok; // token `wave`
+    const int ub = TOK == 1 || it.ntok <= 2 ? 16 : 8;        // ranks of a block
+    const int b0 = wave * ub, b1 = ub == 16 ? b0 + 8 : b0 + 32; // this wavefront's two eights of a window of 64 ranks
+    Y8<DT, Y16> yv;
+    void *y_row = static_cast<unsigned char *>(y) + (int64_t)tok_idx[it.pos0 + (finishes ? wave : 0)] * H * (Y16 ? 2 : 4);
+    if (finishes && live) yv.load(y_row, (uint32_t)col);
+    std::conditional_t<TOK == 1, float, f32x4> acc[8] = {}; // sums of the lane's eight columns, of four tokens each if there are several
+#pragma nounroll
+    for (int w0 = 0; w0 < it.rank && b0 < it.rank - w0; w0 += kWave) {
+        const int wr = min(kWave, it.rank - w0);
+        const bool two = b1 < wr;
+        const int pages = pb[w0 + min((lane & 8 ? b1 : b0) + (lane & 7), wr - 1)]; // lane k: the page of the k-th of the sixteen
+        u32x4 w[2][8];
+        // v of token lane % 4: that of this wavefront's sixteen ranks
+        const int mine = (lane & 32 ? b1 : b0) + ((lane >> 2) & 7);
+        float v;
+        for (int finds = 0;; ++finds) {
+            auto rows = [&](int first, u32x4(&o)[8]) { // ranks beyond the last: the last one's row meets v = 0
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int64_t page = __builtin_amdgcn_readlane(pages, first + u);
+                    const u32x4 *row = reinterpret_cast<const u32x4 *>(pool + page * H + col_ld);
+                    o[u] = TOK == 1 ? __builtin_nontemporal_load(row) : *row;
+                }
+            };
+            rows(0, w[0]);
+            if (two) rows(8, w[1]);
+            if (hand.get(it, lane & 3, w0 + mine, mine < wr, v) || finds == kFinds) break;
+            hand.find(it, w0, wr);
+        }
+        if constexpr (TOK == 1) {
+            auto add = [&](int first, const u32x4(&o)[8]) {
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    float f[8];
+                    widen2<DT>(o[u].x, f[0], f[1]);
+                    widen2<DT>(o[u].y, f[2], f[3]);
+                    widen2<DT>(o[u].z, f[4], f[5]);
+                    widen2<DT>(o[u].w, f[6], f[7]);
+                    const float vv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), first + 4 * u));
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) acc[e] = fmaf(vv, f[e], acc[e]);
+                }
+            };
+            add(0, w[0]);
+            if (two) add(32, w[1]);
+        } else {
+            add_eight<DT, 0>(v, w[0], acc);
+            if (two) add_eight<DT, 8>(v, w[1], acc);
+        }
+    }
+    f32x4 *out = red + wave * TOK * 2 * kWave + lane; // red[wave][t][columns' half][lane]
+    if constexpr (TOK == 1) {
+        out[0] = f32x4{acc[0], acc[1], acc[2], acc[3]};
+        out[kWave] = f32x4{acc[4], acc[5], acc[6], acc[7]};
+    } else {
+#pragma unroll
+        for (int t = 0; t < TOK; ++t)
+            if (t < it.ntok) {
+                out[t * 2 * kWave] = f32x4{acc[0][t], acc[1][t], acc[2][t], acc[3][t]};
+                out[t * 2 * kWave + kWave] = f32x4{acc[4][t], acc[5][t], acc[6][t], acc[7][t]};
+            }
+    }
+    __syncthreads();
+    if (!finishes) return;
+    const int n_rows = (it.rank + ub - 1) / ub; // wavefronts with blocks
+    const f32x4 *in = red + wave * 2 * kWave + lane;
+    f32x4 a = in[0], b = in[kWave];
+#pragma unroll
+    for (int k = 1; k < kSplitWaves; ++k) {
+        const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+        a += k < n_rows ? in[k * TOK * 2 * kWave] : zero;
+        b += k < n_rows ? in[k * TOK * 2 * kWave + kWave] : zero;
+    }
+    const float d[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+    if (live) yv.add_store(y_row, (uint32_t)col, d);
+}
+
+template <int DT, bool Y16, int U>
+__global__ __launch_bounds__(kShrinkThreads, U > 8 ? 3 : 4) void lora_vec_chain_kernel(ChainLists lists, const int32_t *__restrict__ arena,
+                                                                                       const uint16_t *__restrict__ pool,
+                                                                                       const int32_t *__restrict__ tok_idx, int H, int v_stride,
+                                                                                       MultiArgs args)
+{
+    extern __shared__ u32x4 smem[]; // rows of x, or the sums of an expand item's wavefronts
+    const int cs = blockIdx.x;      // slots vary fastest, so workgroups are dispatched in the order of the work lists
+    const bool shrinks = blockIdx.y < lists.n_shrink;
+    const unsigned no = shrinks ? blockIdx.y : blockIdx.y - lists.n_shrink, strip = shrinks ? 0 : no % lists.strips;
+    Item it = shrinks ? lists.shrink[no] : lists.expand[no / lists.strips];
+    const uint16_t *x = static_cast<const uint16_t *>(args.x[cs]);
+    const int32_t *pa = arena + it.arena_off + (int64_t)args.slot[cs] * 2 * it.rank;
+    const HandOver<DT> hand{lists.hand + cs * lists.hand_slot, lists.launch, lists.polls, pa, pool, x, tok_idx, H};
+    if (shrinks) {
+        float *v = args.v[cs];
+        shrink_page_item<DT, U>(it, pa + it.a, pool, x, tok_idx, H, smem, [&](int t, int j, float s) {
+            hand.leave(it, t, it.a + j, s);
+            v[(int64_t)(it.pos0 + t) * v_stride + it.a + j] = s; // for a later expand
+        });
+    } else {
+        it.a += strip * 512; // the item's columns in strips of 512
+        it.b = min(it.b - (int)strip * 512, 512);
+        if (it.b <= 0) return;
+        const int32_t *pb = pa + it.rank;
+        f32x4 *red = reinterpret_cast<f32x4 *>(smem);
+        void *y = args.y[cs];
+        if (it.ntok == 1 && it.tile) expand_hand_item<DT, Y16, 1>(it, pb, pool, tok_idx, H, y, hand, red);
+        else expand_hand_item<DT, Y16, kExpandTok>(it, pb, pool, tok_idx, H, y, hand, red);
+    }
+}
+
+__global__ __launch_bounds__(256) void clear_kernel(u32x4 *__restrict__ dst, int64_t n)
+{
+    for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) dst[i] = u32x4{0u, 0u, 0u, 0u};
 }
 
 // ---------------------------------------------------------------------------------------
@@ -2379,12 +2682,55 @@ int32_t launch_fused(slora_plan *plan, int32_t n, const MultiArgs &args, void *s
 // LDS of the rank-split expand: its partial sums
 constexpr size_t kSplitLds = (size_t)kSplitWaves * kExpandTok * 8 * kWave * sizeof(float);
 
+int32_t launch_clear(void *dst, size_t bytes, void *stream)
+{
+    const int64_t n = (int64_t)(bytes / 16);
+    hipLaunchKernelGGL(clear_kernel, dim3((unsigned)std::min<int64_t>((n + 255) / 256, 1024)), dim3(256), 0, (hipStream_t)stream,
+                       static_cast<u32x4 *>(dst), n);
+    return check_launch("clear");
+}
+
+int32_t launch_chain(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, bool y16, const Route &route)
+{
+    slora_pool *pool = plan->pool;
+    const uint16_t *base = static_cast<const uint16_t *>(pool->dev_base);
+    hipStream_t st = (hipStream_t)stream;
+    const int H = pool->H;
+    ChainLists c{};
+    c.shrink = plan->d_vs;
+    c.expand = plan->d_ve;
+    c.n_shrink = (unsigned)plan->n_vs(route);
+    c.strips = (unsigned)plan->chain_strips();
+    c.hand = plan->set->hand;
+    c.hand_slot = plan->hand_words;
+    c.launch = plan->set->launch;
+    c.polls = (int32_t)pool->hand_polls;
+    const dim3 grid((unsigned)n, (unsigned)plan->chain_wgs(route));
+    const size_t lds = std::max(kSplitLds, (size_t)plan->max_shrink_tok * chain_chunks(H) * kWave * 16);
+#define SLORA_CHAIN(DT, Y, UU) \
+    case UU: hipLaunchKernelGGL((lora_vec_chain_kernel<DT, Y, UU>), grid, dim3(kShrinkThreads), lds, st, c, pool->d_arena, base, plan->d_tok_idx, H, plan->v_stride, args); break
+#define SLORA_CHAIN_U(DT, Y)                                                                                             \
+    switch (chain_chunks(H)) {                                                                                           \
+        SLORA_CHAIN(DT, Y, 1); SLORA_CHAIN(DT, Y, 2); SLORA_CHAIN(DT, Y, 3); SLORA_CHAIN(DT, Y, 4); SLORA_CHAIN(DT, Y, 5); \
+        SLORA_CHAIN(DT, Y, 6); SLORA_CHAIN(DT, Y, 7); SLORA_CHAIN(DT, Y, 8); SLORA_CHAIN(DT, Y, 10); SLORA_CHAIN(DT, Y, 12); \
+        SLORA_CHAIN(DT, Y, 16);                                                                                          \
+    }
+    if (pool->dtype == SLORA_F16) {
+        if (y16) { SLORA_CHAIN_U(SLORA_F16, true) } else { SLORA_CHAIN_U(SLORA_F16, false) }
+    } else {
+        if (y16) { SLORA_CHAIN_U(SLORA_BF16, true) } else { SLORA_CHAIN_U(SLORA_BF16, false) }
+    }
+#undef SLORA_CHAIN_U
+#undef SLORA_CHAIN
+    return check_launch("lora_vec_chain");
+}
+
 int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, const Route &route)
 {
     slora_pool *pool = plan->pool;
     const uint16_t *base = static_cast<const uint16_t *>(pool->dev_base);
     hipStream_t st = (hipStream_t)stream;
-    const size_t n_vs = plan->n_vs(route);
+    const size_t n_vs = route.chain ? 0 : plan->n_vs(route);
     int32_t rc = SLORA_OK;
     if (n_vs > 0 && route.gang) {
         const dim3 grid((unsigned)(plan->shrink_wgs(route) * (size_t)n));
@@ -2471,7 +2817,7 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *
 #define SLORA_PICK(KERNEL)                                                                   \
     (pool->dtype == SLORA_F16 ? (y16 ? KERNEL<SLORA_F16, true> : KERNEL<SLORA_F16, false>)   \
                               : (y16 ? KERNEL<SLORA_BF16, true> : KERNEL<SLORA_BF16, false>))
-    const size_t n_ve = plan->n_ve(route);
+    const size_t n_ve = route.chain ? 0 : plan->n_ve(route);
     if (n_ve > 0) {
         const dim3 grid((unsigned)(plan->expand_wgs(route) * (size_t)n));
         if (plan->expand_split)

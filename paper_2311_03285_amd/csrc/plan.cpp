@@ -210,6 +210,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         plan->expand_threads = ecols / 8;
         std::vector<Item> vs_tail, ve_tail, vs_dual, ve_dual;
         plan->vf_items.clear();
+        plan->hand_words = 0;
         for (int32_t gi : order) {
             const Group &g = groups[(size_t)gi];
             const int32_t n = (int32_t)g.toks.size();
@@ -291,17 +292,19 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                 const bool both = mfma_group(n); // in the MFMA lists as well
                 std::vector<Item> &vs = fused ? vs_tail : both ? vs_dual : plan->vs_items;
                 std::vector<Item> &ve = fused ? ve_tail : both ? ve_dual : plan->ve_items;
+                const int32_t hand = (int32_t)std::min<int64_t>(plan->hand_words, INT32_MAX);
+                plan->hand_words += (int64_t)n * g.rank;
                 if (fused) plan->vf_items.push_back(Item{off, g.rank, 0, H, pos_base, n, 0, 0});
                 for (int32_t p = 0; p < n; p += shrink_tok) {
                     const int32_t nt = std::min(shrink_tok, n - p);
                     plan->max_shrink_tok = std::max(plan->max_shrink_tok, nt);
                     for (int32_t j = 0; j < g.rank; j += shrink_pages)
-                        vs.push_back(Item{off, g.rank, j, std::min(shrink_pages, g.rank - j), pos_base + p, nt, 0, 0});
+                        vs.push_back(Item{off, g.rank, j, std::min(shrink_pages, g.rank - j), pos_base + p, nt, 0, hand + p * g.rank});
                 }
                 for (int32_t p = 0; p < n; p += kExpandTok) {
                     const int32_t nt = std::min(kExpandTok, n - p);
                     for (int32_t c = 0; c < H; c += ecols)
-                        ve.push_back(Item{off, g.rank, c, std::min(ecols, H - c), pos_base + p, nt, n <= kExpandTok, 0});
+                        ve.push_back(Item{off, g.rank, c, std::min(ecols, H - c), pos_base + p, nt, n <= kExpandTok, hand + p * g.rank});
                 }
             }
         }
@@ -330,11 +333,14 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         if (gang || gang_expand) {
             std::vector<Item> gs_dual, ge_dual;
             int32_t pos = 0;
+            int64_t hand = 0;
             for (int32_t gi : order) {
                 const Group &g = groups[(size_t)gi];
                 const int32_t n = (int32_t)g.toks.size(), off = (int32_t)g.arena_off, pos0 = pos;
                 pos += n;
                 if ((int64_t)n >= min_tokens) continue;
+                const int32_t hand0 = (int32_t)std::min<int64_t>(hand, INT32_MAX);
+                hand += (int64_t)n * g.rank;
                 std::vector<Item> &gs = mfma_group(n) ? gs_dual : plan->gs_items;
                 std::vector<Item> &ge = mfma_group(n) ? ge_dual : plan->ge_items;
                 if (!gang) {
@@ -342,19 +348,19 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                     plan->max_gv_tok = std::max(plan->max_gv_tok, std::min(n, shrink_tok));
                     for (int32_t p = 0; p < n; p += shrink_tok)
                         for (int32_t j = 0; j < g.rank; j += shrink_pages)
-                            plan->gv_items.push_back(Item{off, g.rank, j, std::min(shrink_pages, g.rank - j), pos0 + p, std::min(shrink_tok, n - p), 0, 0});
+                            plan->gv_items.push_back(Item{off, g.rank, j, std::min(shrink_pages, g.rank - j), pos0 + p, std::min(shrink_tok, n - p), 0, hand0 + p * g.rank});
                 } else {
                     const int32_t runs = (g.rank + kGangPages - 1) / kGangPages; // of about equal length
                     for (int32_t p = 0; p < n; p += kGangTok)
                         for (int32_t k = 0; k < runs; ++k) {
                             const int32_t j0 = (int32_t)((int64_t)g.rank * k / runs), j1 = (int32_t)((int64_t)g.rank * (k + 1) / runs);
-                            gs.push_back(Item{off, g.rank, j0, j1 - j0, pos0 + p, std::min(kGangTok, n - p), 0, 0});
+                            gs.push_back(Item{off, g.rank, j0, j1 - j0, pos0 + p, std::min(kGangTok, n - p), 0, hand0 + p * g.rank});
                         }
                 }
                 const int32_t step = g.rank <= kOwnRanks ? kGangExpandTok : kExpandTok;
                 for (int32_t p = 0; gang_expand && p < n; p += step)
                     for (int32_t c = 0; c < H; c += ecols)
-                        ge.push_back(Item{off, g.rank, c, std::min(ecols, H - c), pos0 + p, std::min(step, n - p), n <= kExpandTok, 0});
+                        ge.push_back(Item{off, g.rank, c, std::min(ecols, H - c), pos0 + p, std::min(step, n - p), n <= kExpandTok, hand0 + p * g.rank});
             }
             plan->n_gs_plain = (int32_t)plan->gs_items.size();
             plan->n_ge_plain = (int32_t)plan->ge_items.size();
@@ -513,6 +519,25 @@ Route slora_plan::route(int32_t n, bool apply, bool y16) const
     return r;
 }
 
+// Both stages in one launch.  Larger calls are bound by HBM, and the two kernels hold more wavefronts.  us, two kernels / chain, workgroups of the
+// chain: 128 tokens of rank 32, H = 4096, 1 / 2 / 4 slots, 2048 / 4096 / 8192: 18.5 / 15.5, 29.8 / 26.4, 52.8 / 56.6; 50 of rank 64, 4 slots, 4800: 40.8 / 37.8; 100 of rank 64,
+// H = 2048, 4 slots, 8000: 41.0 / 42.3, fours of them 52.3 / 60.4; 400 of rank 8, 4000: 18.3 / 19.0, 3 slots, 12000: 40 / 51; 20 groups of eight tokens of rank 64, 3 slots,
+// 2880: 29.8 / 23.0; where rows of x leave a compute unit two workgroups, 60 groups of four tokens of rank 64, H = 8192, 2 slots, 3840: 67.8 / 75.9.
+bool slora_plan::chain_pays(int32_t n, const Route &r) const
+{
+    if (!expand_split || pool->fuse_decode == 0 || n_vs(r) == 0 || r.gang || r.gang_expand || pool->H > kChainMaxH || chain_wgs(r) > 65535) return false;
+    const int64_t rows = (int64_t)max_shrink_tok * pool->H * 2;
+    return chain_wgs(r) * n <= (rows <= 40960 ? 4096 : 2048);
+}
+
+size_t slora_plan::chain_words(int32_t n) const
+{
+    for (int32_t m = 1; m <= n; ++m)
+        for (int y16 = 0; y16 <= (dual ? 1 : 0); ++y16)
+            if (chain_pays(m, route(m, true, y16 != 0)) && hand_words * n <= INT32_MAX) return (size_t)(hand_words * n);
+    return 0;
+}
+
 int64_t slora_plan::v_most_floats(int32_t n, int32_t dtype) const
 {
     int64_t most = v_total_floats(n, dtype, !dual);
@@ -589,9 +614,10 @@ int32_t do_shrink(slora_plan *plan, int32_t n, const int32_t *slots, const void 
     DeviceScope dev(plan->pool->device);
     if (dev.status() != SLORA_OK) return dev.status();
     Route route = plan->route(n, y != nullptr, y16);
-    // the two kernels have read all of x before y is written; in the one-launch kernel for small batches the
-    // workgroups of other columns still read it
-    if (route.small && y_overlaps_x(plan, n, x, y, y16)) route.small = false;
+    // the two kernels have read all of x before y is written; in the one-launch kernels other workgroups
+    // still read it
+    const bool overlaps = y && y_overlaps_x(plan, n, x, y, y16);
+    if (overlaps) route.small = false;
     // the page lists of every adapter the plan names went to the device when it was built
     float *v = scratch;
     int32_t rc = SLORA_OK;
@@ -600,12 +626,24 @@ int32_t do_shrink(slora_plan *plan, int32_t n, const int32_t *slots, const void 
         v = plan->set->v;
     }
     if (rc == SLORA_OK) rc = plan->enter(stream);
+    if (rc == SLORA_OK && !scratch) {
+        // (room is made whatever the call, so that a plan's buffers are sized once)
+        if (plan->most_slots < n) {
+            plan->most_words = plan->chain_words(n);
+            plan->most_slots = n;
+        }
+        const bool room = plan->most_words > 0 && plan->pool->hand_room(plan->set, plan->most_words, stream);
+        if (room && y && !overlaps && plan->chain_pays(n, route) && !stream_captures(stream) && plan->pool->next_launch(plan->set, stream)) {
+            route.chain = true;
+            route.small = false;
+        }
+    }
     if (rc != SLORA_OK) return rc;
     plan->fill_args(a, n, v, route);
-    if (route.fused || route.small) {
+    if (route.fused || route.small || route.chain)
         for (int32_t k = 0; k < n; ++k) a.y[k] = y[k];
-        rc = launch_fused(plan, n, a, stream, y16, route);
-    }
+    if (route.fused || route.small) rc = launch_fused(plan, n, a, stream, y16, route);
+    if (rc == SLORA_OK && route.chain) rc = launch_chain(plan, n, a, stream, y16, route);
     if (rc == SLORA_OK && !route.small) rc = launch_shrink(plan, n, a, stream, route);
     if (rc == SLORA_OK) {
         plan->v_slots = n;
@@ -639,7 +677,8 @@ int32_t do_expand(slora_plan *plan, int32_t n, const int32_t *slots, void *const
         a.y[k] = y[k];
         a.slot[k] = slots[k];
     }
-    const Route route = plan->v_route;
+    Route route = plan->v_route;
+    if (!after_apply) route.chain = false; // v is in memory as well
     if (plan->v_slots != n || !plan->v_used || (!after_apply && route.fused))
         return fail(SLORA_EINVAL, "expand of %d slot(s) needs a preceding slora_lora_shrink of %d slot(s)", n, n);
     if (after_apply && route.small) return SLORA_OK; // both stages ran in one launch

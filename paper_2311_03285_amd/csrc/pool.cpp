@@ -141,10 +141,20 @@ void slora_pool::give_set(Buffers *set, void *last_stream)
         if (set->h) (void)hipHostFree(set->h);
         if (set->d) (void)hipFree(set->d);
         if (set->v) (void)hipFree(set->v);
+        if (set->hand) (void)hipFree(set->hand);
         for (void *p : set->outgrown) (void)hipFree(p);
         (void)hipEventDestroy((hipEvent_t)set->order);
         delete set;
     }
+}
+
+bool slora::stream_captures(void *stream)
+{
+    if (!stream) return false; // the default stream cannot be captured
+    hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing((hipStream_t)stream, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+    (void)hipGetLastError();
+    return true;
 }
 
 int32_t slora_pool::grow_v(Buffers *set, size_t floats)
@@ -170,12 +180,50 @@ int32_t slora_pool::grow_v(Buffers *set, size_t floats)
     return SLORA_OK;
 }
 
+bool slora_pool::hand_room(Buffers *set, size_t words, void *stream)
+{
+    if (words <= set->hand_cap) return true;
+    if (stream_captures(stream)) return false; // a captured clear would not have run for a call that is not replayed
+    const size_t cap = round_up_pow2(words, 1 << 12);
+    uint64_t *fresh = nullptr;
+    try {
+        set->outgrown.reserve(set->outgrown.size() + 1);
+    } catch (const std::bad_alloc &) {
+        return false;
+    }
+    if (hipMalloc((void **)&fresh, cap * sizeof(uint64_t)) != hipSuccess) {
+        (void)hipGetLastError();
+        return false;
+    }
+    device_allocs++;
+    if (launch_clear(fresh, cap * sizeof(uint64_t), stream) != SLORA_OK) {
+        (void)hipFree(fresh);
+        return false;
+    }
+    if (set->hand) set->outgrown.push_back(set->hand);
+    set->hand = fresh;
+    set->hand_cap = cap;
+    set->launch = 0;
+    return true;
+}
+
+bool slora_pool::next_launch(Buffers *set, void *stream)
+{
+    if (set->launch == UINT32_MAX) { // numbers start again: none of the last turn may be left
+        if (launch_clear(set->hand, set->hand_cap * sizeof(uint64_t), stream) != SLORA_OK) return false;
+        set->launch = 0;
+    }
+    set->launch++;
+    return true;
+}
+
 void slora_pool::free_sets()
 {
     for (Buffers *set : idle_sets) {
         if (set->h) (void)hipHostFree(set->h);
         if (set->d) (void)hipFree(set->d);
         if (set->v) (void)hipFree(set->v);
+        if (set->hand) (void)hipFree(set->hand);
         for (void *p : set->outgrown) (void)hipFree(p);
         if (set->order) (void)hipEventDestroy((hipEvent_t)set->order);
         delete set;
@@ -678,6 +726,11 @@ int32_t slora_set_option(slora_pool *pool, const char *key, int64_t value)
     if (!std::strcmp(key, "mfma_split_min_h")) {
         if (value < 128) return fail(SLORA_EINVAL, "mfma_split_min_h must be >= 128");
         pool->mfma_split_min_h = value;
+        return SLORA_OK;
+    }
+    if (!std::strcmp(key, "hand_polls")) {
+        if (value < 0 || value > 1 << 20) return fail(SLORA_EINVAL, "hand_polls must be in [0, 2^20]");
+        pool->hand_polls = value;
         return SLORA_OK;
     }
     if (!std::strcmp(key, "fuse_decode")) {

@@ -34,7 +34,8 @@ struct Item {
     int32_t ntok;      // tokens handled by this item (MFMA expand: by its first tile)
     int32_t tile;      // MFMA lists: number of the (adapter, 32-token) tile, shared by shrink and expand; vector expand: 1 if no other item of
                        // the group reads these B rows
-    int32_t run;       // MFMA expand: tiles the workgroup walks from `tile` on + 256 * tokens of the last one
+    int32_t run;       // MFMA expand: tiles the workgroup walks from `tile` on + 256 * tokens of the last one; vector lists: the first of
+                       // the item's entries where v is handed over inside a launch, rank after rank, token after token
 };
 static_assert(sizeof(Item) == 32, "Item must stay 32 bytes");
 
@@ -68,10 +69,22 @@ struct MultiArgs {
     int64_t part_off;  // floats from v[k] to the partial sums of split tiles
 };
 
+// The lists of a launch in which the shrink hands v over to the expand
+struct ChainLists {
+    const Item *shrink, *expand;
+    uint32_t n_shrink; // shrink items; then every expand item in `strips` strips of at most 512 columns
+    uint32_t strips;
+    uint64_t *hand;    // words {value, number of the launch} of the first slot,
+    int64_t hand_slot; // those of a slot
+    uint32_t launch;
+    int32_t polls;     // reads before a wavefront computes what it waits for
+};
+
 // Which kernels one call of a plan takes.  The expand follows the shrink whose v it reads.
 struct Route {
     bool wide = false;  // a dual plan's groups of many tokens on the MFMA kernels
     bool small = false; // both stages in the one-launch kernel for small batches
+    bool chain = false; // an apply: both vector stages in one launch that hands v over
     bool gang = false;        // vector groups of many tokens: the shrink for them,
     bool gang_expand = false; // the expand's longer items
     bool fused = false; // an apply: launch_fused serves the groups of the one-launch decode kernel
@@ -92,6 +105,7 @@ constexpr int kGangPages = 16;    // pages, at most
 constexpr int kGangFrom = 1400, kGangExpandFrom = 2000; // least workgroups of the small items at which a call takes them (see route)
 constexpr bool gang_pays(int64_t small_items, int64_t large_items) { return 2 * large_items <= small_items; }
 constexpr int kGangExpandTok = 16; // tokens per item of the rank-split expand for such groups of at most kOwnRanks ranks
+constexpr int kChainMaxH = 8192;  // widest rows whose sums the one-launch kernel that hands v over forms: a wavefront holds one in registers
 constexpr int kMfmaTok = 32;      // tokens per v tile = per MFMA-expand item (one 32-row MFMA block)
 constexpr int kMsTok = 128;       // most tokens per MFMA-shrink item
 constexpr int kMsRanks = 128;     // ranks per MFMA-shrink item (up to four blocks of 32)
@@ -128,6 +142,9 @@ struct Buffers {
     size_t d_cap = 0;
     float *v = nullptr;    // device scratch for v = x*A
     size_t v_cap = 0;      // floats
+    uint64_t *hand = nullptr; // words {value, number of a launch} in which a launch hands v over; none has a number that was not given out yet
+    size_t hand_cap = 0;
+    uint32_t launch = 0;   // number of the latest such launch
     std::vector<void *> outgrown; // device buffers replaced while work that names them may be in flight
     void *order = nullptr; // hipEvent_t: last use of the set, or a hand-over point between streams
 };
@@ -173,6 +190,7 @@ struct slora_pool {
     int64_t mfma_min_tokens = 16;
     int64_t mfma_min_tiles = 32;
     int64_t xcd_group = 0;                            // accepted, no effect
+    int64_t hand_polls = 256;                         // reads of v in a launch that hands it over before a wavefront computes it for itself
     int64_t upload_groups = 32;                       // workgroups of an adapter upload from host memory
     int64_t fuse_decode = 1;                          // 0: never, 1: when the batch has enough small groups, 2: always
     int64_t shrink_pages = 0;                         // a caller's pages of A per vector-shrink item (its x rows are staged once for all of them); 0: kShrinkPages, or more
@@ -194,6 +212,8 @@ struct slora_pool {
     int32_t take_set(slora::Buffers **out, size_t h_bytes, size_t d_bytes); // an idle set whose last use has completed, or a new one
     void give_set(slora::Buffers *set, void *last_stream);                  // record `order` on last_stream, park the set
     int32_t grow_v(slora::Buffers *set, size_t floats);
+    bool hand_room(slora::Buffers *set, size_t words, void *stream); // room for the words of a launch on `stream`; false: there is none
+    bool next_launch(slora::Buffers *set, void *stream);             // ... and the number of the next one
     void free_sets();
 
     int32_t sync_device();                            // push dirty arena range
@@ -226,6 +246,9 @@ struct slora_plan {
     bool dual = false;
     int64_t reread = 0, reread_min = 0; // bytes of pages the vector kernels would read again, per slot; what it takes per call
     int32_t n_vs_plain = 0, n_ve_plain = 0;
+    int32_t most_slots = 0;   // most slots of a call so far, and
+    size_t most_words = 0;    // the words that room was made for
+    int64_t hand_words = 0; // words per slot in which v of the vector groups is handed over
     bool mfma_on(const slora::Route &r) const { return !dual || r.wide; }
     // items of the two vector lists that a call runs beside the other kernels
     size_t n_vs(const slora::Route &r) const { return r.wide ? (size_t)n_vs_plain : r.fused ? (size_t)n_vs_head : vs_items.size(); }
@@ -237,6 +260,11 @@ struct slora_plan {
     int32_t max_gv_tok = 0;                      // most tokens of an item of gv
     size_t n_gs(const slora::Route &r) const { return r.wide ? (size_t)n_gs_plain : gs_items.size(); }
     size_t n_ge(const slora::Route &r) const { return r.wide ? (size_t)n_ge_plain : ge_items.size(); }
+    // ... of the one that hands v over
+    int64_t chain_strips() const { return (expand_threads * 8 + 511) / 512; }
+    int64_t chain_wgs(const slora::Route &r) const { return (int64_t)n_vs(r) + (int64_t)n_ve(r) * chain_strips(); }
+    bool chain_pays(int32_t n, const slora::Route &r) const; // ... which an apply of n slots may take
+    size_t chain_words(int32_t n) const; // its words in a call of up to n slots, if any may take it
     // workgroups of the vector kernels, per slot
     size_t shrink_wgs(const slora::Route &r) const { return r.gang ? n_gs(r) + gv_items.size() : n_vs(r); }
     size_t expand_wgs(const slora::Route &r) const { return r.gang_expand ? n_ge(r) : n_ve(r); }
@@ -306,10 +334,14 @@ int32_t build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids, int32
 int32_t launch_write_pages(slora_pool *pool, const int32_t *d_idx, int64_t n, const void *d_src,
                            void *stream, int32_t max_groups = 0); // max_groups > 0 caps the grid
 int32_t launch_copy(void *dst, const void *src, size_t bytes, void *stream); // 16-byte aligned; src may be pinned host memory
+bool stream_captures(void *stream); // whether a HIP graph captures it
+int32_t launch_clear(void *dst, size_t bytes, void *stream); // whole multiples of 16 bytes
 int32_t launch_gather(slora_pool *pool, int64_t arena_entry, int32_t rank, void *dev_out, void *stream);
 int32_t static_scratch_address(int device, void **out); // `device` must be current
 int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, const Route &route);
 int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, bool y16, const Route &route);
+// both stages of the vector groups that are not in launch_fused
+int32_t launch_chain(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, bool y16, const Route &route);
 // the groups of the one-launch decode kernel or, on a small route, the whole batch
 int32_t launch_fused(slora_plan *plan, int32_t n, const MultiArgs &args, void *stream, bool y16, const Route &route);
 

@@ -190,7 +190,8 @@ static std::vector<uint8_t> served_elsewhere(const slora_plan *plan, const Route
 
 // what the latest apply, shrink or expand launched
 struct Log {
-    bool small = false, fused = false, mfma_shrink = false, mfma_expand = false;
+    bool small = false, chain = false; // a small batch in one launch; both vector stages in the one that hands v over
+    bool fused = false, mfma_shrink = false, mfma_expand = false;
     bool wide = false, gang = false, gang_expand = false; // the larger items of the vector kernels
     size_t vec_shrink = 0, vec_expand = 0; // items
     size_t mfma_shrink_wgs = 0, mfma_expand_wgs = 0; // workgroups with work
@@ -198,6 +199,116 @@ struct Log {
 static Log g_log;
 static std::map<const slora_plan *, bool> g_wide; // whether the latest shrink of a plan left v in the MFMA layout of a dual plan
 static volatile float g_sink; // reads of the stand-in kernels end here
+
+// Items of the vector shrink of a call; words: of a launch that hands v over, how often each was left
+static void vec_shrink(const slora_plan *plan, const MultiArgs &a, int32_t k, const Route &route, std::vector<uint8_t> *words)
+{
+    const slora_pool *pool = plan->pool;
+    const size_t n_vs = plan->n_vs(route);
+    const bool gang = n_vs > 0 && route.gang; // the larger items, then the small ones of the groups that are not in them
+    REQUIRE(0 <= plan->n_gs_plain && (size_t)plan->n_gs_plain <= plan->gs_items.size());
+    const size_t n_gs = gang ? plan->n_gs(route) : 0, n_vec = gang ? n_gs + plan->gv_items.size() : n_vs;
+    REQUIRE(n_vec == plan->shrink_wgs(route));
+    const std::vector<uint8_t> elsewhere = served_elsewhere(plan, route);
+    float *v = a.v[k];
+    Cover cover(plan->T_act, (size_t)plan->v_stride);
+    for (size_t i = 0; i < n_vec; ++i) {
+        const bool large = i < n_gs;
+        const Item &it = large ? plan->d_gs[i] : gang ? plan->d_gv[i - n_gs] : plan->d_vs[i];
+        REQUIRE(std::memcmp(&it, large ? &plan->gs_items[i] : gang ? &plan->gv_items[i - n_gs] : &plan->vs_items[i], sizeof it) == 0);
+        check_pages(plan, it.arena_off, it.rank, a.slot[k]);
+        check_tokens(plan, it.pos0, it.ntok);
+        REQUIRE(it.a >= 0 && it.b > 0 && it.a + it.b <= it.rank);
+        if (large) {
+            REQUIRE(it.ntok <= kGangTok && it.b <= kGangPages && pool->shrink_pages == 0);
+        } else { // its rows of x fit the LDS of the launch
+            REQUIRE(it.ntok <= kShrinkTok && it.ntok <= (gang ? plan->max_gv_tok : plan->max_shrink_tok) && it.b <= (pool->shrink_pages > 0 ? pool->shrink_pages : kShrinkPages));
+            REQUIRE(it.ntok == 1 || it.ntok * pool->H * 2 <= 65536);
+        }
+        cover.add(it, it.rank, it.a, it.a + it.b);
+        for (int32_t t = 0; t < it.ntok; ++t)
+            for (int32_t j = it.a; j < it.a + it.b; ++j) {
+                v[(int64_t)(it.pos0 + t) * plan->v_stride + j] = 0.f;
+                if (words) { // every word is left once
+                    const int64_t w = it.run + (int64_t)t * it.rank + j;
+                    REQUIRE(w >= 0 && w < plan->hand_words && !(*words)[(size_t)w]++);
+                }
+            }
+    }
+    cover.check(elsewhere);
+}
+
+// ... of the vector expand
+static void vec_expand(const slora_plan *plan, const MultiArgs &a, int32_t k, const Route &route, const std::vector<uint8_t> *words)
+{
+    const slora_pool *pool = plan->pool;
+    const size_t n_ve = plan->n_ve(route);
+    const bool gang = n_ve > 0 && route.gang_expand;
+    REQUIRE(!gang || plan->expand_split);
+    REQUIRE(0 <= plan->n_ge_plain && (size_t)plan->n_ge_plain <= plan->ge_items.size());
+    const size_t n_vec = gang ? plan->n_ge(route) : n_ve;
+    REQUIRE(n_vec == plan->expand_wgs(route));
+    const std::vector<uint8_t> elsewhere = served_elsewhere(plan, route);
+    Cover cover(plan->T_act, (size_t)pool->H / 8);
+    std::map<std::pair<int32_t, int32_t>, int> readers; // of the B rows of an adapter in a column range
+    for (size_t i = 0; i < n_vec; ++i) readers[{(gang ? plan->d_ge : plan->d_ve)[i].arena_off, (gang ? plan->d_ge : plan->d_ve)[i].a}]++;
+    for (size_t i = 0; i < n_vec; ++i) {
+        const Item &it = gang ? plan->d_ge[i] : plan->d_ve[i];
+        REQUIRE(std::memcmp(&it, gang ? &plan->ge_items[i] : &plan->ve_items[i], sizeof it) == 0);
+        check_pages(plan, it.arena_off, it.rank, a.slot[k]);
+        check_tokens(plan, it.pos0, it.ntok);
+        REQUIRE(it.ntok <= (gang && it.rank <= kOwnRanks ? kGangExpandTok : kExpandTok));
+        REQUIRE(it.a >= 0 && it.b > 0 && it.a % 8 == 0 && it.b % 8 == 0 && it.a + it.b <= pool->H);
+        REQUIRE(it.b <= (plan->expand_split ? 512 : plan->expand_threads * 8));
+        const int read_by = readers[std::make_pair(it.arena_off, it.a)];
+        REQUIRE(it.tile == 0 || (it.tile == 1 && read_by == 1)); // streamed: read by this item only
+        REQUIRE(it.tile == 1 || it.ntok > 2 || read_by > 1);
+        cover.add(it, pool->H / 8, it.a / 8, (it.a + it.b) / 8);
+        for (int32_t t = 0; t < it.ntok; ++t)
+            for (int32_t j = 0; j < it.rank; j += words ? 1 : 16) {
+                if (words) { // a word that is waited for is left
+                    const int64_t w = it.run + (int64_t)t * it.rank + j;
+                    REQUIRE(w >= 0 && w < plan->hand_words && (*words)[(size_t)w] == 1);
+                } else {
+                    g_sink = a.v[k][(int64_t)(it.pos0 + t) * plan->v_stride + j];
+                }
+            }
+    }
+    cover.check(elsewhere);
+}
+
+int32_t launch_clear(void *dst, size_t bytes, void *)
+{
+    REQUIRE(bytes > 0 && bytes % 16 == 0);
+    std::memset(dst, 0, bytes);
+    return SLORA_OK;
+}
+
+// both vector stages in one launch: the small items of both lists, v through the words of the plan's buffer set
+int32_t launch_chain(slora_plan *plan, int32_t n, const MultiArgs &a, void *, bool y16, const Route &route)
+{
+    REQUIRE(a.n == n && route.chain && !route.small && !route.gang && !route.gang_expand && plan->expand_split);
+    REQUIRE(plan->pool->H <= kChainMaxH && plan->pool->fuse_decode != 0 && plan->chain_wgs(route) <= 65535);
+    REQUIRE(plan->chain_strips() == 1);
+    REQUIRE(plan->set->launch > 0 && (size_t)(plan->hand_words * n) <= plan->set->hand_cap);
+    for (size_t w = 0; w < plan->set->hand_cap; ++w) REQUIRE((uint32_t)(plan->set->hand[w] >> 32) != plan->set->launch); // a number of its own
+    for (int32_t k = 0; k < n; ++k) {
+        REQUIRE(a.x[k] && a.y[k] && a.v[k]);
+        g_seen = -1;
+        std::vector<uint8_t> words((size_t)plan->hand_words);
+        vec_shrink(plan, a, k, route, &words);
+        g_seen = -1;
+        vec_expand(plan, a, k, route, &words);
+        for (size_t w = 0; w < words.size(); ++w)
+            if (words[w]) plan->set->hand[(size_t)(k * plan->hand_words) + w] = (uint64_t)plan->set->launch << 32;
+    }
+    g_log.chain = true;
+    g_log.small = plan->route(n, true, y16).small; // a batch of that kind
+    g_log.vec_shrink = g_log.small ? 0 : plan->n_vs(route);
+    g_log.vec_expand = g_log.small ? 0 : plan->n_ve(route);
+    g_wide[plan] = route.wide;
+    return SLORA_OK;
+}
 
 int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &a, void *, const Route &route)
 {
@@ -207,41 +318,17 @@ int32_t launch_shrink(slora_plan *plan, int32_t n, const MultiArgs &a, void *, c
     const int n_kk = plan->v_stride / 16;
     REQUIRE(a.n == n && plan->v_stride % kRankPad == 0);
     REQUIRE(0 <= plan->n_vs_plain && plan->n_vs_plain <= plan->n_vs_head && (size_t)plan->n_vs_head <= plan->vs_items.size());
-    const size_t n_vs = plan->n_vs(route);
-    const bool gang = n_vs > 0 && route.gang; // the larger items, then the small ones of the groups that are not in them
-    REQUIRE(0 <= plan->n_gs_plain && (size_t)plan->n_gs_plain <= plan->gs_items.size());
-    const size_t n_gs = gang ? plan->n_gs(route) : 0, n_vec = gang ? n_gs + plan->gv_items.size() : n_vs;
-    REQUIRE(n_vec == plan->shrink_wgs(route));
-    const std::vector<uint8_t> elsewhere = served_elsewhere(plan, route);
     g_seen = -1;
     check_scratch(plan, n, a, route);
-    g_log.vec_shrink = n_vs;
+    if (!route.chain) g_log.vec_shrink = plan->n_vs(route);
     g_log.wide = route.wide;
-    g_log.gang = gang;
+    g_log.gang = !route.chain && plan->n_vs(route) > 0 && route.gang;
     g_wide[plan] = route.wide;
     g_log.mfma_shrink = plan->mfma_on(route) && !plan->ms_items.empty();
     for (int32_t k = 0; k < n; ++k) {
         REQUIRE(a.x[k] && a.v[k]);
         float *v = a.v[k];
-        Cover cover(plan->T_act, (size_t)plan->v_stride);
-        for (size_t i = 0; i < n_vec; ++i) {
-            const bool large = i < n_gs;
-            const Item &it = large ? plan->d_gs[i] : gang ? plan->d_gv[i - n_gs] : plan->d_vs[i];
-            REQUIRE(std::memcmp(&it, large ? &plan->gs_items[i] : gang ? &plan->gv_items[i - n_gs] : &plan->vs_items[i], sizeof it) == 0);
-            check_pages(plan, it.arena_off, it.rank, a.slot[k]);
-            check_tokens(plan, it.pos0, it.ntok);
-            REQUIRE(it.a >= 0 && it.b > 0 && it.a + it.b <= it.rank);
-            if (large) {
-                REQUIRE(it.ntok <= kGangTok && it.b <= kGangPages && pool->shrink_pages == 0);
-            } else { // its rows of x fit the LDS of the launch
-                REQUIRE(it.ntok <= kShrinkTok && it.ntok <= (gang ? plan->max_gv_tok : plan->max_shrink_tok) && it.b <= (pool->shrink_pages > 0 ? pool->shrink_pages : kShrinkPages));
-                REQUIRE(it.ntok == 1 || it.ntok * pool->H * 2 <= 65536);
-            }
-            cover.add(it, it.rank, it.a, it.a + it.b);
-            for (int32_t t = 0; t < it.ntok; ++t)
-                for (int32_t j = it.a; j < it.a + it.b; ++j) v[(int64_t)(it.pos0 + t) * plan->v_stride + j] = 0.f;
-        }
-        cover.check(elsewhere);
+        if (!route.chain) vec_shrink(plan, a, k, route, nullptr);
         uint16_t *frag = reinterpret_cast<uint16_t *>(v + a.vfrag_off);
         int8_t *vexp = reinterpret_cast<int8_t *>(v + a.vexp_off);
         float *part = v + a.part_off;
@@ -289,41 +376,16 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &a, void *, b
     const slora_pool *pool = plan->pool;
     REQUIRE(a.n == n);
     REQUIRE(0 <= plan->n_ve_plain && plan->n_ve_plain <= plan->n_ve_head && (size_t)plan->n_ve_head <= plan->ve_items.size());
-    const size_t n_ve = plan->n_ve(route);
-    const bool gang = n_ve > 0 && route.gang_expand;
-    REQUIRE(!gang || plan->expand_split);
-    REQUIRE(0 <= plan->n_ge_plain && (size_t)plan->n_ge_plain <= plan->ge_items.size());
-    const size_t n_vec = gang ? plan->n_ge(route) : n_ve;
-    REQUIRE(n_vec == plan->expand_wgs(route));
-    const std::vector<uint8_t> elsewhere = served_elsewhere(plan, route);
     g_seen = -1;
     check_scratch(plan, n, a, route);
-    g_log.vec_expand = n_ve;
-    g_log.gang_expand = gang;
+    if (!route.chain) g_log.vec_expand = plan->n_ve(route);
+    g_log.gang_expand = !route.chain && plan->n_ve(route) > 0 && route.gang_expand;
     REQUIRE(g_wide.count(plan) && g_wide[plan] == route.wide);
     g_log.mfma_expand = plan->mfma_on(route) && !plan->me_items.empty();
     const int n_kk = plan->v_stride / 16, np = plan->pieces(pool->dtype);
     for (int32_t k = 0; k < n; ++k) {
         REQUIRE(a.y[k] && a.v[k]);
-        Cover cover(plan->T_act, (size_t)pool->H / 8);
-        std::map<std::pair<int32_t, int32_t>, int> readers; // of the B rows of an adapter in a column range
-        for (size_t i = 0; i < n_vec; ++i) readers[{(gang ? plan->d_ge : plan->d_ve)[i].arena_off, (gang ? plan->d_ge : plan->d_ve)[i].a}]++;
-        for (size_t i = 0; i < n_vec; ++i) {
-            const Item &it = gang ? plan->d_ge[i] : plan->d_ve[i];
-            REQUIRE(std::memcmp(&it, gang ? &plan->ge_items[i] : &plan->ve_items[i], sizeof it) == 0);
-            check_pages(plan, it.arena_off, it.rank, a.slot[k]);
-            check_tokens(plan, it.pos0, it.ntok);
-            REQUIRE(it.ntok <= (gang && it.rank <= kOwnRanks ? kGangExpandTok : kExpandTok));
-            REQUIRE(it.a >= 0 && it.b > 0 && it.a % 8 == 0 && it.b % 8 == 0 && it.a + it.b <= pool->H);
-            REQUIRE(it.b <= (plan->expand_split ? 512 : plan->expand_threads * 8));
-            const int read_by = readers[std::make_pair(it.arena_off, it.a)];
-            REQUIRE(it.tile == 0 || (it.tile == 1 && read_by == 1)); // streamed: read by this item only
-            REQUIRE(it.tile == 1 || it.ntok > 2 || read_by > 1);
-            cover.add(it, pool->H / 8, it.a / 8, (it.a + it.b) / 8);
-            for (int32_t t = 0; t < it.ntok; ++t)
-                for (int32_t j = 0; j < it.rank; j += 16) g_sink = a.v[k][(int64_t)(it.pos0 + t) * plan->v_stride + j];
-        }
-        cover.check(elsewhere);
+        if (!route.chain) vec_expand(plan, a, k, route, nullptr);
         std::set<std::pair<int, int>> done; // every tile and column range is in one run
         for (size_t i = 0; plan->mfma_on(route) && i < plan->me_items.size(); ++i) {
             const Item &it = plan->d_me[i];
@@ -629,7 +691,42 @@ static void shrink_pages_of_the_caller()
     }
 }
 
+// Both vector stages in one launch that hands v over: calls of up to a few thousand workgroups, beside MFMA groups too, never with the static
+// scratch, the two-stage calls, "fuse_decode" 0, a y that overlaps an x or no memory for the words; a later expand finds v.
+static void hand_over()
+{
+    std::vector<std::pair<int, int>> groups;
+    for (int g = 0; g < 24; ++g) groups.push_back({8 + 24 * (g % 4), 1 + g % 5});
+    const std::vector<std::pair<const char *, int64_t>> never{{"fuse_decode", 0}};
+    for (int32_t H : {520, 4096, 8192, 8200}) {
+        Bench b(H, 4, SLORA_BF16, groups), off(H, 4, SLORA_BF16, groups, never);
+        for (int32_t n = 1; n <= 4; ++n) {
+            const int64_t wgs = (b.plan->chain_wgs(Route{})) * n;
+            const bool pays = H <= 8192 && wgs <= (std::min(b.plan->max_shrink_tok, 4) * H * 2 <= 40960 ? 4096 : 2048);
+            REQUIRE(b.apply(n) == SLORA_OK && g_log.chain == pays && g_log.vec_expand > 0);
+            REQUIRE(b.expand(n) == SLORA_OK && !g_log.chain);
+            REQUIRE(b.apply16(n) == SLORA_OK && g_log.chain == pays);
+            REQUIRE(b.apply_static(n) == SLORA_OK && !g_log.chain);
+            REQUIRE(b.shrink(n) == SLORA_OK && !g_log.chain && b.expand(n) == SLORA_OK && !g_log.chain);
+            REQUIRE(off.apply(n) == SLORA_OK && !g_log.chain);
+        }
+    }
+    Bench b(1024, 2, SLORA_F16, groups);
+    const void *const x1 = b.xs[1];
+    b.xs[1] = b.ys[0]; // slot 0 writes what slot 1 reads
+    REQUIRE(b.apply16(2) == SLORA_OK && !g_log.chain);
+    b.plan->set->launch = UINT32_MAX - 1; // numbers run out, and start again with none of theirs in the words
+    b.xs[1] = x1;
+    for (int i = 0; i < 3; ++i) REQUIRE(b.apply(2) == SLORA_OK && g_log.chain);
+    REQUIRE(b.plan->set->launch == 2);
+    std::vector<std::pair<int, int>> mixed(20, {32, 64}); // 40 tiles
+    mixed.push_back({16, 3});
+    Bench m(2048, 3, SLORA_F16, mixed);
+    REQUIRE(m.apply(3) == SLORA_OK && g_log.chain && g_log.mfma_expand && g_log.vec_expand > 0);
+}
+
 static const struct { const char *name; void (*run)(); } kCases[] = {
+    {"hand_over", hand_over},
     {"shrink_pages_of_the_caller", shrink_pages_of_the_caller},
     {"expand_lds", expand_lds},
     {"larger_items_of_no_call", larger_items_of_no_call},
@@ -658,7 +755,7 @@ int main(int argc, char **argv)
     const unsigned seed = argc > 1 ? (unsigned)std::atoi(argv[1]) : 1u;
     std::mt19937 rng(seed);
     auto rnd = [&](int lo, int hi) { return lo + (int)(rng() % (unsigned)(hi - lo + 1)); };
-    long calls = 0, plans_made = 0, both_families = 0, larger = 0;
+    long calls = 0, plans_made = 0, both_families = 0, larger = 0, chains = 0;
     for (int round = 0; round < 12; ++round) {
         const int32_t H = 8 * rnd(8, 160);
         const int64_t n_pages = rnd(200, 3000);
@@ -706,6 +803,7 @@ int main(int argc, char **argv)
                 g_fail_malloc = false;
                 both_families += plan->dual && g_log.mfma_expand;
                 larger += g_log.gang || g_log.gang_expand;
+                chains += g_log.chain;
                 REQUIRE(rc == SLORA_OK || rc == SLORA_EBUSY || (rc == SLORA_ERANGE && entry == 0) ||
                         (rc == SLORA_EINVAL && (entry == 3 || entry == 4)) || (rc == SLORA_EHIP && no_memory));
             }
@@ -773,6 +871,7 @@ int main(int argc, char **argv)
         REQUIRE(slora_pool_destroy(pool) == SLORA_OK);
     }
     REQUIRE(both_families > 0); // MFMA calls on plans that hold both kernel families' lists
+    REQUIRE(chains > 0);        // calls that hand v over inside a launch
     REQUIRE(larger > 0);        // calls that take the vector kernels' larger items
     std::printf("host_san OK: seed %u, %ld calls, %ld plans, %ld on both families, %ld of larger items\n", seed, calls, plans_made, both_families, larger);
     return 0;
