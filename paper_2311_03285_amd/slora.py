@@ -105,8 +105,26 @@ def _stream(s) -> Optional[int]:
     return int(getattr(s, "cuda_stream", s)) or None
 
 
+# The calls of a layer are enqueued back to back, and the smallest take as long as their enqueueing.  Of a call of four slots numpy's ctypes view
+# and an object per pointer were 1.3 us: one token of rank 16, 4 slots 5.9 -> 4.6 us, 1 slot 5.2 -> 4.3.
+_POINTERS = [C.c_void_p * n for n in range(MAX_MULTI + 1)]
+_SLOTS = [C.c_int32 * n for n in range(MAX_MULTI + 1)]
+
+
 def _ptr_array(ptrs: Sequence[int]):
-    return (C.c_void_p * len(ptrs))(*[C.c_void_p(int(p)) for p in ptrs])
+    n = len(ptrs)
+    try:
+        return (_POINTERS[n] if n <= MAX_MULTI else C.c_void_p * n)(*ptrs)
+    except TypeError:  # numbers of another type than int
+        return (C.c_void_p * n)(*[C.c_void_p(int(p)) for p in ptrs])
+
+
+def _slot_array(slots):
+    """(number of slots, what the library reads them from)"""
+    if type(slots) is np.ndarray and slots.dtype == np.int32 and slots.ndim == 1 and slots.size <= MAX_MULTI:
+        return slots.size, _SLOTS[slots.size](*slots.tolist())
+    s = _i32(slots)
+    return s.size, s.ctypes.data_as(C.c_void_p)  # (keeps the array)
 
 
 # ---- the C calls, one to one ---------------------------------------------------------------
@@ -206,35 +224,35 @@ def lora_apply(plan, slot: int, x: int, y: int, stream=None) -> None:
 
 
 def lora_apply_multi(plan, slots, xs: Sequence[int], ys: Sequence[int], stream=None) -> None:
-    s = _i32(slots)
-    _check(lib().slora_lora_apply_multi(plan, s.size, _ptr(s), _ptr_array(xs), _ptr_array(ys), _stream(stream)))
+    n, s = _slot_array(slots)
+    _check(lib().slora_lora_apply_multi(plan, n, s, _ptr_array(xs), _ptr_array(ys), _stream(stream)))
 
 
 def lora_apply_multi_static(plan, slots, xs: Sequence[int], ys: Sequence[int], stream=None) -> None:
     """As lora_apply_multi, with v in the library's static scratch: allocates nothing."""
-    s = _i32(slots)
-    _check(lib().slora_lora_apply_multi_static(plan, s.size, _ptr(s), _ptr_array(xs), _ptr_array(ys), _stream(stream)))
+    n, s = _slot_array(slots)
+    _check(lib().slora_lora_apply_multi_static(plan, n, s, _ptr_array(xs), _ptr_array(ys), _stream(stream)))
 
 
 def lora_apply_multi_y16(plan, slots, xs: Sequence[int], ys: Sequence[int], stream=None) -> None:
     """As lora_apply_multi, with every y of the pool's 16-bit storage type."""
-    s = _i32(slots)
-    _check(lib().slora_lora_apply_multi_y16(plan, s.size, _ptr(s), _ptr_array(xs), _ptr_array(ys), _stream(stream)))
+    n, s = _slot_array(slots)
+    _check(lib().slora_lora_apply_multi_y16(plan, n, s, _ptr_array(xs), _ptr_array(ys), _stream(stream)))
 
 
 def lora_expand_y16(plan, slots, ys: Sequence[int], stream=None) -> None:
-    s = _i32(slots)
-    _check(lib().slora_lora_expand_y16(plan, s.size, _ptr(s), _ptr_array(ys), _stream(stream)))
+    n, s = _slot_array(slots)
+    _check(lib().slora_lora_expand_y16(plan, n, s, _ptr_array(ys), _stream(stream)))
 
 
 def lora_shrink(plan, slots, xs: Sequence[int], stream=None) -> None:
-    s = _i32(slots)
-    _check(lib().slora_lora_shrink(plan, s.size, _ptr(s), _ptr_array(xs), _stream(stream)))
+    n, s = _slot_array(slots)
+    _check(lib().slora_lora_shrink(plan, n, s, _ptr_array(xs), _stream(stream)))
 
 
 def lora_expand(plan, slots, ys: Sequence[int], stream=None) -> None:
-    s = _i32(slots)
-    _check(lib().slora_lora_expand(plan, s.size, _ptr(s), _ptr_array(ys), _stream(stream)))
+    n, s = _slot_array(slots)
+    _check(lib().slora_lora_expand(plan, n, s, _ptr_array(ys), _stream(stream)))
 
 
 def lora_shrink_expand(pool, slot: int, x: int, token_adapter_ids, seg_offsets, y: int, stream=None) -> None:
