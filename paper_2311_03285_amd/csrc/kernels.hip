@@ -957,8 +957,242 @@ __device__ __forceinline__ void expand_shared(const Item &it, const int32_t *__r
     if (live) yv.add_store(y, yoff, d);
 }
 
-// An item: up to kGangExpandTok tokens of an adapter of at most kOwnRanks ranks, kExpandTok of another
-template <int DT, bool Y16>
+// acc[e][t] += v of token t and rank K0 + k of the wavefront's sixteen (lane 4 * (K0 + k) + t of v) times element e of row k, rank after rank.  The matrix
+// instruction is sixteen products of a column of four and a row of four; block K0 + k of its first operand is sent to all of them.
+template <int DT, int K0, int K, int FOURS>
+__device__ __forceinline__ void add_ranks(const float (&v)[FOURS], const u32x4 (&row)[8], float (&f)[8], f32x4 (&acc)[FOURS][8])
+{
+    // the elements of a rank are widened while the products of the one before run: all in registers of their own first
+    asm volatile("" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]), "+v"(f[6]), "+v"(f[7]));
+    float next[8];
+#pragma unroll
+    for (int k = 0; k < FOURS; ++k)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[k][e] = __builtin_amdgcn_mfma_f32_4x4x1f32(v[k], f[e], acc[k][e], 4, K0 + K, 0);
+    if constexpr (K < 7) {
+        widen2<DT>(row[K + 1].x, next[0], next[1]);
+        widen2<DT>(row[K + 1].y, next[2], next[3]);
+        widen2<DT>(row[K + 1].z, next[4], next[5]);
+        widen2<DT>(row[K + 1].w, next[6], next[7]);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) {
+            __builtin_amdgcn_sched_group_barrier(0x8, FOURS, 0); // products,
+            __builtin_amdgcn_sched_group_barrier(0x2, 1, 0); // an element
+        }
+        add_ranks<DT, K0, K + 1, FOURS>(v, row, next, acc);
+    }
+}
+template <int DT, int K0, int FOURS>
+__device__ __forceinline__ void add_eight(const float (&v)[FOURS], const u32x4 (&row)[8], f32x4 (&acc)[FOURS][8])
+{
+    float f[8];
+    widen2<DT>(row[0].x, f[0], f[1]);
+    widen2<DT>(row[0].y, f[2], f[3]);
+    widen2<DT>(row[0].z, f[4], f[5]);
+    widen2<DT>(row[0].w, f[6], f[7]);
+    add_ranks<DT, K0, 0, FOURS>(v, row, f, acc);
+}
+
+// Turns of find() at most: calls that overlap although they use one plan's words could otherwise keep each other's wavefronts
+constexpr int kFinds = 2;
+
+// acc[e] += v of lane FIRST + 4 k times element e of row k, rank after rank: one token
+template <int DT, int FIRST>
+__device__ __forceinline__ void add_eight_alone(float v, const u32x4 (&row)[8], float (&acc)[8])
+{
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+        float f[8];
+        widen2<DT>(row[u].x, f[0], f[1]);
+        widen2<DT>(row[u].y, f[2], f[3]);
+        widen2<DT>(row[u].z, f[4], f[5]);
+        widen2<DT>(row[u].w, f[6], f[7]);
+        const float vv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), FIRST + 4 * u));
+#pragma unroll
+        for (int e = 0; e < 8; ++e) acc[e] = fmaf(vv, f[e], acc[e]);
+    }
+}
+
+// Where an item's wavefronts find v: get() returns the value of a token and a rank of each lane's own, where `mine` and there is such a
+// token; false: not all are there, and find() makes those of ranks [w0, w0 + wr).  Rows that an earlier launch has left:
+struct RowsOfV {
+    static constexpr bool kMayFail = false;
+    const float *v;
+    int v_stride;
+    __device__ __forceinline__ bool get(const Item &it, int t, int j, bool mine, float &out) const
+    {
+        out = mine && t < it.ntok ? v[(int64_t)(it.pos0 + t) * v_stride + j] : 0.f;
+        return true;
+    }
+    __device__ __forceinline__ void find(const Item &, int, int) const {}
+};
+
+// An item of one token (its B rows are streamed: nobody else reads them), or of at most TOK = 4 or 8, with the ranks shared out over the wavefronts: the sums of expand_shared.
+// The fp32 vector operations bound groups of many tokens, nine of them for a row of B and a token; the matrix instruction does four tokens
+// at once in the time of two, adds them as fmaf does, and eight tokens share the rows and their conversion.  us per call, expand_shared / this one, calls of the
+// larger items: 672 tokens of 16 adapters of ranks 16-128, H = 4096, 4 slots, 16-bit y 102.5 / 85.5; 452 of 10, ranks 5-130, H = 3072, bf16 50.2 / 44.3;
+// 50 tokens each of 12 adapters of rank 48, 3 slots 56.4 / 50.5.  For two to four tokens an item it is 4-6 % slower where the launch is large (its rows are requested after
+// the page numbers of all its blocks, and two tokens leave half of the instruction idle), so only the one-launch kernel below uses it there.
+template <int DT, bool Y16, int TOK, class V>
+__device__ __forceinline__ void expand_split_item(const Item &it, const int32_t *__restrict__ pb, const uint16_t *__restrict__ pool,
+                                                  const int32_t *__restrict__ tok_idx, int H, void *__restrict__ y, const V &vs, f32x4 *red)
+{
+    constexpr int kFours = (TOK + 3) / 4;                    // fours of tokens
+    constexpr int kRedTok = TOK < 4 ? TOK : 4;               // tokens whose parts are in LDS at a time
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
+    const int col = it.a + lane * 8;
+    const bool live = col < it.a + it.b;
+    const int col_ld = live ? col : it.a;
+    const int ub = TOK == 1 || it.ntok <= 2 ? 16 : 8;        // ranks of a block
+    const int b0 = wave * ub, b1 = ub == 16 ? b0 + 8 : b0 + 32; // this wavefront's two eights of a window of 64 ranks
+    // the y of the token that this wavefront finishes: requested first, if registers are left for it
+    Y8<DT, Y16> yv;
+    auto y_row = [&](int t) { return static_cast<unsigned char *>(y) + (int64_t)tok_idx[it.pos0 + min(t, it.ntok - 1)] * H * (Y16 ? 2 : 4); };
+    if (TOK <= 4 && wave < it.ntok && live) yv.load(y_row(wave), (uint32_t)col);
+    std::conditional_t<TOK == 1, float, f32x4> acc[kFours][8] = {}; // sums of the lane's eight columns, of four tokens each if there are several
+#pragma nounroll
+    for (int w0 = 0; w0 < it.rank && b0 < it.rank - w0; w0 += kWave) {
+        const int wr = min(kWave, it.rank - w0);
+        const bool two = b1 < wr;
+        const int pages = pb[w0 + min((lane & 8 ? b1 : b0) + (lane & 7), wr - 1)]; // lane k: the page of the k-th of the sixteen
+        u32x4 w[2][8];
+        // v of token lane % 4: that of this wavefront's sixteen ranks
+        const int mine = (lane & 32 ? b1 : b0) + ((lane >> 2) & 7);
+        float v[kFours];
+        for (int finds = 0;; ++finds) {
+            auto rows = [&](int first, u32x4(&o)[8]) { // ranks beyond the last: the last one's row meets v = 0
+#pragma unroll
+                for (int u = 0; u < 8; ++u) {
+                    const int64_t page = __builtin_amdgcn_readlane(pages, first + u);
+                    const u32x4 *row = reinterpret_cast<const u32x4 *>(pool + page * H + col_ld);
+                    o[u] = TOK == 1 ? __builtin_nontemporal_load(row) : *row;
+                }
+            };
+            rows(0, w[0]);
+            if (two) rows(8, w[1]);
+            bool there = true;
+#pragma unroll
+            for (int k = 0; k < kFours; ++k) there = vs.get(it, 4 * k + (lane & 3), w0 + mine, mine < wr, v[k]) && there;
+            if (!V::kMayFail || there || finds == kFinds) break;
+            vs.find(it, w0, wr);
+        }
+        if constexpr (TOK == 1) {
+            add_eight_alone<DT, 0>(v[0], w[0], acc[0]);
+            if (two) add_eight_alone<DT, 32>(v[0], w[1], acc[0]);
+        } else {
+            add_eight<DT, 0>(v, w[0], acc);
+            if (two) add_eight<DT, 8>(v, w[1], acc);
+        }
+    }
+    const int n_rows = (it.rank + ub - 1) / ub; // wavefronts with blocks
+    f32x4 *out = red + wave * kRedTok * 2 * kWave + lane; // red[wave][t][columns' half][lane]
+#pragma unroll
+    for (int k = 0; k < kFours; ++k) {
+        const int mine = 4 * k + wave; // the token that this wavefront finishes
+        if (TOK > 4 && mine < it.ntok && live) yv.load(y_row(mine), (uint32_t)col);
+        if (k > 0) __syncthreads();    // the parts before these have been read
+        if constexpr (TOK == 1) {
+            out[0] = f32x4{acc[0][0], acc[0][1], acc[0][2], acc[0][3]};
+            out[kWave] = f32x4{acc[0][4], acc[0][5], acc[0][6], acc[0][7]};
+        } else {
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                if (4 * k + t < it.ntok) {
+                    out[t * 2 * kWave] = f32x4{acc[k][0][t], acc[k][1][t], acc[k][2][t], acc[k][3][t]};
+                    out[t * 2 * kWave + kWave] = f32x4{acc[k][4][t], acc[k][5][t], acc[k][6][t], acc[k][7][t]};
+                }
+        }
+        __syncthreads();
+        if (mine < it.ntok) {
+            const f32x4 *in = red + wave * 2 * kWave + lane;
+            f32x4 a = in[0], b = in[kWave];
+#pragma unroll
+            for (int r = 1; r < kSplitWaves; ++r) {
+                const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
+                a += r < n_rows ? in[r * kRedTok * 2 * kWave] : zero;
+                b += r < n_rows ? in[r * kRedTok * 2 * kWave + kWave] : zero;
+            }
+            const float d[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
+            if (live) yv.add_store(y_row(mine), (uint32_t)col, d);
+        }
+        if (4 * k + 4 >= it.ntok) return; // the whole workgroup
+    }
+}
+
+// An item of up to 4 * PER <= kGangOwnTok tokens of an adapter of at most kOwnRanks ranks: a wavefront forms whole sums, of a quarter of the
+// tokens, sixteen ranks at a time, as expand_own does token after token.  us per call, expand_own / this one: 30 tokens each of 20 adapters of rank 32, H = 4096, bf16,
+// 4 slots, 16-bit y 47.0 / 39.2; 746 tokens, ranks 1-50, 8 slots 22.3 / 20.2; 960 tokens of rank 8, H = 2928, 3 slots 23.2 / 22.9.
+template <int DT, bool Y16, int PER>
+__device__ __forceinline__ void expand_own_fours(const Item &it, const int32_t *__restrict__ pb, const uint16_t *__restrict__ pool,
+                                                const int32_t *__restrict__ tok_idx, int H, void *__restrict__ y, const RowsOfV &vs)
+{
+    const int lane = threadIdx.x & (kWave - 1);
+    const int per = (it.ntok + kSplitWaves - 1) / kSplitWaves; // tokens of a wavefront, at most four
+    const int t0 = per * __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), t1 = min(t0 + per, it.ntok);
+    if (t0 >= t1) return; // no barrier is used
+    const int col = it.a + lane * 8;
+    const bool live = col < it.a + it.b;
+    const int col_ld = live ? col : it.a;
+    Y8<DT, Y16> yv[PER];
+    unsigned char *row[PER];
+#pragma unroll
+    for (int t = 0; t < PER; ++t)
+        row[t] = static_cast<unsigned char *>(y) + (int64_t)tok_idx[it.pos0 + min(t0 + t, it.ntok - 1)] * H * (Y16 ? 2 : 4);
+    auto load_y = [&]() {
+#pragma unroll
+        for (int t = 0; t < PER; ++t)
+            if (t0 + t < t1 && live) yv[t].load(row[t], (uint32_t)col);
+    };
+    constexpr bool kAheadY = PER <= 2; // registers are left for it
+    if (kAheadY) load_y();
+    const int left = it.ntok & 3;      // one or two: their blocks are of 16 ranks
+    const int by16 = left == 1 || left == 2 ? it.ntok - left : it.ntok; // tokens from here on
+    f32x4 sum[8] = {};
+#pragma nounroll
+    for (int j0 = 0; j0 < it.rank; j0 += 16) {
+        const int pages = pb[min(j0 + (lane & 15), it.rank - 1)];
+        float v[1];
+        vs.get(it, t0 + (lane & 3), j0 + (lane >> 2), (lane & 3) < per && j0 + (lane >> 2) < it.rank, v[0]);
+        const bool two = j0 + 8 < it.rank;
+        u32x4 w[2][8];
+        auto rows = [&](int first, u32x4(&o)[8]) { // ranks beyond the last: the last one's row meets v = 0
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const int64_t page = __builtin_amdgcn_readlane(pages, first + u);
+                o[u] = *reinterpret_cast<const u32x4 *>(pool + page * H + col_ld);
+            }
+        };
+        rows(0, w[0]);
+        if (two) rows(8, w[1]);
+        f32x4 acc[1][8] = {};
+        add_eight<DT, 0>(v, w[0], acc);
+        if (two) {
+#pragma unroll
+            for (int t = 0; t < PER; ++t)
+                if (t0 + t < by16) { // the end of a block
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        sum[e][t] += acc[0][e][t];
+                        acc[0][e][t] = 0.f;
+                    }
+                }
+            add_eight<DT, 8>(v, w[1], acc);
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) sum[e] += acc[0][e];
+    }
+    if (!kAheadY) load_y();
+    if (!live) return;
+#pragma unroll
+    for (int t = 0; t < PER; ++t) {
+        const float d[8] = {sum[0][t], sum[1][t], sum[2][t], sum[3][t], sum[4][t], sum[5][t], sum[6][t], sum[7][t]};
+        if (t0 + t < t1) yv[t].add_store(row[t], (uint32_t)col, d);
+    }
+}
+
+// An item: up to kExpandTok tokens; Gang: up to kGangOwnTok of an adapter of at most kOwnRanks ranks, kGangExpandTok of another
+template <int DT, bool Y16, bool Gang>
 __global__ __launch_bounds__(kSplitWaves *kWave, 3) void expand_vec_split_kernel(const Item *__restrict__ items,
                                                                               const int32_t *__restrict__ arena,
                                                                               const uint16_t *__restrict__ pool,
@@ -972,6 +1206,15 @@ __global__ __launch_bounds__(kSplitWaves *kWave, 3) void expand_vec_split_kernel
     const int32_t *pb = arena + it.arena_off + (int64_t)args.slot[cs] * 2 * it.rank + it.rank;
     const float *v = args.v[cs];
     void *y = args.y[cs];
+    if constexpr (Gang) {
+        if (it.ntok > kExpandTok) {
+            const RowsOfV vs{v, v_stride};
+            if (it.rank > kOwnRanks) expand_split_item<DT, Y16, kGangExpandTok>(it, pb, pool, tok_idx, H, y, vs, reinterpret_cast<f32x4 *>(smem));
+            else if (it.ntok <= 8) expand_own_fours<DT, Y16, 2>(it, pb, pool, tok_idx, H, y, vs);
+            else expand_own_fours<DT, Y16, 4>(it, pb, pool, tok_idx, H, y, vs);
+            return;
+        }
+    }
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     if (it.rank <= 8)
         expand_own<DT, Y16, 8>(it, wave, pb, pool, tok_idx, H, v_stride, y, v);
@@ -1011,6 +1254,7 @@ __global__ __launch_bounds__(kSplitWaves *kWave, 3) void expand_vec_split_kernel
 // ---------------------------------------------------------------------------------------
 template <int DT>
 struct HandOver {
+    static constexpr bool kMayFail = true;
     uint64_t *hand; // the slot's words; an item's begin at its `run`, token after token, rank after rank
     uint32_t launch;
     int polls;
@@ -1057,8 +1301,6 @@ struct HandOver {
         asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); // the words are where get() reads them
     }
 };
-// ... at most: calls that overlap although they use one plan's words could otherwise keep each other's wavefronts
-constexpr int kFinds = 2;
 
 // Chunks of a row that a lane holds: its U-th part, or a little more (the kernel is not made for every number)
 constexpr int chain_chunks(int H)
@@ -1126,129 +1368,6 @@ __device__ __forceinline__ void shrink_page_item(const Item &it, const int32_t *
     }
 }
 
-// acc[e][t] += v of token t and rank K0 + k of the wavefront's sixteen (lane 4 * (K0 + k) + t of v) times element e of row k, rank after rank.  The matrix
-// instruction is sixteen products of a column of four and a row of four; block K0 + k of its first operand is sent to all of them.
-template <int DT, int K0, int K>
-__device__ __forceinline__ void add_ranks(float v, const u32x4 (&row)[8], float (&f)[8], f32x4 (&acc)[8])
-{
-    // the elements of a rank are widened while the products of the one before run: all in registers of their own first
-    asm volatile("" : "+v"(f[0]), "+v"(f[1]), "+v"(f[2]), "+v"(f[3]), "+v"(f[4]), "+v"(f[5]), "+v"(f[6]), "+v"(f[7]));
-    float next[8];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = __builtin_amdgcn_mfma_f32_4x4x1f32(v, f[e], acc[e], 4, K0 + K, 0);
-    if constexpr (K < 7) {
-        widen2<DT>(row[K + 1].x, next[0], next[1]);
-        widen2<DT>(row[K + 1].y, next[2], next[3]);
-        widen2<DT>(row[K + 1].z, next[4], next[5]);
-        widen2<DT>(row[K + 1].w, next[6], next[7]);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) {
-            __builtin_amdgcn_sched_group_barrier(0x8, 1, 0); // a product,
-            __builtin_amdgcn_sched_group_barrier(0x2, 1, 0); // an element
-        }
-        add_ranks<DT, K0, K + 1>(v, row, next, acc);
-    }
-}
-template <int DT, int K0>
-__device__ __forceinline__ void add_eight(float v, const u32x4 (&row)[8], f32x4 (&acc)[8])
-{
-    float f[8];
-    widen2<DT>(row[0].x, f[0], f[1]);
-    widen2<DT>(row[0].y, f[2], f[3]);
-    widen2<DT>(row[0].z, f[4], f[5]);
-    widen2<DT>(row[0].w, f[6], f[7]);
-    add_ranks<DT, K0, 0>(v, row, f, acc);
-}
-
-// An item of the rank-split expand of one token, or of at most TOK = kExpandTok
-template <int DT, bool Y16, int TOK>
-__device__ __forceinline__ void expand_hand_item(const Item &it, const int32_t *__restrict__ pb, const uint16_t *__restrict__ pool,
-                                                 const int32_t *__restrict__ tok_idx, int H, void *__restrict__ y, const HandOver<DT> &hand,
-                                                 f32x4 *red)
-{
-    const int lane = threadIdx.x & (kWave - 1);
-    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
-    const int col = it.a + lane * 8;
-    const bool live = col < it.a + it.b;
-    const int col_ld = live ? col : it.a;
-    const bool finishes = wave < it.ntok; // token `wave`
-    const int ub = TOK == 1 || it.ntok <= 2 ? 16 : 8;        // ranks of a block
-    const int b0 = wave * ub, b1 = ub == 16 ? b0 + 8 : b0 + 32; // this wavefront's two eights of a window of 64 ranks
-    Y8<DT, Y16> yv;
-    void *y_row = static_cast<unsigned char *>(y) + (int64_t)tok_idx[it.pos0 + (finishes ? wave : 0)] * H * (Y16 ? 2 : 4);
-    if (finishes && live) yv.load(y_row, (uint32_t)col);
-    std::conditional_t<TOK == 1, float, f32x4> acc[8] = {}; // sums of the lane's eight columns, of four tokens each if there are several
-#pragma nounroll
-    for (int w0 = 0; w0 < it.rank && b0 < it.rank - w0; w0 += kWave) {
-        const int wr = min(kWave, it.rank - w0);
-        const bool two = b1 < wr;
-        const int pages = pb[w0 + min((lane & 8 ? b1 : b0) + (lane & 7), wr - 1)]; // lane k: the page of the k-th of the sixteen
-        u32x4 w[2][8];
-        // v of token lane % 4: that of this wavefront's sixteen ranks
-        const int mine = (lane & 32 ? b1 : b0) + ((lane >> 2) & 7);
-        float v;
-        for (int finds = 0;; ++finds) {
-            auto rows = [&](int first, u32x4(&o)[8]) { // ranks beyond the last: the last one's row meets v = 0
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    const int64_t page = __builtin_amdgcn_readlane(pages, first + u);
-                    const u32x4 *row = reinterpret_cast<const u32x4 *>(pool + page * H + col_ld);
-                    o[u] = TOK == 1 ? __builtin_nontemporal_load(row) : *row;
-                }
-            };
-            rows(0, w[0]);
-            if (two) rows(8, w[1]);
-            if (hand.get(it, lane & 3, w0 + mine, mine < wr, v) || finds == kFinds) break;
-            hand.find(it, w0, wr);
-        }
-        if constexpr (TOK == 1) {
-            auto add = [&](int first, const u32x4(&o)[8]) {
-#pragma unroll
-                for (int u = 0; u < 8; ++u) {
-                    float f[8];
-                    widen2<DT>(o[u].x, f[0], f[1]);
-                    widen2<DT>(o[u].y, f[2], f[3]);
-                    widen2<DT>(o[u].z, f[4], f[5]);
-                    widen2<DT>(o[u].w, f[6], f[7]);
-                    const float vv = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(v), first + 4 * u));
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) acc[e] = fmaf(vv, f[e], acc[e]);
-                }
-            };
-            add(0, w[0]);
-            if (two) add(32, w[1]);
-        } else {
-            add_eight<DT, 0>(v, w[0], acc);
-            if (two) add_eight<DT, 8>(v, w[1], acc);
-        }
-    }
-    f32x4 *out = red + wave * TOK * 2 * kWave + lane; // red[wave][t][columns' half][lane]
-    if constexpr (TOK == 1) {
-        out[0] = f32x4{acc[0], acc[1], acc[2], acc[3]};
-        out[kWave] = f32x4{acc[4], acc[5], acc[6], acc[7]};
-    } else {
-#pragma unroll
-        for (int t = 0; t < TOK; ++t)
-            if (t < it.ntok) {
-                out[t * 2 * kWave] = f32x4{acc[0][t], acc[1][t], acc[2][t], acc[3][t]};
-                out[t * 2 * kWave + kWave] = f32x4{acc[4][t], acc[5][t], acc[6][t], acc[7][t]};
-            }
-    }
-    __syncthreads();
-    if (!finishes) return;
-    const int n_rows = (it.rank + ub - 1) / ub; // wavefronts with blocks
-    const f32x4 *in = red + wave * 2 * kWave + lane;
-    f32x4 a = in[0], b = in[kWave];
-#pragma unroll
-    for (int k = 1; k < kSplitWaves; ++k) {
-        const f32x4 zero = f32x4{0.f, 0.f, 0.f, 0.f};
-        a += k < n_rows ? in[k * TOK * 2 * kWave] : zero;
-        b += k < n_rows ? in[k * TOK * 2 * kWave + kWave] : zero;
-    }
-    const float d[8] = {a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w};
-    if (live) yv.add_store(y_row, (uint32_t)col, d);
-}
-
 template <int DT, bool Y16, int U>
 __global__ __launch_bounds__(kShrinkThreads, U > 8 ? 3 : 4) void lora_vec_chain_kernel(ChainLists lists, const int32_t *__restrict__ arena,
                                                                                        const uint16_t *__restrict__ pool,
@@ -1276,8 +1395,8 @@ __global__ __launch_bounds__(kShrinkThreads, U > 8 ? 3 : 4) void lora_vec_chain_
         const int32_t *pb = pa + it.rank;
         f32x4 *red = reinterpret_cast<f32x4 *>(smem);
         void *y = args.y[cs];
-        if (it.ntok == 1 && it.tile) expand_hand_item<DT, Y16, 1>(it, pb, pool, tok_idx, H, y, hand, red);
-        else expand_hand_item<DT, Y16, kExpandTok>(it, pb, pool, tok_idx, H, y, hand, red);
+        if (it.ntok == 1 && it.tile) expand_split_item<DT, Y16, 1>(it, pb, pool, tok_idx, H, y, hand, red);
+        else expand_split_item<DT, Y16, 4>(it, pb, pool, tok_idx, H, y, hand, red);
     }
 }
 
@@ -2820,11 +2939,15 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *
     const size_t n_ve = route.chain ? 0 : plan->n_ve(route);
     if (n_ve > 0) {
         const dim3 grid((unsigned)(plan->expand_wgs(route) * (size_t)n));
-        if (plan->expand_split)
-            hipLaunchKernelGGL(SLORA_PICK(expand_vec_split_kernel), grid, dim3(kSplitWaves * kWave), kSplitLds, st,
-                               route.gang_expand ? plan->d_ge : plan->d_ve, pool->d_arena, base, plan->d_tok_idx, pool->H,
-                               plan->v_stride, args);
-        else
+        if (plan->expand_split) {
+#define SLORA_SPLIT(DT, Y)                                                                                                  \
+    (route.gang_expand ? &expand_vec_split_kernel<DT, Y, true> : &expand_vec_split_kernel<DT, Y, false>)
+            auto *kernel = pool->dtype == SLORA_F16 ? (y16 ? SLORA_SPLIT(SLORA_F16, true) : SLORA_SPLIT(SLORA_F16, false))
+                                                    : (y16 ? SLORA_SPLIT(SLORA_BF16, true) : SLORA_SPLIT(SLORA_BF16, false));
+#undef SLORA_SPLIT
+            hipLaunchKernelGGL(kernel, grid, dim3(kSplitWaves * kWave), kSplitLds, st, route.gang_expand ? plan->d_ge : plan->d_ve,
+                               pool->d_arena, base, plan->d_tok_idx, pool->H, plan->v_stride, args);
+        } else
             hipLaunchKernelGGL(SLORA_PICK(expand_vec_kernel), grid, dim3((unsigned)plan->expand_threads), 0, st,
                                plan->d_ve, pool->d_arena, base, plan->d_tok_idx, pool->H, plan->v_stride, args);
         int32_t rc = check_launch("expand_vec");

@@ -188,13 +188,12 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         const int32_t me_run = (int32_t)std::min<int64_t>(kMfmaRunMax, std::max<int64_t>(1, me_pairs / 1024));
         plan->me_run = me_run;
         plan->me_stages = 0;
-        int32_t n_vec_groups = 0, most_vec_tokens = 0, most_own_tokens = 0; // (own: of an adapter of at most kOwnRanks ranks)
+        int32_t n_vec_groups = 0, most_vec_tokens = 0;
         for (int32_t gi : order) {
             const int64_t n = (int64_t)groups[(size_t)gi].toks.size();
             if (n >= min_tokens) continue;
             n_vec_groups++;
             most_vec_tokens = std::max(most_vec_tokens, (int32_t)n);
-            if (groups[(size_t)gi].rank <= kOwnRanks) most_own_tokens = std::max(most_own_tokens, (int32_t)n);
         }
         // vector-expand items: long runs of columns, halved while a launch would have fewer
         // workgroups than the GPU has CUs
@@ -319,8 +318,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         const bool crowds = plan->expand_split && plan->vf_items.empty() && most_vec_tokens > kExpandTok;
         const int64_t n_vs = (int64_t)plan->vs_items.size(), n_vs_all = n_vs + (int64_t)vs_dual.size();
         bool gang = crowds && pool->shrink_pages == 0 && n_vs_all * most_slots >= kGangFrom;
-        const bool gang_expand = crowds && most_own_tokens > kExpandTok &&
-                                 (int64_t)(plan->ve_items.size() + ve_dual.size()) * most_slots >= kGangExpandFrom;
+        const bool gang_expand = crowds && (int64_t)(plan->ve_items.size() + ve_dual.size()) * most_slots >= kGangExpandFrom;
         if (gang) {
             int64_t few = 0, few_dual = 0; // shrink items of a call that takes the larger ones
             for (int32_t gi : order) {
@@ -357,10 +355,13 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                             gs.push_back(Item{off, g.rank, j0, j1 - j0, pos0 + p, std::min(kGangTok, n - p), 0, hand0 + p * g.rank});
                         }
                 }
-                const int32_t step = g.rank <= kOwnRanks ? kGangExpandTok : kExpandTok;
-                for (int32_t p = 0; gang_expand && p < n; p += step)
+                // (one or two tokens left over from the fours have blocks of 16 ranks: an item of their own, unless a wavefront forms whole sums)
+                const int32_t fours = g.rank > kOwnRanks && n % kExpandTok <= 2 ? n - n % kExpandTok : n;
+                for (int32_t p = 0, nt; gang_expand && p < n; p += nt) {
+                    nt = p < fours ? std::min(g.rank <= kOwnRanks ? kGangOwnTok : kGangExpandTok, fours - p) : n - p;
                     for (int32_t c = 0; c < H; c += ecols)
-                        ge.push_back(Item{off, g.rank, c, std::min(ecols, H - c), pos0 + p, std::min(step, n - p), n <= kExpandTok, hand0 + p * g.rank});
+                        ge.push_back(Item{off, g.rank, c, std::min(ecols, H - c), pos0 + p, nt, n <= kExpandTok, hand0 + p * g.rank});
+                }
             }
             plan->n_gs_plain = (int32_t)plan->gs_items.size();
             plan->n_ge_plain = (int32_t)plan->ge_items.size();

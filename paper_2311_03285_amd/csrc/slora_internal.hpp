@@ -99,12 +99,13 @@ constexpr int kExpandTok = 4;     // tokens per vector-expand item (accumulators
 constexpr int kSmallRanks = 32;   // most ranks of an adapter in a batch that runs in the one-launch kernel for small batches
 constexpr int kExpandColsMax = 1024; // most columns per vector-expand item (a multiple of 512, <= 4096; measured best on cfg4: 1024)
 constexpr int kSplitWaves = 4;    // rank-split expand: wavefronts of a workgroup, and parts of a sum over the ranks
-constexpr int kOwnRanks = 32;     // ... up to this many ranks a wavefront forms whole sums
 constexpr int kGangTok = 8;       // tokens per item of the shrink for groups of many tokens,
 constexpr int kGangPages = 16;    // pages, at most
 constexpr int kGangFrom = 1400, kGangExpandFrom = 2000; // least workgroups of the small items at which a call takes them (see route)
 constexpr bool gang_pays(int64_t small_items, int64_t large_items) { return 2 * large_items <= small_items; }
-constexpr int kGangExpandTok = 16; // tokens per item of the rank-split expand for such groups of at most kOwnRanks ranks
+constexpr int kOwnRanks = 32;     // rank-split expand of groups of many tokens: up to this many ranks a wavefront forms whole sums,
+constexpr int kGangOwnTok = 16;   // of that many tokens an item;
+constexpr int kGangExpandTok = 8; // tokens per item of more ranks
 constexpr int kChainMaxH = 8192;  // widest rows whose sums the one-launch kernel that hands v over forms: a wavefront holds one in registers
 constexpr int kMfmaTok = 32;      // tokens per v tile = per MFMA-expand item (one 32-row MFMA block)
 constexpr int kMsTok = 128;       // most tokens per MFMA-shrink item

@@ -257,7 +257,7 @@ static void vec_expand(const slora_plan *plan, const MultiArgs &a, int32_t k, co
         REQUIRE(std::memcmp(&it, gang ? &plan->ge_items[i] : &plan->ve_items[i], sizeof it) == 0);
         check_pages(plan, it.arena_off, it.rank, a.slot[k]);
         check_tokens(plan, it.pos0, it.ntok);
-        REQUIRE(it.ntok <= (gang && it.rank <= kOwnRanks ? kGangExpandTok : kExpandTok));
+        REQUIRE(it.ntok <= (!gang ? kExpandTok : it.rank <= kOwnRanks ? kGangOwnTok : kGangExpandTok));
         REQUIRE(it.a >= 0 && it.b > 0 && it.a % 8 == 0 && it.b % 8 == 0 && it.a + it.b <= pool->H);
         REQUIRE(it.b <= (plan->expand_split ? 512 : plan->expand_threads * 8));
         const int read_by = readers[std::make_pair(it.arena_off, it.a)];
