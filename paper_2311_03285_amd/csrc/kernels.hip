@@ -541,7 +541,8 @@ __global__ __launch_bounds__(1024, U <= 6 ? 5 : 4) void lora_vec_fused_kernel(co
 }
 
 // ---------------------------------------------------------------------------------------
-// decode path, both stages in one launch, for SMALL batches: a workgroup = one item of the rank-split
+// decode path, both stages in one launch, for SMALL batches whose call is captured or keeps v in the static scratch (others: lora_vec_chain_kernel,
+// 6.3 / 6.1 us for one token of rank 16, 4 slots, 9.2 / 6.4 at rank 32, 9.4 / 6.1 for six groups of two tokens): a workgroup = one item of the rank-split
 // expand (512 columns of a group of at most kExpandTok tokens), which computes the group's v = x*A for
 // itself.  Its eight wavefronts share out the A pages and leave v in LDS; the first four then do the
 // rank-split expand, whose B rows and y were requested before the first A page.  A is read once per 512
@@ -799,7 +800,7 @@ __global__ __launch_bounds__(kShrinkThreads) void shrink_gang_kernel(const Item 
 // 51 tokens of ranks 30-130, H = 1168, 4 slots 15.2 -> 9.2; 142 tokens of ranks 5-130, H = 4096, 2 slots 17.0 -> 13.5; 376
 // tokens of rank 1, H = 4096, 8 slots 39.5 -> 22.6, with 16 tokens per workgroup 15.8; 960 tokens of rank 8, H = 2928, 3 slots
 // 31.4 -> 16.0 -> 11.1.  kOwnRanks = 16 (fewer registers, four workgroups per compute unit instead of three): up to 20 %
-// slower, half as fast on groups of many tokens (spills).
+// slower, half as fast on groups of many tokens (spills).  Items of more than four tokens: expand_own_fours, expand_split_item.
 // ---------------------------------------------------------------------------------------
 // v of ranks w0 + lane, where `mine`, of tokens t0 .. t0 + TOK - 1 of an item
 template <int TOK>
