@@ -524,10 +524,14 @@ Route slora_plan::route(int32_t n, bool apply, bool y16) const
 // chain: 128 tokens of rank 32, H = 4096, 1 / 2 / 4 slots, 2048 / 4096 / 8192: 18.5 / 15.5, 29.8 / 26.4, 52.8 / 56.6; 50 of rank 64, 4 slots, 4800: 40.8 / 37.8; 100 of rank 64,
 // H = 2048, 4 slots, 8000: 41.0 / 42.3, fours of them 52.3 / 60.4; 400 of rank 8, 4000: 18.3 / 19.0, 3 slots, 12000: 40 / 51; 20 groups of eight tokens of rank 64, 3 slots,
 // 2880: 29.8 / 23.0; where rows of x leave a compute unit two workgroups, 60 groups of four tokens of rank 64, H = 8192, 2 slots, 3840: 67.8 / 75.9.
+// Short rows of many ranks are mostly shrink, whose wavefronts then have little in flight; four of its workgroups fit a compute unit here, five or more in a kernel of
+// its own; and rows of a second 64 ranks are requested after the wait.  Tokens of rank 128, H = 2048: 30 in 1080 workgroups 12.3 / 13.2, 40 in 1440 13.5 / 14.9, 60 in 2160 16.8 / 18.9, 100 pairs in 3600 25.5 / 30.4; but H = 3072, 75 in 2850: 25.0 / 24.2,
+// rank 64, 100 in two slots, 4000: 24.2 / 22.7, and 20 of rank 128, H = 1024, 680: 10.4 / 7.9.
 bool slora_plan::chain_pays(int32_t n, const Route &r) const
 {
     if (!expand_split || pool->fuse_decode == 0 || n_vs(r) == 0 || r.gang || r.gang_expand || pool->H > kChainMaxH || chain_wgs(r) > 65535) return false;
     const int64_t rows = (int64_t)max_shrink_tok * pool->H * 2;
+    if (n_vs(r) > 6 * n_ve(r) && (int64_t)n_vs(r) * n > 640) return false;
     return chain_wgs(r) * n <= (rows <= 40960 ? 4096 : 2048);
 }
 
