@@ -107,15 +107,19 @@ def _stream(s) -> Optional[int]:
 
 # The calls of a layer are enqueued back to back, and the smallest take as long as their enqueueing.  Of a call of four slots numpy's ctypes view
 # and an object per pointer were 1.3 us: one token of rank 16, 4 slots 5.9 -> 4.6 us, 1 slot 5.2 -> 4.3.
-_POINTERS = [C.c_void_p * n for n in range(MAX_MULTI + 1)]
+class _Address(C.c_uint64):
+    """An element that takes whole numbers only: c_void_p takes None and other c_void_p as well."""
+
+
+_POINTERS = [_Address * n for n in range(MAX_MULTI + 1)]
 _SLOTS = [C.c_int32 * n for n in range(MAX_MULTI + 1)]
 
 
 def _ptr_array(ptrs: Sequence[int]):
     n = len(ptrs)
     try:
-        return (_POINTERS[n] if n <= MAX_MULTI else C.c_void_p * n)(*ptrs)
-    except TypeError:  # numbers of another type than int
+        return (_POINTERS[n] if n <= MAX_MULTI else _Address * n)(*ptrs)
+    except TypeError:  # numbers of another type, or no numbers: int() says
         return (C.c_void_p * n)(*[C.c_void_p(int(p)) for p in ptrs])
 
 
