@@ -262,10 +262,12 @@ int32_t slora_lora_apply_multi(slora_plan *plan, int32_t n, const int32_t *slots
 
 /*
  * slora_lora_apply_multi for callers that cannot allocate device memory: code under HIP graph
- * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same kernels,
- * same results bit for bit; the only difference is where v = x*A is kept between the two
- * launches: in a scratch array that is part of the library's code object (one copy per GPU,
- * SLORA_STATIC_SCRATCH_BYTES, held until the process ends) instead of the plan's own buffer.
+ * capture, tight serving loops, harnesses that forbid hipMalloc.  Same arguments, same results
+ * bit for bit (infinite weights included).  v = x*A is kept between the two
+ * launches in a scratch array that is part of the library's code object (one copy per GPU,
+ * SLORA_STATIC_SCRATCH_BYTES, held until the process ends) instead of the plan's own buffer; calls
+ * that slora_lora_apply_multi runs in one launch that hands v over are two launches, or one
+ * of another kernel, here.
  * The call makes no hipMalloc / hipFree and no other allocating call, on any path.
  * Limit: n * (tokens with an adapter * v row stride * 4 bytes + the MFMA tiles' operand
  * fragments and partial sums) must fit the scratch, else SLORA_ERANGE and nothing is enqueued

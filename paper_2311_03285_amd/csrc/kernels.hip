@@ -612,18 +612,22 @@ __device__ __forceinline__ void small_body(const Item &it, const int32_t *__rest
         for (int e = 0; e < 8; ++e) acc[t][e] = 0.f;
     if (expands) {
 #pragma unroll
-        for (int u = 0; u < UB; ++u) {
-            const int j = wave * UB + u;
-            float f[8];
-            widen2<DT>(w[u].x, f[0], f[1]);
-            widen2<DT>(w[u].y, f[2], f[3]);
-            widen2<DT>(w[u].z, f[4], f[5]);
-            widen2<DT>(w[u].w, f[6], f[7]);
+        for (int u0 = 0; u0 < UB; u0 += 8) {
+            if (u0 > 0 && wave * UB + u0 >= it.rank) break; // no eight whose rows would all be the last one, times zero
 #pragma unroll
-            for (int t = 0; t < TOK; ++t) {
-                const float vv = t < it.ntok && j < it.rank ? vl[t * kSmallRanks + j] : 0.f;
+            for (int u = u0; u < u0 + 8; ++u) {
+                const int j = wave * UB + u;
+                float f[8];
+                widen2<DT>(w[u].x, f[0], f[1]);
+                widen2<DT>(w[u].y, f[2], f[3]);
+                widen2<DT>(w[u].z, f[4], f[5]);
+                widen2<DT>(w[u].w, f[6], f[7]);
 #pragma unroll
-                for (int e = 0; e < 8; ++e) acc[t][e] = fmaf(vv, f[e], acc[t][e]);
+                for (int t = 0; t < TOK; ++t) {
+                    const float vv = t < it.ntok && j < it.rank ? vl[t * kSmallRanks + j] : 0.f;
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) acc[t][e] = fmaf(vv, f[e], acc[t][e]);
+                }
             }
         }
     }
@@ -783,7 +787,7 @@ __global__ __launch_bounds__(kShrinkThreads) void shrink_gang_kernel(const Item 
 // decode path, expand for batches whose launch has fewer workgroups than the GPU can hold ("rank-split"): a
 // workgroup = 512 columns (a lane owns 8) of some tokens of one adapter group.  A sum over the ranks is made of the
 // sums of four rows of blocks - blocks of 8 ranks, 16 where a token is one of at most two left over from the
-// group's fours; row w has the blocks w, w + 4, ... - which are added in the order of w.  Who forms them does not matter:
+// group's fours; row w has the blocks w, w + 4, ... - which are added in the order of w; half a block without ranks is left out.  Who forms them does not matter:
 //   up to kOwnRanks ranks: a wavefront keeps all B rows of its columns in registers and forms whole sums, of
 //     every fourth token of the workgroup's;
 //   more, or one or two tokens of more than 16: wavefront w forms row w for up to four tokens, the parts meet in LDS, and wavefront t
@@ -876,16 +880,17 @@ __device__ __forceinline__ void expand_own(const Item &it, int t0, const int32_t
     }
 }
 
-// An item of at most TOK tokens (1 or 2: exactly); UB: ranks per block; Once: its B rows are streamed.  One token has an instance of its own: with the
+// An item of at most TOK tokens (1 or 2: exactly); UB: ranks per block; Once: its B rows are streamed; Half: the last block of 16 ranks has at most
+// eight (an instance of its own: a branch between the halves of every block costs single tokens of rank 64 4.5 -> 5.0 us).  One token has an instance of its own: with the
 // two-token one it requested, multiplied and passed through LDS a second token of zeros.  v is requested beside the page numbers, which
 // the B rows wait for anyway.  us of the expand, pages from memory, before and with the streaming loads: 24 tokens of rank 64, H = 4096 6.8 -> 5.7; two
 // of rank 128, 8 slots 9.4 -> 7.1; 37 of ranks 16-128, H = 3072 9.5 -> 7.6; pages from the caches 5.9 -> 5.1, 7.7 -> 7.1, 7.9 -> 7.1.
-template <int DT, bool Y16, int TOK, int UB, bool Once>
+template <int DT, bool Y16, int TOK, int UB, bool Once, bool Half>
 __device__ __forceinline__ void expand_shared(const Item &it, const int32_t *__restrict__ pb,
                                               const uint16_t *__restrict__ pool, const int32_t *__restrict__ tok_idx,
                                               int H, int v_stride, void *__restrict__ y, const float *__restrict__ vs, float *red)
 {
-    constexpr int NB = 16 / UB; // blocks of a wavefront in a window of 64 ranks
+    constexpr bool kWhole = UB == 16 && !Half; // both eights have ranks
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int col = it.a + lane * 8;
@@ -905,13 +910,14 @@ __device__ __forceinline__ void expand_shared(const Item &it, const int32_t *__r
         const int pwin = lane < wr ? pb[w0 + lane] : 0;
         float v[TOK]; // rank w0 + lane, if it is in one of this wavefront's blocks
         load_v(it, 0, w0, lane < wr && lane / UB % kSplitWaves == wave, vs, v_stride, v);
-        u32x4 w[NB][UB];
+        u32x4 w[2][8]; // this wavefront's two eights of a window of 64 ranks: a block, or half of one
+        auto first = [&](int i) { return UB == 16 ? (2 * wave + i) * 8 : (wave + kSplitWaves * i) * 8; };
 #pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            const int j0 = (wave + kSplitWaves * i) * UB;
-            if (i == 0 || j0 < wr) {
+        for (int i = 0; i < 2; ++i) {
+            const int j0 = first(i);
+            if (kWhole || i == 0 || j0 < wr) {
 #pragma unroll
-                for (int u = 0; u < UB; ++u) { // ranks beyond the last: the last one's row meets v = 0
+                for (int u = 0; u < 8; ++u) { // ranks beyond the last: the last one's row meets v = 0
                     const int64_t page = __builtin_amdgcn_readlane(pwin, min(j0 + u, wr - 1));
                     const u32x4 *row = reinterpret_cast<const u32x4 *>(pool + page * H + col_ld);
                     w[i][u] = Once ? __builtin_nontemporal_load(row) : *row;
@@ -919,11 +925,11 @@ __device__ __forceinline__ void expand_shared(const Item &it, const int32_t *__r
             }
         }
 #pragma unroll
-        for (int i = 0; i < NB; ++i) {
-            const int j0 = (wave + kSplitWaves * i) * UB;
-            if (i == 0 || j0 < wr) {
+        for (int i = 0; i < 2; ++i) {
+            const int j0 = first(i);
+            if (kWhole || i == 0 || j0 < wr) {
 #pragma unroll
-                for (int u = 0; u < UB; ++u) {
+                for (int u = 0; u < 8; ++u) {
                     float f[8];
                     widen2<DT>(w[i][u].x, f[0], f[1]);
                     widen2<DT>(w[i][u].y, f[2], f[3]);
@@ -1223,17 +1229,25 @@ __global__ __launch_bounds__(kSplitWaves *kWave, 3) void expand_vec_split_kernel
         expand_own<DT, Y16, 16>(it, wave, pb, pool, tok_idx, H, v_stride, y, v);
     else if (it.rank <= kOwnRanks && it.ntok > 2)
         expand_own<DT, Y16, kOwnRanks>(it, wave, pb, pool, tok_idx, H, v_stride, y, v);
-    else if (it.ntok <= 2) { // two blocks or more: a wavefront each, while whole sums would keep one of them busy
+    else if (it.ntok > 2)
+        expand_shared<DT, Y16, kExpandTok, 8, false, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+    else if ((it.rank - 1) & 8) { // two blocks or more: a wavefront each, while whole sums would keep one of them busy
         if (it.ntok == 1 && it.tile)
-            expand_shared<DT, Y16, 1, 16, true>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+            expand_shared<DT, Y16, 1, 16, true, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
         else if (it.ntok == 1)
-            expand_shared<DT, Y16, 1, 16, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+            expand_shared<DT, Y16, 1, 16, false, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
         else if (it.tile)
-            expand_shared<DT, Y16, 2, 16, true>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+            expand_shared<DT, Y16, 2, 16, true, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
         else
-            expand_shared<DT, Y16, 2, 16, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
-    } else
-        expand_shared<DT, Y16, kExpandTok, 8, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+            expand_shared<DT, Y16, 2, 16, false, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+    } else if (it.ntok == 1 && it.tile)
+        expand_shared<DT, Y16, 1, 16, true, true>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+    else if (it.ntok == 1)
+        expand_shared<DT, Y16, 1, 16, false, true>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+    else if (it.tile)
+        expand_shared<DT, Y16, 2, 16, true, true>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+    else
+        expand_shared<DT, Y16, 2, 16, false, true>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
 }
 
 // ---------------------------------------------------------------------------------------
