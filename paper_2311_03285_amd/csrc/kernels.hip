@@ -1021,7 +1021,7 @@ __device__ __forceinline__ void add_eight_alone(float v, const u32x4 (&row)[8], 
 }
 
 // Where an item's wavefronts find v: get() returns the value of a token and a rank of each lane's own, where `mine` and there is such a
-// token; false: not all are there, and find() makes those of ranks [w0, w0 + wr).  Rows that an earlier launch has left:
+// token; false: not all are there, and find() makes those of `n` ranks from j0 on.  Rows that an earlier launch has left:
 struct RowsOfV {
     static constexpr bool kMayFail = false;
     const float *v;
@@ -1082,7 +1082,8 @@ __device__ __forceinline__ void expand_split_item(const Item &it, const int32_t 
 #pragma unroll
             for (int k = 0; k < kFours; ++k) there = vs.get(it, 4 * k + (lane & 3), w0 + mine, mine < wr, v[k]) && there;
             if (!V::kMayFail || there || finds == kFinds) break;
-            vs.find(it, w0, wr);
+            vs.find(it, w0 + b0, min(8, wr - b0));
+            if (two) vs.find(it, w0 + b1, min(8, wr - b1));
         }
         if constexpr (TOK == 1) {
             add_eight_alone<DT, 0>(v[0], w[0], acc[0]);
@@ -1261,7 +1262,10 @@ __global__ __launch_bounds__(kSplitWaves *kWave, 3) void expand_vec_split_kernel
 // has this launch's number is whole and needs no other order; words of earlier launches have other numbers, so nothing is
 // cleared between calls.  Workgroups are dispatched in order, so those that are waited for run first; where another stream's kernel holds
 // the GPU that may fail, and a wait is bounded: after `polls` reads a wavefront computes what it waits for, with the same sums, leaves it in
-// the words and goes on.  Calls that a HIP graph captures keep the two kernels: a replay would repeat the number.
+// the words and goes on (if all waits ran out at once: a group of four tokens of rank 64, H = 4096, 7 -> 90 us, 20 of them on 4 slots 19 -> 38).  Beside
+// products of 8192 x 4096 x 8192 on another stream, one call every 0.4 ms, median us of the two kernels / this one: 32 tokens of ranks 8-64 800 / 230,
+// 96 of 4 adapters 815 / 250, 45 of ranks 3-100 800 / 185; beside products of 2048 x 4096 x 2048 21 / 20, 45 / 32, 35 / 28 - two launches are
+// delayed by the other stream's kernels twice.  Calls that a HIP graph captures keep the two kernels: a replay would repeat the number.
 //
 // Sums and their order are those of the vector shrink and of the rank-split expand: the same bits.  us per call, two kernels / chain:
 // 32 tokens of ranks 8-64, H = 4096 9.9 / 7.3; 96 tokens of 4 adapters, 3 slots, bf16, 16-bit y 15.5 / 11.9; 45 tokens of ranks 3-100, H = 3080, 3 slots
@@ -1296,12 +1300,13 @@ struct HandOver {
             __builtin_amdgcn_s_sleep(1);
         }
     }
-    // ranks [w0, w0 + wr) of all tokens: each lane adds the products of chunks lane, lane + 64, ... as the shrink's lanes do
-    __device__ __forceinline__ void find(const Item &it, int w0, int wr) const
+    // n ranks from j0 on, of all tokens: each lane adds the products of chunks lane, lane + 64, ... as the shrink's lanes do.  A wavefront finds the
+    // ranks of its own blocks only (all of a window's 64 took four times as long where rank and H are large)
+    __device__ __forceinline__ void find(const Item &it, int j0, int n) const
     {
         const int lane = threadIdx.x & (kWave - 1), nch = H >> 3;
 #pragma nounroll
-        for (int j = w0; j < w0 + wr; ++j) {
+        for (int j = j0; j < j0 + n; ++j) {
             const u32x4 *page = reinterpret_cast<const u32x4 *>(pool + (int64_t)pa[j] * H);
 #pragma nounroll
             for (int t = 0; t < it.ntok; ++t) {

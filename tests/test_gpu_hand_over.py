@@ -162,3 +162,25 @@ def test_infinite_weights(H, rank, y16, side):
                 assert bool(torch.isinf(y[hit, 3]).all())
             assert torch.equal(torch.isnan(y), torch.isnan(ys[0]))
             assert torch.equal(torch.nan_to_num(y, 0.0, 7.0, -7.0), torch.nan_to_num(ys[0], 0.0, 7.0, -7.0))
+
+
+def test_an_expired_wait_costs_a_wavefront_its_own_ranks():
+    """Whoever gives up waiting finds the ranks of its own blocks: 16 of a group's 64 for a wavefront, 8 of 8 where there is one block.  So the call of 64
+    ranks takes about twice as long (2.0 measured); with all of the 64 for every wavefront it would be eight times (7.7 measured)."""
+    us = {}
+    for rank in (8, 64):
+        w = workload(4096, synth.F16, (rank,), (4,), slots=1)
+        with DeviceWorkload(w, real_adapters="all") as dw:
+            slora.set_option(dw.pool, "hand_polls", 0)
+            plan, x, y = dw.plan(), dw.x_dev(0), dw.y_dev(0)
+            best = float("inf")
+            for _ in range(10):
+                e0, e1 = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+                e0.record()
+                for _ in range(20):
+                    slora.lora_apply_multi(plan, [0], [x.data_ptr()], [y.data_ptr()])
+                e1.record()
+                torch.cuda.synchronize()
+                best = min(best, e0.elapsed_time(e1))
+            us[rank] = best
+    assert us[64] < 4 * us[8], us
