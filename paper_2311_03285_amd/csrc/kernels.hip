@@ -1128,15 +1128,16 @@ __device__ __forceinline__ void expand_split_item(const Item &it, const int32_t 
     }
 }
 
-// An item of up to 4 * PER <= kGangOwnTok tokens of an adapter of at most kOwnRanks ranks: a wavefront forms whole sums, of a quarter of the
+// An item of up to kGangOwnTok tokens of an adapter of at most kOwnRanks ranks: a wavefront forms whole sums, of a quarter of the
 // tokens, sixteen ranks at a time, as expand_own does token after token.  us per call, expand_own / this one: 30 tokens each of 20 adapters of rank 32, H = 4096, bf16,
 // 4 slots, 16-bit y 47.0 / 39.2; 746 tokens, ranks 1-50, 8 slots 22.3 / 20.2; 960 tokens of rank 8, H = 2928, 3 slots 23.2 / 22.9.
-template <int DT, bool Y16, int PER>
+template <int DT, bool Y16>
 __device__ __forceinline__ void expand_own_fours(const Item &it, const int32_t *__restrict__ pb, const uint16_t *__restrict__ pool,
                                                 const int32_t *__restrict__ tok_idx, int H, void *__restrict__ y, const RowsOfV &vs)
 {
     const int lane = threadIdx.x & (kWave - 1);
-    const int per = (it.ntok + kSplitWaves - 1) / kSplitWaves; // tokens of a wavefront, at most four
+    constexpr int PER = kGangOwnTok / kSplitWaves;
+    const int per = (it.ntok + kSplitWaves - 1) / kSplitWaves; // tokens of a wavefront, at most PER
     const int t0 = per * __builtin_amdgcn_readfirstlane(threadIdx.x / kWave), t1 = min(t0 + per, it.ntok);
     if (t0 >= t1) return; // no barrier is used
     const int col = it.a + lane * 8;
@@ -1147,13 +1148,6 @@ __device__ __forceinline__ void expand_own_fours(const Item &it, const int32_t *
 #pragma unroll
     for (int t = 0; t < PER; ++t)
         row[t] = static_cast<unsigned char *>(y) + (int64_t)tok_idx[it.pos0 + min(t0 + t, it.ntok - 1)] * H * (Y16 ? 2 : 4);
-    auto load_y = [&]() {
-#pragma unroll
-        for (int t = 0; t < PER; ++t)
-            if (t0 + t < t1 && live) yv[t].load(row[t], (uint32_t)col);
-    };
-    constexpr bool kAheadY = PER <= 2; // registers are left for it
-    if (kAheadY) load_y();
     const int left = it.ntok & 3;      // one or two: their blocks are of 16 ranks
     const int by16 = left == 1 || left == 2 ? it.ntok - left : it.ntok; // tokens from here on
     f32x4 sum[8] = {};
@@ -1190,7 +1184,9 @@ __device__ __forceinline__ void expand_own_fours(const Item &it, const int32_t *
 #pragma unroll
         for (int e = 0; e < 8; ++e) sum[e] += acc[0][e];
     }
-    if (!kAheadY) load_y();
+#pragma unroll
+    for (int t = 0; t < PER; ++t)
+        if (t0 + t < t1 && live) yv[t].load(row[t], (uint32_t)col);
     if (!live) return;
 #pragma unroll
     for (int t = 0; t < PER; ++t) {
@@ -1199,8 +1195,9 @@ __device__ __forceinline__ void expand_own_fours(const Item &it, const int32_t *
     }
 }
 
-// An item: up to kExpandTok tokens; Gang: up to kGangOwnTok of an adapter of at most kOwnRanks ranks, kGangExpandTok of another
-template <int DT, bool Y16, bool Gang>
+// An item: up to kExpandTok tokens, or of a larger item's list kGangOwnTok of an adapter of at most kOwnRanks ranks; Fours: kGangExpandTok of another, and some
+// of them on the matrix instruction (an instance of its own: with both kinds of code the items of the first are up to 6 % slower)
+template <int DT, bool Y16, bool Fours>
 __global__ __launch_bounds__(kSplitWaves *kWave, 3) void expand_vec_split_kernel(const Item *__restrict__ items,
                                                                               const int32_t *__restrict__ arena,
                                                                               const uint16_t *__restrict__ pool,
@@ -1214,12 +1211,15 @@ __global__ __launch_bounds__(kSplitWaves *kWave, 3) void expand_vec_split_kernel
     const int32_t *pb = arena + it.arena_off + (int64_t)args.slot[cs] * 2 * it.rank + it.rank;
     const float *v = args.v[cs];
     void *y = args.y[cs];
-    if constexpr (Gang) {
+    if constexpr (Fours) {
         if (it.ntok > kExpandTok) {
             const RowsOfV vs{v, v_stride};
+            const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
             if (it.rank > kOwnRanks) expand_split_item<DT, Y16, kGangExpandTok>(it, pb, pool, tok_idx, H, y, vs, reinterpret_cast<f32x4 *>(smem));
-            else if (it.ntok <= 8) expand_own_fours<DT, Y16, 2>(it, pb, pool, tok_idx, H, y, vs);
-            else expand_own_fours<DT, Y16, 4>(it, pb, pool, tok_idx, H, y, vs);
+            else if (fours_pay(DT, Y16, it.rank, it.ntok)) expand_own_fours<DT, Y16>(it, pb, pool, tok_idx, H, y, vs);
+            else if (it.rank <= 8) expand_own<DT, Y16, 8>(it, wave, pb, pool, tok_idx, H, v_stride, y, v);
+            else if (it.rank <= 16) expand_own<DT, Y16, 16>(it, wave, pb, pool, tok_idx, H, v_stride, y, v);
+            else expand_own<DT, Y16, 32>(it, wave, pb, pool, tok_idx, H, v_stride, y, v);
             return;
         }
     }
@@ -2961,7 +2961,7 @@ int32_t launch_expand(slora_plan *plan, int32_t n, const MultiArgs &args, void *
         const dim3 grid((unsigned)(plan->expand_wgs(route) * (size_t)n));
         if (plan->expand_split) {
 #define SLORA_SPLIT(DT, Y)                                                                                                  \
-    (route.gang_expand ? &expand_vec_split_kernel<DT, Y, true> : &expand_vec_split_kernel<DT, Y, false>)
+    (route.gang_expand && plan->fours[y16] ? &expand_vec_split_kernel<DT, Y, true> : &expand_vec_split_kernel<DT, Y, false>)
             auto *kernel = pool->dtype == SLORA_F16 ? (y16 ? SLORA_SPLIT(SLORA_F16, true) : SLORA_SPLIT(SLORA_F16, false))
                                                     : (y16 ? SLORA_SPLIT(SLORA_BF16, true) : SLORA_SPLIT(SLORA_BF16, false));
 #undef SLORA_SPLIT

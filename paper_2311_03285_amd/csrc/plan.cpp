@@ -313,6 +313,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         plan->gv_items.clear();
         plan->ge_items.clear();
         plan->n_gs_plain = plan->n_ge_plain = plan->max_gv_tok = 0;
+        plan->fours[0] = plan->fours[1] = false;
         // (only if a call of most_slots may take them, see route: they make a plan dearer, 40 groups of eight tokens of rank 64, H = 4096,
         // 22 -> 27 us on the host.  A call that names a slot twice may have more; it takes the small items.)
         const bool crowds = plan->expand_split && plan->vf_items.empty() && most_vec_tokens > kExpandTok;
@@ -359,6 +360,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                 const int32_t fours = g.rank > kOwnRanks && n % kExpandTok <= 2 ? n - n % kExpandTok : n;
                 for (int32_t p = 0, nt; gang_expand && p < n; p += nt) {
                     nt = p < fours ? std::min(g.rank <= kOwnRanks ? kGangOwnTok : kGangExpandTok, fours - p) : n - p;
+                    for (int y16 = 0; y16 < 2; ++y16) plan->fours[y16] = plan->fours[y16] || fours_pay(pool->dtype, y16, g.rank, nt);
                     for (int32_t c = 0; c < H; c += ecols)
                         ge.push_back(Item{off, g.rank, c, std::min(ecols, H - c), pos0 + p, nt, n <= kExpandTok, hand0 + p * g.rank});
                 }

@@ -106,6 +106,16 @@ constexpr bool gang_pays(int64_t small_items, int64_t large_items) { return 2 * 
 constexpr int kOwnRanks = 32;     // rank-split expand of groups of many tokens: up to this many ranks a wavefront forms whole sums,
 constexpr int kGangOwnTok = 16;   // of that many tokens an item;
 constexpr int kGangExpandTok = 8; // tokens per item of more ranks
+// ... items whose tokens go through the 4x4x1 matrix instruction, four at a time: all that share the ranks out over the wavefronts, of the others those that leave
+// a wavefront three or four tokens.  It takes the time of two tokens' fmaf, rows in f16 need a conversion that v_fma_mix does without, and up to 8 ranks half
+// a block is all there is.  us of the call, fmaf / matrix instruction: 8 tokens of rank 16, H = 6144, 4 slots 30.5 / 32.9, 7 of rank 9, H = 5120, 4 slots 22.6 / 25.9, 5
+// of rank 17, H = 3072 27.2 / 30.1; 12 of rank 9 in f16 28.5 / 29.7, of rank 16 25.1 / 25.9, of rank 32, H = 8192 42.6 / 43.4; in bf16 12 of rank 24, H = 6144 35.1 / 32.6, 9 of
+// rank 24, H = 3072 33.5 / 31.9; 30 of rank 24 40.0 / 32.1.  Up to 8 ranks with y in fp32 16 of rank 1, H = 5120 16.6 / 18.3, 9 of rank 4, H = 8192 20.2 / 21.4, in 16 bits
+// 13 of rank 4, H = 6144 19.5 / 17.9, 30 of rank 8, H = 5120 23.9 / 21.8, 12 of rank 4 16.5 / 16.3.
+constexpr bool fours_pay(int dtype, bool y16, int32_t rank, int32_t tok)
+{
+    return rank > kOwnRanks ? tok > kExpandTok : rank > 8 ? tok > (dtype == SLORA_F16 ? 12 : 8) : y16 && tok > 8;
+}
 constexpr int kChainMaxH = 8192;  // widest rows whose sums the one-launch kernel that hands v over forms: a wavefront holds one in registers
 constexpr int kMfmaTok = 32;      // tokens per v tile = per MFMA-expand item (one 32-row MFMA block)
 constexpr int kMsTok = 128;       // most tokens per MFMA-shrink item
@@ -259,6 +269,7 @@ struct slora_plan {
     std::vector<slora::Item> ge_items;           // expand: all groups
     int32_t n_gs_plain = 0, n_ge_plain = 0;      // without a dual plan's groups of many tokens
     int32_t max_gv_tok = 0;                      // most tokens of an item of gv
+    bool fours[2] = {false, false};              // an item of ge is one of fours_pay, for y in fp32 and in 16 bits
     size_t n_gs(const slora::Route &r) const { return r.wide ? (size_t)n_gs_plain : gs_items.size(); }
     size_t n_ge(const slora::Route &r) const { return r.wide ? (size_t)n_ge_plain : ge_items.size(); }
     // ... of the one that hands v over

@@ -258,6 +258,7 @@ static void vec_expand(const slora_plan *plan, const MultiArgs &a, int32_t k, co
         check_pages(plan, it.arena_off, it.rank, a.slot[k]);
         check_tokens(plan, it.pos0, it.ntok);
         REQUIRE(it.ntok <= (!gang ? kExpandTok : it.rank <= kOwnRanks ? kGangOwnTok : kGangExpandTok));
+        for (int y16 = 0; gang && y16 < 2; ++y16) REQUIRE(plan->fours[y16] || !fours_pay(pool->dtype, y16, it.rank, it.ntok)); // the kernel instance has the code for it
         REQUIRE(it.a >= 0 && it.b > 0 && it.a % 8 == 0 && it.b % 8 == 0 && it.a + it.b <= pool->H);
         REQUIRE(it.b <= (plan->expand_split ? 512 : plan->expand_threads * 8));
         const int read_by = readers[std::make_pair(it.arena_off, it.a)];
@@ -666,6 +667,24 @@ static void larger_items_of_no_call()
     }
 }
 
+// Their tokens go through the matrix instruction, four at a time, where that pays: items of more than 32 ranks, those of 9 to 32 ranks that
+// leave a wavefront three tokens (bf16) or four, and with a y in 16 bits those of up to 8 ranks that leave it three.
+static void larger_items_in_fours()
+{
+    const auto with = [](int32_t dtype, int rank, int tok, bool fours, bool fours16) {
+        Bench b(4096, 8, dtype, std::vector<std::pair<int, int>>(tok <= 16 ? 24 : 12, {rank, tok}));
+        REQUIRE(b.apply16(8) == SLORA_OK && g_log.gang_expand && b.plan->fours[0] == fours && b.plan->fours[1] == fours16);
+    };
+    for (int32_t dtype : {SLORA_F16, SLORA_BF16}) {
+        const bool bf16 = dtype == SLORA_BF16;
+        for (int rank : {1, 8}) for (int tok : {5, 8, 9, 16, 33}) with(dtype, rank, tok, false, tok > 8);
+        for (int rank : {9, 32})
+            for (int tok : {5, 8, 9, 12, 13, 16, 24, 33}) with(dtype, rank, tok, tok > (bf16 ? 8 : 12), tok > (bf16 ? 8 : 12));
+        for (int tok : {7, 8, 9, 33}) with(dtype, 33, tok, true, true);
+        for (int tok : {5, 6}) with(dtype, 33, tok, false, false); // four, and one or two of their own
+    }
+}
+
 // LDS of the MFMA expand: adapters of 129 to 256 ranks use its buffers but where v is in scaled pieces
 static void expand_lds()
 {
@@ -732,6 +751,7 @@ static const struct { const char *name; void (*run)(); } kCases[] = {
     {"larger_items_of_no_call", larger_items_of_no_call},
     {"larger_items_pay", larger_items_pay},
     {"larger_items", larger_items},
+    {"larger_items_in_fours", larger_items_in_fours},
     {"failed_apply", failed_apply},
     {"static_route", static_route},
     {"scratch_is_sized_once", scratch_is_sized_once},

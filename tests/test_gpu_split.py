@@ -1,6 +1,6 @@
 """GPU parity of the rank-split vector kernels: whole sums in a wavefront up to 32 ranks, shared ones beyond, blocks of
 8 ranks or (one or two tokens left over) 16, and the larger items that calls of many workgroups take (shrink: 8
-tokens x 16 pages in pieces of 2048 elements; expand: 16 tokens).  Ranks and tokens per group at the edges of all
+tokens x 16 pages in pieces of 2048 elements; expand: 16 tokens of up to 32 ranks, 8 of more, with fmaf or the 4x4x1 matrix instruction).  Ranks and tokens per group at the edges of all
 of these.  Who forms a sum never changes its bits."""
 import numpy as np
 import pytest
@@ -17,10 +17,10 @@ RANKS = (1, 8, 9, 16, 17, 32, 33, 40, 64, 65, 100, 130)
 TOKENS = (17, 5, 33, 6, 19, 18, 7, 9, 10, 4, 2, 1)
 
 
-def crowd(H, dtype):
-    ids = np.concatenate([np.repeat(np.arange(len(RANKS)), TOKENS), [-1, -1]])
+def crowd(H, dtype, ranks=RANKS, tokens=TOKENS):
+    ids = np.concatenate([np.repeat(np.arange(len(ranks)), tokens), [-1, -1]])
     ids = ids[np.random.default_rng(H).permutation(ids.size)].astype(np.int32)
-    return synth.make_workload("crowd", 800 + H, H, dtype, 2 * 8 * sum(RANKS) + 8, 8, RANKS, ids)   # calls of eight slots
+    return synth.make_workload("crowd", 800 + H, H, dtype, 2 * 8 * sum(ranks) + 8, 8, ranks, ids)   # calls of eight slots
 
 
 @pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
@@ -59,6 +59,38 @@ def test_larger_items_are_bit_identical(H, dtype):
                 else:
                     rel, _ = assert_close(one[s].cpu().numpy(), oracle_slot(w, s), f"slot {s}")
                     assert rel <= 2e-6, rel
+
+
+@pytest.mark.parametrize("y16", [False, True])
+@pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
+@pytest.mark.parametrize("tokens", [(5, 6, 7, 8), (8, 9, 12, 13), (12, 16, 17, 30)])   # none, some and most of the items on the matrix instruction
+def test_larger_items_of_few_ranks(dtype, tokens, y16):
+    """Adapters of at most 32 ranks: calls of eight slots (larger items) against calls of one (small ones), and the first slot against the oracle."""
+    ranks = (1, 4, 8, 9, 15, 16, 17, 24, 25, 32)
+    w = crowd(5128, dtype, ranks * 2, (tokens * 5)[:20])
+    with DeviceWorkload(w, real_adapters="all") as dw:
+        plan = dw.plan()
+        info = slora.plan_info(plan)
+        assert info["groups_mfma"] == 0 and info["vec_expand_items"] < 2000 <= 8 * info["vec_expand_items"]
+        x = [dw.x_dev(s) for s in range(8)]
+        new = lambda s: bits_to_device(w.y16_bits(s), dw.device) if y16 else dw.y_dev(s)
+        shrink_expand = slora.lora_expand_y16 if y16 else slora.lora_expand
+        many, one = [new(s) for s in range(8)], [new(s) for s in range(8)]
+        slora.lora_shrink(plan, list(range(8)), [t.data_ptr() for t in x])
+        shrink_expand(plan, list(range(8)), [t.data_ptr() for t in many])
+        for s in range(8):
+            slora.lora_shrink(plan, [s], [x[s].data_ptr()])
+            shrink_expand(plan, [s], [one[s].data_ptr()])
+        torch.cuda.synchronize()
+        for a, b in zip(many, one):
+            assert torch.equal(a, b)
+        if y16:
+            ref, exact = oracle_y16(w, 0)
+            assert_y16_close(many[0].cpu().numpy().view(np.uint16).reshape(w.T, w.H), ref, exact, w.y16_bits(0), dtype, "slot 0")
+        else:
+            rel, _ = assert_close(many[0].cpu().numpy(), oracle_slot(w, 0), "slot 0")
+            assert rel <= 2e-6, rel
+
 
 
 @pytest.mark.parametrize("dtype", [synth.F16, synth.BF16])
