@@ -880,17 +880,16 @@ __device__ __forceinline__ void expand_own(const Item &it, int t0, const int32_t
     }
 }
 
-// An item of at most TOK tokens (1 or 2: exactly); UB: ranks per block; Once: its B rows are streamed; Half: the last block of 16 ranks has at most
-// eight (an instance of its own: a branch between the halves of every block costs single tokens of rank 64 4.5 -> 5.0 us).  One token has an instance of its own: with the
+// An item of at most TOK tokens (1 or 2: exactly); UB: ranks per block; Once: its B rows are streamed.  Half a block of
+// 16 ranks without ranks is multiplied all the same, and left out by a select: with a branch between the halves single tokens of rank 64 took 4.5 -> 5.0 us.  One token has an instance of its own: with the
 // two-token one it requested, multiplied and passed through LDS a second token of zeros.  v is requested beside the page numbers, which
 // the B rows wait for anyway.  us of the expand, pages from memory, before and with the streaming loads: 24 tokens of rank 64, H = 4096 6.8 -> 5.7; two
 // of rank 128, 8 slots 9.4 -> 7.1; 37 of ranks 16-128, H = 3072 9.5 -> 7.6; pages from the caches 5.9 -> 5.1, 7.7 -> 7.1, 7.9 -> 7.1.
-template <int DT, bool Y16, int TOK, int UB, bool Once, bool Half>
+template <int DT, bool Y16, int TOK, int UB, bool Once>
 __device__ __forceinline__ void expand_shared(const Item &it, const int32_t *__restrict__ pb,
                                               const uint16_t *__restrict__ pool, const int32_t *__restrict__ tok_idx,
                                               int H, int v_stride, void *__restrict__ y, const float *__restrict__ vs, float *red)
 {
-    constexpr bool kWhole = UB == 16 && !Half; // both eights have ranks
     const int lane = threadIdx.x & (kWave - 1);
     const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x / kWave);
     const int col = it.a + lane * 8;
@@ -915,7 +914,7 @@ __device__ __forceinline__ void expand_shared(const Item &it, const int32_t *__r
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int j0 = first(i);
-            if (kWhole || i == 0 || j0 < wr) {
+            if (UB == 16 || i == 0 || j0 < wr) {
 #pragma unroll
                 for (int u = 0; u < 8; ++u) { // ranks beyond the last: the last one's row meets v = 0
                     const int64_t page = __builtin_amdgcn_readlane(pwin, min(j0 + u, wr - 1));
@@ -924,10 +923,11 @@ __device__ __forceinline__ void expand_shared(const Item &it, const int32_t *__r
                 }
             }
         }
+        float half[TOK][8];
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int j0 = first(i);
-            if (kWhole || i == 0 || j0 < wr) {
+            if (UB == 16 || i == 0 || j0 < wr) {
 #pragma unroll
                 for (int u = 0; u < 8; ++u) {
                     float f[8];
@@ -944,6 +944,15 @@ __device__ __forceinline__ void expand_shared(const Item &it, const int32_t *__r
                         }
                     }
                 }
+            }
+            if (UB == 16) {
+#pragma unroll
+                for (int t = 0; t < TOK; ++t)
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) {
+                        if (i == 0) half[t][e] = acc[t][e];
+                        else acc[t][e] = j0 < wr ? acc[t][e] : half[t][e];
+                    }
             }
         }
     }
@@ -1231,24 +1240,17 @@ __global__ __launch_bounds__(kSplitWaves *kWave, 3) void expand_vec_split_kernel
     else if (it.rank <= kOwnRanks && it.ntok > 2)
         expand_own<DT, Y16, kOwnRanks>(it, wave, pb, pool, tok_idx, H, v_stride, y, v);
     else if (it.ntok > 2)
-        expand_shared<DT, Y16, kExpandTok, 8, false, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
-    else if ((it.rank - 1) & 8) { // two blocks or more: a wavefront each, while whole sums would keep one of them busy
+        expand_shared<DT, Y16, kExpandTok, 8, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+    else { // two blocks or more: a wavefront each, while whole sums would keep one of them busy
         if (it.ntok == 1 && it.tile)
-            expand_shared<DT, Y16, 1, 16, true, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+            expand_shared<DT, Y16, 1, 16, true>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
         else if (it.ntok == 1)
-            expand_shared<DT, Y16, 1, 16, false, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+            expand_shared<DT, Y16, 1, 16, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
         else if (it.tile)
-            expand_shared<DT, Y16, 2, 16, true, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+            expand_shared<DT, Y16, 2, 16, true>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
         else
-            expand_shared<DT, Y16, 2, 16, false, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
-    } else if (it.ntok == 1 && it.tile)
-        expand_shared<DT, Y16, 1, 16, true, true>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
-    else if (it.ntok == 1)
-        expand_shared<DT, Y16, 1, 16, false, true>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
-    else if (it.tile)
-        expand_shared<DT, Y16, 2, 16, true, true>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
-    else
-        expand_shared<DT, Y16, 2, 16, false, true>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+            expand_shared<DT, Y16, 2, 16, false>(it, pb, pool, tok_idx, H, v_stride, y, v, red);
+    }
 }
 
 // ---------------------------------------------------------------------------------------
