@@ -1397,7 +1397,13 @@ __global__ __launch_bounds__(kShrinkThreads, U > 8 ? 3 : 4) void lora_vec_chain_
                                                                                        MultiArgs args)
 {
     extern __shared__ u32x4 smem[]; // rows of x, or the sums of an expand item's wavefronts
-    const int cs = blockIdx.x;      // slots vary fastest, so workgroups are dispatched in the order of the work lists
+    // Slots vary fastest, so workgroups are dispatched in the order of the work lists.  They go round the eight XCDs one by one: with a power of two of slots
+    // each slot would stay on its own XCDs, and with eight of them the launch was up to 15 % slower than the two kernels instead of 20 % faster.  A slot
+    // moves on every four items (which share rows of x).  us, two kernels / slots that stay / that move: six groups of ranks 16-64 and 1-3 tokens, 8 slots,
+    // H = 5120 16.7 / 17.1 / 12.0, H = 4096 14.6 / 14.3 / 11.4; four groups of four tokens, rank 64 15.3 / 14.8 / 11.8; 21 tokens of rank 4 9.8 / 10.5 / 8.6; every item
+    // the first of these takes 13.4, every two or eight items most calls are the same or a little slower.
+    const unsigned slots = gridDim.x;
+    const int cs = slots & (slots - 1) ? blockIdx.x : (blockIdx.x + blockIdx.y / 4) & (slots - 1);
     const bool shrinks = blockIdx.y < lists.n_shrink;
     const unsigned no = shrinks ? blockIdx.y : blockIdx.y - lists.n_shrink, strip = shrinks ? 0 : no % lists.strips;
     Item it = shrinks ? lists.shrink[no] : lists.expand[no / lists.strips];
