@@ -2849,7 +2849,7 @@ int32_t launch_chain(slora_plan *plan, int32_t n, const MultiArgs &args, void *s
     c.n_shrink = (unsigned)plan->n_vs(route);
     c.strips = (unsigned)plan->chain_strips();
     c.hand = plan->set->hand;
-    c.hand_slot = plan->hand_words;
+    c.hand_slot = plan->chain_words(route);
     c.launch = plan->set->launch;
     c.polls = (int32_t)pool->hand_polls;
     const dim3 grid((unsigned)n, (unsigned)plan->chain_wgs(route));

@@ -209,7 +209,8 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         plan->expand_threads = ecols / 8;
         std::vector<Item> vs_tail, ve_tail, vs_dual, ve_dual;
         plan->vf_items.clear();
-        plan->hand_words = 0;
+        plan->hand_words[0] = plan->hand_words[1] = 0; // of the plain items, and of the dual ones until they are behind those
+        auto word = [](int64_t w) { return (int32_t)std::min<int64_t>(w, INT32_MAX); }; // (plans of so many hand nothing over)
         for (int32_t gi : order) {
             const Group &g = groups[(size_t)gi];
             const int32_t n = (int32_t)g.toks.size();
@@ -291,19 +292,19 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                 const bool both = mfma_group(n); // in the MFMA lists as well
                 std::vector<Item> &vs = fused ? vs_tail : both ? vs_dual : plan->vs_items;
                 std::vector<Item> &ve = fused ? ve_tail : both ? ve_dual : plan->ve_items;
-                const int32_t hand = (int32_t)std::min<int64_t>(plan->hand_words, INT32_MAX);
-                plan->hand_words += (int64_t)n * g.rank;
+                const int64_t hand = fused ? 0 : plan->hand_words[both]; // (a call that hands v over runs the others in launch_fused)
+                if (!fused) plan->hand_words[both] += (int64_t)n * g.rank;
                 if (fused) plan->vf_items.push_back(Item{off, g.rank, 0, H, pos_base, n, 0, 0});
                 for (int32_t p = 0; p < n; p += shrink_tok) {
                     const int32_t nt = std::min(shrink_tok, n - p);
                     plan->max_shrink_tok = std::max(plan->max_shrink_tok, nt);
                     for (int32_t j = 0; j < g.rank; j += shrink_pages)
-                        vs.push_back(Item{off, g.rank, j, std::min(shrink_pages, g.rank - j), pos_base + p, nt, 0, hand + p * g.rank});
+                        vs.push_back(Item{off, g.rank, j, std::min(shrink_pages, g.rank - j), pos_base + p, nt, 0, word(hand + (int64_t)p * g.rank)});
                 }
                 for (int32_t p = 0; p < n; p += kExpandTok) {
                     const int32_t nt = std::min(kExpandTok, n - p);
                     for (int32_t c = 0; c < H; c += ecols)
-                        ve.push_back(Item{off, g.rank, c, std::min(ecols, H - c), pos_base + p, nt, n <= kExpandTok, hand + p * g.rank});
+                        ve.push_back(Item{off, g.rank, c, std::min(ecols, H - c), pos_base + p, nt, n <= kExpandTok, word(hand + (int64_t)p * g.rank)});
                 }
             }
         }
@@ -332,14 +333,11 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         if (gang || gang_expand) {
             std::vector<Item> gs_dual, ge_dual;
             int32_t pos = 0;
-            int64_t hand = 0;
             for (int32_t gi : order) {
                 const Group &g = groups[(size_t)gi];
                 const int32_t n = (int32_t)g.toks.size(), off = (int32_t)g.arena_off, pos0 = pos;
                 pos += n;
                 if ((int64_t)n >= min_tokens) continue;
-                const int32_t hand0 = (int32_t)std::min<int64_t>(hand, INT32_MAX);
-                hand += (int64_t)n * g.rank;
                 std::vector<Item> &gs = mfma_group(n) ? gs_dual : plan->gs_items;
                 std::vector<Item> &ge = mfma_group(n) ? ge_dual : plan->ge_items;
                 if (!gang) {
@@ -347,13 +345,13 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                     plan->max_gv_tok = std::max(plan->max_gv_tok, std::min(n, shrink_tok));
                     for (int32_t p = 0; p < n; p += shrink_tok)
                         for (int32_t j = 0; j < g.rank; j += shrink_pages)
-                            plan->gv_items.push_back(Item{off, g.rank, j, std::min(shrink_pages, g.rank - j), pos0 + p, std::min(shrink_tok, n - p), 0, hand0 + p * g.rank});
+                            plan->gv_items.push_back(Item{off, g.rank, j, std::min(shrink_pages, g.rank - j), pos0 + p, std::min(shrink_tok, n - p), 0, 0});
                 } else {
                     const int32_t runs = (g.rank + kGangPages - 1) / kGangPages; // of about equal length
                     for (int32_t p = 0; p < n; p += kGangTok)
                         for (int32_t k = 0; k < runs; ++k) {
                             const int32_t j0 = (int32_t)((int64_t)g.rank * k / runs), j1 = (int32_t)((int64_t)g.rank * (k + 1) / runs);
-                            gs.push_back(Item{off, g.rank, j0, j1 - j0, pos0 + p, std::min(kGangTok, n - p), 0, hand0 + p * g.rank});
+                            gs.push_back(Item{off, g.rank, j0, j1 - j0, pos0 + p, std::min(kGangTok, n - p), 0, 0});
                         }
                 }
                 // (one or two tokens left over from the fours have blocks of 16 ranks: an item of their own, unless a wavefront forms whole sums)
@@ -362,7 +360,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                     nt = p < fours ? std::min(g.rank <= kOwnRanks ? kGangOwnTok : kGangExpandTok, fours - p) : n - p;
                     for (int y16 = 0; y16 < 2; ++y16) plan->fours[y16] = plan->fours[y16] || fours_pay(pool->dtype, y16, g.rank, nt);
                     for (int32_t c = 0; c < H; c += ecols)
-                        ge.push_back(Item{off, g.rank, c, std::min(ecols, H - c), pos0 + p, nt, n <= kExpandTok, hand0 + p * g.rank});
+                        ge.push_back(Item{off, g.rank, c, std::min(ecols, H - c), pos0 + p, nt, n <= kExpandTok, 0});
                 }
             }
             plan->n_gs_plain = (int32_t)plan->gs_items.size();
@@ -372,6 +370,9 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         }
         plan->n_vs_plain = (int32_t)plan->vs_items.size();
         plan->n_ve_plain = (int32_t)plan->ve_items.size();
+        for (std::vector<Item> *items : {&vs_dual, &ve_dual}) // their words follow those of the plain items
+            for (Item &i : *items) i.run = word(i.run + plan->hand_words[0]);
+        plan->hand_words[1] += plan->hand_words[0];
         plan->vs_items.insert(plan->vs_items.end(), vs_dual.begin(), vs_dual.end());
         plan->ve_items.insert(plan->ve_items.end(), ve_dual.begin(), ve_dual.end());
         plan->n_vs_head = (int32_t)plan->vs_items.size();
@@ -531,18 +532,21 @@ Route slora_plan::route(int32_t n, bool apply, bool y16) const
 // rank 64, 100 in two slots, 4000: 24.2 / 22.7, and 20 of rank 128, H = 1024, 680: 10.4 / 7.9.
 bool slora_plan::chain_pays(int32_t n, const Route &r) const
 {
-    if (!expand_split || pool->fuse_decode == 0 || n_vs(r) == 0 || r.gang || r.gang_expand || pool->H > kChainMaxH || chain_wgs(r) > 65535) return false;
+    if (!expand_split || pool->fuse_decode == 0 || n_vs(r) == 0 || r.gang || r.gang_expand || pool->H > kChainMaxH || chain_wgs(r) > 65535 || chain_words(r) * n > INT32_MAX) return false;
     const int64_t rows = (int64_t)max_shrink_tok * pool->H * 2;
     if (n_vs(r) > 6 * n_ve(r) && (int64_t)n_vs(r) * n > 640) return false;
     return chain_wgs(r) * n <= (rows <= 40960 ? 4096 : 2048);
 }
 
-size_t slora_plan::chain_words(int32_t n) const
+size_t slora_plan::most_chain_words(int32_t n) const
 {
+    int64_t most = 0;
     for (int32_t m = 1; m <= n; ++m)
-        for (int y16 = 0; y16 <= (dual ? 1 : 0); ++y16)
-            if (chain_pays(m, route(m, true, y16 != 0)) && hand_words * n <= INT32_MAX) return (size_t)(hand_words * n);
-    return 0;
+        for (int y16 = 0; y16 <= (dual ? 1 : 0); ++y16) {
+            const Route r = route(m, true, y16 != 0);
+            if (chain_pays(m, r)) most = std::max(most, chain_words(r) * m);
+        }
+    return (size_t)most;
 }
 
 int64_t slora_plan::v_most_floats(int32_t n, int32_t dtype) const
@@ -629,21 +633,19 @@ int32_t do_shrink(slora_plan *plan, int32_t n, const int32_t *slots, const void 
     float *v = scratch;
     int32_t rc = SLORA_OK;
     if (!v) {
-        rc = plan->pool->grow_v(plan->set, (size_t)plan->v_most_floats(n, plan->pool->dtype));
+        // (room for the words is made whatever the call, so that a plan's buffers are sized once)
+        if (plan->most_slots < n) {
+            plan->most_words = plan->most_chain_words(n);
+            plan->most_slots = n;
+        }
+        rc = plan->pool->grow_v(plan->set, (size_t)plan->v_most_floats(n, plan->pool->dtype), plan->most_words, stream);
         v = plan->set->v;
     }
     if (rc == SLORA_OK) rc = plan->enter(stream);
-    if (rc == SLORA_OK && !scratch) {
-        // (room is made whatever the call, so that a plan's buffers are sized once)
-        if (plan->most_slots < n) {
-            plan->most_words = plan->chain_words(n);
-            plan->most_slots = n;
-        }
-        const bool room = plan->most_words > 0 && plan->pool->hand_room(plan->set, plan->most_words, stream);
-        if (room && y && !overlaps && plan->chain_pays(n, route) && !stream_captures(stream) && plan->pool->next_launch(plan->set, stream)) {
-            route.chain = true;
-            route.small = false;
-        }
+    if (rc == SLORA_OK && !scratch && y && !overlaps && plan->chain_pays(n, route) && (size_t)(plan->chain_words(route) * n) <= plan->set->hand_cap &&
+        !stream_captures(stream) && plan->pool->next_launch(plan->set, stream)) {
+        route.chain = true;
+        route.small = false;
     }
     if (rc != SLORA_OK) return rc;
     plan->fill_args(a, n, v, route);

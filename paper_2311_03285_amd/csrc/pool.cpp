@@ -121,6 +121,7 @@ int32_t slora_pool::take_set(Buffers **out, size_t h_bytes, size_t d_bytes)
         for (void *p : set->outgrown) (void)hipFree(p);
         set->outgrown.clear();
     }
+    set->hand_refused = SIZE_MAX;
     if (e != hipSuccess) {
         idle_sets.push_back(set); // still consistent (event complete, buffers null or valid)
         return hip_fail(e, "allocating a buffer set");
@@ -141,7 +142,6 @@ void slora_pool::give_set(Buffers *set, void *last_stream)
         if (set->h) (void)hipHostFree(set->h);
         if (set->d) (void)hipFree(set->d);
         if (set->v) (void)hipFree(set->v);
-        if (set->hand) (void)hipFree(set->hand);
         for (void *p : set->outgrown) (void)hipFree(p);
         (void)hipEventDestroy((hipEvent_t)set->order);
         delete set;
@@ -157,60 +157,45 @@ bool slora::stream_captures(void *stream)
     return true;
 }
 
-int32_t slora_pool::grow_v(Buffers *set, size_t floats)
+int32_t slora_pool::grow_v(Buffers *set, size_t floats, size_t words, void *stream)
 {
-    if (floats <= set->v_cap) return SLORA_OK;
-    const size_t cap = round_up_pow2(floats, 1 << 14);
-    float *fresh = nullptr;
-    hipError_t e = hipMalloc((void **)&fresh, cap * sizeof(float));
-    if (e != hipSuccess) return hip_fail(e, "hipMalloc(v scratch)");
-    device_allocs++;
-    if (set->v) {
-        // launches in flight, and applies captured in a HIP graph, still name the old scratch: it
-        // is released when the set is next handed out (after its event) or with the pool
-        try {
-            set->outgrown.push_back(set->v);
-        } catch (const std::bad_alloc &) {
-            (void)hipFree(fresh);
-            return fail(SLORA_ENOMEM, "out of host memory");
-        }
-    }
-    set->v = fresh;
-    set->v_cap = cap;
-    return SLORA_OK;
-}
-
-bool slora_pool::hand_room(Buffers *set, size_t words, void *stream)
-{
-    if (words <= set->hand_cap) return true;
-    if (stream_captures(stream)) return false; // a captured clear would not have run for a call that is not replayed
-    const size_t cap = round_up_pow2(words, 1 << 12);
-    uint64_t *fresh = nullptr;
+    bool more_words = words > set->hand_cap && words < set->hand_refused;
+    if (floats <= set->v_cap && (!more_words || stream_captures(stream))) return SLORA_OK;
+    const size_t cap = std::max(set->v_cap, round_up_pow2(floats, 1 << 14));
+    size_t hand_cap = more_words ? round_up_pow2(words, 1 << 12) : set->hand_cap;
     try {
         set->outgrown.reserve(set->outgrown.size() + 1);
     } catch (const std::bad_alloc &) {
-        return false;
+        return fail(SLORA_ENOMEM, "out of host memory");
     }
-    if (hipMalloc((void **)&fresh, cap * sizeof(uint64_t)) != hipSuccess) {
+    float *fresh = nullptr;
+    hipError_t e = hipMalloc((void **)&fresh, cap * sizeof(float) + hand_cap * sizeof(uint64_t));
+    if (e != hipSuccess && hand_cap > 0) { // a call without the words takes the two kernels
         (void)hipGetLastError();
-        return false;
+        if (more_words) set->hand_refused = words; // (asked for again when the set is next handed out)
+        if (floats <= set->v_cap) return SLORA_OK;
+        hand_cap = 0;
+        e = hipMalloc((void **)&fresh, cap * sizeof(float));
     }
+    if (e != hipSuccess) return hip_fail(e, "hipMalloc(v scratch)");
     device_allocs++;
-    if (launch_clear(fresh, cap * sizeof(uint64_t), stream) != SLORA_OK) {
-        (void)hipFree(fresh);
-        return false;
-    }
-    if (set->hand) set->outgrown.push_back(set->hand);
-    set->hand = fresh;
-    set->hand_cap = cap;
-    set->launch = 0;
-    return true;
+    // launches in flight, and applies captured in a HIP graph, still name the old scratch: it
+    // is released when the set is next handed out (after its event) or with the pool
+    if (set->v) set->outgrown.push_back(set->v);
+    set->v = fresh;
+    set->v_cap = cap;
+    set->hand = reinterpret_cast<uint64_t *>(fresh + cap);
+    set->hand_cap = hand_cap;
+    set->hand_clear = false;
+    return SLORA_OK;
 }
 
 bool slora_pool::next_launch(Buffers *set, void *stream)
 {
-    if (set->launch == UINT32_MAX) { // numbers start again: none of the last turn may be left
+    // words that no launch has written yet; or the numbers start again, and none of the last turn may be left
+    if (!set->hand_clear || set->launch == UINT32_MAX) {
         if (launch_clear(set->hand, set->hand_cap * sizeof(uint64_t), stream) != SLORA_OK) return false;
+        set->hand_clear = true;
         set->launch = 0;
     }
     set->launch++;
@@ -223,7 +208,6 @@ void slora_pool::free_sets()
         if (set->h) (void)hipHostFree(set->h);
         if (set->d) (void)hipFree(set->d);
         if (set->v) (void)hipFree(set->v);
-        if (set->hand) (void)hipFree(set->hand);
         for (void *p : set->outgrown) (void)hipFree(p);
         if (set->order) (void)hipEventDestroy((hipEvent_t)set->order);
         delete set;

@@ -151,10 +151,12 @@ struct Buffers {
     size_t h_cap = 0;
     void *d = nullptr;     // device copy of h
     size_t d_cap = 0;
-    float *v = nullptr;    // device scratch for v = x*A
-    size_t v_cap = 0;      // floats
-    uint64_t *hand = nullptr; // words {value, number of a launch} in which a launch hands v over; none has a number that was not given out yet
+    float *v = nullptr;    // device scratch for v = x*A, and behind its v_cap floats
+    size_t v_cap = 0;
+    uint64_t *hand = nullptr; // words {value, number of a launch} in which a launch hands v over; none has a number that was not given out yet,
     size_t hand_cap = 0;
+    bool hand_clear = false;  // once they have been cleared, which the first such launch does
+    size_t hand_refused = SIZE_MAX; // from this many on there was no memory for them
     uint32_t launch = 0;   // number of the latest such launch
     std::vector<void *> outgrown; // device buffers replaced while work that names them may be in flight
     void *order = nullptr; // hipEvent_t: last use of the set, or a hand-over point between streams
@@ -222,9 +224,9 @@ struct slora_pool {
 
     int32_t take_set(slora::Buffers **out, size_t h_bytes, size_t d_bytes); // an idle set whose last use has completed, or a new one
     void give_set(slora::Buffers *set, void *last_stream);                  // record `order` on last_stream, park the set
-    int32_t grow_v(slora::Buffers *set, size_t floats);
-    bool hand_room(slora::Buffers *set, size_t words, void *stream); // room for the words of a launch on `stream`; false: there is none
-    bool next_launch(slora::Buffers *set, void *stream);             // ... and the number of the next one
+    // room for v and, if there is memory for them, for the words of launches on `stream` that hand it over
+    int32_t grow_v(slora::Buffers *set, size_t floats, size_t words, void *stream);
+    bool next_launch(slora::Buffers *set, void *stream); // the number of the next such launch
     void free_sets();
 
     int32_t sync_device();                            // push dirty arena range
@@ -258,8 +260,8 @@ struct slora_plan {
     int64_t reread = 0, reread_min = 0; // bytes of pages the vector kernels would read again, per slot; what it takes per call
     int32_t n_vs_plain = 0, n_ve_plain = 0;
     int32_t most_slots = 0;   // most slots of a call so far, and
-    size_t most_words = 0;    // the words that room was made for
-    int64_t hand_words = 0; // words per slot in which v of the vector groups is handed over
+    size_t most_words = 0;    // the words that they may take
+    int64_t hand_words[2] = {0, 0}; // words per slot in which a call hands v of its vector groups over: on a wide route (without those of the MFMA kernels), on another
     bool mfma_on(const slora::Route &r) const { return !dual || r.wide; }
     // items of the two vector lists that a call runs beside the other kernels
     size_t n_vs(const slora::Route &r) const { return r.wide ? (size_t)n_vs_plain : r.fused ? (size_t)n_vs_head : vs_items.size(); }
@@ -276,7 +278,8 @@ struct slora_plan {
     int64_t chain_strips() const { return (expand_threads * 8 + 511) / 512; }
     int64_t chain_wgs(const slora::Route &r) const { return (int64_t)n_vs(r) + (int64_t)n_ve(r) * chain_strips(); }
     bool chain_pays(int32_t n, const slora::Route &r) const; // ... which an apply of n slots may take
-    size_t chain_words(int32_t n) const; // its words in a call of up to n slots, if any may take it
+    int64_t chain_words(const slora::Route &r) const { return hand_words[r.wide ? 0 : 1]; } // its words per slot
+    size_t most_chain_words(int32_t n) const; // ... in a call of up to n slots, if any may take it
     // workgroups of the vector kernels, per slot
     size_t shrink_wgs(const slora::Route &r) const { return r.gang ? n_gs(r) + gv_items.size() : n_vs(r); }
     size_t expand_wgs(const slora::Route &r) const { return r.gang_expand ? n_ge(r) : n_ve(r); }

@@ -35,6 +35,9 @@
 // ---------------------------------------------------------------------------------------------
 static long g_device_mallocs = 0;  // hipMalloc calls so far
 static bool g_fail_malloc = false; // hipMalloc is out of memory
+static size_t g_free_bytes = SIZE_MAX; // ... for a request of more than this
+static long g_clears = 0;          // launches that clear memory so far
+static bool g_captures = false;    // a HIP graph captures every stream but the default one
 
 extern "C" {
 hipError_t hipGetDevice(int *d) { *d = 0; return hipSuccess; }
@@ -45,7 +48,7 @@ const char *hipGetErrorString(hipError_t) { return "stand-in"; }
 hipError_t hipMalloc(void **p, size_t n)
 {
     g_device_mallocs++;
-    *p = g_fail_malloc ? nullptr : std::malloc(n ? n : 1);
+    *p = g_fail_malloc || n > g_free_bytes ? nullptr : std::malloc(n ? n : 1);
     return *p ? hipSuccess : hipErrorOutOfMemory;
 }
 hipError_t hipFree(void *p) { std::free(p); return hipSuccess; }
@@ -60,7 +63,7 @@ hipError_t hipEventSynchronize(hipEvent_t) { return hipSuccess; }
 hipError_t hipStreamCreateWithFlags(hipStream_t *s, unsigned) { *s = (hipStream_t)std::malloc(1); return hipSuccess; }
 hipError_t hipStreamDestroy(hipStream_t s) { std::free((void *)s); return hipSuccess; }
 hipError_t hipStreamWaitEvent(hipStream_t, hipEvent_t, unsigned) { return hipSuccess; }
-hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) { *s = hipStreamCaptureStatusNone; return hipSuccess; }
+hipError_t hipStreamIsCapturing(hipStream_t, hipStreamCaptureStatus *s) { *s = g_captures ? hipStreamCaptureStatusActive : hipStreamCaptureStatusNone; return hipSuccess; }
 hipError_t hipPointerGetAttributes(hipPointerAttribute_t *a, const void *p)
 {
     std::memset(a, 0, sizeof *a);
@@ -231,7 +234,7 @@ static void vec_shrink(const slora_plan *plan, const MultiArgs &a, int32_t k, co
                 v[(int64_t)(it.pos0 + t) * plan->v_stride + j] = 0.f;
                 if (words) { // every word is left once
                     const int64_t w = it.run + (int64_t)t * it.rank + j;
-                    REQUIRE(w >= 0 && w < plan->hand_words && !(*words)[(size_t)w]++);
+                    REQUIRE(w >= 0 && w < plan->chain_words(route) && !(*words)[(size_t)w]++);
                 }
             }
     }
@@ -269,7 +272,7 @@ static void vec_expand(const slora_plan *plan, const MultiArgs &a, int32_t k, co
             for (int32_t j = 0; j < it.rank; j += words ? 1 : 16) {
                 if (words) { // a word that is waited for is left
                     const int64_t w = it.run + (int64_t)t * it.rank + j;
-                    REQUIRE(w >= 0 && w < plan->hand_words && (*words)[(size_t)w] == 1);
+                    REQUIRE(w >= 0 && w < plan->chain_words(route) && (*words)[(size_t)w] == 1);
                 } else {
                     g_sink = a.v[k][(int64_t)(it.pos0 + t) * plan->v_stride + j];
                 }
@@ -281,6 +284,7 @@ static void vec_expand(const slora_plan *plan, const MultiArgs &a, int32_t k, co
 int32_t launch_clear(void *dst, size_t bytes, void *)
 {
     REQUIRE(bytes > 0 && bytes % 16 == 0);
+    g_clears++;
     std::memset(dst, 0, bytes);
     return SLORA_OK;
 }
@@ -291,17 +295,20 @@ int32_t launch_chain(slora_plan *plan, int32_t n, const MultiArgs &a, void *, bo
     REQUIRE(a.n == n && route.chain && !route.small && !route.gang && !route.gang_expand && plan->expand_split);
     REQUIRE(plan->pool->H <= kChainMaxH && plan->pool->fuse_decode != 0 && plan->chain_wgs(route) <= 65535);
     REQUIRE(plan->chain_strips() == 1);
-    REQUIRE(plan->set->launch > 0 && (size_t)(plan->hand_words * n) <= plan->set->hand_cap);
+    const int64_t words_per_slot = plan->chain_words(route);
+    REQUIRE(plan->set->launch > 0 && (size_t)(words_per_slot * n) <= plan->set->hand_cap);
+    REQUIRE(plan->set->hand == (uint64_t *)(plan->set->v + plan->set->v_cap)); // behind every v
     for (size_t w = 0; w < plan->set->hand_cap; ++w) REQUIRE((uint32_t)(plan->set->hand[w] >> 32) != plan->set->launch); // a number of its own
     for (int32_t k = 0; k < n; ++k) {
         REQUIRE(a.x[k] && a.y[k] && a.v[k]);
         g_seen = -1;
-        std::vector<uint8_t> words((size_t)plan->hand_words);
+        std::vector<uint8_t> words((size_t)words_per_slot);
         vec_shrink(plan, a, k, route, &words);
         g_seen = -1;
         vec_expand(plan, a, k, route, &words);
         for (size_t w = 0; w < words.size(); ++w)
-            if (words[w]) plan->set->hand[(size_t)(k * plan->hand_words) + w] = (uint64_t)plan->set->launch << 32;
+            plan->set->hand[(size_t)(k * words_per_slot) + w] = (uint64_t)plan->set->launch << 32;
+        for (uint8_t w : words) REQUIRE(w == 1); // no room for more
     }
     g_log.chain = true;
     g_log.small = plan->route(n, true, y16).small; // a batch of that kind
@@ -734,8 +741,9 @@ static void hand_over()
     const void *const x1 = b.xs[1];
     b.xs[1] = b.ys[0]; // slot 0 writes what slot 1 reads
     REQUIRE(b.apply16(2) == SLORA_OK && !g_log.chain);
-    b.plan->set->launch = UINT32_MAX - 1; // numbers run out, and start again with none of theirs in the words
     b.xs[1] = x1;
+    REQUIRE(b.apply(2) == SLORA_OK && g_log.chain && b.plan->set->launch == 1);
+    b.plan->set->launch = UINT32_MAX - 1; // numbers run out, and start again with none of theirs in the words
     for (int i = 0; i < 3; ++i) REQUIRE(b.apply(2) == SLORA_OK && g_log.chain);
     REQUIRE(b.plan->set->launch == 2);
     std::vector<std::pair<int, int>> mixed(20, {32, 64}); // 40 tiles
@@ -744,8 +752,50 @@ static void hand_over()
     REQUIRE(m.apply(3) == SLORA_OK && g_log.chain && g_log.mfma_expand && g_log.vec_expand > 0);
 }
 
+// Room for the words lies behind v, in one allocation; the first launch that uses it clears it, so calls that never hand v over launch
+// nothing for it.  Without memory for it calls take the two kernels, and ask once per hand-out of the buffers.
+static void words_of_the_calls_that_use_them()
+{
+    const std::vector<std::pair<int, int>> prompt{{64, 256}}, two{{64, 400}, {64, 200}}, crowd(40, {32, 8});
+    for (auto *groups : {&prompt, &two, &crowd}) {
+        Bench b(4096, 4, SLORA_BF16, *groups);
+        const long mallocs = g_device_mallocs, clears = g_clears;
+        REQUIRE(b.apply(4) == SLORA_OK && !g_log.chain && (g_log.mfma_expand || g_log.gang_expand));
+        REQUIRE(g_device_mallocs == mallocs + 1 && g_clears == clears);
+    }
+    const std::vector<std::pair<int, int>> some(20, {16, 2});
+    {
+        Bench b(1024, 4, SLORA_F16, some);
+        const long mallocs = g_device_mallocs, clears = g_clears;
+        for (int i = 0; i < 3; ++i)
+            for (int32_t n : {4, 1, 3}) REQUIRE(b.apply(n) == SLORA_OK && g_log.chain && b.shrink(n) == SLORA_OK && b.apply16(n) == SLORA_OK && g_log.chain);
+        REQUIRE(g_device_mallocs == mallocs + 1 && g_clears == clears + 1);
+        REQUIRE(b.plan->chain_words(Route{}) == 20 * 2 * 16);
+    }
+    int place = 0;
+    void *const stream = &place;
+    Bench few(1024, 1, SLORA_F16, std::vector<std::pair<int, int>>(60, {40, 4})); // 15360 floats and 9600 words: 64 and 128 KiB
+    g_free_bytes = (size_t)1 << 16;
+    long mallocs = g_device_mallocs;
+    REQUIRE(few.apply(1) == SLORA_OK && !g_log.chain && g_log.vec_expand > 0 && g_device_mallocs == mallocs + 2);
+    for (int i = 0; i < 3; ++i) REQUIRE(few.apply(1) == SLORA_OK && !g_log.chain && g_device_mallocs == mallocs + 2); // not asked for again
+    g_free_bytes = SIZE_MAX;
+    REQUIRE(few.apply(1) == SLORA_OK && !g_log.chain);
+    REQUIRE(slora_plan_destroy(few.plan) == SLORA_OK && slora_batch_plan(few.pool, &few.plan, few.ids.data(), few.T, nullptr, 0) == SLORA_OK);
+    mallocs = g_device_mallocs;
+    g_captures = true; // nothing is allocated, and nothing cleared, under capture
+    REQUIRE(slora_lora_apply_multi(few.plan, 1, few.slots, few.xs.data(), few.ys.data(), stream) == SLORA_OK && g_device_mallocs == mallocs);
+    g_captures = false;
+    REQUIRE(few.apply(1) == SLORA_OK && g_log.chain && g_device_mallocs == mallocs + 1);
+    g_captures = true;
+    g_log = {};
+    REQUIRE(slora_lora_apply_multi(few.plan, 1, few.slots, few.xs.data(), few.ys.data(), stream) == SLORA_OK && !g_log.chain && g_log.vec_expand > 0);
+    g_captures = false;
+}
+
 static const struct { const char *name; void (*run)(); } kCases[] = {
     {"hand_over", hand_over},
+    {"words_of_the_calls_that_use_them", words_of_the_calls_that_use_them},
     {"shrink_pages_of_the_caller", shrink_pages_of_the_caller},
     {"expand_lds", expand_lds},
     {"larger_items_of_no_call", larger_items_of_no_call},
