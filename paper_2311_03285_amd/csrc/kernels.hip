@@ -1276,7 +1276,7 @@ __global__ __launch_bounds__(kSplitWaves *kWave, 3) void expand_vec_split_kernel
 template <int DT>
 struct HandOver {
     static constexpr bool kMayFail = true;
-    uint64_t *hand; // the slot's words; an item's begin at its `run`, token after token, rank after rank
+    uint64_t *hand; // the item's words, token after token, rank after rank
     uint32_t launch;
     int polls;
     const int32_t *pa; // the item's A list
@@ -1285,13 +1285,13 @@ struct HandOver {
     int H;
     __device__ __forceinline__ void leave(const Item &it, int t, int j, float s) const
     {
-        __hip_atomic_store(hand + it.run + (int64_t)t * it.rank + j, (uint64_t)launch << 32 | __float_as_uint(s), __ATOMIC_RELAXED,
+        __hip_atomic_store(hand + (int64_t)t * it.rank + j, (uint64_t)launch << 32 | __float_as_uint(s), __ATOMIC_RELAXED,
                            __HIP_MEMORY_SCOPE_AGENT);
     }
     // the value of a token and a rank of each lane's own, where `mine` and there is such a token; false: not all are there
     __device__ __forceinline__ bool get(const Item &it, int t, int j, bool mine, float &out) const
     {
-        const uint64_t *at = hand + it.run + (int64_t)t * it.rank + j;
+        const uint64_t *at = hand + (int64_t)t * it.rank + j;
         const bool asks = mine && t < it.ntok;
         for (int k = 0;; ++k) {
             uint64_t word = (uint64_t)launch << 32;
@@ -1405,11 +1405,10 @@ __global__ __launch_bounds__(kShrinkThreads, U > 8 ? 3 : 4) void lora_vec_chain_
     const unsigned slots = gridDim.x;
     const int cs = slots & (slots - 1) ? blockIdx.x : (blockIdx.x + blockIdx.y / 4) & (slots - 1);
     const bool shrinks = blockIdx.y < lists.n_shrink;
-    const unsigned no = shrinks ? blockIdx.y : blockIdx.y - lists.n_shrink, strip = shrinks ? 0 : no % lists.strips;
-    Item it = shrinks ? lists.shrink[no] : lists.expand[no / lists.strips];
+    const Item it = shrinks ? lists.shrink[blockIdx.y] : lists.expand[blockIdx.y - lists.n_shrink];
     const uint16_t *x = static_cast<const uint16_t *>(args.x[cs]);
     const int32_t *pa = arena + it.arena_off + (int64_t)args.slot[cs] * 2 * it.rank;
-    const HandOver<DT> hand{lists.hand + cs * lists.hand_slot, lists.launch, lists.polls, pa, pool, x, tok_idx, H};
+    const HandOver<DT> hand{lists.hand + cs * lists.hand_slot + it.run, lists.launch, lists.polls, pa, pool, x, tok_idx, H};
     if (shrinks) {
         float *v = args.v[cs];
         shrink_page_item<DT, U>(it, pa + it.a, pool, x, tok_idx, H, smem, [&](int t, int j, float s) {
@@ -1417,9 +1416,6 @@ __global__ __launch_bounds__(kShrinkThreads, U > 8 ? 3 : 4) void lora_vec_chain_
             v[(int64_t)(it.pos0 + t) * v_stride + it.a + j] = s; // for a later expand
         });
     } else {
-        it.a += strip * 512; // the item's columns in strips of 512
-        it.b = min(it.b - (int)strip * 512, 512);
-        if (it.b <= 0) return;
         const int32_t *pb = pa + it.rank;
         f32x4 *red = reinterpret_cast<f32x4 *>(smem);
         void *y = args.y[cs];
@@ -2847,7 +2843,6 @@ int32_t launch_chain(slora_plan *plan, int32_t n, const MultiArgs &args, void *s
     c.shrink = plan->d_vs;
     c.expand = plan->d_ve;
     c.n_shrink = (unsigned)plan->n_vs(route);
-    c.strips = (unsigned)plan->chain_strips();
     c.hand = plan->set->hand;
     c.hand_slot = plan->chain_words(route);
     c.launch = plan->set->launch;

@@ -72,8 +72,7 @@ struct MultiArgs {
 // The lists of a launch in which the shrink hands v over to the expand
 struct ChainLists {
     const Item *shrink, *expand;
-    uint32_t n_shrink; // shrink items; then every expand item in `strips` strips of at most 512 columns
-    uint32_t strips;
+    uint32_t n_shrink; // shrink items; then the expand items
     uint64_t *hand;    // words {value, number of the launch} of the first slot,
     int64_t hand_slot; // those of a slot
     uint32_t launch;
@@ -275,8 +274,7 @@ struct slora_plan {
     size_t n_gs(const slora::Route &r) const { return r.wide ? (size_t)n_gs_plain : gs_items.size(); }
     size_t n_ge(const slora::Route &r) const { return r.wide ? (size_t)n_ge_plain : ge_items.size(); }
     // ... of the one that hands v over
-    int64_t chain_strips() const { return (expand_threads * 8 + 511) / 512; }
-    int64_t chain_wgs(const slora::Route &r) const { return (int64_t)n_vs(r) + (int64_t)n_ve(r) * chain_strips(); }
+    int64_t chain_wgs(const slora::Route &r) const { return (int64_t)(n_vs(r) + n_ve(r)); }
     bool chain_pays(int32_t n, const slora::Route &r) const; // ... which an apply of n slots may take
     int64_t chain_words(const slora::Route &r) const { return hand_words[r.wide ? 0 : 1]; } // its words per slot
     size_t most_chain_words(int32_t n) const; // ... in a call of up to n slots, if any may take it

@@ -294,7 +294,6 @@ int32_t launch_chain(slora_plan *plan, int32_t n, const MultiArgs &a, void *, bo
 {
     REQUIRE(a.n == n && route.chain && !route.small && !route.gang && !route.gang_expand && plan->expand_split);
     REQUIRE(plan->pool->H <= kChainMaxH && plan->pool->fuse_decode != 0 && plan->chain_wgs(route) <= 65535);
-    REQUIRE(plan->chain_strips() == 1);
     const int64_t words_per_slot = plan->chain_words(route);
     REQUIRE(plan->set->launch > 0 && (size_t)(words_per_slot * n) <= plan->set->hand_cap);
     REQUIRE(plan->set->hand == (uint64_t *)(plan->set->v + plan->set->v_cap)); // behind every v
