@@ -2844,11 +2844,11 @@ int32_t launch_chain(slora_plan *plan, int32_t n, const MultiArgs &args, void *s
     c.expand = plan->d_ve;
     c.n_shrink = (unsigned)plan->n_vs(route);
     c.hand = plan->set->hand;
-    c.hand_slot = plan->chain_words(route);
+    c.hand_slot = plan->chain_of(route).words;
     c.launch = plan->set->launch;
     c.polls = (int32_t)pool->hand_polls;
     const dim3 grid((unsigned)n, (unsigned)plan->chain_wgs(route));
-    const size_t lds = std::max(kSplitLds, (size_t)plan->max_shrink_tok * chain_chunks(H) * kWave * 16);
+    const size_t lds = std::max(kSplitLds, (size_t)plan->chain_of(route).tok * chain_chunks(H) * kWave * 16);
 #define SLORA_CHAIN(DT, Y, UU) \
     case UU: hipLaunchKernelGGL((lora_vec_chain_kernel<DT, Y, UU>), grid, dim3(kShrinkThreads), lds, st, c, pool->d_arena, base, plan->d_tok_idx, H, plan->v_stride, args); break
 #define SLORA_CHAIN_U(DT, Y)                                                                                             \

@@ -209,7 +209,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         plan->expand_threads = ecols / 8;
         std::vector<Item> vs_tail, ve_tail, vs_dual, ve_dual;
         plan->vf_items.clear();
-        plan->hand_words[0] = plan->hand_words[1] = 0; // of the plain items, and of the dual ones until they are behind those
+        plan->chain[0] = plan->chain[1] = {}; // of the plain items, and of the dual ones until they are behind those
         auto word = [](int64_t w) { return (int32_t)std::min<int64_t>(w, INT32_MAX); }; // (plans of so many hand nothing over)
         for (int32_t gi : order) {
             const Group &g = groups[(size_t)gi];
@@ -292,8 +292,11 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                 const bool both = mfma_group(n); // in the MFMA lists as well
                 std::vector<Item> &vs = fused ? vs_tail : both ? vs_dual : plan->vs_items;
                 std::vector<Item> &ve = fused ? ve_tail : both ? ve_dual : plan->ve_items;
-                const int64_t hand = fused ? 0 : plan->hand_words[both]; // (a call that hands v over runs the others in launch_fused)
-                if (!fused) plan->hand_words[both] += (int64_t)n * g.rank;
+                slora_plan::Chain none, &chain = fused ? none : plan->chain[both]; // (a call that hands v over runs the others in launch_fused)
+                const int64_t hand = chain.words;
+                chain.words += (int64_t)n * g.rank;
+                chain.work += (int64_t)n * g.rank * ((H + ecols - 1) / ecols);
+                chain.tok = std::max(chain.tok, std::min(n, shrink_tok));
                 if (fused) plan->vf_items.push_back(Item{off, g.rank, 0, H, pos_base, n, 0, 0});
                 for (int32_t p = 0; p < n; p += shrink_tok) {
                     const int32_t nt = std::min(shrink_tok, n - p);
@@ -371,8 +374,10 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         plan->n_vs_plain = (int32_t)plan->vs_items.size();
         plan->n_ve_plain = (int32_t)plan->ve_items.size();
         for (std::vector<Item> *items : {&vs_dual, &ve_dual}) // their words follow those of the plain items
-            for (Item &i : *items) i.run = word(i.run + plan->hand_words[0]);
-        plan->hand_words[1] += plan->hand_words[0];
+            for (Item &i : *items) i.run = word(i.run + plan->chain[0].words);
+        plan->chain[1].words += plan->chain[0].words;
+        plan->chain[1].work += plan->chain[0].work;
+        plan->chain[1].tok = std::max(plan->chain[1].tok, plan->chain[0].tok);
         plan->vs_items.insert(plan->vs_items.end(), vs_dual.begin(), vs_dual.end());
         plan->ve_items.insert(plan->ve_items.end(), ve_dual.begin(), ve_dual.end());
         plan->n_vs_head = (int32_t)plan->vs_items.size();
@@ -523,19 +528,32 @@ Route slora_plan::route(int32_t n, bool apply, bool y16) const
     return r;
 }
 
-// Both stages in one launch.  Larger calls are bound by HBM, and the two kernels hold more wavefronts.  us, two kernels / chain, workgroups of the
-// chain: 128 tokens of rank 32, H = 4096, 1 / 2 / 4 slots, 2048 / 4096 / 8192: 18.5 / 15.5, 29.8 / 26.4, 52.8 / 56.6; 50 of rank 64, 4 slots, 4800: 40.8 / 37.8; 100 of rank 64,
-// H = 2048, 4 slots, 8000: 41.0 / 42.3, fours of them 52.3 / 60.4; 400 of rank 8, 4000: 18.3 / 19.0, 3 slots, 12000: 40 / 51; 20 groups of eight tokens of rank 64, 3 slots,
-// 2880: 29.8 / 23.0; where rows of x leave a compute unit two workgroups, 60 groups of four tokens of rank 64, H = 8192, 2 slots, 3840: 67.8 / 75.9.
-// Short rows of many ranks are mostly shrink, whose wavefronts then have little in flight; four of its workgroups fit a compute unit here, five or more in a kernel of
-// its own; and rows of a second 64 ranks are requested after the wait.  Tokens of rank 128, H = 2048: 30 in 1080 workgroups 12.3 / 13.2, 40 in 1440 13.5 / 14.9, 60 in 2160 16.8 / 18.9, 100 pairs in 3600 25.5 / 30.4; but H = 3072, 75 in 2850: 25.0 / 24.2,
-// rank 64, 100 in two slots, 4000: 24.2 / 22.7, and 20 of rank 128, H = 1024, 680: 10.4 / 7.9.
+// Both stages in one launch, us two kernels / one launch.  Large calls are bound by HBM, and the two kernels hold more wavefronts: 4096 workgroups, four (three from H = 6152 on)
+// of which a compute unit holds at a time.  128 tokens of rank 32, H = 4096, 1 / 2 / 4 slots, 2048 / 4096 / 8192: 18.5 / 15.5, 29.8 / 26.4, 52.8 / 56.6; 60 groups of four of
+// rank 32, 4 slots, 3840: 39.4 / 36.9; 100 of rank 64, H = 2048, 4 slots, 8000: 41.0 / 42.3, fours of them 52.3 / 60.4; 20 groups of eight tokens of rank 64, 3 slots, 2880: 29.8 / 23.0.
+// Fewer where
+//  - an expand item is little work (ranks x tokens below 16, below 4): its workgroups wait in their places all the same.  71 tokens of rank 1, H = 3072, 8 slots, 3976: 13.2 / 14.6, 252
+//    pairs, H = 1024, 4 slots, 3024: 10.6 / 11.2, but 200 of rank 4, 2400: 10.6 / 9.8; 63 of rank 8, H = 3072, 8 slots, 4032: 15.9 / 16.6, but 70 groups of four of rank 1, 3360: 18.8 / 17.8.
+//  - rows of x leave a compute unit three or two workgroups (more than 40 or 56 KiB): 60 groups of four tokens of rank 64, H = 8192, 2 slots, 3840: 67.8 / 75.9, but 20 of rank 32, 4 slots,
+//    1920: 30.0 / 26.1; with little work in an expand item 30 groups of eight of rank 4, H = 8192, 2 slots, 2040: 18.7 / 20.6, ten of sixteen of rank 8, 1440: 16.4 / 17.3, but of rank 4, 1360: 16.0 / 15.8.
+// Calls that are mostly shrink (many ranks of short rows) have little in flight in its wavefronts; five or more workgroups fit a compute unit in a kernel of its own; and rows
+// of a second 64 ranks are requested after the wait.
+//  - Six times as many shrink items as expand items: 640 of them.  60 tokens of rank 128, H = 2048, 2160: 16.8 / 18.9, 100 pairs in 3600 25.5 / 30.4, but 20 of rank 128, H = 1024, 680: 10.4 / 7.9.
+//  - Four times, pairs of tokens (whose B rows are not streamed here): 2048.  20 of rank 128, H = 3072, 4 slots, 3040: 29.0 / 34.0; 14 of rank 128, H = 4096, 4 slots, 2240: 26.4 / 28.6; 9, 6 slots, 2160: 26.9 / 28.7, but
+//    7 of them, 7 slots, 1960: 26.5 / 25.7.  (Four tokens: 17 of rank 100, H = 3072, 5 slots, 2635: 30.5 / 28.3.)
+//  - Four and a half times, single tokens: not between one round of the GPU's 1024 places and one and a half.  Ten of rank 100, H = 2560, 4 slots, 1200: 13.3 / 14.5, five, 8 slots 12.9 / 14.6, but 6 slots, 900: 12.0 / 11.0;
+//    13, 8 slots, 3120: 25.2 / 23.7; 30 of rank 128, H = 2048, 1080: 12.3 / 13.2.
 bool slora_plan::chain_pays(int32_t n, const Route &r) const
 {
-    if (!expand_split || pool->fuse_decode == 0 || n_vs(r) == 0 || r.gang || r.gang_expand || pool->H > kChainMaxH || chain_wgs(r) > 65535 || chain_words(r) * n > INT32_MAX) return false;
-    const int64_t rows = (int64_t)max_shrink_tok * pool->H * 2;
-    if (n_vs(r) > 6 * n_ve(r) && (int64_t)n_vs(r) * n > 640) return false;
-    return chain_wgs(r) * n <= (rows <= 40960 ? 4096 : 2048);
+    const Chain &c = chain_of(r);
+    const int64_t shrinks = (int64_t)n_vs(r) * n, expands = (int64_t)n_ve(r) * n, wgs = shrinks + expands;
+    if (!expand_split || pool->fuse_decode == 0 || shrinks == 0 || r.gang || r.gang_expand || pool->H > kChainMaxH || wgs > 65535 || c.words * n > INT32_MAX) return false;
+    if (shrinks > 6 * expands && shrinks > 640) return false;
+    if (shrinks >= 4 * expands && c.tok == 2 && wgs > 2048) return false;
+    if (2 * shrinks > 9 * expands && c.tok == 1 && wgs > 1024 && wgs <= 1536) return false;
+    const int64_t work = c.work * n / expands, rows = (int64_t)c.tok * pool->H * 2;
+    if (rows > 40960) return wgs <= (rows > 57344 && work < 64 ? 1408 : 2048);
+    return wgs <= (work < 4 ? 2560 : work < 16 ? 3584 : 4096);
 }
 
 size_t slora_plan::most_chain_words(int32_t n) const
@@ -544,7 +562,7 @@ size_t slora_plan::most_chain_words(int32_t n) const
     for (int32_t m = 1; m <= n; ++m)
         for (int y16 = 0; y16 <= (dual ? 1 : 0); ++y16) {
             const Route r = route(m, true, y16 != 0);
-            if (chain_pays(m, r)) most = std::max(most, chain_words(r) * m);
+            if (chain_pays(m, r)) most = std::max(most, chain_of(r).words * m);
         }
     return (size_t)most;
 }
@@ -642,7 +660,7 @@ int32_t do_shrink(slora_plan *plan, int32_t n, const int32_t *slots, const void 
         v = plan->set->v;
     }
     if (rc == SLORA_OK) rc = plan->enter(stream);
-    if (rc == SLORA_OK && !scratch && y && !overlaps && plan->chain_pays(n, route) && (size_t)(plan->chain_words(route) * n) <= plan->set->hand_cap &&
+    if (rc == SLORA_OK && !scratch && y && !overlaps && plan->chain_pays(n, route) && (size_t)(plan->chain_of(route).words * n) <= plan->set->hand_cap &&
         !stream_captures(stream) && plan->pool->next_launch(plan->set, stream)) {
         route.chain = true;
         route.small = false;

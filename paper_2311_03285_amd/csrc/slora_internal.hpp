@@ -260,7 +260,13 @@ struct slora_plan {
     int32_t n_vs_plain = 0, n_ve_plain = 0;
     int32_t most_slots = 0;   // most slots of a call so far, and
     size_t most_words = 0;    // the words that they may take
-    int64_t hand_words[2] = {0, 0}; // words per slot in which a call hands v of its vector groups over: on a wide route (without those of the MFMA kernels), on another
+    // of the vector items that a call which hands v over runs: on a wide route (without those of groups on the MFMA kernels), on another
+    struct Chain {
+        int64_t words = 0; // per slot, a value of v each
+        int64_t work = 0;  // ranks times tokens of all expand items
+        int32_t tok = 0;   // most tokens of a shrink item
+    } chain[2];
+    const Chain &chain_of(const slora::Route &r) const { return chain[r.wide ? 0 : 1]; }
     bool mfma_on(const slora::Route &r) const { return !dual || r.wide; }
     // items of the two vector lists that a call runs beside the other kernels
     size_t n_vs(const slora::Route &r) const { return r.wide ? (size_t)n_vs_plain : r.fused ? (size_t)n_vs_head : vs_items.size(); }
@@ -276,8 +282,7 @@ struct slora_plan {
     // ... of the one that hands v over
     int64_t chain_wgs(const slora::Route &r) const { return (int64_t)(n_vs(r) + n_ve(r)); }
     bool chain_pays(int32_t n, const slora::Route &r) const; // ... which an apply of n slots may take
-    int64_t chain_words(const slora::Route &r) const { return hand_words[r.wide ? 0 : 1]; } // its words per slot
-    size_t most_chain_words(int32_t n) const; // ... in a call of up to n slots, if any may take it
+    size_t most_chain_words(int32_t n) const; // its words in a call of up to n slots, if any may take it
     // workgroups of the vector kernels, per slot
     size_t shrink_wgs(const slora::Route &r) const { return r.gang ? n_gs(r) + gv_items.size() : n_vs(r); }
     size_t expand_wgs(const slora::Route &r) const { return r.gang_expand ? n_ge(r) : n_ve(r); }

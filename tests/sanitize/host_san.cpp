@@ -227,6 +227,7 @@ static void vec_shrink(const slora_plan *plan, const MultiArgs &a, int32_t k, co
         } else { // its rows of x fit the LDS of the launch
             REQUIRE(it.ntok <= kShrinkTok && it.ntok <= (gang ? plan->max_gv_tok : plan->max_shrink_tok) && it.b <= (pool->shrink_pages > 0 ? pool->shrink_pages : kShrinkPages));
             REQUIRE(it.ntok == 1 || it.ntok * pool->H * 2 <= 65536);
+            REQUIRE(!words || it.ntok <= plan->chain_of(route).tok);
         }
         cover.add(it, it.rank, it.a, it.a + it.b);
         for (int32_t t = 0; t < it.ntok; ++t)
@@ -234,7 +235,7 @@ static void vec_shrink(const slora_plan *plan, const MultiArgs &a, int32_t k, co
                 v[(int64_t)(it.pos0 + t) * plan->v_stride + j] = 0.f;
                 if (words) { // every word is left once
                     const int64_t w = it.run + (int64_t)t * it.rank + j;
-                    REQUIRE(w >= 0 && w < plan->chain_words(route) && !(*words)[(size_t)w]++);
+                    REQUIRE(w >= 0 && w < plan->chain_of(route).words && !(*words)[(size_t)w]++);
                 }
             }
     }
@@ -272,7 +273,7 @@ static void vec_expand(const slora_plan *plan, const MultiArgs &a, int32_t k, co
             for (int32_t j = 0; j < it.rank; j += words ? 1 : 16) {
                 if (words) { // a word that is waited for is left
                     const int64_t w = it.run + (int64_t)t * it.rank + j;
-                    REQUIRE(w >= 0 && w < plan->chain_words(route) && (*words)[(size_t)w] == 1);
+                    REQUIRE(w >= 0 && w < plan->chain_of(route).words && (*words)[(size_t)w] == 1);
                 } else {
                     g_sink = a.v[k][(int64_t)(it.pos0 + t) * plan->v_stride + j];
                 }
@@ -294,7 +295,7 @@ int32_t launch_chain(slora_plan *plan, int32_t n, const MultiArgs &a, void *, bo
 {
     REQUIRE(a.n == n && route.chain && !route.small && !route.gang && !route.gang_expand && plan->expand_split);
     REQUIRE(plan->pool->H <= kChainMaxH && plan->pool->fuse_decode != 0 && plan->chain_wgs(route) <= 65535);
-    const int64_t words_per_slot = plan->chain_words(route);
+    const int64_t words_per_slot = plan->chain_of(route).words;
     REQUIRE(plan->set->launch > 0 && (size_t)(words_per_slot * n) <= plan->set->hand_cap);
     REQUIRE(plan->set->hand == (uint64_t *)(plan->set->v + plan->set->v_cap)); // behind every v
     for (size_t w = 0; w < plan->set->hand_cap; ++w) REQUIRE((uint32_t)(plan->set->hand[w] >> 32) != plan->set->launch); // a number of its own
@@ -727,7 +728,7 @@ static void hand_over()
         Bench b(H, 4, SLORA_BF16, groups), off(H, 4, SLORA_BF16, groups, never);
         for (int32_t n = 1; n <= 4; ++n) {
             const int64_t wgs = (b.plan->chain_wgs(Route{})) * n;
-            const bool pays = H <= 8192 && wgs <= (std::min(b.plan->max_shrink_tok, 4) * H * 2 <= 40960 ? 4096 : 2048);
+            const bool pays = H <= 8192 && wgs <= (std::min(b.plan->max_shrink_tok, 4) * H * 2 <= 40960 ? 4096 : 2048); // (more than 64 ranks times tokens an expand item)
             REQUIRE(b.apply(n) == SLORA_OK && g_log.chain == pays && g_log.vec_expand > 0);
             REQUIRE(b.expand(n) == SLORA_OK && !g_log.chain);
             REQUIRE(b.apply16(n) == SLORA_OK && g_log.chain == pays);
@@ -751,6 +752,31 @@ static void hand_over()
     REQUIRE(m.apply(3) == SLORA_OK && g_log.chain && g_log.mfma_expand && g_log.vec_expand > 0);
 }
 
+// Which calls take it, on both sides of every line.
+static void hand_over_pays()
+{
+    const auto calls = [](int32_t H, int groups, int tok, int rank, std::initializer_list<std::pair<int32_t, bool>> slots) {
+        Bench b(H, 8, SLORA_F16, std::vector<std::pair<int, int>>(groups, {rank, tok}));
+        for (auto &s : slots) REQUIRE(b.apply16(s.first) == SLORA_OK && g_log.chain == s.second && !g_log.gang && !g_log.gang_expand);
+    };
+    calls(4096, 60, 4, 32, {{4, true}, {5, false}});           // 3840 and 4800 workgroups
+    calls(3072, 71, 1, 1, {{5, true}, {6, false}});            // 2485, 2982: an expand item is one product a column
+    calls(3072, 63, 1, 8, {{7, true}, {8, false}});            // 3528, 4032: eight
+    calls(2560, 70, 4, 1, {{8, true}});                        // 3360: four
+    calls(8192, 20, 4, 32, {{4, true}, {5, false}});           // 1920, 2400: 64 KiB of x
+    calls(8192, 20, 4, 4, {{4, true}, {5, false}});            // 1360, 1700: and sixteen products
+    calls(1024, 20, 1, 128, {{1, true}, {2, false}});          // 640 and 1280 shrink items, sixteen times as many as expand items
+    calls(3072, 20, 2, 128, {{2, true}, {3, false}});          // 1520, 2280: pairs, 5.3 times
+    calls(3072, 20, 3, 128, {{3, true}});
+    calls(2560, 5, 1, 100, {{6, true}, {8, false}});           // 900, 1200: single tokens, five times
+    calls(2560, 13, 1, 100, {{2, true}, {3, false}, {4, true}}); // 780, 1170, 1560
+    // a call whose groups of many tokens are on the MFMA kernels keeps rows for the tokens of the others only
+    std::vector<std::pair<int, int>> mixed{{64, 1}, {64, 3}, {64, 2}, {32, 400}};
+    Bench b(8192, 4, SLORA_F16, mixed);
+    REQUIRE(b.plan->dual && b.plan->max_shrink_tok == 4 && b.plan->chain[0].tok == 3 && b.plan->chain[1].tok == 4);
+    REQUIRE(b.apply(4) == SLORA_OK && g_log.wide && g_log.chain && b.plan->chain[0].words == 64 * 6);
+}
+
 // Room for the words lies behind v, in one allocation; the first launch that uses it clears it, so calls that never hand v over launch
 // nothing for it.  Without memory for it calls take the two kernels, and ask once per hand-out of the buffers.
 static void words_of_the_calls_that_use_them()
@@ -769,7 +795,7 @@ static void words_of_the_calls_that_use_them()
         for (int i = 0; i < 3; ++i)
             for (int32_t n : {4, 1, 3}) REQUIRE(b.apply(n) == SLORA_OK && g_log.chain && b.shrink(n) == SLORA_OK && b.apply16(n) == SLORA_OK && g_log.chain);
         REQUIRE(g_device_mallocs == mallocs + 1 && g_clears == clears + 1);
-        REQUIRE(b.plan->chain_words(Route{}) == 20 * 2 * 16);
+        REQUIRE(b.plan->chain_of(Route{}).words == 20 * 2 * 16);
     }
     int place = 0;
     void *const stream = &place;
@@ -794,6 +820,7 @@ static void words_of_the_calls_that_use_them()
 
 static const struct { const char *name; void (*run)(); } kCases[] = {
     {"hand_over", hand_over},
+    {"hand_over_pays", hand_over_pays},
     {"words_of_the_calls_that_use_them", words_of_the_calls_that_use_them},
     {"shrink_pages_of_the_caller", shrink_pages_of_the_caller},
     {"expand_lds", expand_lds},

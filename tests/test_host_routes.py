@@ -24,7 +24,7 @@ def exe(tmp_path_factory):
 
 @pytest.mark.parametrize("case", ["failed_apply", "static_route", "scratch_is_sized_once", "fuse_decode_never",
                                   "y_in_the_buffer_of_x", "expand_runs", "slots_of_the_call", "larger_items",
-                                  "larger_items_pay", "larger_items_in_fours", "larger_items_of_no_call", "expand_lds", "shrink_pages_of_the_caller", "hand_over",
+                                  "larger_items_pay", "larger_items_in_fours", "larger_items_of_no_call", "expand_lds", "shrink_pages_of_the_caller", "hand_over", "hand_over_pays",
                                   "words_of_the_calls_that_use_them"])
 def test_case(exe, case):
     assert f"host_san OK: {case}" in run(exe, case)
