@@ -1398,12 +1398,12 @@ __global__ __launch_bounds__(kShrinkThreads, U > 8 ? 3 : 4) void lora_vec_chain_
 {
     extern __shared__ u32x4 smem[]; // rows of x, or the sums of an expand item's wavefronts
     // Slots vary fastest, so workgroups are dispatched in the order of the work lists.  They go round the eight XCDs one by one: with a power of two of slots
-    // each slot would stay on its own XCDs, and with eight of them the launch was up to 15 % slower than the two kernels instead of 20 % faster.  A slot
-    // moves on every four items (which share rows of x).  us, two kernels / slots that stay / that move: six groups of ranks 16-64 and 1-3 tokens, 8 slots,
-    // H = 5120 16.7 / 17.1 / 12.0, H = 4096 14.6 / 14.3 / 11.4; four groups of four tokens, rank 64 15.3 / 14.8 / 11.8; 21 tokens of rank 4 9.8 / 10.5 / 8.6; every item
-    // the first of these takes 13.4, every two or eight items most calls are the same or a little slower.
+    // each slot would stay on its own XCDs, which made calls of eight up to 25 % slower.  A slot moves on every 32 items, or 64 where several items read
+    // the same pages.  us, two kernels / slots that stay / that move every 4 / 16 / 32 / 64 items, 8 slots: six groups of ranks 16-64 and 1-3 tokens, H = 5120 16.7 / 16.2 / 11.7 /
+    // 10.9 / 10.9 / 10.9; five of ranks 32-64, H = 8192 18.9 / 21.0 / 16.9 / 14.5 / 14.6 / -; 29 tokens of rank 4, H = 5120 12.3 / 14.5 / 11.8 / - / 11.8 / 13.1; eight groups of eight tokens, ranks
+    // 16-64, H = 2024 15.1 / 15.5 / 16.7 / 13.6 / 12.9 / -; four of 5-30 tokens, ranks 16-128, H = 5120 25.7 / 17.4 / 20.4 / 19.4 / 18.6 / 17.4
     const unsigned slots = gridDim.x;
-    const int cs = slots & (slots - 1) ? blockIdx.x : (blockIdx.x + blockIdx.y / 4) & (slots - 1);
+    const int cs = slots & (slots - 1) ? blockIdx.x : (blockIdx.x + (blockIdx.y >> lists.turn)) & (slots - 1);
     const bool shrinks = blockIdx.y < lists.n_shrink;
     const Item it = shrinks ? lists.shrink[blockIdx.y] : lists.expand[blockIdx.y - lists.n_shrink];
     const uint16_t *x = static_cast<const uint16_t *>(args.x[cs]);
@@ -2843,6 +2843,7 @@ int32_t launch_chain(slora_plan *plan, int32_t n, const MultiArgs &args, void *s
     c.shrink = plan->d_vs;
     c.expand = plan->d_ve;
     c.n_shrink = (unsigned)plan->n_vs(route);
+    c.turn = plan->chain_of(route).shared ? 6 : 5;
     c.hand = plan->set->hand;
     c.hand_slot = plan->chain_of(route).words;
     c.launch = plan->set->launch;

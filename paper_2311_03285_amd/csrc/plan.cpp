@@ -297,6 +297,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                 chain.words += (int64_t)n * g.rank;
                 chain.work += (int64_t)n * g.rank * ((H + ecols - 1) / ecols);
                 chain.tok = std::max(chain.tok, std::min(n, shrink_tok));
+                chain.shared = chain.shared || n > kExpandTok;
                 if (fused) plan->vf_items.push_back(Item{off, g.rank, 0, H, pos_base, n, 0, 0});
                 for (int32_t p = 0; p < n; p += shrink_tok) {
                     const int32_t nt = std::min(shrink_tok, n - p);
@@ -378,6 +379,7 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         plan->chain[1].words += plan->chain[0].words;
         plan->chain[1].work += plan->chain[0].work;
         plan->chain[1].tok = std::max(plan->chain[1].tok, plan->chain[0].tok);
+        plan->chain[1].shared = plan->chain[1].shared || plan->chain[0].shared;
         plan->vs_items.insert(plan->vs_items.end(), vs_dual.begin(), vs_dual.end());
         plan->ve_items.insert(plan->ve_items.end(), ve_dual.begin(), ve_dual.end());
         plan->n_vs_head = (int32_t)plan->vs_items.size();

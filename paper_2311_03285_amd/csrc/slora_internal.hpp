@@ -73,6 +73,7 @@ struct MultiArgs {
 struct ChainLists {
     const Item *shrink, *expand;
     uint32_t n_shrink; // shrink items; then the expand items
+    uint32_t turn;     // a slot moves on by one XCD every 2^turn items
     uint64_t *hand;    // words {value, number of the launch} of the first slot,
     int64_t hand_slot; // those of a slot
     uint32_t launch;
@@ -265,6 +266,7 @@ struct slora_plan {
         int64_t words = 0; // per slot, a value of v each
         int64_t work = 0;  // ranks times tokens of all expand items
         int32_t tok = 0;   // most tokens of a shrink item
+        bool shared = false; // pages that several items read: a group of more than kExpandTok tokens
     } chain[2];
     const Chain &chain_of(const slora::Route &r) const { return chain[r.wide ? 0 : 1]; }
     bool mfma_on(const slora::Route &r) const { return !dual || r.wide; }
