@@ -94,10 +94,11 @@ int32_t slora_pool_destroy(slora_pool *pool);
  * Allocation statistics, for tests and tuning: fills out[0..n) (n <= SLORA_POOL_STATS_N) with
  *  [0] buffer sets (pinned image + device image + v scratch) ever created for plans, page
  *      writes and page-list uploads   [1] device / pinned allocations made for them and for
- *      the page-list image            [2] sets waiting to be handed out again.
+ *      the page-list image            [2] sets waiting to be handed out again   [3] applies
+ *      that handed v over inside one launch ("fuse_decode" below).
  * [0] and [1] stop growing once the caller's mix of batch sizes has been seen.
  */
-#define SLORA_POOL_STATS_N 3
+#define SLORA_POOL_STATS_N 4
 int32_t slora_pool_stats(const slora_pool *pool, int64_t *out, int32_t n);
 
 /*

@@ -672,7 +672,10 @@ int32_t do_shrink(slora_plan *plan, int32_t n, const int32_t *slots, const void 
     if (route.fused || route.small || route.chain)
         for (int32_t k = 0; k < n; ++k) a.y[k] = y[k];
     if (route.fused || route.small) rc = launch_fused(plan, n, a, stream, y16, route);
-    if (rc == SLORA_OK && route.chain) rc = launch_chain(plan, n, a, stream, y16, route);
+    if (rc == SLORA_OK && route.chain) {
+        rc = launch_chain(plan, n, a, stream, y16, route);
+        plan->pool->hand_overs += rc == SLORA_OK;
+    }
     if (rc == SLORA_OK && !route.small) rc = launch_shrink(plan, n, a, stream, route);
     if (rc == SLORA_OK) {
         plan->v_slots = n;

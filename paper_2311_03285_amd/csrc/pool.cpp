@@ -448,7 +448,7 @@ int32_t slora_pool_stats(const slora_pool *pool, int64_t *out, int32_t n)
 {
     clear_error();
     if (!pool || !out || n < 0 || n > SLORA_POOL_STATS_N) return fail(SLORA_EINVAL, "bad arguments");
-    const int64_t v[SLORA_POOL_STATS_N] = {pool->sets_made, pool->device_allocs, (int64_t)pool->idle_sets.size()};
+    const int64_t v[SLORA_POOL_STATS_N] = {pool->sets_made, pool->device_allocs, (int64_t)pool->idle_sets.size(), pool->hand_overs};
     for (int32_t k = 0; k < n; ++k) out[k] = v[k];
     return SLORA_OK;
 }

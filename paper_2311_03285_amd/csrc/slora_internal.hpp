@@ -214,6 +214,7 @@ struct slora_pool {
     std::vector<slora::Buffers *> idle_sets;
     int64_t sets_made = 0;                            // buffer sets ever allocated (steady state: constant)
     int64_t device_allocs = 0;                        // hipMalloc / hipHostMalloc calls made for them
+    int64_t hand_overs = 0;                           // applies that handed v over inside a launch
     void *static_scratch = nullptr;                   // this GPU's copy of the library's static scratch
     void *upload_stream = nullptr;                    // hipStream_t, created on first use
     void *arena_event = nullptr;                      // hipEvent_t: the device page-list image is complete after it

@@ -18,7 +18,7 @@ OK, EINVAL, ERANGE, EBUSY, ENOENT, ESEG, EHIP, ENOMEM = 0, -1, -2, -3, -4, -5, -
 MAX_MULTI = 8
 STATIC_SCRATCH_BYTES = 64 << 20
 PLAN_INFO_N = 13
-POOL_STATS_N = 3
+POOL_STATS_N = 4
 PLAN_INFO_KEYS = ("tokens", "groups", "groups_vec", "groups_mfma", "vec_shrink_items", "vec_expand_items",
                   "mfma_shrink_items", "mfma_expand_items", "v_stride", "sum_rank", "split_tiles",
                   "scratch_bytes_per_slot", "groups_fused")
@@ -146,7 +146,7 @@ def pool_destroy(pool) -> None:
 def pool_stats(pool) -> dict:
     out = np.zeros(POOL_STATS_N, dtype=np.int64)
     _check(lib().slora_pool_stats(pool, _ptr(out), POOL_STATS_N))
-    return dict(zip(("sets_made", "allocations", "idle_sets"), (int(v) for v in out)))
+    return dict(zip(("sets_made", "allocations", "idle_sets", "hand_overs"), (int(v) for v in out)))
 
 
 def pool_mark_kv(pool, page_idx, owned: bool = True) -> None:

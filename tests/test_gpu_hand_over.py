@@ -27,8 +27,13 @@ def side():
     return torch.cuda.Stream()
 
 
+def hand_overs(dw):
+    return slora.pool_stats(dw.pool)["hand_overs"]
+
+
 def both(dw, slots, plan, y16, calls=1):
-    """y after `calls` applies, and after as many pairs of shrink and expand."""
+    """y after `calls` applies, each of which hands v over, and after as many pairs of shrink and expand, which do not."""
+    before = hand_overs(dw)
     keep = [dw.x_dev(s) for s in slots]
     xs = [t.data_ptr() for t in keep]
     dtype = (torch.float16 if dw.w.dtype == synth.F16 else torch.bfloat16) if y16 else torch.float32
@@ -39,6 +44,7 @@ def both(dw, slots, plan, y16, calls=1):
         slora.lora_shrink(plan, slots, xs)
         (slora.lora_expand_y16 if y16 else slora.lora_expand)(plan, slots, [t.data_ptr() for t in two])
     torch.cuda.synchronize()
+    assert hand_overs(dw) == before + calls
     return one, two
 
 
@@ -81,6 +87,7 @@ def test_plans_and_streams_share_the_words():
                 slora.lora_expand(plan, list(range(n)), [t.data_ptr() for t in two[:n]])
             slora.plan_destroy(plan)
             torch.cuda.synchronize()
+            assert hand_overs(dw) == 3 * (i + 1)
             for a, b in zip(one, two):
                 assert torch.equal(a, b), i
 
@@ -99,6 +106,7 @@ def test_captured_calls_between_eager_ones(side):
         g = torch.cuda.CUDAGraph()
         with torch.cuda.graph(g, stream=st):
             slora.lora_apply_multi(plan, slots, xp, [t.data_ptr() for t in y], torch.cuda.current_stream().cuda_stream)
+        assert hand_overs(dw) == 1
         for i in range(4):
             for t in xs:
                 t.view(torch.bfloat16).mul_(1.25)
@@ -106,6 +114,7 @@ def test_captured_calls_between_eager_ones(side):
             torch.cuda.synchronize()
             slora.lora_apply_multi(plan, slots, xp, [t.data_ptr() for t in y], st.cuda_stream)
             torch.cuda.synchronize()
+        assert hand_overs(dw) == 5
         xs2 = [dw.x_dev(s) for s in slots]
         xp2 = [t.data_ptr() for t in xs2]
 
@@ -155,6 +164,7 @@ def test_infinite_weights(H, rank, y16, side):
             apply(plan, [0], [x.data_ptr()], [ys[2].data_ptr()], torch.cuda.current_stream().cuda_stream)
         g.replay()
         torch.cuda.synchronize()
+        assert hand_overs(dw) == 2
         hit = torch.from_numpy((w.ids >= 0) & (w.ids < 3)).to(ys[0].device)
         for y in ys:
             assert not bool(torch.isfinite(y[hit, 3]).any()) and bool(torch.isfinite(y[~hit]).all())
