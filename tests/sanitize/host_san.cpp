@@ -193,7 +193,7 @@ static std::vector<uint8_t> served_elsewhere(const slora_plan *plan, const Route
 
 // what the latest apply, shrink or expand launched
 struct Log {
-    bool small = false, chain = false; // a small batch in one launch; both vector stages in the one that hands v over
+    bool small = false, chain = false; // both vector stages in one launch: every workgroup computes v for itself; v is handed over
     bool fused = false, mfma_shrink = false, mfma_expand = false;
     bool wide = false, gang = false, gang_expand = false; // the larger items of the vector kernels
     size_t vec_shrink = 0, vec_expand = 0; // items
@@ -311,9 +311,8 @@ int32_t launch_chain(slora_plan *plan, int32_t n, const MultiArgs &a, void *, bo
         for (uint8_t w : words) REQUIRE(w == 1); // no room for more
     }
     g_log.chain = true;
-    g_log.small = plan->route(n, true, y16).small; // a batch of that kind
-    g_log.vec_shrink = g_log.small ? 0 : plan->n_vs(route);
-    g_log.vec_expand = g_log.small ? 0 : plan->n_ve(route);
+    g_log.vec_shrink = plan->n_vs(route);
+    g_log.vec_expand = plan->n_ve(route);
     g_wide[plan] = route.wide;
     return SLORA_OK;
 }
@@ -512,6 +511,15 @@ struct Bench {
     }
     int32_t apply(int32_t n) { g_log = {}; return slora_lora_apply_multi(plan, n, slots, xs.data(), ys.data(), nullptr); }
     int32_t apply_static(int32_t n) { g_log = {}; return slora_lora_apply_multi_static(plan, n, slots, xs.data(), ys.data(), nullptr); }
+    int32_t apply_captured(int32_t n, bool y16)
+    {
+        g_log = {};
+        g_captures = true;
+        void *const stream = &n_slots; // a stream that is not the default one
+        const int32_t rc = y16 ? slora_lora_apply_multi_y16(plan, n, slots, xs.data(), (void *const *)ys.data(), stream) : slora_lora_apply_multi(plan, n, slots, xs.data(), ys.data(), stream);
+        g_captures = false;
+        return rc;
+    }
     int32_t apply16(int32_t n) { g_log = {}; return slora_lora_apply_multi_y16(plan, n, slots, xs.data(), (void *const *)ys.data(), nullptr); }
     int32_t shrink(int32_t n) { g_log = {}; return slora_lora_shrink(plan, n, slots, xs.data(), nullptr); }
     int32_t expand(int32_t n) { g_log = {}; return slora_lora_expand(plan, n, slots, ys.data(), nullptr); }
@@ -561,19 +569,24 @@ static void scratch_is_sized_once()
         }
 }
 
-// "fuse_decode" 0: never one launch for both stages.
+// "fuse_decode" 0: never one launch for both stages.  Otherwise a small batch takes the one that hands v over or, with the static scratch and
+// under capture, the one in which every workgroup computes v for itself.
 static void fuse_decode_never()
 {
     for (int64_t mode : {0, 1, 2}) {
         Bench b(4096, 2, SLORA_BF16, {{8, 1}, {16, 2}}, {{"fuse_decode", mode}});
-        REQUIRE(b.apply(2) == SLORA_OK);
-        REQUIRE(g_log.small == (mode == 1) && g_log.fused == (mode == 2));
-        REQUIRE((g_log.vec_expand > 0) == (mode == 0));
+        for (bool y16 : {false, true}) {
+            REQUIRE((y16 ? b.apply16(2) : b.apply(2)) == SLORA_OK);
+            REQUIRE(g_log.chain == (mode == 1) && g_log.fused == (mode == 2) && !g_log.small);
+            REQUIRE((g_log.vec_expand > 0) == (mode != 2));
+            REQUIRE((y16 ? b.apply_captured(2, true) : b.apply_static(2)) == SLORA_OK);
+            REQUIRE(g_log.small == (mode == 1) && g_log.fused == (mode == 2) && !g_log.chain);
+            REQUIRE((g_log.vec_expand > 0) == (mode == 0));
+        }
     }
 }
 
-// A workgroup of the one-launch kernel for small batches writes y while others still read x: calls in which a
-// y overlaps an x take the two kernels.
+// A workgroup of a kernel for both stages writes y while others still read x: calls in which a y overlaps an x take the two kernels.
 static void y_in_the_buffer_of_x()
 {
     Bench b(4096, 2, SLORA_BF16, {{8, 1}, {16, 2}});
@@ -583,8 +596,11 @@ static void y_in_the_buffer_of_x()
     const auto one_launch = [&](int64_t y_off, bool y16) { // y of slot 1 at this offset from x of slot 0
         b.ys[1] = (float *)(room.data() + 3 * row + y_off);
         REQUIRE((y16 ? b.apply16(2) : b.apply(2)) == SLORA_OK);
-        REQUIRE(g_log.small == (g_log.vec_expand == 0));
-        return g_log.small;
+        const bool one = g_log.chain;
+        REQUIRE(g_log.vec_expand > 0 && !g_log.small);
+        REQUIRE((y16 ? b.apply_captured(2, true) : b.apply_static(2)) == SLORA_OK);
+        REQUIRE(g_log.small == one && (g_log.vec_expand == 0) == one && !g_log.chain);
+        return one;
     };
     REQUIRE(!one_launch(0, true) && !one_launch((int64_t)(2 * row), true) && !one_launch(-(int64_t)(2 * row), true));
     REQUIRE(one_launch((int64_t)(3 * row), true) && one_launch(-(int64_t)(3 * row), true));
@@ -738,11 +754,17 @@ static void hand_over()
         }
     }
     Bench b(1024, 2, SLORA_F16, groups);
+    const auto hand_overs = [&] {
+        int64_t stats[SLORA_POOL_STATS_N];
+        REQUIRE(slora_pool_stats(b.pool, stats, SLORA_POOL_STATS_N) == SLORA_OK);
+        return stats[3];
+    };
+    REQUIRE(b.apply(1) == SLORA_OK && hand_overs() == 1 && b.apply_static(1) == SLORA_OK && b.apply_captured(1, false) == SLORA_OK && hand_overs() == 1);
     const void *const x1 = b.xs[1];
     b.xs[1] = b.ys[0]; // slot 0 writes what slot 1 reads
     REQUIRE(b.apply16(2) == SLORA_OK && !g_log.chain);
     b.xs[1] = x1;
-    REQUIRE(b.apply(2) == SLORA_OK && g_log.chain && b.plan->set->launch == 1);
+    REQUIRE(b.apply(2) == SLORA_OK && g_log.chain && b.plan->set->launch == 1 && hand_overs() == 2); // (larger words than those of one slot)
     b.plan->set->launch = UINT32_MAX - 1; // numbers run out, and start again with none of theirs in the words
     for (int i = 0; i < 3; ++i) REQUIRE(b.apply(2) == SLORA_OK && g_log.chain);
     REQUIRE(b.plan->set->launch == 2);
