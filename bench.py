@@ -151,6 +151,7 @@ def measure(args, workload: int, no_cpu: bool) -> dict:
         torch.cuda.synchronize()
         args.steps = max(R, args.steps // R * R)
     e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    handed = slora.pool_stats(dw.pool)["hand_overs"]
     t0 = time.perf_counter()
     if graph is None:
         e0.record(stream)
@@ -166,6 +167,7 @@ def measure(args, workload: int, no_cpu: bool) -> dict:
     torch.cuda.synchronize()
     wall = time.perf_counter() - t0
     ev_ms = e0.elapsed_time(e1)
+    handed = slora.pool_stats(dw.pool)["hand_overs"] - handed
     ms_per_step = wall * 1e3 / args.steps
 
     def per_step_ms(batches, n):
@@ -312,6 +314,13 @@ def measure(args, workload: int, no_cpu: bool) -> dict:
                          "avg_launch_us": round((sh_t if dom == "expand" else ex_t) * 1e6, 2)},
         "slots_per_launch": min(n_slots, slora.MAX_MULTI),
     }
+    if handed and kinds == "vec":
+        # the timed applies ran both stages in one launch each, which hands v over; the stage timings above are those of the two-stage calls
+        one_t, one_b = ev_ms * 1e-3 / handed, bytes_step * args.steps / handed
+        two = f"{sh_t * 1e6:.2f} + {ex_t * 1e6:.2f} us as shrink_vec + expand_vec (two-stage calls)"
+        dom_gbs = one_b / one_t / 1e9
+        roofline.update(kernel="vec_chain", achieved=round(dom_gbs, 1), frac=round(dom_gbs / HBM_PEAK_GBS, 4), traffic=None, traffic_source=None,
+                        algorithmic_bytes_per_launch=int(one_b), avg_launch_us=round(one_t * 1e6, 2), other_kernel={"kernel": two})
 
     # ---- parity of the timed launch shape: batch 0, EVERY slot, against the oracle -----------------
     # The GPU side is the call the timed loop makes (all slots, up to 8 per launch pair, on the

@@ -215,3 +215,38 @@ def test_a_slot_does_not_stay_on_one_die():
                 torch.cuda.synchronize()
                 ms[n] = min(ms[n], e0.elapsed_time(e1))
         assert ms[8] < 1.15 * ms[7], ms
+
+
+@pytest.mark.parametrize("down,up", [(-60, -10), (-60, -20), (-70, 4), (-64, -3)])
+def test_products_and_sums_below_the_normal_range(down, up):
+    """Values of v and products with B of about 2^(down - 60) and 2^(down - 60 + up): subnormal products, sums and values of v, on the matrix instruction as
+    with fmaf.  Against 64 bits every sum of `rank` products is off by half a unit of the subnormal range (2^-149) per rounding."""
+    rank, H = 24, 1032
+    w = workload(H, synth.BF16, (rank, rank, rank), (4, 3, 1), slots=8)
+    with DeviceWorkload(w, real_adapters="all") as dw:
+        plan = dw.plan()
+        gen = torch.Generator(device="cuda")
+        gen.manual_seed(1)
+        pool = dw.pool_t.view(torch.bfloat16)
+        for a in range(3):
+            for which, e in ((0, down), (1, up)):
+                rows = torch.randn((rank, H), device="cuda", generator=gen) * 2.0 ** e
+                pool[torch.from_numpy(w.page_idx[a][0, which].astype(np.int64)).cuda()] = rows.to(torch.bfloat16)
+        x = (torch.randn((w.T, H), device="cuda", generator=gen) * 2.0 ** -60 / H ** 0.5).to(torch.bfloat16)
+        one, two = [torch.zeros((w.T, H), device="cuda") for _ in range(2)]
+        slora.lora_apply_multi(plan, [0], [x.data_ptr()], [one.data_ptr()])
+        assert hand_overs(dw) == 1
+        slora.lora_shrink(plan, [0], [x.data_ptr()])
+        slora.lora_expand(plan, [0], [two.data_ptr()])
+        torch.cuda.synchronize()
+        assert torch.equal(one, two)
+        for a in range(3):
+            t = torch.from_numpy(np.nonzero(w.ids == a)[0]).cuda()
+            d, u = (pool[torch.from_numpy(w.page_idx[a][0, k].astype(np.int64)).cuda()].double() for k in (0, 1))
+            v = x[t].double() @ d.t()
+            ref = v @ u
+            # v: a lane adds the products of up to three chunks of eight, 64 lanes meet in six steps; then `rank` products and four partial sums
+            units = (3 * 8 + 6) * u.abs().sum(0).max() + rank + 4
+            bound = 2.0 ** -150 * units + 2e-6 * (v.abs() @ u.abs())
+            assert bool(((one[t].double() - ref).abs() <= bound).all())
+            assert float(ref.abs().max()) > 2.0 ** -146 and bool((one[t] != 0).any())

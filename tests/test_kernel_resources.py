@@ -68,6 +68,23 @@ def test_wavefronts_of_the_streaming_kernels(report):
         assert v["Occupancy"] >= 5, (k, v)
 
 
+def test_workgroups_of_the_launch_that_hands_v_over(report):
+    """A workgroup has a wavefront per SIMD: four of them per compute unit up to rows of 12 chunks a lane, three beyond (the plan's rule counts on it)."""
+    kernels, _ = report
+    chain = {k: v for k, v in kernels.items() if "lora_vec_chain_kernel" in k}
+    assert len(chain) == 44
+    for k, v in chain.items():
+        assert v["Occupancy"] == (3 if re.search(r"ILi\dELb\dELi16EE", k) else 4), (k, v)
+
+
+def test_rank_split_expand_keeps_three_workgroups(report):
+    kernels, _ = report
+    split = {k: v for k, v in kernels.items() if "expand_vec_split_kernel" in k}
+    assert len(split) == 8
+    for k, v in split.items():
+        assert v["Occupancy"] >= 3, (k, v)
+
+
 def test_no_packed_fp32_instructions(report):
     _, asm = report
     assert not re.search(r"\bv_pk_(add|mul|fma)_f32\b", asm)
