@@ -1402,8 +1402,7 @@ __global__ __launch_bounds__(kShrinkThreads, U > 8 ? 3 : 4) void lora_vec_chain_
     // the same pages.  us, two kernels / slots that stay / that move every 4 / 16 / 32 / 64 items, 8 slots: six groups of ranks 16-64 and 1-3 tokens, H = 5120 16.7 / 16.2 / 11.7 /
     // 10.9 / 10.9 / 10.9; five of ranks 32-64, H = 8192 18.9 / 21.0 / 16.9 / 14.5 / 14.6 / -; 29 tokens of rank 4, H = 5120 12.3 / 14.5 / 11.8 / - / 11.8 / 13.1; eight groups of eight tokens, ranks
     // 16-64, H = 2024 15.1 / 15.5 / 16.7 / 13.6 / 12.9 / -; four of 5-30 tokens, ranks 16-128, H = 5120 25.7 / 17.4 / 20.4 / 19.4 / 18.6 / 17.4
-    const unsigned slots = gridDim.x;
-    const int cs = slots & (slots - 1) ? blockIdx.x : (blockIdx.x + (blockIdx.y >> lists.turn)) & (slots - 1);
+    const int cs = args.n & (args.n - 1) ? blockIdx.x : (blockIdx.x + (blockIdx.y >> lists.turn)) & (args.n - 1);
     const bool shrinks = blockIdx.y < lists.n_shrink;
     const Item it = shrinks ? lists.shrink[blockIdx.y] : lists.expand[blockIdx.y - lists.n_shrink];
     const uint16_t *x = static_cast<const uint16_t *>(args.x[cs]);
