@@ -543,7 +543,8 @@ Route slora_plan::route(int32_t n, bool apply, bool y16) const
 //  - Six times as many shrink items as expand items: 640 of them.  60 tokens of rank 128, H = 2048, 2160: 16.8 / 18.9, 100 pairs in 3600 25.5 / 30.4, but 20 of rank 128, H = 1024, 680: 10.4 / 7.9.
 //  - Four times, pairs of tokens (whose B rows are not streamed here): 2048.  20 of rank 128, H = 3072, 4 slots, 3040: 29.0 / 34.0; 14 of rank 128, H = 4096, 4 slots, 2240: 26.4 / 28.6; 9, 6 slots, 2160: 26.9 / 28.7, but
 //    7 of them, 7 slots, 1960: 26.5 / 25.7.  Threes and fours: 3072.  42 fours of rank 128, H = 4096, 2 slots, 3360: 42.8 / 45.6, but 17 of rank 100, H = 3072, 5 slots, 2635: 30.5 / 28.3.
-//  - Four and a half times, single tokens, H >= 2048: not between one round of the GPU's 1024 places and one and a half.  Ten of rank 100, H = 2560, 4 slots, 1200: 13.3 / 14.5, five, 8 slots 12.9 / 14.6, but 6 slots, 900: 12.0 / 11.0;
+//  - Four and a half times, single tokens: H < 2048 2048.  18 of ranks 30-130, H = 1920, 8 slots, 3744: 21.9 / 23.9; 15 of rank 64, H = 1072, 8 slots, 2280: 12.7 / 13.0; but 59 of rank 64, H = 1536, 3 slots, 3363: 19.5 / 18.1.
+//    H >= 2048 not between one round of the GPU's 1024 places and one and a half.  Ten of rank 100, H = 2560, 4 slots, 1200: 13.3 / 14.5, five, 8 slots 12.9 / 14.6, but 6 slots, 900: 12.0 / 11.0;
 //    13, 8 slots, 3120: 25.2 / 23.7; 30 of rank 128, H = 2048, 1080: 12.3 / 13.2; but 32 of ranks 5-130, H = 1120, 2 slots, 1292: 13.0 / 12.0.
 bool slora_plan::chain_pays(int32_t n, const Route &r) const
 {
@@ -552,7 +553,7 @@ bool slora_plan::chain_pays(int32_t n, const Route &r) const
     if (!expand_split || pool->fuse_decode == 0 || shrinks == 0 || r.gang || r.gang_expand || pool->H > kChainMaxH || wgs > 65535 || c.words * n > INT32_MAX) return false;
     if (shrinks > 6 * expands && shrinks > 640) return false;
     if (shrinks >= 4 * expands && c.tok >= 2 && wgs > (c.tok == 2 ? 2048 : 3072)) return false;
-    if (2 * shrinks > 9 * expands && c.tok == 1 && pool->H >= 2048 && wgs > 1024 && wgs <= 1536) return false;
+    if (2 * shrinks > 9 * expands && c.tok == 1 && (pool->H < 2048 ? wgs > 2048 : wgs > 1024 && wgs <= 1536)) return false;
     const int64_t work = c.work * n / expands, rows = (int64_t)c.tok * pool->H * 2;
     if (rows > 40960) return wgs <= (rows > 57344 && work < 64 ? 1408 : 2048);
     return wgs <= (work < 4 ? 2560 : work < 16 ? 3584 : 4096);

@@ -792,7 +792,7 @@ static void hand_over_pays()
     calls(3072, 20, 3, 128, {{3, true}});
     calls(2560, 5, 1, 100, {{6, true}, {8, false}});           // 900, 1200: single tokens, five times
     calls(2560, 13, 1, 100, {{2, true}, {3, false}, {4, true}}); // 780, 1170, 1560
-    calls(1120, 40, 1, 64, {{1, true}, {2, true}});            // 760, 1520: short rows
+    calls(1120, 40, 1, 64, {{1, true}, {2, true}, {3, false}}); // 760, 1520, 2280: short rows
     calls(4096, 42, 4, 128, {{1, true}, {2, false}});          // 1680, 3360: fours, four times
     // a call whose groups of many tokens are on the MFMA kernels keeps rows for the tokens of the others only
     std::vector<std::pair<int, int>> mixed{{64, 1}, {64, 3}, {64, 2}, {32, 400}};
