@@ -22,9 +22,9 @@ def workload(H, dtype, ranks, toks, slots=2, seed=0):
 
 @pytest.fixture(scope="module")
 def side():
-    """One stream for all captured calls: streams share a few hardware queues, in the order in which a process makes them, and tests of
-    work that overlaps want two that do not."""
-    return torch.cuda.Stream()
+    """The stream that was handed out last (torch hands out 32 in turn): streams share a few hardware queues, in the order in which a process
+    takes them into use, and tests of work that overlaps want two that do not."""
+    return [torch.cuda.Stream() for _ in range(32)][-1]
 
 
 def hand_overs(dw):
@@ -92,7 +92,7 @@ def test_plans_and_streams_share_the_words():
                 assert torch.equal(a, b), i
 
 
-def test_captured_calls_between_eager_ones(side):
+def test_captured_calls_between_eager_ones():
     w = workload(2048, synth.BF16, (64, 24, 8), (1, 3, 2))
     with DeviceWorkload(w, real_adapters="all") as dw:
         plan = dw.plan()
@@ -100,7 +100,7 @@ def test_captured_calls_between_eager_ones(side):
         xs = [dw.x_dev(s) for s in slots]
         xp = [t.data_ptr() for t in xs]
         y, ref = [dw.y_dev(s) for s in slots], [dw.y_dev(s) for s in slots]
-        st = side
+        st = torch.cuda.Stream()
         slora.lora_apply_multi(plan, slots, xp, [t.data_ptr() for t in y], st.cuda_stream)
         torch.cuda.synchronize()
         g = torch.cuda.CUDAGraph()
@@ -133,9 +133,23 @@ def test_captured_calls_between_eager_ones(side):
             assert torch.equal(a, b)
 
 
+@pytest.mark.parametrize("rank", [8, 24, 70])
+def test_infinite_weights(rank):
+    """An infinity in the last row of B reaches what it reaches through the two kernels, and stays an infinity where it does there."""
+    w = workload(1024, synth.F16, (rank, 16), (2, 1))
+    with DeviceWorkload(w, real_adapters="all") as dw:
+        plan = dw.plan()
+        dw.pool_t[int(w.page_idx[0][0, 1, rank - 1]), 3] = 0x7C00  # infinity
+        for a, b in zip(*both(dw, [0], plan, False)):
+            # (stricter below)
+            assert bool((torch.isinf(a) | ~torch.isinf(b)).all()) and bool((torch.isnan(b) | ~torch.isnan(a)).all())
+            assert not bool(torch.isfinite(a).all()) and torch.equal(torch.isfinite(a), torch.isfinite(b))
+            assert torch.equal(a[torch.isfinite(a)], b[torch.isfinite(b)])
+
+
 @pytest.mark.parametrize("y16", [False, True])
 @pytest.mark.parametrize("H,rank", [(1024, 8), (1024, 12), (1024, 17), (1024, 20), (1024, 24), (4096, 24), (1024, 32), (1024, 40), (1024, 70), (1024, 72), (1024, 100)])
-def test_infinite_weights(H, rank, y16, side):
+def test_infinite_weights_from_every_form_of_a_call(H, rank, y16, side):
     """An infinity in the last row of B gives the same from every form of a call: handed over, as two kernels, with the static
     scratch, captured (the one-launch kernel for small batches takes the last two up to 32 ranks).  It stays an infinity where the ranks fill their last eight."""
     w = workload(H, synth.F16, (rank, rank, rank, 16), (2, 1, 4, 1))
