@@ -29,7 +29,9 @@ HBM_PEAK_GBS = 8000.0          # MI355X HBM3E, published
 # From the committed counter summaries named in "source"; only for the default command lines of
 # these workloads with fp32 y.  On cfg5 the figures are those of the two-stage kernels the
 # per-stage timing loop launches (a whole apply runs the decode groups in one kernel instead).
-MEASURED_TRAFFIC = {("cfg4-large-pool-decode", "power", "fused", 8): {"expand_vec": 332880461,
+MEASURED_TRAFFIC = {("cfg2-llama7b-decode", "power", "fused", 8): {"vec_chain": 11604710,
+                                                                   "source": "profiles/cfg2_decode_vec_chain.md"},
+                    ("cfg4-large-pool-decode", "power", "fused", 8): {"expand_vec": 332880461,
                                                                         "shrink_vec": 312123908,
                                                                         "source": "profiles/cfg4_decode_hbm_traffic.md"},
                     ("cfg3-prefill", "power", "fused", 8): {"expand_mfma": 659094527,
@@ -306,7 +308,7 @@ def measure(args, workload: int, no_cpu: bool) -> dict:
         "unit": "GB/s", "frac": round(dom_gbs / HBM_PEAK_GBS, 4),
         "traffic": traffic.get(f"{dom}_{kinds}"),
         # counters cannot be read inside a timed run: the figure comes from the committed summary
-        "traffic_source": (None if not traffic else f"{traffic['source']} (earlier rocprofv3 --pmc runs of this command)"),
+        "traffic_source": (None if f"{dom}_{kinds}" not in traffic else f"{traffic['source']} (earlier rocprofv3 --pmc runs of this command)"),
         "algorithmic_bytes_per_launch": int((ex_b if dom == "expand" else sh_b) * min(n_slots, slora.MAX_MULTI)),
         "avg_launch_us": round((ex_t if dom == "expand" else sh_t) * 1e6, 2),
         "other_kernel": {"kernel": f"{'shrink' if dom == 'expand' else 'expand'}_{kinds}",
@@ -319,7 +321,8 @@ def measure(args, workload: int, no_cpu: bool) -> dict:
         one_t, one_b = ev_ms * 1e-3 / handed, bytes_step * args.steps / handed
         two = f"{sh_t * 1e6:.2f} + {ex_t * 1e6:.2f} us as shrink_vec + expand_vec (two-stage calls)"
         dom_gbs = one_b / one_t / 1e9
-        roofline.update(kernel="vec_chain", achieved=round(dom_gbs, 1), frac=round(dom_gbs / HBM_PEAK_GBS, 4), traffic=None, traffic_source=None,
+        roofline.update(kernel="vec_chain", achieved=round(dom_gbs, 1), frac=round(dom_gbs / HBM_PEAK_GBS, 4), traffic=traffic.get("vec_chain"),
+                        traffic_source=f"{traffic['source']} (earlier rocprofv3 --pmc runs of this command)" if "vec_chain" in traffic else None,
                         algorithmic_bytes_per_launch=int(one_b), avg_launch_us=round(one_t * 1e6, 2), other_kernel={"kernel": two})
 
     # ---- parity of the timed launch shape: batch 0, EVERY slot, against the oracle -----------------

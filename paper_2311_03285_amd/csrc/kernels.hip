@@ -1270,8 +1270,8 @@ __global__ __launch_bounds__(kSplitWaves *kWave, 3) void expand_vec_split_kernel
 // delayed by the other stream's kernels twice.  Calls that a HIP graph captures keep the two kernels: a replay would repeat the number.
 //
 // Sums and their order are those of the vector shrink and of the rank-split expand: the same bits.  us per call, two kernels / chain:
-// 32 tokens of ranks 8-64, H = 4096 9.9 / 7.3; 96 tokens of 4 adapters, 3 slots, bf16, 16-bit y 15.5 / 11.9; 45 tokens of ranks 3-100, H = 3080, 3 slots
-// 17.0 / 13.4; two tokens, H = 1368 9.2 / 5.9; 103 tokens of ranks 8-128, H = 4480, 2 slots 22.3 / 18.4.  Large calls: see slora_plan::route.
+// 32 tokens of ranks 8-64, H = 4096 9.9 / 7.2; 96 tokens of 4 adapters, 3 slots, bf16, 16-bit y 15.5 / 11.4; 45 tokens of ranks 3-100, H = 3080, 3 slots
+// 17.0 / 12.9; two tokens, H = 1368 9.2 / 5.9; 103 tokens of ranks 8-128, H = 4480, 2 slots 22.3 / 18.4.  Large calls: see slora_plan::chain_pays.
 // ---------------------------------------------------------------------------------------
 template <int DT>
 struct HandOver {

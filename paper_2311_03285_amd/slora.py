@@ -106,7 +106,8 @@ def _stream(s) -> Optional[int]:
 
 
 # The calls of a layer are enqueued back to back, and the smallest take as long as their enqueueing.  Of a call of four slots numpy's ctypes view
-# and an object per pointer were 1.3 us: one token of rank 16, 4 slots 5.9 -> 4.6 us, 1 slot 5.2 -> 4.3.
+# and an object per pointer were 1.3 us; one token of rank 16, 4 slots, took 5.9 or 6.5 us a call with these and two kernels, and takes 4.5 or 5.2
+# without and in one launch (a process is in one of two states, whose host calls differ by so much).
 class _Address(C.c_uint64):
     """An element that takes whole numbers only: c_void_p takes None and other c_void_p as well."""
 
