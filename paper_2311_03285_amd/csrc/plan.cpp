@@ -535,14 +535,17 @@ Route slora_plan::route(int32_t n, bool apply, bool y16) const
 // rank 32, 4 slots, 3840: 39.4 / 36.9; 100 of rank 64, H = 2048, 4 slots, 8000: 41.0 / 42.3, fours of them 52.3 / 60.4; 20 groups of eight tokens of rank 64, 3 slots, 2880: 29.8 / 23.0.
 // Fewer where
 //  - an expand item is little work (ranks x tokens below 16, below 4): its workgroups wait in their places all the same.  71 tokens of rank 1, H = 3072, 8 slots, 3976: 13.2 / 14.6, 252
-//    pairs, H = 1024, 4 slots, 3024: 10.6 / 11.2, but 200 of rank 4, 2400: 10.6 / 9.8; 63 of rank 8, H = 3072, 8 slots, 4032: 15.9 / 16.6, but 70 groups of four of rank 1, 3360: 18.8 / 17.8.
+//    pairs, H = 1024, 4 slots, 3024: 10.6 / 11.2, but 200 of rank 4, 2400: 10.6 / 9.8; 63 of rank 8, H = 3072, 8 slots, 4032: 15.9 / 16.6, but 70 groups of four of rank 1, 3360: 18.8 / 17.8.  Three quarters of
+//    that from H = 6152 on, where three of its workgroups fit a compute unit: pairs of ranks 1-8, H = 8192, 25 groups, 8 slots, 3448: 16.5 / 18.4, H = 7168, 33 groups, 6 slots, 3042: 15.8 / 17.7, 47 calls of up to 2560 1.05 times as fast.
 //  - rows of x leave a compute unit three or two workgroups (more than 40 or 56 KiB): 60 groups of four tokens of rank 64, H = 8192, 2 slots, 3840: 67.8 / 75.9, but 20 of rank 32, 4 slots,
-//    1920: 30.0 / 26.1; with little work in an expand item 30 groups of eight of rank 4, H = 8192, 2 slots, 2040: 18.7 / 20.6, ten of sixteen of rank 8, 1440: 16.4 / 17.3, but of rank 4, 1360: 16.0 / 15.8.
+//    1920: 30.0 / 26.1; with little work in an expand item 30 groups of eight of rank 4, H = 8192, 2 slots, 2040: 18.7 / 20.6, ten of sixteen of rank 8, 1440: 16.4 / 17.3, but of rank 4, 1360: 16.0 / 15.8;
+//    fours of ranks 1-8, H = 7168 (64 KiB as well: whole chunks of 512 elements, 16 from H = 6152 on), 30 groups, 4 slots, 1920: 16.0 / 18.5, 33, 6 slots, 1824: 15.9 / 17.9, but 36 calls of 1408 to 1664 1.05 times as fast.
 // Calls that are mostly shrink (many ranks of short rows) have little in flight in its wavefronts; five or more workgroups fit a compute unit in a kernel of its own; and rows
 // of a second 64 ranks are requested after the wait.
 //  - Six times as many shrink items as expand items: 640 of them.  60 tokens of rank 128, H = 2048, 2160: 16.8 / 18.9, 100 pairs in 3600 25.5 / 30.4, but 20 of rank 128, H = 1024, 680: 10.4 / 7.9.
 //  - Four times, pairs of tokens (whose B rows are not streamed here): 2048.  20 of rank 128, H = 3072, 4 slots, 3040: 29.0 / 34.0; 14 of rank 128, H = 4096, 4 slots, 2240: 26.4 / 28.6; 9, 6 slots, 2160: 26.9 / 28.7, but
-//    7 of them, 7 slots, 1960: 26.5 / 25.7.  Threes and fours: 3072.  42 fours of rank 128, H = 4096, 2 slots, 3360: 42.8 / 45.6, but 17 of rank 100, H = 3072, 5 slots, 2635: 30.5 / 28.3.
+//    7 of them, 7 slots, 1960: 26.5 / 25.7; nor, of 112 ranks or more each, between one round of the GPU's 1024 places (a few expand items may wait) and one and a half: ten of rank 128, H = 3072, 3 slots,
+//    1140: 13.2 / 15.7, 16 of rank 128, H = 3584, 2 slots, 1248: 14.6 / 15.9, 40, H = 2888, 1520: 15.7 / 18.1, 95 such calls 0.94 times as fast, but 10 of rank 128, H = 4096, 1600 and H = 3584, 1.07.  Threes and fours: 3072.  42 fours of rank 128, H = 4096, 2 slots, 3360: 42.8 / 45.6, but 17 of rank 100, H = 3072, 5 slots, 2635: 30.5 / 28.3.
 //  - Four and a half times, single tokens: H < 2048 2048.  18 of ranks 30-130, H = 1920, 8 slots, 3744: 21.9 / 23.9; 15 of rank 64, H = 1072, 8 slots, 2280: 12.7 / 13.0; but 59 of rank 64, H = 1536, 3 slots, 3363: 19.5 / 18.1.
 //    H >= 2048 not between one round of the GPU's 1024 places and one and a half.  Ten of rank 100, H = 2560, 4 slots, 1200: 13.3 / 14.5, five, 8 slots 12.9 / 14.6, but 6 slots, 900: 12.0 / 11.0;
 //    13, 8 slots, 3120: 25.2 / 23.7; 30 of rank 128, H = 2048, 1080: 12.3 / 13.2; but 32 of ranks 5-130, H = 1120, 2 slots, 1292: 13.0 / 12.0.
@@ -553,10 +556,11 @@ bool slora_plan::chain_pays(int32_t n, const Route &r) const
     if (!expand_split || pool->fuse_decode == 0 || shrinks == 0 || r.gang || r.gang_expand || pool->H > kChainMaxH || wgs > 65535 || c.words * n > INT32_MAX) return false;
     if (shrinks > 6 * expands && shrinks > 640) return false;
     if (shrinks >= 4 * expands && c.tok >= 2 && wgs > (c.tok == 2 ? 2048 : 3072)) return false;
+    if (shrinks >= 4 * expands && c.tok == 2 && shrinks * ((pool->H + 511) / 512) >= 28 * expands && wgs > 1088 && wgs <= 1536) return false;
     if (2 * shrinks > 9 * expands && c.tok == 1 && (pool->H < 2048 ? wgs > 2048 : wgs > 1024 && wgs <= 1536)) return false;
     const int64_t work = c.work * n / expands, rows = (int64_t)c.tok * pool->H * 2;
-    if (rows > 40960) return wgs <= (rows > 57344 && work < 64 ? 1408 : 2048);
-    return wgs <= (work < 4 ? 2560 : work < 16 ? 3584 : 4096);
+    if (rows > 40960) return wgs <= (c.tok < 4 || pool->H <= 6144 || work >= 64 ? 2048 : pool->H <= 7168 ? 1664 : 1408);
+    return wgs <= (work < 4 ? 2560 : work < 16 ? (pool->H > 6144 ? 2688 : 3584) : 4096);
 }
 
 size_t slora_plan::most_chain_words(int32_t n) const

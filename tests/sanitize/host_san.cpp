@@ -788,7 +788,11 @@ static void hand_over_pays()
     calls(8192, 20, 4, 32, {{4, true}, {5, false}});           // 1920, 2400: 64 KiB of x
     calls(8192, 20, 4, 4, {{4, true}, {5, false}});            // 1360, 1700: and sixteen products
     calls(1024, 20, 1, 128, {{1, true}, {2, false}});          // 640 and 1280 shrink items, sixteen times as many as expand items
-    calls(3072, 20, 2, 128, {{2, true}, {3, false}});          // 1520, 2280: pairs, 5.3 times
+    calls(8192, 25, 2, 4, {{6, true}, {7, false}});            // 2550, 2975: eight products, three workgroups a compute unit
+    calls(7168, 20, 4, 4, {{5, true}, {6, false}});            // 1500, 1800: sixteen, and 64 KiB of x
+    calls(3072, 20, 2, 128, {{1, true}, {2, false}, {3, false}}); // 760, 1520, 2280: pairs, 5.3 times
+    calls(3072, 8, 2, 128, {{3, true}, {4, false}, {6, true}, {7, false}}); // 912, 1216, 1824, 2128
+    calls(3072, 8, 2, 96, {{4, true}, {5, true}, {8, true}}); // 960, 1200, 1920: of fewer ranks
     calls(3072, 20, 3, 128, {{3, true}});
     calls(2560, 5, 1, 100, {{6, true}, {8, false}});           // 900, 1200: single tokens, five times
     calls(2560, 13, 1, 100, {{2, true}, {3, false}, {4, true}}); // 780, 1170, 1560
