@@ -300,15 +300,15 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
                 chain.shared = chain.shared || n > kExpandTok;
                 if (fused) plan->vf_items.push_back(Item{off, g.rank, 0, H, pos_base, n, 0, 0});
                 for (int32_t p = 0; p < n; p += shrink_tok) {
-                    const int32_t nt = std::min(shrink_tok, n - p);
+                    const int32_t nt = std::min(shrink_tok, n - p), run = word(hand + (int64_t)p * g.rank);
                     plan->max_shrink_tok = std::max(plan->max_shrink_tok, nt);
                     for (int32_t j = 0; j < g.rank; j += shrink_pages)
-                        vs.push_back(Item{off, g.rank, j, std::min(shrink_pages, g.rank - j), pos_base + p, nt, 0, word(hand + (int64_t)p * g.rank)});
+                        vs.push_back(Item{off, g.rank, j, std::min(shrink_pages, g.rank - j), pos_base + p, nt, 0, run});
                 }
                 for (int32_t p = 0; p < n; p += kExpandTok) {
-                    const int32_t nt = std::min(kExpandTok, n - p);
+                    const int32_t nt = std::min(kExpandTok, n - p), run = word(hand + (int64_t)p * g.rank);
                     for (int32_t c = 0; c < H; c += ecols)
-                        ve.push_back(Item{off, g.rank, c, std::min(ecols, H - c), pos_base + p, nt, n <= kExpandTok, word(hand + (int64_t)p * g.rank)});
+                        ve.push_back(Item{off, g.rank, c, std::min(ecols, H - c), pos_base + p, nt, n <= kExpandTok, run});
                 }
             }
         }
@@ -374,8 +374,9 @@ int32_t slora::build_plan(slora_pool *pool, slora_plan *plan, const int32_t *ids
         }
         plan->n_vs_plain = (int32_t)plan->vs_items.size();
         plan->n_ve_plain = (int32_t)plan->ve_items.size();
-        for (std::vector<Item> *items : {&vs_dual, &ve_dual}) // their words follow those of the plain items
-            for (Item &i : *items) i.run = word(i.run + plan->chain[0].words);
+        if (plan->chain[0].words > 0)
+            for (std::vector<Item> *items : {&vs_dual, &ve_dual}) // their words follow those of the plain items
+                for (Item &i : *items) i.run = word(i.run + plan->chain[0].words);
         plan->chain[1].words += plan->chain[0].words;
         plan->chain[1].work += plan->chain[0].work;
         plan->chain[1].tok = std::max(plan->chain[1].tok, plan->chain[0].tok);
